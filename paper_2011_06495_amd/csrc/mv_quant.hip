@@ -15,7 +15,13 @@
 // code = (interval - 1) | sign << (q-1); value k occupies bits [k q, (k+1) q) of the
 // row's stream, bit b of a stream being bit b % 32 of word b / 32.
 //
-// One workgroup per row: the data is tiny (K values), the work is latency.
+// Encoding is latency, not bandwidth (a row of 111,740 values is 447 KB): what counts is
+// how many compute units share a row and how long the dependent chain is.  Rows of up to
+// kTile values are done whole by one workgroup in one launch; longer rows are cut into
+// tiles of kTile values over up to kMaxBlocks workgroups, in three launches: the blocks'
+// largest and smallest magnitudes; codes and the blocks' sums per interval; the means.
+// 10 rows of 111,740 values, q = 4: 188 us with one workgroup per row, 14.6 us so (3.8 + 6.8 + 2.7
+// us in the kernels).
 #include "../../include/mv.h"
 
 #include <hip/hip_runtime.h>
@@ -23,9 +29,10 @@
 
 namespace mvq {
 
-constexpr int kThreads = 1024;
-constexpr int kMaxL = 128;          // q <= 8
-constexpr int kGroup = 32;          // most values per packing group (32 values = q whole words)
+constexpr int kTile = 2048;         // values a workgroup works on at a time
+constexpr int kMaxBlocks = 256;     // workgroups per row: every one reads the ranges of all
+constexpr int kRangeThreads = 256;
+constexpr int kMeanThreads = 1024;
 
 // values per packing group: the fewest whose codes fill whole words
 __host__ __device__ constexpr int group_size(int q)
@@ -35,117 +42,234 @@ __host__ __device__ constexpr int group_size(int q)
     return g;
 }
 
-__device__ __forceinline__ uint32_t interval_of(double m, const double* edges, int L)
+// Wavefronts per workgroup of quant_codes_kernel: every wavefront has a table of L x 64 sums
+// (8 bytes) and counts (4 bytes) in LDS, 96 KB of tables at most.
+constexpr int code_waves(int q) { return q <= 6 ? 4 : q == 7 ? 2 : 1; }
+
+struct Range {                      // of the non-zero magnitudes, as bit patterns (same order as the values)
+    uint32_t vmax, vmin;            // 0 and 0xFFFFFFFF: none
+};
+
+__device__ __forceinline__ void widen(Range& r, float x)
 {
-    uint32_t l = 0;
-    for (int j = 1; j < L; ++j) l += (m <= edges[j]) ? 1u : 0u;
-    return l;                       // interval - 1
+    const uint32_t m = __float_as_uint(x) & 0x7FFFFFFFu;
+    r.vmax = max(r.vmax, m);
+    if (m) r.vmin = min(r.vmin, m);
 }
 
-// partial[row][group][l] = sum of the magnitudes of the group's values in interval l, in index order
-template <int q>                      // the bit budget is a template parameter: the packing indexes registers
-__global__ __launch_bounds__(kThreads) void quant_encode_kernel(
-    const float* __restrict__ vals, int64_t ld_vals, int64_t n, uint32_t* __restrict__ streams,
-    int64_t ld_words, float* __restrict__ means, double* __restrict__ partial, uint32_t* __restrict__ pcount,
-    int64_t n_groups)
+// All lanes of the wavefront get the wavefront's range.
+__device__ __forceinline__ Range wave_range(Range r)
 {
-    __shared__ uint32_t red_max[kThreads / 64], red_min[kThreads / 64];
-    __shared__ double edges[kMaxL];
-    constexpr int L = 1 << (q - 1);
-    const uint32_t row = blockIdx.x, t = threadIdx.x;
-    const float* v = vals + (int64_t)row * ld_vals;
-
-    // largest and smallest non-zero magnitude, as bit patterns (same order as the values)
-    uint32_t vmax = 0, vmin = 0xFFFFFFFFu;
-    for (int64_t k = t; k < n; k += kThreads) {
-        const uint32_t m = __float_as_uint(v[k]) & 0x7FFFFFFFu;
-        vmax = max(vmax, m);
-        if (m) vmin = min(vmin, m);
-    }
     for (int o = 32; o >= 1; o >>= 1) {
-        vmax = max(vmax, (uint32_t)__shfl_xor(vmax, o, 64));
-        vmin = min(vmin, (uint32_t)__shfl_xor(vmin, o, 64));
+        r.vmax = max(r.vmax, (uint32_t)__shfl_xor(r.vmax, o, 64));
+        r.vmin = min(r.vmin, (uint32_t)__shfl_xor(r.vmin, o, 64));
     }
-    if ((t & 63) == 0) {
-        red_max[t / 64] = vmax;
-        red_min[t / 64] = vmin;
+    return r;
+}
+
+// Tiles b, b + gridDim.x, ... of the row: their range.
+__global__ __launch_bounds__(kRangeThreads) void quant_range_kernel(const float* __restrict__ vals, int64_t ld_vals,
+                                                                    int64_t n, Range* __restrict__ ranges)
+{
+    __shared__ Range waves[kRangeThreads / 64];
+    const uint32_t t = threadIdx.x;
+    const float* v = vals + (int64_t)blockIdx.y * ld_vals;
+    constexpr int kPer = kTile / kRangeThreads;
+    Range r = {0u, 0xFFFFFFFFu};
+    for (int64_t k0 = (int64_t)blockIdx.x * kTile; k0 < n; k0 += (int64_t)gridDim.x * kTile) {
+        float x[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int64_t k = k0 + i * kRangeThreads + t;
+            x[i] = k < n ? v[k] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) widen(r, x[i]);
+    }
+    r = wave_range(r);
+    if ((t & 63u) == 0u) waves[t / 64] = r;
+    __syncthreads();
+    if (t == 0) {
+        for (int w = 1; w < kRangeThreads / 64; ++w) {
+            r.vmax = max(r.vmax, waves[w].vmax);
+            r.vmin = min(r.vmin, waves[w].vmin);
+        }
+        ranges[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = r;
+    }
+}
+
+// Codes of tiles b, b + gridDim.x, ... of the row, and the workgroup's sum and count per interval.
+//  * The interval of a magnitude comes from a bisection of the edges (they descend, and when one of
+//    them is not a number all behind it are not), q-1 steps instead of L-1 comparisons.
+//  * A lane adds its magnitudes to sums of its own, table[interval][lane] of its wavefront: every
+//    sum is formed in one order whatever the timing, and equal intervals do not queue up.
+//  * Codes go through LDS bytes, so that loads are coalesced and a thread packs whole words.
+// ALONE: the workgroup has the whole row (n <= kTile): range, codes and means in this one launch.
+// Bound by its dependent chain: q - 1 square roots and L divisions in fp64 before the first code
+// (about 1 us at q = 4), LDS round trips behind it.
+template <int q, bool ALONE>
+__global__ __launch_bounds__(64 * code_waves(q)) void quant_codes_kernel(
+    const float* __restrict__ vals, int64_t ld_vals, int64_t n, uint32_t* __restrict__ streams, int64_t ld_words,
+    const Range* __restrict__ ranges, double* __restrict__ partial, uint32_t* __restrict__ pcount,
+    float* __restrict__ means)
+{
+    constexpr int L = 1 << (q - 1);
+    constexpr int kWaves = code_waves(q), kThreads = 64 * kWaves;
+    constexpr int kPer = kTile / kThreads;
+    __shared__ double   sums[kWaves * L * 64];
+    __shared__ uint32_t count[kWaves * L * 64];
+    __shared__ double   edges[L];
+    __shared__ uint8_t  codes[kTile];
+    __shared__ Range    waves[kWaves];
+    const uint32_t row = blockIdx.y, t = threadIdx.x, lane = t & 63u, wave = t / 64;
+    const float* v = vals + (int64_t)row * ld_vals;
+    float x[kPer];
+    auto load_tile = [&](int64_t k0) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int64_t k = k0 + i * kThreads + t;
+            x[i] = k < n ? v[k] : 0.0f;
+        }
+    };
+    int64_t k0 = (int64_t)blockIdx.x * kTile;
+    load_tile(k0);
+
+    // the row's range
+    Range r = {0u, 0xFFFFFFFFu};
+    if constexpr (ALONE) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) widen(r, x[i]);
+    } else {
+        for (uint32_t b = t; b < gridDim.x; b += kThreads) {
+            const Range o = ranges[(size_t)row * gridDim.x + b];
+            r.vmax = max(r.vmax, o.vmax);
+            r.vmin = min(r.vmin, o.vmin);
+        }
+    }
+    r = wave_range(r);
+    if (lane == 0) waves[wave] = r;
+    for (int i = t; i < kWaves * L * 64; i += kThreads) {
+        sums[i] = 0.0;
+        count[i] = 0u;
     }
     __syncthreads();
     if (t == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) {
-            vmax = max(vmax, red_max[w]);
-            vmin = min(vmin, red_min[w]);
+        for (int w = 1; w < kWaves; ++w) {
+            r.vmax = max(r.vmax, waves[w].vmax);
+            r.vmin = min(r.vmin, waves[w].vmin);
         }
-        if (vmax == 0) {
+        if (r.vmax == 0) {
             for (int l = 0; l < L; ++l) edges[l] = 0.0;
         } else {
-            const double hi = (double)__uint_as_float(vmax), lo = (double)__uint_as_float(vmin);
+            const double hi = (double)__uint_as_float(r.vmax), lo = (double)__uint_as_float(r.vmin);
             double alpha = hi / lo;
-            for (int r = 0; r < q - 1; ++r) alpha = sqrt(alpha);
-            edges[0] = hi;
-            for (int l = 1; l < L; ++l) edges[l] = edges[l - 1] / alpha;
+            for (int i = 0; i < q - 1; ++i) alpha = sqrt(alpha);
+            double edge = hi;
+            edges[0] = edge;
+            for (int l = 1; l < L; ++l) {
+                edge /= alpha;
+                edges[l] = edge;
+            }
         }
     }
     __syncthreads();
 
-    // codes: a thread packs groups of 32 consecutive values into q whole words
     uint32_t* out = streams + (int64_t)row * ld_words;
-    double* prow = partial + (int64_t)row * n_groups * L;
-    uint32_t* crow = pcount + (int64_t)row * n_groups * L;
-    constexpr int G = group_size(q);                 // G values = G q / 32 whole words
-    constexpr int gw = G * q / 32;
-    for (int64_t g = t; g < n_groups; g += kThreads) {
-        // the group's values in registers: codes first, then per-interval sums in index order
-        uint32_t words[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        float    mag[kGroup];
-        uint8_t  lv[kGroup];
+    const int64_t n_words = (n * q + 31) / 32;
+    double*   my_sums = sums + wave * (L * 64) + lane;
+    uint32_t* my_count = count + wave * (L * 64) + lane;
+    for (;;) {
 #pragma unroll
-        for (int i = 0; i < G; ++i) {
-            const int64_t k = g * G + i;
-            const bool live = k < n;
-            const float x = live ? v[k] : 0.0f;
-            mag[i] = fabsf(x);
-            const uint32_t l = live ? interval_of((double)mag[i], edges, L) : 0xFFu;
-            lv[i] = (uint8_t)l;
+        for (int i = 0; i < kPer; ++i) {
+            const bool live = k0 + i * kThreads + t < n;
+            const double m = (double)fabsf(x[i]);
+            uint32_t l = 0;                       // interval - 1 = #{ j in 1 .. L-1 : m <= edges[j] }
+#pragma unroll
+            for (int s = L / 2; s >= 1; s >>= 1)
+                if (m <= edges[l + s]) l += s;
+            uint32_t code = 0;
             if (live) {
-                const uint32_t code = l | ((__float_as_uint(x) >> 31) << (q - 1));
-                const uint32_t bit = (uint32_t)i * (uint32_t)q;
-                words[bit >> 5] |= code << (bit & 31);
-                if ((bit & 31) + q > 32) words[(bit >> 5) + 1] |= code >> (32 - (bit & 31));
+                code = l | ((__float_as_uint(x[i]) >> 31) << (q - 1));
+                my_sums[l * 64] += m;
+                my_count[l * 64] += 1u;
+            }
+            codes[i * kThreads + t] = (uint8_t)code;
+        }
+        __syncthreads();
+        // word w of the tile holds stream bits [32 w, 32 w + 32): the codes that overlap it
+        constexpr int kTileWords = kTile * q / 32;
+        for (int w = t; w < kTileWords; w += kThreads) {
+            const int first = 32 * w / q;
+            uint32_t word = 0;
+#pragma unroll
+            for (int i = 0; i <= (31 + q) / q; ++i) {
+                const int at = (first + i) * q - 32 * w;               // the code's first bit, from -q + 1 on
+                const uint32_t c = (at < 32 && first + i < kTile) ? codes[first + i] : 0u;
+                word |= at >= 0 ? c << (at & 31) : c >> -at;
+            }
+            const int64_t at = k0 / 32 * q + w;
+            if (at < n_words) out[at] = word;
+        }
+        k0 += (int64_t)gridDim.x * kTile;
+        if (ALONE || k0 >= n) break;              // uniform
+        load_tile(k0);
+        __syncthreads();                          // the codes' bytes are free
+    }
+    // the loop's barrier has passed since the last addition to the tables
+
+    // per interval: kLanes lanes add up the columns of all wavefronts' tables, each its share in a fixed
+    // order, then each other's in a fixed tree.  The columns a wavefront reads together are all different.
+    constexpr int kLanes = kThreads / L >= 64 ? 64 : kThreads / L >= 1 ? kThreads / L : 1;
+    for (int i = t; i < L * kLanes; i += kThreads) {
+        const int l = i / kLanes, p = i % kLanes;
+        double   s = 0.0;
+        uint32_t c = 0;
+        for (int w = 0; w < kWaves; ++w)
+#pragma unroll 4
+            for (int j = 0; j < 64 / kLanes; ++j) {
+                const int col = (j * kLanes + p + l * kLanes) & 63;
+                s += sums[(w * L + l) * 64 + col];
+                c += count[(w * L + l) * 64 + col];
+            }
+        for (int o = kLanes / 2; o >= 1; o >>= 1) {
+            s += __shfl_xor(s, o, 64);
+            c += __shfl_xor(c, o, 64);
+        }
+        if (p == 0) {
+            if constexpr (ALONE) {
+                means[(int64_t)row * L + l] = c ? (float)(s / (double)c) : 0.0f;
+            } else {
+                partial[((size_t)row * gridDim.x + blockIdx.x) * L + l] = s;
+                pcount[((size_t)row * gridDim.x + blockIdx.x) * L + l] = c;
             }
         }
-        for (int l = 0; l < L; ++l) {
-            double s = 0.0;
-            uint32_t c = 0;
-#pragma unroll
-            for (int i = 0; i < G; ++i)
-                if (lv[i] == (uint8_t)l) {
-                    s += (double)mag[i];
-                    ++c;
-                }
-            prow[g * L + l] = s;
-            crow[g * L + l] = c;
-        }
-        const int64_t w0 = g * gw;
-        const int64_t n_words = ((int64_t)n * q + 31) / 32;
-        for (int w = 0; w < gw; ++w)
-            if (w0 + w < n_words) out[w0 + w] = words[w];
     }
-    __syncthreads();
-    // means: one wavefront per interval; lane j adds the partial sums of groups j, j+64, ...
-    // and the lanes are then added in a fixed tree, so the result does not depend on timing
-    for (int l = (int)(t / 64); l < L; l += kThreads / 64) {
-        double s = 0.0;
+}
+
+// Means of a row: one wavefront per interval; lane j adds the sums of blocks j, j + 64, ... and the
+// lanes are then added in a fixed tree.
+__global__ __launch_bounds__(kMeanThreads) void quant_means_kernel(const double* __restrict__ partial,
+                                                                   const uint32_t* __restrict__ pcount,
+                                                                   uint32_t n_blocks, int L, float* __restrict__ means)
+{
+    const size_t row = blockIdx.x;
+    const uint32_t lane = threadIdx.x & 63u;
+    for (int l = (int)(threadIdx.x / 64); l < L; l += kMeanThreads / 64) {
+        double   s = 0.0;
         uint32_t c = 0;
-        for (int64_t g = t & 63; g < n_groups; g += 64) {
-            s += prow[g * L + l];
-            c += crow[g * L + l];
+#pragma unroll
+        for (int u = 0; u < kMaxBlocks / 64; ++u) {
+            const uint32_t b = lane + 64u * u;
+            if (b < n_blocks) {
+                s += partial[(row * n_blocks + b) * L + l];
+                c += pcount[(row * n_blocks + b) * L + l];
+            }
         }
         for (int o = 32; o >= 1; o >>= 1) {
             s += __shfl_xor(s, o, 64);
             c += __shfl_xor(c, o, 64);
         }
-        if ((t & 63) == 0) means[(int64_t)row * L + l] = c ? (float)(s / (double)c) : 0.0f;
+        if (lane == 0) means[row * L + l] = c ? (float)(s / (double)c) : 0.0f;
     }
 }
 
@@ -186,16 +310,30 @@ mv_status mv_quant_encode(const float* vals, int64_t ld_vals, int64_t n, int32_t
     if (n < 1 || rows < 1 || rows > 65535 || q < 2 || q > 8 || ld_vals < n) return MV_ERR_INVALID_ARG;
     if (ld_words < (n * q + 31) / 32) return MV_ERR_INVALID_ARG;
     if (scratch_bytes < mv_quant_scratch_bytes(n, rows, q)) return MV_ERR_INVALID_ARG;
-    const int64_t groups = (n + mvq::group_size(q) - 1) / mvq::group_size(q);
     const int L = 1 << (q - 1);
+    const int64_t tiles = (n + mvq::kTile - 1) / mvq::kTile;
+    const uint32_t blocks = (uint32_t)(tiles < mvq::kMaxBlocks ? tiles : mvq::kMaxBlocks);
+    // Per row and block L sums, L counts and a range, 12 L + 8 bytes: b > 1 blocks have more than
+    // 64 (b - 1) >= 2 b packing groups (of at most 32 values), for each of which mv_quant_scratch_bytes counts 12 L.
+    static_assert(mvq::kTile >= 64 * 32, "the blocks' records fit the scratch");
     uintptr_t base = (reinterpret_cast<uintptr_t>(scratch) + 255) & ~(uintptr_t)255;
+    const size_t records = (size_t)rows * blocks;
     double* partial = reinterpret_cast<double*>(base);
-    uint32_t* pcount = reinterpret_cast<uint32_t*>(base + (size_t)rows * groups * L * sizeof(double));
+    mvq::Range* ranges = reinterpret_cast<mvq::Range*>(partial + records * L);
+    uint32_t* pcount = reinterpret_cast<uint32_t*>(ranges + records);
     hipStream_t st = static_cast<hipStream_t>(stream);
-#define MV_QUANT_LAUNCH(Q)                                                                                     \
-    case Q:                                                                                                    \
-        hipLaunchKernelGGL(mvq::quant_encode_kernel<Q>, dim3((uint32_t)rows), dim3(mvq::kThreads), 0, st, vals, \
-                           ld_vals, n, streams, ld_words, means, partial, pcount, groups);                     \
+    const dim3 grid(blocks, (uint32_t)rows);
+    if (blocks > 1)
+        hipLaunchKernelGGL(mvq::quant_range_kernel, grid, dim3(mvq::kRangeThreads), 0, st, vals, ld_vals, n, ranges);
+#define MV_QUANT_LAUNCH(Q)                                                                                        \
+    case Q:                                                                                                       \
+        if (blocks > 1)                                                                                           \
+            hipLaunchKernelGGL((mvq::quant_codes_kernel<Q, false>), grid, dim3(64 * mvq::code_waves(Q)), 0, st,   \
+                               vals, ld_vals, n, streams, ld_words, (const mvq::Range*)ranges, partial, pcount, means); \
+        else                                                                                                      \
+            hipLaunchKernelGGL((mvq::quant_codes_kernel<Q, true>), grid, dim3(64 * mvq::code_waves(Q)), 0, st,    \
+                               vals, ld_vals, n, streams, ld_words, (const mvq::Range*)nullptr, (double*)nullptr, \
+                               (uint32_t*)nullptr, means);                                                        \
         break;
     switch (q) {
         MV_QUANT_LAUNCH(2) MV_QUANT_LAUNCH(3) MV_QUANT_LAUNCH(4) MV_QUANT_LAUNCH(5)
@@ -203,6 +341,9 @@ mv_status mv_quant_encode(const float* vals, int64_t ld_vals, int64_t n, int32_t
         default: return MV_ERR_INVALID_ARG;
     }
 #undef MV_QUANT_LAUNCH
+    if (blocks > 1)
+        hipLaunchKernelGGL(mvq::quant_means_kernel, dim3((uint32_t)rows), dim3(mvq::kMeanThreads), 0, st,
+                           (const double*)partial, (const uint32_t*)pcount, blocks, L, means);
     return hipGetLastError() == hipSuccess ? MV_OK : MV_ERR_DEVICE;
 }
 

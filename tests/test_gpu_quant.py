@@ -60,6 +60,20 @@ def test_quant_random_values(oracle, q, n, rows):
     gpu_quant(oracle, vals, q)
 
 
+@pytest.mark.parametrize("q,n,rows", [(4, 2047, 2), (4, 2048, 2), (4, 2049, 2), (6, 2048, 1), (7, 2049, 3), (8, 2049, 2),
+                                      (2, 4097, 2), (3, 20011, 2), (6, 6143, 2), (7, 70001, 1), (8, 33333, 2),
+                                      (4, 524288, 1), (5, 524289, 1), (8, 1050001, 1)])
+def test_quant_tiles(oracle, q, n, rows):
+    """Around the edges of a workgroup's tile (2048 values; one launch up to there, three beyond) and of the
+    most workgroups per row (256, beyond which each works on several tiles)."""
+    say("quant tiles q=%d n=%d rows=%d" % (q, n, rows))
+    rng = np.random.default_rng(q * 1000 + n)
+    vals = (rng.standard_normal((rows, n)) * np.exp(rng.standard_normal((rows, n)))).astype(np.float32)
+    vals[:, ::1021] = 0.0
+    vals[-1, n - 1] = -1e-30                                    # the smallest magnitude sits in the last tile
+    gpu_quant(oracle, vals, q)
+
+
 def test_quant_degenerate_rows(oracle):
     say("quant degenerate")
     n = 300
