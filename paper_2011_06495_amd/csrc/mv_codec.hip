@@ -15,14 +15,16 @@
 // word once: no atomics, no clearing pass, coalesced stores.
 //
 // Decoder: the receiver's parse is a finite automaton (state = offset bits still
-// to skip, 0..B).  Each 64-bit chunk of the stream is run once for every possible
-// entry state (exit state, codes begun, blocks closed); composing these maps along
-// the stream gives every chunk its true entry state and the number of codes and
-// closed blocks before it; a last pass parses each chunk for real and writes
-// coordinate = closed blocks * block_len + offset at its place in the list.
+// to skip, 0..B).  Every 64-bit chunk of the stream becomes a map from entry state to
+// (exit state, codes begun); composing these maps along the stream gives every chunk
+// its true entry state and the number of codes before it; then each chunk is parsed for
+// real and writes coordinate = closed blocks * block_len + offset at its place in the
+// list.  Closed blocks are not counted: a flag at stream bit p with c codes before it
+// has p - c (1 + B) closing bits before it.
 #include "../../include/mv.h"
 
 #include <mutex>
+#include <utility>
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -32,18 +34,17 @@ namespace mvc {
 constexpr int kThreads = 256;
 constexpr int kMaxB = 31;
 constexpr int kChunkBits = 64;
-constexpr int kWalkThreads = 1024;
+constexpr int kTileChunks = kThreads;          // chunks a workgroup maps at a time, one per thread
+constexpr int kGroupChunks = 16;               // chunks composed by one thread
+constexpr int kGroups = kTileChunks / kGroupChunks;
+constexpr int kMaxTiles = 256;                 // per row: longer streams give every workgroup several runs of kTileChunks
+constexpr int kTileGroup = 16;                 // tiles composed by one thread
 
 __host__ __device__ inline int offset_bits(int64_t block_len)
 {
     int b = 0;
     while (((int64_t)1 << b) < block_len) ++b;
     return b;
-}
-
-__device__ __forceinline__ uint32_t stream_bit(const uint32_t* __restrict__ w, uint64_t k)
-{
-    return (w[k >> 5] >> (k & 31u)) & 1u;
 }
 
 // first bit of the code of list entry i
@@ -90,235 +91,304 @@ __global__ __launch_bounds__(kThreads) void codec_encode_kernel(
 }
 
 // ---- decoder -----------------------------------------------------------------
+// The chain is what costs, not the bytes (10 streams of 1 Mbit are 1.3 MB), so the stream is
+// cut finely -- 256 chunks per workgroup -- and composed in levels: chunks to groups of 16,
+// groups to a tile, tiles to the row.  Two launches: maps of every level; then every workgroup
+// walks the tile maps before its own, its groups and its chunks, and emits.  A stream of one
+// tile takes one launch and no scratch.  10 lists of 111,740 positions, B = 7: 140 us when one
+// workgroup per row composed all chunks, 15 us so (maps 6.2, emission 9.8).
+//
+// A map entry is exit state | codes begun << 8: 16 bits for a chunk (at most 64 codes), 32
+// for a group, a tile or a row's tiles.
 
-struct ChunkMap {                // what a chunk does to the parse, for one entry state
-    uint8_t  exit_state;
-    uint8_t  codes;              // codes begun in the chunk (at most 64)
-    uint8_t  closed;             // blocks closed in the chunk (at most 64)
+__device__ __forceinline__ uint32_t map_exit(uint32_t m) { return m & 255u; }
+// entry `m` (state reached, codes so far) carried on through `next`, the map's value at that state
+__device__ __forceinline__ uint32_t carry(uint32_t m, uint32_t next) { return (m & ~255u) + next; }
+
+// stream words i, i + 1, i + 2 with the bits at or beyond `total` read as zero
+struct ChunkBits {
+    uint64_t lo;                 // the chunk, first bit in bit 0
+    uint32_t hi;                 // the 32 bits behind it (an offset may reach into them)
 };
-
-// up to 64 stream bits from bit `first` (a multiple of 64), first bit in bit 0;
-// bits at or beyond `total` read as zero
-__device__ __forceinline__ uint64_t load_chunk(const uint32_t* __restrict__ words, uint64_t first, uint64_t total)
+__device__ __forceinline__ ChunkBits load_chunk(const uint32_t* __restrict__ words, uint64_t chunk, uint64_t total)
 {
-    const uint64_t n_words = (total + 31) / 32, i = first >> 5;
-    uint64_t v = (i < n_words) ? words[i] : 0u;
-    if (i + 1 < n_words) v |= (uint64_t)words[i + 1] << 32;
-    const uint64_t len = total - first;
-    return len < 64 ? (v & ((1ull << len) - 1)) : v;
-}
-
-// `len` (at most 31) stream bits from bit k, first bit in bit 0; zero beyond `total`
-__device__ __forceinline__ uint32_t load_field(const uint32_t* __restrict__ words, uint64_t k, uint32_t len,
-                                               uint64_t total)
-{
-    const uint64_t n_words = (total + 31) / 32, i = k >> 5;
-    uint64_t v = (i < n_words) ? words[i] : 0u;
-    if (i + 1 < n_words) v |= (uint64_t)words[i + 1] << 32;
-    uint32_t f = (uint32_t)(v >> (k & 31u)) & ((1u << len) - 1u);
-    if (k + len > total) f &= (k < total) ? ((1u << (uint32_t)(total - k)) - 1u) : 0u;
-    return f;
-}
-
-// Parse the `len` bits of a chunk held in `w`, entering with `state` offset bits
-// still to skip.  Runs of zero flags are taken in one step, so the loop runs once
-// per code.
-__device__ __forceinline__ ChunkMap run_chunk(uint64_t w, uint32_t len, uint32_t state, uint32_t B)
-{
-    ChunkMap m = {0, 0, 0};
-    uint32_t j = min(state, len);
-    state -= j;
-    while (j < len) {
-        const uint64_t rest = w >> j;
-        const uint32_t zeros = rest ? (uint32_t)__builtin_ctzll(rest) : 64u;
-        const uint32_t run = min(zeros, len - j);
-        m.closed += (uint8_t)run;
-        j += run;
-        if (j >= len) break;
-        ++m.codes;                                   // flag bit, then B offset bits
-        const uint32_t end = j + 1 + B;
-        state = end > len ? end - len : 0;
-        j = min(end, len);
+    const uint64_t n_words = (total + 31) / 32, i = chunk * 2;
+    uint32_t w[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        w[u] = i + u < n_words ? words[i + u] : 0u;
+        if ((i + u + 1) * 32 > total && i + u < n_words) w[u] &= (1u << (total & 31u)) - 1u;
     }
-    m.exit_state = (uint8_t)state;
-    return m;
+    return ChunkBits{(uint64_t)w[1] << 32 | w[0], w[2]};
 }
 
-// Three byte tables per row, each [chunk][state] with B + 1 states per chunk:
-// exit state, codes begun, blocks closed.
-struct MapTables {
-    uint8_t* exit_state;
-    uint8_t* codes;
-    uint8_t* closed;
+// The chunk's map for entry states 0..B into tab[state * pitch]: backwards over the bits,
+// f(j) = what happens from bit j on when a flag is due there, = f(j + 1) behind a 0 and one
+// code more than f(j + 1 + B) behind a 1; entering with s offset bits to skip is f(s).  With B
+// known the last B + 1 values stay in registers: three instructions per bit, no divergence.
+template <int B>
+__device__ __forceinline__ void chunk_map(uint64_t bits, uint16_t* tab, uint32_t pitch)
+{
+    uint32_t f[kChunkBits + 1 + B];
+#pragma unroll
+    for (int i = 0; i <= B; ++i) f[kChunkBits + i] = (uint32_t)i;
+#pragma unroll
+    for (int j = kChunkBits - 1; j >= 0; --j) {
+        const uint32_t word = j >= 32 ? (uint32_t)(bits >> 32) : (uint32_t)bits;
+        f[j] = (word >> (j & 31)) & 1u ? f[j + 1 + B] + 256u : f[j + 1];
+    }
+#pragma unroll
+    for (int s = 0; s <= B; ++s) tab[s * pitch] = (uint16_t)f[s];
+}
+
+// LDS of the maps of up to kTileChunks chunks
+struct TileLds {
+    uint16_t chunk[(kMaxB + 1) * kTileChunks];    // [state][chunk], pitch = the chunks there are
+    uint32_t group[kGroups][kMaxB + 1];
 };
 
-__device__ __forceinline__ MapTables row_tables(uint8_t* base, uint64_t max_chunks, uint32_t row)
+// group maps from the chunk maps; all threads, ends without a barrier
+__device__ __forceinline__ void compose_groups(TileLds& lds, uint32_t n_chunks, uint32_t n_states)
 {
-    const uint64_t per_table = max_chunks * (kMaxB + 1);
-    uint8_t* r = base + (uint64_t)row * 3 * per_table;
-    return MapTables{r, r + per_table, r + 2 * per_table};
+    for (uint32_t i = threadIdx.x; i < kGroups * n_states; i += kThreads) {
+        const uint32_t g = i / n_states, s = i % n_states;
+        const uint32_t c1 = min((g + 1) * kGroupChunks, n_chunks);
+        uint32_t m = s;
+        for (uint32_t c = g * kGroupChunks; c < c1; ++c) m = carry(m, lds.chunk[map_exit(m) * n_chunks + c]);
+        lds.group[g][s] = m;
+    }
 }
 
-__global__ __launch_bounds__(kThreads) void codec_chunk_maps_kernel(
-    const uint32_t* __restrict__ streams, int64_t ld_words, const unsigned long long* __restrict__ n_bits,
-    uint64_t max_bits, uint32_t B, uint8_t* __restrict__ maps, uint64_t max_chunks)
+struct WalkLds {
+    uint32_t group_entry[kGroups + 1];            // state | codes << 8, codes from the start of the run
+    uint32_t chunk_entry[kTileChunks];
+};
+
+// Entries of the run's groups and chunks from `state`, the run's entry state; returns (to all) the run's
+// exit: state | codes << 8.  The maps must be in LDS, a barrier behind them.
+__device__ __forceinline__ uint32_t walk_run(const TileLds& lds, WalkLds& walk, uint32_t n_chunks, uint32_t state)
 {
-    const uint32_t row = blockIdx.y;
-    // the received length is wire-side data: clamped to what the scratch tables were sized for
+    const uint32_t t = threadIdx.x;
+    if (t == 0) {
+        uint32_t m = state;
+        for (uint32_t g = 0; g < (uint32_t)kGroups; ++g) {
+            walk.group_entry[g] = m;
+            m = carry(m, lds.group[g][map_exit(m)]);
+        }
+        walk.group_entry[kGroups] = m;
+    }
+    __syncthreads();
+    if (t < (uint32_t)kGroups) {
+        uint32_t m = walk.group_entry[t];
+        const uint32_t c1 = min((t + 1) * kGroupChunks, n_chunks);
+        for (uint32_t c = t * kGroupChunks; c < c1; ++c) {
+            walk.chunk_entry[c] = m;
+            m = carry(m, lds.chunk[map_exit(m) * n_chunks + c]);
+        }
+    }
+    __syncthreads();
+    return walk.group_entry[kGroups];
+}
+
+// Parses a chunk for real, entering with `state` offset bits to skip and `codes` codes before it.
+__device__ __forceinline__ void emit_chunk(ChunkBits c, uint64_t first_bit, uint32_t state, uint32_t codes, uint32_t B,
+                                           int64_t d, uint32_t block_len, uint32_t* __restrict__ out, uint32_t max_n)
+{
+    uint32_t j = state;
+    while (j < (uint32_t)kChunkBits) {
+        const uint64_t rest = c.lo >> j;
+        if (rest == 0) break;                          // only closing bits are left
+        j += (uint32_t)__builtin_ctzll(rest);          // the next code's flag
+        // the offset lies MSB first in the stream and may run into the next chunk
+        const uint32_t sh = j + 1;
+        uint64_t v = sh < 64 ? c.lo >> sh : 0;
+        if (sh + B > 64) v |= (uint64_t)c.hi << (64 - sh);               // B <= 31, so 64 - sh < 32
+        const uint32_t off = B ? __brev((uint32_t)v) >> (32 - B) : 0u;
+        const uint64_t closed = first_bit + j - (uint64_t)codes * (1 + B);
+        const uint64_t pos = closed * block_len + off;
+        if (codes < max_n && pos < (uint64_t)d) out[codes] = (uint32_t)pos;
+        ++codes;
+        j += 1 + B;
+    }
+}
+
+// Scratch of a row: chunk maps (per run of kTileChunks chunks [state][chunk]), group maps
+// (per run [group][state]), tile maps ([tile][state]).
+struct Scratch {
+    uint32_t* base;
+    uint64_t  chunk_words, group_words, tile_words;   // 32-bit words of each per row
+    __device__ uint32_t* chunks(uint32_t row, uint64_t run, uint32_t n_states) const
+    {
+        return base + (uint64_t)row * (chunk_words + group_words + tile_words) + run * (kTileChunks / 2) * n_states;
+    }
+    __device__ uint32_t* groups(uint32_t row, uint64_t run, uint32_t n_states) const
+    {
+        return chunks(row, 0, n_states) + chunk_words + run * kGroups * n_states;
+    }
+    __device__ uint32_t* tiles(uint32_t row, uint32_t n_states) const
+    {
+        return chunks(row, 0, n_states) + chunk_words + group_words;
+    }
+};
+
+// Workgroup (tile, row): the maps of the tile's `runs` runs of kTileChunks chunks, and the tile's.
+// `alone` (the row is one run): emits as well, nothing goes to scratch.
+template <int B>
+__global__ __launch_bounds__(kThreads) void codec_maps_kernel(
+    const uint32_t* __restrict__ streams, int64_t ld_words, const unsigned long long* __restrict__ n_bits,
+    uint64_t max_bits, uint64_t runs, Scratch scratch, int alone, int64_t d, uint32_t block_len,
+    uint32_t* __restrict__ idx_out, int64_t ld_idx, uint32_t max_n, uint32_t* __restrict__ counts_out)
+{
+    __shared__ TileLds lds;
+    __shared__ WalkLds walk;
+    constexpr uint32_t n_states = B + 1;
+    const uint32_t row = blockIdx.y, t = threadIdx.x;
+    // the received length is wire-side data: clamped to what the scratch was sized for
     const uint64_t total = min((uint64_t)n_bits[row], max_bits);
     const uint64_t n_chunks = (total + kChunkBits - 1) / kChunkBits;
     const uint32_t* words = streams + (int64_t)row * ld_words;
-    const uint32_t n_states = B + 1;
-    const MapTables tb = row_tables(maps, max_chunks, row);
-    for (uint64_t item = (uint64_t)blockIdx.x * kThreads + threadIdx.x; item < n_chunks * n_states;
-         item += (uint64_t)gridDim.x * kThreads) {
-        const uint64_t c = item / n_states;
-        const uint32_t s = (uint32_t)(item % n_states);
-        const uint64_t first = c * kChunkBits, last = min(first + kChunkBits, total);
-        const ChunkMap m = run_chunk(load_chunk(words, first, total), (uint32_t)(last - first), s, B);
-        tb.exit_state[item] = m.exit_state;      // compact: index = chunk * n_states + state
-        tb.codes[item] = m.codes;
-        tb.closed[item] = m.closed;
+    uint32_t tile_map = t;                        // thread t < n_states: the tile's map at entry state t so far
+    for (uint64_t run = blockIdx.x * runs; run < (blockIdx.x + 1) * runs; ++run) {
+        const uint64_t c0 = run * kTileChunks;
+        if (c0 >= n_chunks && !alone) break;      // uniform
+        const uint32_t n = (uint32_t)min((uint64_t)kTileChunks, n_chunks - c0);
+        ChunkBits bits = {0, 0};
+        if (t < n) {
+            bits = load_chunk(words, c0 + t, total);
+            chunk_map<B>(bits.lo, lds.chunk + t, n);
+        }
+        __syncthreads();
+        compose_groups(lds, n, n_states);
+        if (!alone) {
+            uint32_t* to = scratch.chunks(row, run, n_states);
+            const uint32_t* from = reinterpret_cast<const uint32_t*>(lds.chunk);
+            for (uint32_t i = t; i < (n * n_states + 1) / 2; i += kThreads) to[i] = from[i];
+        }
+        __syncthreads();
+        if (alone) {
+            const uint32_t end = walk_run(lds, walk, n, 0);
+            if (t < n) {
+                const uint32_t m = walk.chunk_entry[t];
+                emit_chunk(bits, (uint64_t)t * kChunkBits, map_exit(m), m >> 8, B, d, block_len,
+                           idx_out + (int64_t)row * ld_idx, max_n);
+            }
+            if (t == 0) counts_out[row] = end >> 8;
+            return;
+        }
+        uint32_t* to = scratch.groups(row, run, n_states);
+        for (uint32_t i = t; i < kGroups * n_states; i += kThreads) to[i] = lds.group[i / n_states][i % n_states];
+        if (t < n_states)
+            for (uint32_t g = 0; g < (uint32_t)kGroups; ++g) tile_map = carry(tile_map, lds.group[g][map_exit(tile_map)]);
+        __syncthreads();                          // the tables are free for the next run
     }
+    if (t < n_states) scratch.tiles(row, n_states)[(uint64_t)blockIdx.x * n_states + t] = tile_map;
 }
 
-struct Entry {                   // the parse at the start of a chunk
-    uint32_t state;
-    uint32_t codes;              // codes begun before the chunk
-    uint32_t closed;             // blocks closed before the chunk
+struct EmitLds {
+    TileLds  tile;
+    WalkLds  walk;
+    // 16 tiles composed: exit states, codes (which need not fit the 24 bits of a map entry)
+    uint8_t  tg_exit[kMaxTiles / kTileGroup][kMaxB + 1];
+    uint32_t tg_codes[kMaxTiles / kTileGroup][kMaxB + 1];
+    uint32_t entry_state, entry_codes;
 };
 
-constexpr int kExitLds = 24576;  // exit-state bytes staged in LDS when the row's table fits
-
-// One workgroup per row.  Thread t owns a contiguous range of chunks and composes
-// the range's exit states for every entry state; 32 threads compose 32 ranges each;
-// one thread walks the 32 groups from state 0; the true entry states then flow back
-// down the two levels, and every thread walks its range for real, counting the codes
-// and closed blocks before each chunk (a workgroup scan joins the ranges).
-__global__ __launch_bounds__(kWalkThreads) void codec_walk_kernel(
-    const unsigned long long* __restrict__ n_bits, uint64_t max_bits, uint32_t B, uint8_t* __restrict__ maps,
-    uint64_t max_chunks, Entry* __restrict__ entries, uint32_t* __restrict__ counts_out)
-{
-    __shared__ uint8_t  ex_lds[kExitLds];
-    __shared__ uint8_t  r_exit[kWalkThreads][kMaxB + 1];
-    __shared__ uint8_t  g_exit[32][kMaxB + 1];
-    __shared__ uint8_t  r_state[kWalkThreads];
-    __shared__ uint8_t  g_state[32];
-    __shared__ unsigned long long wave_sum[kWalkThreads / 64 + 1];
-    const uint32_t row = blockIdx.x, t = threadIdx.x;
-    const uint64_t total = min((uint64_t)n_bits[row], max_bits);
-    const uint64_t n_chunks = (total + kChunkBits - 1) / kChunkBits;
-    const uint64_t per = (n_chunks + kWalkThreads - 1) / kWalkThreads;
-    const uint64_t c0 = min((uint64_t)t * per, n_chunks), c1 = min(c0 + per, n_chunks);
-    const MapTables tb = row_tables(maps, max_chunks, row);
-    const uint32_t n_states = B + 1;
-    const bool staged = n_chunks * n_states <= (uint64_t)kExitLds;
-    if (staged)
-        for (uint64_t i = t; i < n_chunks * n_states; i += kWalkThreads) ex_lds[i] = tb.exit_state[i];
-    __syncthreads();
-    const uint8_t* ex = staged ? ex_lds : tb.exit_state;
-
-    for (uint32_t s = 0; s < n_states; ++s) {                 // range maps
-        uint32_t st = s;
-        for (uint64_t c = c0; c < c1; ++c) st = ex[c * n_states + st];
-        r_exit[t][s] = (uint8_t)st;
-    }
-    __syncthreads();
-    if (t < 32)                                               // group maps: 32 ranges each
-        for (uint32_t s = 0; s < n_states; ++s) {
-            uint32_t st = s;
-            for (uint32_t r = t * 32; r < t * 32 + 32; ++r) st = r_exit[r][st];
-            g_exit[t][s] = (uint8_t)st;
-        }
-    __syncthreads();
-    if (t == 0) {                                             // true entry state of every group
-        uint32_t st = 0;
-        for (uint32_t g = 0; g < 32; ++g) {
-            g_state[g] = (uint8_t)st;
-            st = g_exit[g][st];
-        }
-    }
-    __syncthreads();
-    if (t < 32) {                                             // ... of every range
-        uint32_t st = g_state[t];
-        for (uint32_t r = t * 32; r < t * 32 + 32; ++r) {
-            r_state[r] = (uint8_t)st;
-            st = r_exit[r][st];
-        }
-    }
-    __syncthreads();
-    // codes and closed blocks of the range on its true path, then their prefix over the ranges
-    uint32_t st = r_state[t], codes = 0, closed = 0;
-    for (uint64_t c = c0; c < c1; ++c) {
-        codes += tb.codes[c * n_states + st];
-        closed += tb.closed[c * n_states + st];
-        st = ex[c * n_states + st];
-    }
-    unsigned long long v = ((unsigned long long)codes << 32) | closed, incl = v;
-    const uint32_t lane = t & 63, wave = t / 64;
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned long long up = __shfl_up(incl, o, 64);
-        if (lane >= (uint32_t)o) incl += up;
-    }
-    if (lane == 63) wave_sum[wave] = incl;
-    __syncthreads();
-    if (t == 0) {
-        unsigned long long run = 0;
-        for (int w = 0; w < kWalkThreads / 64; ++w) {
-            const unsigned long long x = wave_sum[w];
-            wave_sum[w] = run;
-            run += x;
-        }
-        wave_sum[kWalkThreads / 64] = run;
-        counts_out[row] = (uint32_t)(run >> 32);
-    }
-    __syncthreads();
-    const unsigned long long before = wave_sum[wave] + incl - v;
-    Entry e;
-    e.state = r_state[t];
-    e.codes = (uint32_t)(before >> 32);
-    e.closed = (uint32_t)before;
-    for (uint64_t c = c0; c < c1; ++c) {                      // every chunk's entry
-        entries[(uint64_t)row * max_chunks + c] = e;
-        const uint64_t i = c * n_states + e.state;
-        e.codes += tb.codes[i];
-        e.closed += tb.closed[i];
-        e.state = ex[i];
-    }
-}
-
+// Workgroup (tile, row): the tile's entry from the maps of the tiles before it, then its chunks' entries
+// and their codes.  The row's last tile also knows how many codes there are.
 __global__ __launch_bounds__(kThreads) void codec_emit_kernel(
     const uint32_t* __restrict__ streams, int64_t ld_words, const unsigned long long* __restrict__ n_bits,
-    uint64_t max_bits, int64_t d, uint32_t block_len, uint32_t B, const Entry* __restrict__ entries,
-    uint64_t max_chunks, uint32_t* __restrict__ idx_out, int64_t ld_idx, uint32_t max_n)
+    uint64_t max_bits, uint64_t runs, Scratch scratch, uint32_t B, int64_t d, uint32_t block_len,
+    uint32_t* __restrict__ idx_out, int64_t ld_idx, uint32_t max_n, uint32_t* __restrict__ counts_out)
 {
-    const uint32_t row = blockIdx.y;
+    __shared__ EmitLds lds;
+    extern __shared__ uint32_t tile_maps[];       // gridDim.x * n_states
+    const uint32_t row = blockIdx.y, t = threadIdx.x, n_states = B + 1, tile = blockIdx.x;
     const uint64_t total = min((uint64_t)n_bits[row], max_bits);
     const uint64_t n_chunks = (total + kChunkBits - 1) / kChunkBits;
+    const uint64_t n_runs = (n_chunks + kTileChunks - 1) / kTileChunks;
+    if (n_runs == 0 && tile == 0 && t == 0) counts_out[row] = 0;
+    if (tile * runs >= n_runs) return;            // whole workgroup
     const uint32_t* words = streams + (int64_t)row * ld_words;
-    uint32_t* out = idx_out + (int64_t)row * ld_idx;
-    for (uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x; c < n_chunks; c += (uint64_t)gridDim.x * kThreads) {
-        Entry e = entries[(uint64_t)row * max_chunks + c];
-        const uint64_t first = c * kChunkBits;
-        const uint32_t len = (uint32_t)(min(first + kChunkBits, total) - first);
-        const uint64_t w = load_chunk(words, first, total);
-        uint32_t j = min(e.state, len);                                // rest of a code begun earlier
-        while (j < len) {
-            const uint64_t rest = w >> j;
-            const uint32_t zeros = rest ? (uint32_t)__builtin_ctzll(rest) : 64u;
-            const uint32_t run = min(zeros, len - j);
-            e.closed += run;
-            j += run;
-            if (j >= len) break;
-            // the offset lies MSB first in the stream and may run into the next chunk
-            const uint32_t field = B ? load_field(words, first + j + 1, B, total) : 0u;
-            const uint32_t off = B ? (__brev(field) >> (32 - B)) : 0u;
-            const uint64_t pos = (uint64_t)e.closed * block_len + off;
-            if (e.codes < max_n && pos < (uint64_t)d) out[e.codes] = (uint32_t)pos;
-            ++e.codes;
-            j += 1 + B;
+
+    // what the first run needs is fetched beside the tile maps
+    ChunkBits bits = {0, 0};
+    uint32_t  n = 0;
+    auto fetch_run = [&](uint64_t run) {
+        n = (uint32_t)min((uint64_t)kTileChunks, n_chunks - run * kTileChunks);
+        bits = t < n ? load_chunk(words, run * kTileChunks + t, total) : ChunkBits{0, 0};
+        const uint32_t* from = scratch.chunks(row, run, n_states);
+        uint32_t* to = reinterpret_cast<uint32_t*>(lds.tile.chunk);
+#pragma unroll 4
+        for (uint32_t i = t; i < (n * n_states + 1) / 2; i += kThreads) to[i] = from[i];
+        const uint32_t* groups = scratch.groups(row, run, n_states);
+        for (uint32_t i = t; i < kGroups * n_states; i += kThreads) lds.tile.group[i / n_states][i % n_states] = groups[i];
+    };
+    const uint32_t* maps = scratch.tiles(row, n_states);
+#pragma unroll 4
+    for (uint32_t i = t; i < tile * n_states; i += kThreads) tile_maps[i] = maps[i];
+    fetch_run(tile * runs);
+    __syncthreads();
+    const uint32_t n_tile_groups = tile / kTileGroup;
+    for (uint32_t i = t; i < n_tile_groups * n_states; i += kThreads) {
+        const uint32_t g = i / n_states, s = i % n_states;
+        uint32_t st = s, sum = 0;
+        for (uint32_t k = g * kTileGroup; k < (g + 1) * kTileGroup; ++k) {
+            const uint32_t m = tile_maps[k * n_states + st];
+            sum += m >> 8;
+            st = map_exit(m);
         }
+        lds.tg_exit[g][s] = (uint8_t)st;
+        lds.tg_codes[g][s] = sum;
     }
+    __syncthreads();
+    if (t == 0) {
+        uint32_t st = 0, sum = 0;
+        for (uint32_t g = 0; g < n_tile_groups; ++g) {
+            sum += lds.tg_codes[g][st];
+            st = lds.tg_exit[g][st];
+        }
+        for (uint32_t k = n_tile_groups * kTileGroup; k < tile; ++k) {
+            const uint32_t m = tile_maps[k * n_states + st];
+            sum += m >> 8;
+            st = map_exit(m);
+        }
+        lds.entry_state = st;
+        lds.entry_codes = sum;
+    }
+    __syncthreads();
+    uint32_t state = lds.entry_state, codes = lds.entry_codes;
+    for (uint64_t run = tile * runs;;) {
+        const uint32_t end = walk_run(lds.tile, lds.walk, n, state);
+        if (t < n) {
+            const uint32_t m = lds.walk.chunk_entry[t];
+            emit_chunk(bits, (run * kTileChunks + t) * kChunkBits, map_exit(m), codes + (m >> 8), B, d, block_len,
+                       idx_out + (int64_t)row * ld_idx, max_n);
+        }
+        state = map_exit(end);
+        codes += end >> 8;
+        if (++run >= n_runs) {
+            if (t == 0) counts_out[row] = codes;
+            return;
+        }
+        if (run == (tile + 1) * runs) return;
+        __syncthreads();                          // the tables are free for the next run
+        fetch_run(run);
+        __syncthreads();
+    }
+}
+
+// Host side of the scratch: 108 bytes per chunk is what mv_codec_scratch_bytes counts.  Used are, with
+// S <= 32 states: 2 S bytes per chunk, and 4 (kGroups + 1) S bytes per run of 256 chunks (rounded up),
+// at most 64 c + 2176 (c / 256 + 1) < 108 c for the c > 256 chunks of a stream that needs scratch.
+constexpr uint64_t kScratchPerChunk = 108;
+
+// the instance of codec_maps_kernel for this B, 0 .. kMaxB
+template <int... Bs, typename... Args>
+void launch_maps(uint32_t B, std::integer_sequence<int, Bs...>, dim3 grid, hipStream_t st, Args... args)
+{
+    (void)((B == (uint32_t)Bs
+                ? (codec_maps_kernel<Bs><<<grid, dim3(kThreads), 0, st>>>(args...), true)
+                : false) || ...);
 }
 
 }  // namespace mvc
@@ -335,7 +405,7 @@ size_t mv_codec_scratch_bytes(uint64_t max_bits, int32_t rows)
 {
     if (rows < 1) return 0;
     const uint64_t chunks = (max_bits + mvc::kChunkBits - 1) / mvc::kChunkBits;
-    return (size_t)rows * chunks * (3 * (mvc::kMaxB + 1) + sizeof(mvc::Entry)) + 512;
+    return (size_t)rows * chunks * mvc::kScratchPerChunk + 512;
 }
 
 mv_status mv_codec_encode(const uint32_t* idx, int64_t ld_idx, const uint32_t* counts, int64_t counts_stride,
@@ -394,24 +464,26 @@ static mv_status decode_with_scratch(const uint32_t* streams, int64_t ld_words, 
                                      void* scratch, void* stream)
 {
     const uint64_t max_chunks = (max_bits + mvc::kChunkBits - 1) / mvc::kChunkBits;
+    const uint64_t max_runs = (max_chunks + mvc::kTileChunks - 1) / mvc::kTileChunks;
+    const uint64_t runs = (max_runs + mvc::kMaxTiles - 1) / mvc::kMaxTiles;      // per tile
+    const uint32_t tiles = (uint32_t)((max_runs + runs - 1) / runs);
+    const uint32_t B = (uint32_t)mvc::offset_bits(block_len), n_states = B + 1;
     uintptr_t base = (reinterpret_cast<uintptr_t>(scratch) + 255) & ~(uintptr_t)255;
-    uint8_t* maps = reinterpret_cast<uint8_t*>(base);
-    const size_t maps_bytes = ((size_t)rows * max_chunks * 3 * (mvc::kMaxB + 1) + 255) & ~(size_t)255;
-    mvc::Entry* entries = reinterpret_cast<mvc::Entry*>(base + maps_bytes);
-    const uint32_t B = (uint32_t)mvc::offset_bits(block_len);
+    mvc::Scratch sc;
+    sc.base = reinterpret_cast<uint32_t*>(base);
+    sc.chunk_words = (max_chunks * n_states + 1) / 2;
+    sc.group_words = max_runs * mvc::kGroups * n_states;
+    sc.tile_words = (uint64_t)tiles * n_states;
+    const int alone = max_runs == 1;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const unsigned long long* nb = reinterpret_cast<const unsigned long long*>(n_bits);
-    uint64_t bx = (max_chunks * (B + 1) + mvc::kThreads - 1) / mvc::kThreads;
-    if (bx > 4096) bx = 4096;
-    hipLaunchKernelGGL(mvc::codec_chunk_maps_kernel, dim3((uint32_t)bx, (uint32_t)rows), dim3(mvc::kThreads), 0, st,
-                       streams, ld_words, nb, max_bits, B, maps, max_chunks);
-    hipLaunchKernelGGL(mvc::codec_walk_kernel, dim3((uint32_t)rows), dim3(mvc::kWalkThreads), 0, st, nb, max_bits, B,
-                       maps, max_chunks, entries, counts_out);
-    uint64_t bx2 = (max_chunks + mvc::kThreads - 1) / mvc::kThreads;
-    if (bx2 > 4096) bx2 = 4096;
-    hipLaunchKernelGGL(mvc::codec_emit_kernel, dim3((uint32_t)bx2, (uint32_t)rows), dim3(mvc::kThreads), 0, st,
-                       streams, ld_words, nb, max_bits, d, (uint32_t)block_len, B, entries, max_chunks, idx_out,
-                       ld_idx, (uint32_t)max_n);
+    const dim3 grid(tiles, (uint32_t)rows);
+    mvc::launch_maps(B, std::make_integer_sequence<int, mvc::kMaxB + 1>(), grid, st, streams, ld_words, nb, max_bits,
+                     runs, sc, alone, d, (uint32_t)block_len, idx_out, ld_idx, (uint32_t)max_n, counts_out);
+    if (!alone)
+        hipLaunchKernelGGL(mvc::codec_emit_kernel, grid, dim3(mvc::kThreads), tiles * n_states * 4, st, streams,
+                           ld_words, nb, max_bits, runs, sc, B, d, (uint32_t)block_len, idx_out, ld_idx,
+                           (uint32_t)max_n, counts_out);
     return hipGetLastError() == hipSuccess ? MV_OK : MV_ERR_DEVICE;
 }
 

@@ -74,6 +74,18 @@ def test_codec_random_lists(oracle, d, L, n, rows):
     gpu_codec_round_trip(oracle, lists, d, L, n)
 
 
+@pytest.mark.parametrize("d,L,n,rows", [(100000, 100, 1923, 2), (100000, 100, 1924, 2), (11173962, 100, 111740, 2),
+                                        (2147483647, (1 << 30) + 1, 511, 1), (2147483647, (1 << 30) + 1, 1600, 2),
+                                        (300001, 2, 150000, 2), (4000003, 1, 1000001, 2), (90000, 1, 90000, 1)])
+def test_codec_tiles(oracle, d, L, n, rows):
+    """Around the decoder's cuts of a stream: 16,384 bits (one workgroup, one launch), 16 and 256 tiles of that size
+    (beyond 256 a workgroup takes several), with the shortest and the longest offsets (0 and 31 bits)."""
+    say("codec tiles d=%d block=%d n=%d rows=%d" % (d, L, n, rows))
+    rng = np.random.default_rng(d + n)
+    lists = [np.sort(rng.choice(d, n if r == 0 else n - n // 3, replace=False)).astype(np.uint32) for r in range(rows)]
+    gpu_codec_round_trip(oracle, lists, d, L, n)
+
+
 def test_codec_clustered_lists(oracle):
     d, L = 300000, 128
     say("codec clustered")
