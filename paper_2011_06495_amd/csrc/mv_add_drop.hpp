@@ -29,13 +29,13 @@ namespace mvk {
 __device__ __forceinline__ uint32_t reserve_in_list(uint32_t n_mine, uint32_t* __restrict__ counter,
                                                     uint64_t* scan_lds, uint32_t* bcast)
 {
-    uint64_t total;
-    const uint64_t ex = block_excl_scan64<kVoteThreads>(n_mine, scan_lds, total);
-    if (threadIdx.x == 0) bcast[0] = total ? atomicAdd(counter, (uint32_t)total) : 0u;
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kVoteThreads>(n_mine, scan_lds, total);
+    if (threadIdx.x == 0) bcast[0] = total ? atomicAdd(counter, total) : 0u;
     __syncthreads();
     const uint32_t base = bcast[0];
     __syncthreads();
-    return base + (uint32_t)ex;
+    return base + ex;
 }
 
 __device__ __forceinline__ bool vote_bit(const uint32_t* __restrict__ bits_row, uint32_t j)
@@ -124,15 +124,15 @@ __device__ __forceinline__ void ad_collect_drop_block(
         }
         n_bits += __popc(w[it][0]) + __popc(w[it][1]) + __popc(w[it][2]) + __popc(w[it][3]);
     }
-    uint64_t total;
-    const uint64_t ex = block_excl_scan64<kVoteThreads>(n_bits, scan_lds, total);
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kVoteThreads>(n_bits, scan_lds, total);
     if (total == 0) return;                                  // whole workgroup
     u32x2* drow = d_list + (size_t)row * cap_d;
     // The members' coordinates are parked in LDS (kDropStage at a time; one round unless the
     // stretch is crowded with votes) and their values then fetched by all lanes together,
     // instead of one dependent load per set bit inside each thread's own loop.
     auto one_round = [&](const uint32_t c0) {
-        uint32_t sp = (uint32_t)ex;
+        uint32_t sp = ex;
 #pragma unroll
         for (int it = 0; it < kBitIt; ++it) {
             const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + t) * 4;
@@ -148,7 +148,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
             }
         }
         __syncthreads();
-        const uint32_t cnt = min((uint32_t)kDropStage, (uint32_t)total - c0);
+        const uint32_t cnt = min((uint32_t)kDropStage, total - c0);
         constexpr int kRounds = kDropStage / kVoteThreads;
         u32x2 c[kRounds];
         uint32_t n_keep = 0, keep = 0;
@@ -179,10 +179,10 @@ __device__ __forceinline__ void ad_collect_drop_block(
             }
         }
     };
-    if (total <= (uint64_t)kDropStage) {                     // uniform; the usual case
+    if (total <= (uint32_t)kDropStage) {                     // uniform; the usual case
         one_round(0u);
     } else {
-        for (uint32_t c0 = 0; c0 < (uint32_t)total; c0 += kDropStage) one_round(c0);
+        for (uint32_t c0 = 0; c0 < total; c0 += kDropStage) one_round(c0);
     }
 }
 

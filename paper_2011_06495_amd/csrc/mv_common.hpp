@@ -36,49 +36,78 @@ constexpr int      kFineShift      = 12;     // 2048 bins of 4096 bit patterns =
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & (kWave - 1); }
 
+// Scans over the lanes of a wavefront by DPP moves (row shifts inside 16 lanes, then the two row
+// broadcasts): adds that read a neighbour's register, where a shuffle goes through the LDS crossbar.
+// The step's small kernels are chains of such scans: with shuffles, and a second barrier in the
+// workgroup's scan, a step of 4 x 10,007 coordinates took 38.8 us and one of 4 x 2^20 62.2 us; so
+// they take 35.2 and 58.5.  All lanes of the wavefront must be active.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+// inclusive sums inside every row of 16 lanes
+__device__ __forceinline__ uint32_t row_incl_scan(uint32_t v)
+{
+    v += dpp_or_zero<0x111, 0xf>(v);              // row_shr:1, :2, :4, :8
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);
+    return v;
+}
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        uint32_t t = __shfl_up(v, o, kWave);
-        if (lane >= (uint32_t)o) v += t;
-    }
+    v = row_incl_scan(v);
+    v += dpp_or_zero<0x142, 0xa>(v);              // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xc>(v);              // row_bcast:31 into rows 2 and 3
     return v;
 }
+// lane `l`'s value in every lane (l uniform)
+__device__ __forceinline__ uint32_t from_lane(uint32_t v, uint32_t l)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+}
 
+__device__ __forceinline__ uint64_t pack2(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
+
+// a pair of 32-bit counts whose sums stay below 2^32: no carry between the halves
 __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v)
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        uint64_t t = __shfl_up((unsigned long long)v, o, kWave);
-        if (lane >= (uint32_t)o) v += t;
-    }
-    return v;
+    return pack2(wave_incl_scan((uint32_t)(v >> 32)), wave_incl_scan((uint32_t)v));
 }
 
-// Exclusive scan of one 64-bit value per thread over the whole workgroup
-// (thread order).  `lds` holds NT/64 + 1 entries.  Returns the exclusive prefix;
-// `total` receives the workgroup sum.  Ends with the LDS scratch free to reuse
-// only after the caller's next __syncthreads().
+// Exclusive scan of one value per thread over the whole workgroup (thread order),
+// one barrier.  `lds` holds at least NT/64 entries.  Returns the exclusive prefix;
+// `total` receives the workgroup sum.  The LDS scratch is free to reuse only after
+// the caller's next __syncthreads().
+template <int NT>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint64_t* lds, uint32_t& total)
+{
+    constexpr int NW = NT / kWave;
+    static_assert(NW <= 16, "the wavefronts' sums are scanned in one row of lanes");
+    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t incl = wave_incl_scan(v);
+    if (lane == kWave - 1) lds[wave] = incl;
+    __syncthreads();
+    const uint32_t w = row_incl_scan(lane < (uint32_t)NW ? (uint32_t)lds[lane] : 0u);
+    total = from_lane(w, NW - 1);
+    return (wave ? from_lane(w, wave - 1) : 0u) + incl - v;
+}
+// the same for a pair of 32-bit counts (pack2) whose sums stay below 2^32
 template <int NT>
 __device__ __forceinline__ uint64_t block_excl_scan64(uint64_t v, uint64_t* lds, uint64_t& total)
 {
     constexpr int NW = NT / kWave;
-    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
-    uint64_t incl = wave_incl_scan64(v);
+    static_assert(NW <= 16, "the wavefronts' sums are scanned in one row of lanes");
+    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint64_t incl = wave_incl_scan64(v);
     if (lane == kWave - 1) lds[wave] = incl;
     __syncthreads();
-    if (wave == 0) {
-        uint64_t w = (lane < (uint32_t)NW) ? lds[lane] : 0;
-        uint64_t wi = wave_incl_scan64(w);
-        if (lane < (uint32_t)NW) lds[lane] = wi - w;
-        if (lane == (uint32_t)NW - 1) lds[NW] = wi;
-    }
-    __syncthreads();
-    total = lds[NW];
-    return lds[wave] + incl - v;
+    const uint64_t mine = lane < (uint32_t)NW ? lds[lane] : 0u;
+    const uint32_t hi = row_incl_scan((uint32_t)(mine >> 32)), lo = row_incl_scan((uint32_t)mine);
+    total = pack2(from_lane(hi, NW - 1), from_lane(lo, NW - 1));
+    const uint64_t before = wave ? pack2(from_lane(hi, wave - 1), from_lane(lo, wave - 1)) : 0u;
+    return before + incl - v;
 }
 
 // f(std::integral_constant<int, I>) for I = A .. B-1, unrolled at compile time
@@ -90,8 +119,6 @@ __device__ __forceinline__ void static_for(F&& f)
         static_for<A + 1, B>(f);
     }
 }
-
-__device__ __forceinline__ uint64_t pack2(uint32_t hi, uint32_t lo) { return ((uint64_t)hi << 32) | lo; }
 
 // bin of a candidate's magnitude key (>= tau) in the row's fine histogram; order preserving
 __device__ __forceinline__ uint32_t fine_bin(uint32_t key, uint32_t tau)

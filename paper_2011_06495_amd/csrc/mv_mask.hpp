@@ -52,39 +52,47 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_votes(
 // mv_gather_update turns the counts of the earlier stretches into positions: each of
 // its workgroups emits the part of the mask it gathers.
 
-// All threads of the workgroup: vstar / take_eq from the level counters.
+// All threads of the workgroup: vstar / take_eq from the level counters.  Thread v has level v: which
+// level the K-th falls into is one comparison per thread, not a walk down the levels one by one.
 __device__ __forceinline__ void vote_threshold(const uint32_t* __restrict__ lvl_sets, uint32_t N, uint32_t K,
                                                uint32_t* lvl /*LDS, 256*/, uint32_t* thr /*LDS, 2*/,
-                                               uint32_t& vstar, uint32_t& take_eq, int exact_levels)
+                                               uint64_t* scan_lds, uint32_t& vstar, uint32_t& take_eq,
+                                               int exact_levels)
 {
-    if (threadIdx.x < 256) {                      // thread v adds up level v's sets, all loads in flight together
+    const uint32_t t = threadIdx.x;
+    // exact_levels: thread t has level N - t (t < N), so that the scan runs from the top down
+    const uint32_t v = exact_levels ? (t < N ? N - t : 256u) : t;
+    uint32_t sum = 0;
+    if (t < 256) {                                // the level's sets are added up, all loads in flight together
         uint32_t c[kLvlSets];
-        const uint32_t v = threadIdx.x;
 #pragma unroll
         for (int q = 0; q < kLvlSets; ++q) c[q] = (v <= N) ? lvl_sets[(size_t)q * 256 + v] : 0u;
-        uint32_t sum = 0;
 #pragma unroll
         for (int q = 0; q < kLvlSets; ++q) sum += c[q];
-        lvl[v] = sum;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        if (exact_levels) {
-            // coordinates with EXACTLY v votes, v = 1..N: walk down from N until K coordinates are
-            // covered; level 0 (every other coordinate) covers whatever is left
-            uint32_t above = 0, v = N;
-            while (v > 0 && above + lvl[v] < K) {
-                above += lvl[v];
-                --v;
-            }
+    if (exact_levels) {
+        // coordinates with EXACTLY v votes, v = N..1: the level at which K coordinates are covered from the
+        // top; level 0 (every other coordinate) covers whatever is left
+        uint32_t total;
+        const uint32_t above = block_excl_scan<kMaskThreads>(sum, scan_lds, total);
+        if (above < K && K <= above + sum) {
             thr[0] = v;
             thr[1] = K - above;
-        } else {
-            // coordinates with AT LEAST v votes; at least K coordinates hold a vote
-            uint32_t v = N;
-            while (v > 1 && lvl[v] < K) --v;
-            thr[0] = v;
-            thr[1] = K - ((v < N) ? lvl[v + 1] : 0u);
+        }
+        if (t == 0 && total < K) {
+            thr[0] = 0;
+            thr[1] = K - total;
+        }
+    } else {
+        // coordinates with AT LEAST v votes, v = 1..N; at least K coordinates hold a vote
+        if (t < 256) lvl[t] = sum;
+        __syncthreads();
+        if (t >= 1 && t <= N) {
+            const uint32_t above = t < N ? lvl[t + 1] : 0u;
+            if (above < K && (sum >= K || t == 1)) {
+                thr[0] = t;
+                thr[1] = K - above;
+            }
         }
     }
     __syncthreads();
@@ -132,16 +140,16 @@ __device__ __forceinline__ void seg_scan_part(const uint32_t* __restrict__ ssel,
         v[q] = (s0 + q < nseg) ? ssel[s0 + q] : 0u;
         sum += v[q];
     }
-    uint64_t total;
-    uint64_t ex = block_excl_scan64<kMaskThreads>(sum, scan_lds, total);
-    if ((t & 255u) == 0u) bound[t >> 8] = (uint32_t)ex;      // threads 256 k .. 256 k + 255 hold block k of the four
-    if (t == 0) bound[4] = (uint32_t)total;
+    uint32_t total;
+    uint32_t ex = block_excl_scan<kMaskThreads>(sum, scan_lds, total);
+    if ((t & 255u) == 0u) bound[t >> 8] = ex;                // threads 256 k .. 256 k + 255 hold block k of the four
+    if (t == 0) bound[4] = total;
     __syncthreads();
     const uint32_t k = t >> 8;
     ex -= bound[k];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        if (s0 + q < nseg) spre[s0 + q] = (uint32_t)ex;
+        if (s0 + q < nseg) spre[s0 + q] = ex;
         ex += v[q];
     }
     if ((t & 255u) == 0u && part * 4u + k < (nseg + 1023u) / 1024u) blk_total[part * 4u + k] = bound[k + 1] - bound[k];
@@ -196,7 +204,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         w[q] = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;   // padded to 16 bytes with zeros
     }
     uint32_t vstar, take_eq;
-    vote_threshold(lvl_sets, N, K, lvl, thr, vstar, take_eq, exact_levels);
+    vote_threshold(lvl_sets, N, K, lvl, thr, scan_lds, vstar, take_eq, exact_levels);
     uint32_t ww[4 * Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -213,15 +221,17 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     }
     uint32_t gt, eq;
     count_above_and_at<Q>(ww, j0, d, vstar, gt, eq);
-    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
+    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;   // (vote_threshold ended with a barrier)
     const uint64_t both = pack2(gt, eq);
     uint64_t block_total;
     const uint64_t ex = block_excl_scan64<kMaskThreads>(both, scan_lds, block_total);   // before this thread, in the block
     {
         // the counts per wavefront stretch and per block: what mv_gather_update scans when the
         // mask could not be written here
-        const uint64_t stretch = (uint64_t)__shfl((unsigned long long)(ex + both), kWave - 1, kWave) -
-                                 (uint64_t)__shfl((unsigned long long)ex, 0, kWave);
+        const uint64_t incl = ex + both;
+        const uint64_t stretch =
+            pack2(from_lane((uint32_t)(incl >> 32), kWave - 1) - from_lane((uint32_t)(ex >> 32), 0),
+                  from_lane((uint32_t)incl, kWave - 1) - from_lane((uint32_t)ex, 0));
         if (lane == 0) {
             u32x2 r;
             r.x = (uint32_t)(stretch >> 32);
@@ -289,8 +299,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         uint64_t before = 0;
 #pragma unroll
         for (int r = 0; r <= kPer; ++r) before += counts_of(w[r]);
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) before += (uint64_t)__shfl_xor((unsigned long long)before, o, kWave);
+        before = wave_incl_scan64(before);
+        before = pack2(from_lane((uint32_t)(before >> 32), kWave - 1), from_lane((uint32_t)before, kWave - 1));
         if (lane == 0) {
             if (found)
                 __hip_atomic_store(&lookback[2 * me + 1], word_of(before + block_total), __ATOMIC_RELAXED,
@@ -354,11 +364,11 @@ __device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, u
             v[q] = (b < scan_blocks) ? blk_total[b] : 0u;
             sum += v[q];
         }
-        uint64_t total;
-        uint64_t ex = block_excl_scan64<kMaskThreads>(sum, scan_lds, total);
+        uint32_t total;
+        uint32_t ex = block_excl_scan<kMaskThreads>(sum, scan_lds, total);
 #pragma unroll
         for (int q = 0; q < per; ++q) {
-            blk_pre[threadIdx.x * per + q] = (uint32_t)ex;
+            blk_pre[threadIdx.x * per + q] = ex;
             ex += v[q];
         }
         __syncthreads();

@@ -56,12 +56,12 @@ __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __res
 #pragma unroll
         for (int q = 0; q < 16; ++q) n += ((ww[q >> 2] >> (8 * (q & 3))) & 255u) != 0u;
     }
-    uint64_t total;
-    const uint64_t ex = block_excl_scan64<kVoteThreads>(n, scan_lds, total);
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kVoteThreads>(n, scan_lds, total);
     if (total == 0) return;                                        // whole workgroup
-    if (threadIdx.x == 0) base_sh = atomicAdd(&rs_count[0], (uint32_t)total);
-    if (total <= (uint64_t)kPerIt) {                               // uniform; usual case: one round for the whole block
-        uint32_t sp = (uint32_t)ex;
+    if (threadIdx.x == 0) base_sh = atomicAdd(&rs_count[0], total);
+    if (total <= (uint32_t)kPerIt) {                               // uniform; usual case: one round for the whole block
+        uint32_t sp = ex;
         if (n) {
 #pragma unroll
             for (int it = 0; it < kIt; ++it) {
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __res
         }
         __syncthreads();
         const uint32_t at = base_sh;
-        for (uint32_t i = threadIdx.x; i < (uint32_t)total; i += kVoteThreads) {
+        for (uint32_t i = threadIdx.x; i < total; i += kVoteThreads) {
             const uint32_t s = stage[i];
             if (at + i < list_cap) list[at + i] = rs_entry(rand_exp, (uint32_t)base + (s >> 8), s & 255u);
         }
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __res
         uint32_t n_it = 0;
 #pragma unroll
         for (int q = 0; q < 16; ++q) n_it += ((ww[q >> 2] >> (8 * (q & 3))) & 255u) != 0u;
-        uint64_t round_total;
-        uint32_t sp = (uint32_t)block_excl_scan64<kVoteThreads>(n_it, scan_lds, round_total);
+        uint32_t round_total;
+        uint32_t sp = block_excl_scan<kVoteThreads>(n_it, scan_lds, round_total);
         if (n_it) {
             const uint32_t off0 = ((uint32_t)it * kVoteThreads + threadIdx.x) * 16;   // offset in the block
             for (int q = 0; q < 16; ++q) {
@@ -105,11 +105,11 @@ __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __res
             }
         }
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < (uint32_t)round_total; i += kVoteThreads) {
+        for (uint32_t i = threadIdx.x; i < round_total; i += kVoteThreads) {
             const uint32_t s = stage[i];
             if (first + i < list_cap) list[first + i] = rs_entry(rand_exp, (uint32_t)base + (s >> 8), s & 255u);
         }
-        first += (uint32_t)round_total;
+        first += round_total;
         __syncthreads();
     }
 }

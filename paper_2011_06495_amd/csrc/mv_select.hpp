@@ -60,15 +60,15 @@ __device__ __forceinline__ void find_rank_bin(const uint32_t* hist, uint64_t* sc
         for (int r = 0; r < REP; ++r) h[q] += hist[b * REP + r];
         s += h[q];
     }
-    uint64_t total;
-    const uint64_t ex = block_excl_scan64<kRowThreads>(s, scan_lds, total);
-    if (ex < want && (uint64_t)want <= ex + s) {
-        uint64_t acc = ex;
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kRowThreads>(s, scan_lds, total);
+    if (ex < want && want <= ex + s) {
+        uint32_t acc = ex;
 #pragma unroll
         for (int q = 0; q < per; ++q) {
-            if (acc < want && (uint64_t)want <= acc + h[q]) {
+            if (acc < want && want <= acc + h[q]) {
                 bcast[0] = (uint32_t)(BINS - 1 - ((int)threadIdx.x * per + q));
-                bcast[1] = want - (uint32_t)acc;
+                bcast[1] = want - acc;
                 bcast[2] = h[q];
             }
             acc += h[q];
@@ -616,8 +616,8 @@ __device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, c
         // the members' list positions, in no particular order: count, scan, place
         uint32_t mine = 0;
         bins.each(C, [&](uint32_t b, uint32_t) { mine += (b == bin); });
-        uint64_t total;
-        uint32_t p = (uint32_t)block_excl_scan64<kRowThreads>(mine, lds.scan, total);
+        uint32_t total;
+        uint32_t p = block_excl_scan<kRowThreads>(mine, lds.scan, total);
         if (mine) bins.each(C, [&](uint32_t b, uint32_t i) { if (b == bin) mpos[p++] = i; });
     }
     __syncthreads();
@@ -1006,12 +1006,12 @@ __device__ __forceinline__ void list_split_body(const ListSelect& a, uint32_t ro
         if (bits && valid && b > bin) atomicOr(&bits[c[u].y >> 5], 1u << (c[u].y & 31u));
         mine += (valid && b == bin);
     }
-    uint64_t total;
-    const uint64_t ex = block_excl_scan64<kRowThreads>(mine, lds.scan, total);
+    uint32_t total;
+    const uint32_t ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
     if (total == 0) return;                                          // whole workgroup
-    if (t == 0) lds.base_sh = atomicAdd(&a.count2[row], (uint32_t)total);
+    if (t == 0) lds.base_sh = atomicAdd(&a.count2[row], total);
     __syncthreads();
-    uint32_t pos = lds.base_sh + (uint32_t)ex;
+    uint32_t pos = lds.base_sh + ex;
     u32x2* list2 = a.list2 + (size_t)row * a.cap;
 #pragma unroll
     for (int u = 0; u < kListPerThread; ++u) {

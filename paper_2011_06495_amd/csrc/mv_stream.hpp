@@ -143,13 +143,13 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
 #pragma unroll
     for (int q = 0; q < per; ++q) sum += c[q];
     if (t == 0) lds.found = 0;
-    uint64_t total;
-    const uint64_t excl = block_excl_scan64<kStreamThreads>(sum, lds.scan, total);
-    if (excl < m_target && (uint64_t)m_target <= excl + sum) {
-        uint64_t acc = excl;
+    uint32_t total;
+    const uint32_t excl = block_excl_scan<kStreamThreads>(sum, lds.scan, total);
+    if (excl < m_target && m_target <= excl + sum) {
+        uint32_t acc = excl;
 #pragma unroll
         for (int q = 0; q < per; ++q) {
-            if (acc < m_target && (uint64_t)m_target <= acc + c[q])
+            if (acc < m_target && m_target <= acc + c[q])
                 lds.found = (uint32_t)(kHistBins - 1 - ((int)t * per + q)) << kHistShift;
             acc += c[q];
         }
@@ -293,11 +293,14 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     const bool any = __ballot(flags != 0) != 0ull;       // wave-uniform
     if (any) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t c = __popc((flags >> (4 * u)) & 15u);
-            const uint32_t incl = wave_incl_scan(c);
-            rank[u] = total + incl - c;
-            total += __shfl(incl, kWave - 1, kWave);
+        for (int u = 0; u < 4; u += 2) {          // two sub-blocks' counts (at most 256 each) to a word
+            const uint32_t c0 = __popc((flags >> (4 * u)) & 15u), c1 = __popc((flags >> (4 * u + 4)) & 15u);
+            const uint32_t incl = wave_incl_scan(c0 | c1 << 16);
+            const uint32_t sums = from_lane(incl, kWave - 1);
+            rank[u] = total + (incl & 0xFFFFu) - c0;
+            total += sums & 0xFFFFu;
+            rank[u + 1] = total + (incl >> 16) - c1;
+            total += sums >> 16;
         }
     }
     // one reservation for the workgroup's 8 runs
