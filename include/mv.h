@@ -240,6 +240,7 @@ mv_status mv_step_kernel_ms(mv_ctx* ctx, int32_t steps_back, float* ms, int32_t 
  * fine histogram, 2 = the generic select over the candidates, 1 = the slow exact
  * path over the whole row in memory).  A cand_count with its top bit set marks a row
  * whose wavefronts did not all see the threshold in time (see mv_set_spin_limit).
+ * Rows of at most 32,768 coordinates are selected without an estimate: d, 0 and 0.
  * HOST arrays of N uint32 each; any may be NULL.
  */
 mv_status mv_last_step_row_stats(mv_ctx* ctx, uint32_t* cand_count,

@@ -34,6 +34,9 @@ enum KernelId {
     KID_RS_HIST,
     KID_RS_SPLIT,
     KID_RS_RANK,
+    // short vectors only, in place of all the others
+    KID_SMALL_ROWS,
+    KID_SMALL_MASK,
     KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
@@ -41,7 +44,8 @@ const char* const kKernelNames[KID_COUNT] = {
     "mv_mask_count",     "mv_gather_update",    "mv_ad_collect",      "mv_ad_select",
     "mv_ad_apply",       "mv_ad_compact_count", "mv_ad_compact_emit",
     "mv_sel_hist",       "mv_sel_split",       "mv_sel_rank",
-    "mv_rs_keys",        "mv_rs_hist",         "mv_rs_split",         "mv_rs_rank"};
+    "mv_rs_keys",        "mv_rs_hist",         "mv_rs_split",         "mv_rs_rank",
+    "mv_small_rows",     "mv_small_mask"};
 
 constexpr size_t kAlign = 256;
 constexpr int kEventRing = 64;   // steps whose kernel durations stay readable
@@ -462,7 +466,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     for (int i = 0; i < KID_COUNT; ++i) c->ev_recorded[slot][i] = false;
     const int prof = c->profiling;
     bool ev_ok = true;
-    auto wanted = [&](int kid) { return prof >= 2 || (prof == 1 && kid == KID_STREAM); };
+    auto wanted = [&](int kid) { return prof >= 2 || (prof == 1 && (kid == KID_STREAM || kid == KID_SMALL_ROWS)); };
     auto before = [&](int kid) {
         if (!wanted(kid)) return;
         for (int j = 0; j < 2; ++j)   // events are created on first use
@@ -473,6 +477,65 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         if (!wanted(kid) || !ev_ok) return;
         if (hipEventRecord(c->ev[slot][kid][1], st) == hipSuccess) c->ev_recorded[slot][kid] = true;
     };
+
+    // the step ends here: nothing was left out, or the context is given up
+    auto finish = [&]() {
+        c->last_stream = st;
+        c->steps_done += 1;
+        if (hipGetLastError() != hipSuccess) {
+            // Some kernel of the sequence was not launched: counters that every step leaves at zero, and the
+            // step's number on the device, may be off.  The context refuses further steps.
+            c->broken = true;
+            return MV_ERR_DEVICE;
+        }
+        return ev_ok ? MV_OK : MV_ERR_DEVICE;
+    };
+
+    // Short vectors: two launches for any scheme.  (Every step of a context takes the same way, so the two
+    // ways' scratch need not agree: the rows' bitmaps lie where long vectors have their candidate lists.)
+    if (p.d <= mvk::kSmallMaxD) {
+        const uint32_t d = (uint32_t)p.d;
+        uint32_t* row_bits = ws_ptr<uint32_t>(c, p.off_cand);
+        mvk::SmallAddDrop ad;
+        memset(&ad, 0, sizeof ad);
+        if (add_drop) {
+            ad.vote_bits = a.vote_bits;  ad.ld_bits = a.ld_bits;
+            ad.msum32 = reinterpret_cast<uint32_t*>(a.msum);
+            ad.k_ad = (uint32_t)a.k_ad;  ad.add_idx = a.add_idx;  ad.drop_idx = a.drop_idx;  ad.counts = a.counts;
+        }
+        before(KID_SMALL_ROWS);
+#define MV_LAUNCH_SMALL_ROWS(GT, U)                                                                              \
+        hipLaunchKernelGGL((mvk::mv_small_rows<GT, U>), dim3(p.N), dim3(mvk::kSmallThreads), 0, st,               \
+                           static_cast<const GT*>(a.grads), a.ld_g, a.err, a.ld_e, d, p.K,                        \
+                           add_drop ? (uint32_t*)nullptr : a.worker_idx, row_bits, p.nwords, rowcnt, tau, slow, ad)
+        const uint32_t quads = (d + 4 * mvk::kSmallThreads - 1) / (4 * mvk::kSmallThreads);   // per thread
+        if (bf16) {
+            if (quads <= 1) MV_LAUNCH_SMALL_ROWS(uint16_t, 1);
+            else if (quads <= 2) MV_LAUNCH_SMALL_ROWS(uint16_t, 2);
+            else if (quads <= 4) MV_LAUNCH_SMALL_ROWS(uint16_t, 4);
+            else MV_LAUNCH_SMALL_ROWS(uint16_t, 8);
+        } else {
+            if (quads <= 1) MV_LAUNCH_SMALL_ROWS(float, 1);
+            else if (quads <= 2) MV_LAUNCH_SMALL_ROWS(float, 2);
+            else if (quads <= 4) MV_LAUNCH_SMALL_ROWS(float, 4);
+            else MV_LAUNCH_SMALL_ROWS(float, 8);
+        }
+#undef MV_LAUNCH_SMALL_ROWS
+        after(KID_SMALL_ROWS);
+        // every workgroup finds the whole mask again: one round of positions each while that keeps them within
+        // one per compute unit
+        const uint32_t kb = mvk::kSmallThreads / p.N;
+        uint32_t rounds = (p.K + kb * 256 - 1) / (kb * 256);
+        if (rounds > (uint32_t)mvk::kGatherRounds) rounds = mvk::kGatherRounds;
+        before(KID_SMALL_MASK);
+        auto* mask_kernel = random_sel ? &mvk::mv_small_mask<true> : &mvk::mv_small_mask<false>;
+        hipLaunchKernelGGL(mask_kernel, dim3((p.K + kb * rounds - 1) / (kb * rounds)),
+                           dim3(mvk::kSmallThreads), 0, st, a.err, a.ld_e, d, p.N, p.K, (const uint32_t*)row_bits,
+                           p.nwords, (const uint32_t*)ad.msum32, a.rand_exp, add_drop ? (uint8_t*)nullptr : a.votes,
+                           a.mask_idx, 1.0f / (float)p.N, c->cfg.reduce == MV_REDUCE_MEAN ? 1 : 0, a.agg_vals, rounds);
+        after(KID_SMALL_MASK);
+        return finish();
+    }
 
     // 1. one kernel: sample histogram and threshold estimate per row (its first workgroups, which
     // also reset the per-step counters), and the streaming pass a = g + e over e, candidates out
@@ -680,15 +743,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         }
 #undef MV_LAUNCH_MASK
     }
-    c->last_stream = st;
-    c->steps_done += 1;
-    if (hipGetLastError() != hipSuccess) {
-        // Some kernel of the sequence was not launched: counters that every step leaves at zero, and the
-        // step's number on the device, may be off.  The context refuses further steps.
-        c->broken = true;
-        return MV_ERR_DEVICE;
-    }
-    return ev_ok ? MV_OK : MV_ERR_DEVICE;
+    return finish();
 }
 
 }  // namespace

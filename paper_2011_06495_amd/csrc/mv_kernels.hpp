@@ -45,6 +45,8 @@
 //                         standing votes
 //   6. mv_rs_*            majority voting with random selection (Algorithm 1,
 //                         S_rand-weighted): replaces the mask of step 3
+//   7. mv_small_*         short vectors: the whole step of any of the three in two
+//                         launches, a row per workgroup
 //
 // Things measured on this machine that shape much of the code: a returning
 // atomic completes only after the previous one on the same cache line (so
@@ -65,6 +67,7 @@
 #include "mv_mask.hpp"
 #include "mv_add_drop.hpp"
 #include "mv_random_select.hpp"
+#include "mv_small.hpp"
 
 namespace mvk {
 

@@ -428,6 +428,49 @@ __device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, u
     }
 }
 
+// Positions [k0, k1) of the mask, whose coordinates are in slice[0 .. k1 - k0), at most `rounds` times
+// kMaskThreads / N of them: thread (kl, n) reads a[n][j], stores +0.0 there, and parks the value in LDS;
+// one thread per coordinate then adds the N values in worker order.
+constexpr int kGatherRounds = 4;                  // at most this many rounds of kb positions per workgroup
+
+__device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint32_t* slice /*LDS*/,
+                                                 float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N,
+                                                 uint32_t k0, uint32_t k1, uint32_t rounds, float scale,
+                                                 int apply_scale, float* __restrict__ agg)
+{
+    const uint32_t t = threadIdx.x, kb = kMaskThreads / N;
+    const uint32_t kl = t / N, n = t % N;
+    const uint32_t pitch = N + 1;                     // kb * (N + 1) <= 1024 + kb <= 1536
+    // a thread's loads of all rounds are in flight together
+    float v[kGatherRounds];
+#pragma unroll
+    for (int r = 0; r < kGatherRounds; ++r) {
+        const uint32_t k = k0 + (uint32_t)r * kb + kl;
+        const uint32_t j = ((uint32_t)r < rounds && kl < kb && k < k1) ? slice[k - k0] : 0xFFFFFFFFu;
+        v[r] = 0.0f;
+        if ((int64_t)j < d) {                         // always true for a mask built above
+            float* p = e + (int64_t)n * ld_e + j;
+            v[r] = *p;
+            *p = 0.0f;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kGatherRounds; ++r) {
+        if ((uint32_t)r >= rounds) break;             // uniform over the workgroup
+        if (kl < kb) tile[kl * pitch + n] = v[r];
+        __syncthreads();
+        if (t < kb) {
+            const uint32_t kk = k0 + (uint32_t)r * kb + t;
+            if (kk < k1) {
+                float s = tile[t * pitch];        // worker 0
+                for (uint32_t m = 1; m < N; ++m) s = s + tile[t * pitch + m];
+                agg[kk] = apply_scale ? s * scale : s;
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Workgroups [0, n_gather_blocks): each owns `rounds` times kb = 1024 / N consecutive
 // positions of the mask.
 // (a) Unless the mask is given (random selection writes it elsewhere), the workgroup
@@ -437,15 +480,12 @@ __device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, u
 //     stretches that reach into the workgroup's positions are read again, one wavefront each, and their coordinates above the
 //     vote threshold, and the first take_eq at it, go to their positions -- in LDS for
 //     the gather, and in mask_idx for the caller.  No kernel of its own emits the mask.
-// (b) Thread (kl, n) reads a[n][mask[k]] (held in e), stores +0.0 there (the error
-//     update: the residual of a transmitted coordinate is zero), and parks the value in
-//     LDS; one thread per coordinate then adds the N values in worker order 0..N-1 in
-//     fp32 and applies the 1/N of the mean once.
+// (b) gather_positions reads a[n][mask[k]] (held in e), stores +0.0 there (the error
+//     update: the residual of a transmitted coordinate is zero), adds the N values in
+//     worker order 0..N-1 in fp32 and applies the 1/N of the mean once.
 // Workgroups beyond (only launched when the sorted vote lists are wanted): write
 // row (b / emit_blocks)'s vote list; they start after the gather's workgroups and
 // run beside them.
-constexpr int kGatherRounds = 4;                  // at most this many rounds of kb positions per workgroup
-
 struct GatherLds {
     float    tile[kMaskThreads + kMaskThreads / 2 + 8];
     uint32_t slice[kGatherRounds * kMaskThreads];              // the workgroup's positions' coordinates
@@ -601,36 +641,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
     }
     __syncthreads();
 
-    const uint32_t kl = t / N, n = t % N;
-    const uint32_t pitch = N + 1;                     // kb * (N + 1) <= 1024 + kb <= 1536
-    // a thread's loads of all rounds are in flight together
-    float v[kGatherRounds];
-#pragma unroll
-    for (int r = 0; r < kGatherRounds; ++r) {
-        const uint32_t k = k0 + (uint32_t)r * kb + kl;
-        const uint32_t j = ((uint32_t)r < rounds && kl < kb && k < k1) ? lds.slice[k - k0] : 0xFFFFFFFFu;
-        v[r] = 0.0f;
-        if ((int64_t)j < d) {                         // always true for a mask built above
-            float* p = e + (int64_t)n * ld_e + j;
-            v[r] = *p;
-            *p = 0.0f;
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kGatherRounds; ++r) {
-        if ((uint32_t)r >= rounds) break;             // uniform over the workgroup
-        if (kl < kb) lds.tile[kl * pitch + n] = v[r];
-        __syncthreads();
-        if (t < kb) {
-            const uint32_t kk = k0 + (uint32_t)r * kb + t;
-            if (kk < k1) {
-                float s = lds.tile[t * pitch];        // worker 0
-                for (uint32_t m = 1; m < N; ++m) s = s + lds.tile[t * pitch + m];
-                agg[kk] = apply_scale ? s * scale : s;
-            }
-        }
-        __syncthreads();
-    }
+    gather_positions(lds.tile, lds.slice, e, ld_e, d, N, k0, k1, rounds, scale, apply_scale, agg);
 }
 
 }  // namespace mvk
