@@ -43,7 +43,9 @@ __device__ __forceinline__ bool vote_bit(const uint32_t* __restrict__ bits_row, 
     return (bits_row[j >> 5] >> (j & 31u)) & 1u;
 }
 
-// A-lists.  Rows whose top-K came from the candidate list: one thread per candidate.
+constexpr int kAddUnroll = 4;                     // candidates per thread and reservation
+constexpr int kAddBatch = kVoteThreads * kAddUnroll;
+// A-lists.  Rows whose top-K came from the candidate list: a thread takes kAddUnroll candidates.
 // Rows selected from memory (slow_flag == 1): the whole row is read.
 __device__ __forceinline__ void ad_collect_add_block(
     uint32_t bx, uint32_t nbx, uint64_t* scan_lds, uint32_t* bcast,
@@ -76,23 +78,32 @@ __device__ __forceinline__ void ad_collect_add_block(
     }
     const uint32_t C = row_count[row];
     const u32x2* crow = cand + (size_t)row * cap;
-    for (uint64_t i0 = (uint64_t)bx * kVoteThreads; i0 < C; i0 += (uint64_t)nbx * kVoteThreads) {
-        const uint64_t i = i0 + t;
-        u32x2 c = {0u, 0u};
-        bool in_a = false;
-        if (i < C) {
-            c = crow[i];
-            in_a = is_taken(c, kth, tie_cut) && !vote_bit(bits, c.y);
+    for (uint64_t i0 = (uint64_t)bx * kAddBatch; i0 < C; i0 += (uint64_t)nbx * kAddBatch) {
+        u32x2 c[kAddUnroll];
+        uint32_t in_a = 0;
+#pragma unroll
+        for (int u = 0; u < kAddUnroll; ++u) {
+            const uint64_t i = i0 + (uint32_t)u * kVoteThreads + t;
+            const u32x2 none = {0u, 0xFFFFFFFFu};
+            c[u] = i < C ? crow[i] : none;
         }
-        const uint32_t pos = reserve_in_list(in_a ? 1u : 0u, counter, scan_lds, bcast);
-        if (in_a && pos < cap) arow[pos] = c;
+#pragma unroll
+        for (int u = 0; u < kAddUnroll; ++u)
+            if (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) && !vote_bit(bits, c[u].y)) in_a |= 1u << u;
+        uint32_t pos = reserve_in_list((uint32_t)__popc(in_a), counter, scan_lds, bcast);
+#pragma unroll
+        for (int u = 0; u < kAddUnroll; ++u)
+            if (in_a >> u & 1u) {
+                if (pos < cap) arow[pos] = c[u];
+                ++pos;
+            }
     }
 }
 
 // D-lists: the standing vote's bitmap is scanned, 4 words per thread; a set
 // coordinate that is not in the row's top-K goes to the list with the
 // complemented magnitude, so that "largest first" selects the smallest magnitudes.
-constexpr int kDropStage = 1024;   // set bits of one workgroup's stretch staged in LDS per round
+constexpr int kDropStage = 4096;   // set bits of one workgroup's stretch staged in LDS per round
 constexpr int kBitIt = 1;          // quads of bitmap words per thread in the bitmap kernels (more per thread measured no faster)
 constexpr int kBitBlockWords = kVoteThreads * 4 * kBitIt;   // bitmap words per workgroup
 __device__ __forceinline__ void ad_collect_drop_block(
@@ -196,7 +207,7 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_collect(
     uint32_t nwords, u32x2* __restrict__ a_list, u32x2* __restrict__ d_list, uint32_t cap_d,
     uint32_t* __restrict__ ad_count, uint32_t add_blocks)
 {
-    __shared__ uint64_t scan_lds[kVoteThreads / kWave + 1];
+    __shared__ uint64_t scan_lds[kVoteThreads / kWave];
     __shared__ uint32_t bcast[1];
     __shared__ uint32_t stage[kDropStage];
     if (blockIdx.x < add_blocks)
@@ -207,109 +218,97 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_collect(
                               vote_bits, ld_bits, nwords, d_list, cap_d, ad_count);
 }
 
-// Workgroup (0, n): the K_ad first of row n's A-list under (magnitude desc,
-// coordinate asc); workgroup (1, n): the same for the D-list, whose keys are the
-// complemented magnitudes.  Result: ad_thr[n][2*which] = key threshold,
-// [2*which+1] = tie cut (membership test as for the top-K), and
-// counts_out[2n + which] = how many are taken = min(K_ad, list length).
-__global__ __launch_bounds__(kRowThreads) void mv_ad_select(
-    const u32x2* __restrict__ a_list, uint32_t cap_a, const u32x2* __restrict__ d_list, uint32_t cap_d,
-    const uint32_t* __restrict__ ad_count, uint32_t k_ad, const uint32_t* __restrict__ tau_bits,
-    const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ ad_thr, uint32_t* __restrict__ counts_out)
+// The K_ad first of row n's A-list under (magnitude desc, coordinate asc), and the same for the D-list, whose
+// keys are the complemented magnitudes: list number 2n + which.  All of A is at or above the row's K-th
+// magnitude and all of D at or below it, so the keys start there.  A crowds right above: 1024 bins to an octave
+// for half an octave, then 32; D reaches far down: 128 bins to an octave for four octaves, then 32.
+__device__ __forceinline__ ListView ad_list(uint32_t number, const u32x2* __restrict__ a_list, uint32_t cap_a,
+                                            const u32x2* __restrict__ d_list, uint32_t cap_d,
+                                            const uint32_t* __restrict__ ad_count, uint32_t k_ad,
+                                            const uint32_t* __restrict__ kth_in, uint32_t* __restrict__ sample_hist)
 {
-    __shared__ SelectLds lds;
-    const uint32_t which = blockIdx.x, row = blockIdx.y, t = threadIdx.x;
-    const u32x2* list = which ? d_list + (size_t)row * cap_d : a_list + (size_t)row * cap_a;
-    const uint32_t len = min(ad_count[ad_counter(row, which)], which ? cap_d : cap_a);
-    uint32_t kth, tie_cut;
-    if (len == 0) {
-        kth = 0xFFFFFFFFu;                        // nothing passes the membership test
-        tie_cut = 0;
-    } else if (len <= k_ad) {
-        kth = 0;                                  // everything passes
-        tie_cut = 0xFFFFFFFFu;
+    const uint32_t row = number / 2, which = number % 2;
+    ListView v;
+    v.list = which ? d_list + (size_t)row * cap_d : a_list + (size_t)row * cap_a;
+    v.n = min(ad_count[ad_counter(row, which)], which ? cap_d : cap_a);
+    v.want = k_ad;
+    v.base = which ? kAbsMask - kth_in[row] : kth_in[row];
+    v.fine = which ? 16 : 13;
+    v.coarse = 18;
+    lend_storage(v, sample_hist, row, which);
+    return v;
+}
+
+// Long lists only (see list_split): the histograms
+__global__ __launch_bounds__(kRowThreads) void mv_ad_hist(const u32x2* __restrict__ a_list, uint32_t cap_a,
+                                                          const u32x2* __restrict__ d_list, uint32_t cap_d,
+                                                          const uint32_t* __restrict__ ad_count, uint32_t k_ad,
+                                                          const uint32_t* __restrict__ kth_in,
+                                                          uint32_t* __restrict__ sample_hist)
+{
+    __shared__ uint32_t hist[kListBins];
+    const ListView v = ad_list(blockIdx.y, a_list, cap_a, d_list, cap_d, ad_count, k_ad, kth_in, sample_hist);
+    if (v.n <= k_ad) return;                      // whole workgroup: all of the list is taken
+    list_hist(v, blockIdx.x, gridDim.x, hist);
+}
+
+// Selects and applies the additions and removals: marks them in the row's scratch bitmap (one bitmap for
+// both: a marked coordinate that is in the standing vote is a removal, one that is not is an addition), counts
+// them per block of the bitmap, and moves msum by +1 / -1 (bytes packed four to a word; a byte never carries
+// because 0 <= msum <= N <= 255 holds before and after).  counts_out[2n + which] = how many are taken =
+// min(K_ad, list length).  Grid (workgroups of a list, 2N); ALONE: one workgroup per list.
+template <bool ALONE>
+__global__ __launch_bounds__(kRowThreads) void mv_ad_pick(
+    const u32x2* __restrict__ a_list, uint32_t cap_a, const u32x2* __restrict__ d_list, uint32_t cap_d,
+    const uint32_t* __restrict__ ad_count, uint32_t k_ad, const uint32_t* __restrict__ kth_in,
+    uint32_t* __restrict__ sample_hist, u32x2* __restrict__ list2, uint32_t* __restrict__ ad_bits,
+    uint32_t nwords_pad, uint32_t nblk, u32x2* __restrict__ blk_cnt, uint32_t* __restrict__ msum32,
+    uint32_t* __restrict__ counts_out)
+{
+    __shared__ SplitLds<kMembers> lds;
+    const uint32_t row = blockIdx.y / 2, which = blockIdx.y % 2;
+    ListView v = ad_list(blockIdx.y, a_list, cap_a, d_list, cap_d, ad_count, k_ad, kth_in, sample_hist);
+    // the second lists share a row of storage (at most 2K and at most d entries together): one from each end
+    v.list2 = list2 + (size_t)row * cap_a + (which ? cap_a - 1 : 0);
+    v.step2 = which ? -1 : 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) counts_out[blockIdx.y] = min(v.n, k_ad);
+    uint32_t* bits = ad_bits + (size_t)row * nwords_pad;
+    const BlockTally tally = {lds.tally, reinterpret_cast<uint32_t*>(blk_cnt + (size_t)row * nblk) + which, 2, nblk};
+    tally.clear();
+    auto apply = [&](const u32x2 (&c)[kListUnroll], uint32_t taken) {
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u) {
+            const bool mine = taken >> u & 1u;
+            if (mine) {
+                atomicOr(&bits[c[u].y >> 5], 1u << (c[u].y & 31u));
+                const uint32_t one = 1u << ((c[u].y & 3u) * 8u);
+                if (which) atomicSub(&msum32[c[u].y >> 2], one);
+                else       atomicAdd(&msum32[c[u].y >> 2], one);
+            }
+            tally.add(c[u].y / (32u * kBitBlockWords), mine);
+        }
+    };
+    if (v.n <= k_ad) {                            // all of the list is taken
+        __syncthreads();
+        for (uint64_t i0 = (uint64_t)blockIdx.x * kListBatch; i0 < v.n; i0 += (uint64_t)gridDim.x * kListBatch) {
+            u32x2 c[kListUnroll];
+            uint32_t taken = 0;
+#pragma unroll
+            for (int u = 0; u < kListUnroll; ++u) {
+                const uint64_t i = i0 + (uint32_t)u * kRowThreads + threadIdx.x;
+                const u32x2 none = {0u, 0xFFFFFFFFu};
+                c[u] = i < v.n ? v.list[i] : none;
+                taken |= (i < v.n ? 1u : 0u) << u;
+            }
+            apply(c, taken);
+        }
     } else {
-        uint32_t path;
-        auto at = [list](uint64_t i) { return list[i].x; };
-        const KeysInMemory<decltype(at)> src{at, len};
-        // every A-list magnitude is at least the row's estimate tau when the row's top-K
-        // came from its candidate list; the D-list has no such bound
-        const uint32_t tau = (which || slow_flag[row] == 1u) ? 0u : tau_bits[row];
-        select_among_candidates(src, list, len, k_ad, tau, lds, kth, tie_cut, path);
+        uint32_t kth, tie_cut;
+        (void)list_split<ALONE>(v, blockIdx.x, gridDim.x, lds, apply, kth, tie_cut);
     }
-    if (t == 0) {
-        ad_thr[4 * row + 2 * which] = kth;
-        ad_thr[4 * row + 2 * which + 1] = tie_cut;
-        counts_out[2 * row + which] = min(len, k_ad);
-    }
+    tally.merge();
 }
 
-// Applies the selected additions and removals: marks them in the row's scratch
-// bitmap (one bitmap for both: a marked coordinate that is in the standing vote is a
-// removal, one that is not is an addition) and moves msum by +1 / -1 (bytes packed four
-// to a word; a byte never carries because 0 <= msum <= N <= 255 holds before and after).
-__global__ __launch_bounds__(kVoteThreads) void mv_ad_apply(
-    const u32x2* __restrict__ a_list, uint32_t cap_a, const u32x2* __restrict__ d_list, uint32_t cap_d,
-    const uint32_t* __restrict__ ad_count, const uint32_t* __restrict__ ad_thr,
-    uint32_t* __restrict__ ad_bits, uint32_t nwords_pad, uint32_t* __restrict__ msum32)
-{
-    const uint32_t row = blockIdx.y;
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        const u32x2* list = which ? d_list + (size_t)row * cap_d : a_list + (size_t)row * cap_a;
-        const uint32_t len = min(ad_count[ad_counter(row, which)], which ? cap_d : cap_a);
-        const uint32_t kth = ad_thr[4 * row + 2 * which], tie_cut = ad_thr[4 * row + 2 * which + 1];
-        uint32_t* bits = ad_bits + (size_t)row * nwords_pad;   // additions and removals share the row's bitmap
-        for (uint32_t i = blockIdx.x * kVoteThreads + threadIdx.x; i < len; i += gridDim.x * kVoteThreads) {
-            const u32x2 c = list[i];
-            if (is_taken(c, kth, tie_cut)) {
-                atomicOr(&bits[c.y >> 5], 1u << (c.y & 31u));
-                const uint32_t one = 1u << ((c.y & 3u) * 8u);
-                if (which) atomicSub(&msum32[c.y >> 2], one);
-                else       atomicAdd(&msum32[c.y >> 2], one);
-            }
-        }
-    }
-}
-
-// Ordered compaction of the N scratch bitmaps, in two kernels: marked additions and
-// removals per block of kBitBlockWords words, then (prefix over the blocks before + scan
-// inside the block) each thread writes its marked coordinates in ascending order to the
-// add list or the drop list.  The second kernel also clears the scratch words and folds
-// them into the standing vote.  Without a standing vote (vote_bits == nullptr) every
-// marked coordinate counts as an addition: a plain ordered compaction.
-__device__ __forceinline__ void compact_count_block(const uint32_t* __restrict__ ad_bits, uint32_t nwords_pad,
-                                                    uint32_t nblk, u32x2* __restrict__ blk_cnt,
-                                                    const uint32_t* __restrict__ vote_bits, int64_t ld_bits,
-                                                    uint32_t r, uint32_t bx, uint64_t* scan_lds)
-{
-    const uint32_t* vrow = vote_bits ? vote_bits + (int64_t)r * ld_bits : nullptr;
-    uint32_t n_add = 0, n_drop = 0;
-#pragma unroll
-    for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
-        if (w0 < nwords_pad) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(ad_bits + (size_t)r * nwords_pad + w0);
-            const uint32_t m[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (m[q]) {                       // rare: the standing vote's word decides which is which
-                    const uint32_t in_vote = vrow ? vrow[w0 + q] : 0u;
-                    n_add += __popc(m[q] & ~in_vote);
-                    n_drop += __popc(m[q] & in_vote);
-                }
-            }
-        }
-    }
-    uint64_t total;
-    (void)block_excl_scan64<kVoteThreads>(pack2(n_add, n_drop), scan_lds, total);
-    if (threadIdx.x == 0) {
-        u32x2 c;
-        c.x = (uint32_t)(total >> 32);
-        c.y = (uint32_t)total;
-        blk_cnt[(size_t)r * nblk + bx] = c;
-    }
-}
 // Histogram of the vote levels of msum (one byte per coordinate, values 0..N) over a
 // block of kVoteBlock coordinates: lvl_sets[set][v] += coordinates with exactly v votes.
 __device__ __forceinline__ void ad_levels_block(const uint32_t* __restrict__ msum32, int64_t d,
@@ -326,7 +325,7 @@ __device__ __forceinline__ void ad_levels_block(const uint32_t* __restrict__ msu
         const u32x4 z = {0u, 0u, 0u, 0u};
         w[it] = (j < d) ? *reinterpret_cast<const u32x4*>(msum32 + (j >> 2)) : z;
     }
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < kIt; ++it) {
@@ -343,47 +342,35 @@ __device__ __forceinline__ void ad_levels_block(const uint32_t* __restrict__ msu
         }
     }
     __syncthreads();
-    const uint32_t c = h[threadIdx.x];
+    const uint32_t c = threadIdx.x < 256 ? h[threadIdx.x] : 0u;
     if (c && threadIdx.x) atomicAdd(&lvl_sets[(size_t)(bx % kLvlSets) * 256 + threadIdx.x], c);
 }
 
-// One launch after mv_ad_apply: the first n_count_blocks workgroups count the additions
-// and removals marked in the scratch bitmaps per block (row = id / nblk), the others take
-// the histogram of msum's levels.
-__global__ __launch_bounds__(kVoteThreads) void mv_ad_compact_count(const uint32_t* __restrict__ ad_bits,
-                                                                    uint32_t nwords_pad, uint32_t nblk,
-                                                                    u32x2* __restrict__ blk_cnt,
-                                                                    const uint32_t* __restrict__ vote_bits,
-                                                                    int64_t ld_bits, uint32_t n_count_blocks,
-                                                                    const uint32_t* __restrict__ msum32, int64_t d,
-                                                                    uint32_t* __restrict__ lvl_sets)
+// One launch behind mv_ad_pick.  The first n_emit_blocks workgroups (row = id / nblk): ordered compaction of the
+// scratch bitmaps -- from the counts of the blocks before its own and a scan inside the block every thread writes
+// its marked coordinates in ascending order to the add list or the drop list -- and the scratch words are cleared
+// and folded into the standing vote.  The others take the histogram of msum's levels.
+__global__ __launch_bounds__(kVoteThreads) void mv_ad_emit(uint32_t* __restrict__ ad_bits, uint32_t nwords_pad,
+                                                           uint32_t nblk, const u32x2* __restrict__ blk_cnt,
+                                                           uint32_t k_ad, uint32_t* __restrict__ add_idx,
+                                                           uint32_t* __restrict__ drop_idx,
+                                                           uint32_t* __restrict__ vote_bits, int64_t ld_bits,
+                                                           uint32_t n_emit_blocks, const uint32_t* __restrict__ msum32,
+                                                           int64_t d, uint32_t* __restrict__ lvl_sets)
 {
-    __shared__ uint64_t scan_lds[kVoteThreads / kWave + 1];
+    __shared__ uint64_t scan_lds[kVoteThreads / kWave];
     __shared__ uint32_t h[256];
-    if (blockIdx.x < n_count_blocks)
-        compact_count_block(ad_bits, nwords_pad, nblk, blk_cnt, vote_bits, ld_bits, blockIdx.x / nblk,
-                            blockIdx.x % nblk, scan_lds);
-    else
-        ad_levels_block(msum32, d, lvl_sets, blockIdx.x - n_count_blocks, h);
-}
-
-__global__ __launch_bounds__(kVoteThreads) void mv_ad_compact_emit(uint32_t* __restrict__ ad_bits,
-                                                                   uint32_t nwords_pad, uint32_t nblk,
-                                                                   const u32x2* __restrict__ blk_cnt,
-                                                                   uint32_t k_ad,
-                                                                   uint32_t* __restrict__ add_idx,
-                                                                   uint32_t* __restrict__ drop_idx,
-                                                                   uint32_t* __restrict__ vote_bits,
-                                                                   int64_t ld_bits)
-{
-    __shared__ uint64_t scan_lds[kVoteThreads / kWave + 1];
-    const uint32_t row = blockIdx.y;
-    uint32_t* vrow = vote_bits ? vote_bits + (int64_t)row * ld_bits : nullptr;   // null: compaction only, all additions
+    if (blockIdx.x >= n_emit_blocks) {
+        ad_levels_block(msum32, d, lvl_sets, blockIdx.x - n_emit_blocks, h);
+        return;
+    }
+    const uint32_t row = blockIdx.x / nblk, bx = blockIdx.x % nblk;
+    uint32_t* vrow = vote_bits + (int64_t)row * ld_bits;
     // the block's words first (cleared behind): their latency overlaps the prefix's loads
     uint32_t w[kBitIt][4], in_vote[kBitIt][4];
 #pragma unroll
     for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = blockIdx.x * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
+        const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
 #pragma unroll
         for (int q = 0; q < 4; ++q) w[it][q] = in_vote[it][q] = 0;
         if (w0 < nwords_pad) {
@@ -395,12 +382,12 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_compact_emit(uint32_t* __r
                 *p = z;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (w[it][q] && vrow) in_vote[it][q] = vrow[w0 + q];
+                    if (w[it][q]) in_vote[it][q] = vrow[w0 + q];
             }
         }
     }
     uint64_t mine = 0;
-    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kVoteThreads) {
+    for (uint32_t b = threadIdx.x; b < bx; b += kVoteThreads) {
         const u32x2 c = blk_cnt[(size_t)row * nblk + b];
         mine += pack2(c.x, c.y);
     }
@@ -408,11 +395,11 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_compact_emit(uint32_t* __r
     (void)block_excl_scan64<kVoteThreads>(mine, scan_lds, before);
     __syncthreads();
     uint32_t* out_add = add_idx + (size_t)row * k_ad;
-    uint32_t* out_drop = drop_idx ? drop_idx + (size_t)row * k_ad : nullptr;
+    uint32_t* out_drop = drop_idx + (size_t)row * k_ad;
     uint64_t done = before;                       // (additions, removals) before the current quad row
 #pragma unroll
     for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = blockIdx.x * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
+        const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
         uint32_t n_add = 0, n_drop = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -425,13 +412,13 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_compact_emit(uint32_t* __r
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             uint32_t m = w[it][q];
-            if (m && vrow) atomicXor(&vrow[w0 + q], m);     // additions enter the standing vote, removals leave it
+            if (m) atomicXor(&vrow[w0 + q], m);     // additions enter the standing vote, removals leave it
             while (m) {
                 const uint32_t b = __ffs((int)m) - 1;
                 m &= m - 1;
                 const uint32_t j = (w0 + q) * 32 + b;
                 if ((in_vote[it][q] >> b) & 1u) {
-                    if (out_drop && pos_drop < k_ad) out_drop[pos_drop] = j;
+                    if (pos_drop < k_ad) out_drop[pos_drop] = j;
                     ++pos_drop;
                 } else {
                     if (pos_add < k_ad) out_add[pos_add] = j;

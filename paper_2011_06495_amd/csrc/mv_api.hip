@@ -16,36 +16,29 @@ namespace {
 enum KernelId {
     KID_STREAM = 0,
     KID_ROW_SELECT,
-    KID_ROW_VOTES,
+    // rows' select with many workgroups (large K) in place of the one above
+    KID_SEL_HIST,
+    KID_SEL_SPLIT,
     KID_MASK_COUNT,
     KID_GATHER,
     // add-drop voting only
     KID_AD_COLLECT,
-    KID_AD_SELECT,
-    KID_AD_APPLY,
-    KID_AD_COMPACT_COUNT,
-    KID_AD_COMPACT_EMIT,
-    // rows' select with many workgroups (large K only)
-    KID_SEL_HIST,
-    KID_SEL_SPLIT,
-    KID_SEL_RANK,
+    KID_AD_HIST,
+    KID_AD_PICK,
+    KID_AD_EMIT,
     // random selection only
     KID_RS_KEYS,
     KID_RS_HIST,
-    KID_RS_SPLIT,
-    KID_RS_RANK,
+    KID_RS_PICK,
     // short vectors only, in place of all the others
     KID_SMALL_ROWS,
     KID_SMALL_MASK,
     KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
-    "mv_stream_collect",   "mv_row_select",      "mv_row_votes",
-    "mv_mask_count",     "mv_gather_update",    "mv_ad_collect",      "mv_ad_select",
-    "mv_ad_apply",       "mv_ad_compact_count", "mv_ad_compact_emit",
-    "mv_sel_hist",       "mv_sel_split",       "mv_sel_rank",
-    "mv_rs_keys",        "mv_rs_hist",         "mv_rs_split",         "mv_rs_rank",
-    "mv_small_rows",     "mv_small_mask"};
+    "mv_stream_collect", "mv_row_select", "mv_sel_hist", "mv_sel_split", "mv_mask_count", "mv_gather_update",
+    "mv_ad_collect",     "mv_ad_hist",    "mv_ad_pick",  "mv_ad_emit",   "mv_rs_keys",    "mv_rs_hist",
+    "mv_rs_pick",        "mv_small_rows", "mv_small_mask"};
 
 constexpr size_t kAlign = 256;
 constexpr int kEventRing = 64;   // steps whose kernel durations stay readable
@@ -64,13 +57,12 @@ struct Plan {
     uint32_t n_vote_blocks;     // workgroups of the mask kernels: blocks of 16384 vote_q coordinates
     uint32_t vote_q;            // quads of 16 vote bytes per thread of the mask kernels (1, 2, 3, 4, 6 or 8)
     uint32_t rs_blocks;         // workgroups of mv_rs_keys: blocks of kVoteBlock coordinates
-    uint32_t list_blocks;       // workgroups per row that walk a candidate list, one thread per entry
-    uint32_t vote_blocks;       // workgroups per row of mv_row_votes
+    uint32_t list_blocks;       // workgroups per row of mv_ad_collect that walk the candidate list
+    uint32_t split_blocks;      // workgroups per row of the many-workgroup select
     uint32_t emit_blocks;       // workgroups per row that write the sorted vote list
     uint32_t scan_parts;        // workgroups per row that scan the segment tallies (4096 segments each)
     uint32_t select_parts;      // workgroups per row of mv_row_select when they also cast the votes
     uint32_t n_spec;            // list entries per thread that mv_row_select fetches ahead of the row's count
-    bool     long_lists;        // the expected lists need the instance of mv_row_select that keeps more entries
     uint32_t scan_blocks;       // workgroups per row that scan the segment tallies
     // add-drop voting (only with MV_FLAG_ADD_DROP)
     bool     add_drop;
@@ -79,16 +71,16 @@ struct Plan {
     uint32_t bit_blocks;          // workgroups of kBitBlockWords bitmap words per row
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
-    size_t   off_selhist, off_selcount2, off_selbinwant, off_sellist2;
+    size_t   off_sellist2;
     // random selection
     uint32_t rs_cap;              // most coordinates that can hold a vote: min(N K, d)
-    size_t   off_rshist, off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
+    size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
     // scratch offsets (bytes)
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
     size_t off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_seg, off_segsel,
         off_segpre,
-        off_blktotal, off_alist, off_dlist, off_adcount, off_adthr, off_adbits, off_adblk, off_cand, off_votes, off_blockcnt, off_subcnt, off_votethr, off_emitfail,
+        off_blktotal, off_alist, off_dlist, off_adcount, off_adbits, off_adblk, off_cand, off_votes, off_blockcnt, off_subcnt, off_votethr, off_emitfail,
         off_lookback;
     uint32_t n_zero_words;      // words from off_lvlsets on that a step's first kernel zeroes
     size_t total_bytes;
@@ -172,16 +164,6 @@ Plan make_plan(const mv_config* c)
         const uint64_t per = (uint64_t)mvk::kMaskThreads * 16 * q;
         p.n_vote_blocks = (uint32_t)(((uint64_t)p.d + per - 1) / per);
     }
-    // about 2K candidates per row are expected: one thread per candidate with some room, the kernels
-    // stride over whatever is there
-    {
-        uint64_t eb = (3ull * p.K + mvk::kVoteThreads - 1) / mvk::kVoteThreads;
-        const uint64_t eb_cap = ((uint64_t)p.cap + mvk::kVoteThreads - 1) / mvk::kVoteThreads;
-        if (eb > eb_cap) eb = eb_cap;
-        if (eb > 256) eb = 256;      // more workgroups than this only crowd the atomics (measured at K = 111,740)
-        if (eb < 1) eb = 1;
-        p.list_blocks = (uint32_t)eb;
-    }
     p.scan_blocks = (p.nseg + 1023) / 1024;
     p.scan_parts = (p.nseg + 4095) / 4096;
     {
@@ -192,7 +174,6 @@ Plan make_plan(const mv_config* c)
         const uint64_t in_cap = ((uint64_t)p.cap + mvk::kRowThreads - 1) / mvk::kRowThreads;
         if (slots > in_cap) slots = in_cap;
         if (slots < 1) slots = 1;
-        p.long_lists = slots > (uint64_t)mvk::kKeepShort;
         p.n_spec = (uint32_t)(slots < (uint64_t)mvk::kSpec ? slots : (uint64_t)mvk::kSpec);
         uint64_t parts = (slots + 3) / 4;
         if (parts > 16) parts = 16;
@@ -200,13 +181,17 @@ Plan make_plan(const mv_config* c)
         if (parts < 1) parts = 1;
         p.select_parts = (uint32_t)parts;
         // beyond what one workgroup keeps in registers the lists go through the many-workgroup select
-        p.multi_select = slots > (uint64_t)mvk::kKeepLong;
-        // four list entries per thread in mv_row_votes, eight when writing the sorted lists
-        uint64_t vb = (slots + 3) / 4, eb2 = (slots + 3) / 4;
-        if (vb > 256) vb = 256;
+        p.multi_select = slots > (uint64_t)mvk::kSpec;
+        // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
+        uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
+        if (sb > 256) sb = 256;
         if (eb2 * p.N > 256) eb2 = 256 / p.N;
         if (eb2 < 1) eb2 = 1;
-        p.vote_blocks = (uint32_t)vb;
+        p.split_blocks = (uint32_t)sb;
+        // likewise in mv_ad_collect
+        uint64_t lb = (expect + mvk::kAddBatch - 1) / mvk::kAddBatch;
+        if (lb > 256) lb = 256;
+        p.list_blocks = (uint32_t)lb;
         p.emit_blocks = (uint32_t)eb2;
     }
 
@@ -227,8 +212,19 @@ Plan make_plan(const mv_config* c)
     // and two 64-bit words per block): one stretch of words that every step's first kernel leaves at zero
     p.off_lvlsets = off;  off += (size_t)mvk::kLvlSets * 256 * 4;
     p.off_emitfail = off; off += 8;
-    p.off_lookback = off; off += align_up((size_t)p.n_vote_blocks * 16);
+    p.off_lookback = off; off += (size_t)p.n_vote_blocks * 16;
+    // (and the counts per block of the winners of the random selection and of the additions and removals)
+    p.add_drop = (c->flags & MV_FLAG_ADD_DROP) != 0;
+    p.nwords = (uint32_t)((p.d + 31) / 32);
+    p.nwords_pad = (p.nwords + 3) / 4 * 4;
+    p.cap_d = p.K;
+    p.bit_blocks = (p.nwords_pad + mvk::kBitBlockWords - 1) / mvk::kBitBlockWords;
+    if (p.add_drop) {
+        p.off_adblk = off; off += (size_t)p.N * p.bit_blocks * 8;
+    }
+    p.off_rsblk = off;    off += align_up((size_t)p.n_vote_blocks * 4);
     p.n_zero_words = (uint32_t)((off - p.off_lvlsets) / 4);
+    off = align_up(off);
     p.off_seg = off;      off += align_up((size_t)p.N * p.nseg * 8);
     p.off_segsel = off;   off += align_up((size_t)p.N * p.nseg * 4);
     p.off_segpre = off;   off += align_up((size_t)p.N * p.nseg * 4);
@@ -238,33 +234,19 @@ Plan make_plan(const mv_config* c)
     p.off_blockcnt = off; off += align_up((size_t)p.n_vote_blocks * 8);
     p.off_subcnt = off;   off += align_up((size_t)p.n_vote_blocks * (mvk::kMaskThreads / mvk::kWave) * 8);
     p.off_votethr = off;  off += align_up(2 * 4);
-    p.add_drop = (c->flags & MV_FLAG_ADD_DROP) != 0;
-    p.nwords = (uint32_t)((p.d + 31) / 32);
-    p.nwords_pad = (p.nwords + 3) / 4 * 4;
-    p.cap_d = p.K;
-    p.bit_blocks = (p.nwords_pad + mvk::kBitBlockWords - 1) / mvk::kBitBlockWords;
     if (p.add_drop) {
         p.off_alist = off;   off += align_up((size_t)p.N * p.cap * 8);
         p.off_dlist = off;   off += align_up((size_t)p.N * p.cap_d * 8);
         p.off_adcount = off; off += align_up((size_t)p.N * 2 * mvk::kCounterStride * 4);
-        p.off_adthr = off;   off += align_up((size_t)p.N * 4 * 4);
         p.off_adbits = off;  off += align_up((size_t)p.N * p.nwords_pad * 4);
-        p.off_adblk = off;   off += align_up((size_t)p.N * p.bit_blocks * 8);
     }
-    // (measured: one workgroup per row takes 20 us at 24K candidates, 38 us at 55K, 89 us at 230K; the three
-    // kernels of the many-workgroup select about 40 us)
     if (p.multi_select) {
-        p.off_selhist = off;    off += align_up((size_t)p.N * mvk::kSelBins * 4);
-        p.off_selcount2 = off;  off += align_up((size_t)p.N * 4);
-        p.off_selbinwant = off; off += align_up((size_t)p.N * 2 * 4);
-        p.off_sellist2 = off;   off += align_up((size_t)p.N * p.cap * 8);
+        p.off_sellist2 = off; off += align_up((size_t)p.N * p.cap * 8);
     }
     const uint64_t voted_max = (uint64_t)p.N * p.K;
     p.rs_cap = (uint32_t)(voted_max < (uint64_t)p.d ? voted_max : (uint64_t)p.d);
-    p.off_rshist = off;  off += align_up((size_t)mvk::kSelBins * 4);
-    p.off_rscount = off; off += align_up(4 * 4);
+    p.off_rscount = off; off += align_up(4);
     p.off_rsbits = off;  off += align_up((size_t)p.nwords_pad * 4);
-    p.off_rsblk = off;   off += align_up((size_t)p.bit_blocks * 8);
     p.off_rslist = off;  off += align_up((size_t)p.rs_cap * 8);
     p.off_rslist2 = off; off += align_up((size_t)p.rs_cap * 8);
     p.total_bytes = off;
@@ -360,11 +342,10 @@ mv_status mv_begin(const mv_config* cfg, mv_ctx** out_ctx)
               hipMemset(c->ws + plan.off_votes, 0, ((size_t)plan.d + 15) / 16 * 16) == hipSuccess &&
               hipMemset(c->ws + plan.off_tau, 0, plan.off_seg - plan.off_tau) == hipSuccess;
     if (ok && plan.add_drop)   // the scratch bitmaps start at zero and are left at zero by every step
-        ok = hipMemset(c->ws + plan.off_adcount, 0, plan.off_adblk - plan.off_adcount) == hipSuccess;
-    if (ok && plan.multi_select)   // histograms and counters of the many-workgroup select start at zero
-        ok = hipMemset(c->ws + plan.off_selhist, 0, plan.off_selbinwant - plan.off_selhist) == hipSuccess;
-    // random selection: histogram, counters and bitmap start at zero and are left at zero
-    ok = ok && hipMemset(c->ws + plan.off_rshist, 0, plan.off_rsblk - plan.off_rshist) == hipSuccess;
+        ok = hipMemset(c->ws + plan.off_adcount, 0,
+                       plan.off_adbits - plan.off_adcount + (size_t)plan.N * plan.nwords_pad * 4) == hipSuccess;
+    // random selection: the list's length and the bitmap start at zero and are left at zero
+    ok = ok && hipMemset(c->ws + plan.off_rscount, 0, plan.off_rslist - plan.off_rscount) == hipSuccess;
     ok = ok && hipDeviceSynchronize() == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -451,6 +432,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     mvk::u32x2* cand = ws_ptr<mvk::u32x2>(c, p.off_cand);
     uint32_t* votes32 = ws_ptr<uint32_t>(c, p.off_votes);
     mvk::u32x2* blockcnt = ws_ptr<mvk::u32x2>(c, p.off_blockcnt);
+    uint32_t* rsblk = ws_ptr<uint32_t>(c, p.off_rsblk);
     mvk::u32x2* subcnt = ws_ptr<mvk::u32x2>(c, p.off_subcnt);
     uint32_t* emitfail = ws_ptr<uint32_t>(c, p.off_emitfail);
     unsigned long long* lookback = ws_ptr<unsigned long long>(c, p.off_lookback);
@@ -458,7 +440,6 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     mvk::u32x2* alist = p.add_drop ? ws_ptr<mvk::u32x2>(c, p.off_alist) : nullptr;
     mvk::u32x2* dlist = p.add_drop ? ws_ptr<mvk::u32x2>(c, p.off_dlist) : nullptr;
     uint32_t* adcount = p.add_drop ? ws_ptr<uint32_t>(c, p.off_adcount) : nullptr;
-    uint32_t* adthr = p.add_drop ? ws_ptr<uint32_t>(c, p.off_adthr) : nullptr;
     uint32_t* adbits = p.add_drop ? ws_ptr<uint32_t>(c, p.off_adbits) : nullptr;
     mvk::u32x2* adblk = p.add_drop ? ws_ptr<mvk::u32x2>(c, p.off_adblk) : nullptr;
 
@@ -563,65 +544,37 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }
-    // 3. exact per-row select
-    // (in plain voting with short lists every workgroup of a row also casts the votes of its share of the list)
+    // 2. exact per-row select; in plain voting and random selection the votes are cast in the same launch (short
+    // lists: every workgroup of a row casts those of its share; long lists: many workgroups per row)
     const bool sorted = a.worker_idx != nullptr;
-    const bool votes_in_select = !add_drop && !p.multi_select;
-    before(KID_ROW_SELECT);
-    {
-        const uint32_t parts = votes_in_select ? p.select_parts : 1;
-        // (with the many-workgroup select this launch only serves rows that need the exact path from memory:
-        // nothing of the lists is fetched ahead)
-        const uint32_t n_spec = p.multi_select ? 0u : p.n_spec;
-        const dim3 grid((p.N + 7) / 8 * 8 * parts);
-        if (p.long_lists)
-            hipLaunchKernelGGL(mvk::mv_row_select<mvk::kKeepLong>, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e,
-                               p.d, p.N, p.K, cand, p.cap, rowcnt_sets, rowcnt_set_words, stepno, taupub, poison, rowcnt,
-                               tau, kth, tiecut,
-                               a.worker_idx, votes32,
-                               sorted ? segsel : nullptr, p.nseg, lvlsets, slow, parts, n_spec, add_drop ? 1 : 0,
-                               p.multi_select ? 1 : 0);
-        else
-            hipLaunchKernelGGL(mvk::mv_row_select<mvk::kKeepShort>, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e,
-                               p.d, p.N, p.K, cand, p.cap, rowcnt_sets, rowcnt_set_words, stepno, taupub, poison, rowcnt,
-                               tau, kth, tiecut,
-                               a.worker_idx, votes32,
-                               sorted ? segsel : nullptr, p.nseg, lvlsets, slow, parts, n_spec, add_drop ? 1 : 0,
-                               p.multi_select ? 1 : 0);
-    }
-    after(KID_ROW_SELECT);
+    uint32_t* ssel = sorted ? segsel : nullptr;
+    const int thresholds_only = add_drop ? 1 : 0;
     if (p.multi_select) {
-        // long candidate lists: histogram, split at the bin of the K-th largest, exact rank
-        mvk::ListSelect ls;
-        ls.list = cand;  ls.cap = p.cap;  ls.count = rowcnt;  ls.count_stride = 1;
-        ls.base = tau;  ls.shift = mvk::kFineShift;
-        ls.want = p.K;
-        ls.hist = ws_ptr<uint32_t>(c, p.off_selhist);
-        ls.list2 = ws_ptr<mvk::u32x2>(c, p.off_sellist2);
-        ls.count2 = ws_ptr<uint32_t>(c, p.off_selcount2);
-        ls.bin_want = ws_ptr<uint32_t>(c, p.off_selbinwant);
-        const dim3 grid((p.cap + mvk::kListPerBlock - 1) / mvk::kListPerBlock, p.N);
+        const dim3 grid(p.split_blocks, p.N);
         before(KID_SEL_HIST);
-        hipLaunchKernelGGL(mvk::mv_sel_hist, grid, dim3(mvk::kRowThreads), 0, st, ls);
+        hipLaunchKernelGGL(mvk::mv_sel_hist, grid, dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K, rowcnt_sets,
+                           rowcnt_set_words, stepno, taupub, poison, hist, rowcnt, tau, slow);
         after(KID_SEL_HIST);
         before(KID_SEL_SPLIT);
-        hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, ls);
+        hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
+                           (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
+                           ws_ptr<mvk::u32x2>(c, p.off_sellist2), kth, tiecut, a.worker_idx, votes32, ssel, p.nseg,
+                           lvlsets, thresholds_only);
         after(KID_SEL_SPLIT);
-        before(KID_SEL_RANK);
-        hipLaunchKernelGGL(mvk::mv_sel_rank, dim3(p.N), dim3(mvk::kRowThreads), 0, st, ls, kth, tiecut, slow);
-        after(KID_SEL_RANK);
+    } else {
+        const uint32_t parts = add_drop ? 1 : p.select_parts;
+        before(KID_ROW_SELECT);
+        hipLaunchKernelGGL(mvk::mv_row_select, dim3((p.N + 7) / 8 * 8 * parts), dim3(mvk::kRowThreads), 0, st, a.err,
+                           a.ld_e, p.d, p.N, p.K, cand, p.cap, rowcnt_sets, rowcnt_set_words, stepno, taupub, poison,
+                           rowcnt, tau, kth, tiecut, a.worker_idx, votes32, ssel, p.nseg, lvlsets, slow, parts, p.n_spec,
+                           thresholds_only);
+        after(KID_ROW_SELECT);
     }
 
     uint32_t* mask_votes32 = votes32;     // the packed vote bytes the mask is selected from
-    if (!add_drop && p.multi_select) {
-        // 4. votes of the long lists (and segment tallies when the sorted lists are wanted)
-        before(KID_ROW_VOTES);
-        hipLaunchKernelGGL(mvk::mv_row_votes, dim3(p.vote_blocks, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap,
-                           rowcnt, p.nseg, kth, tiecut, slow, sorted ? segsel : nullptr, votes32, lvlsets);
-        after(KID_ROW_VOTES);
-    } else if (add_drop) {
-        // 4'. add-drop voting: candidates for addition and removal, exact K_ad-selects,
-        // update of msum and of the standing votes, sorted add / drop lists
+    if (add_drop) {
+        // 3'. add-drop voting: candidates for addition and removal, exact K_ad-selects with the update of msum,
+        // then the sorted add / drop lists, the standing votes and the levels of msum
         const uint32_t k_ad = (uint32_t)a.k_ad;
         uint32_t* msum32 = reinterpret_cast<uint32_t*>(a.msum);
         before(KID_AD_COLLECT);
@@ -629,69 +582,58 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                            st, a.err, a.ld_e, p.d, cand, p.cap, rowcnt, kth, tiecut, slow, a.vote_bits, a.ld_bits,
                            p.nwords_pad, alist, dlist, p.cap_d, adcount, p.list_blocks);
         after(KID_AD_COLLECT);
-        before(KID_AD_SELECT);
-        hipLaunchKernelGGL(mvk::mv_ad_select, dim3(2, p.N), dim3(mvk::kRowThreads), 0, st, alist, p.cap, dlist,
-                           p.cap_d, adcount, k_ad, tau, slow, adthr, a.counts);
-        after(KID_AD_SELECT);
-        before(KID_AD_APPLY);
-        hipLaunchKernelGGL(mvk::mv_ad_apply, dim3(p.list_blocks, p.N), dim3(mvk::kVoteThreads), 0, st, alist, p.cap,
-                           dlist, p.cap_d, adcount, adthr, adbits, p.nwords_pad, msum32);
-        after(KID_AD_APPLY);
-        before(KID_AD_COMPACT_COUNT);
-        hipLaunchKernelGGL(mvk::mv_ad_compact_count, dim3(p.N * p.bit_blocks + p.rs_blocks), dim3(mvk::kVoteThreads),
-                           0, st, adbits, p.nwords_pad, p.bit_blocks, adblk, (const uint32_t*)a.vote_bits, a.ld_bits,
+        // (a list has at most K entries; the candidate lists have been used and lend their storage)
+        const bool alone = p.K <= mvk::kAloneList;
+        uint32_t parts = (p.K + mvk::kListBatch - 1) / mvk::kListBatch;
+        parts = alone ? 1 : parts > 64 ? 64 : parts;
+        const dim3 grid(parts, 2 * p.N);
+        if (!alone) {
+            before(KID_AD_HIST);
+            hipLaunchKernelGGL(mvk::mv_ad_hist, grid, dim3(mvk::kRowThreads), 0, st, alist, p.cap, dlist, p.cap_d,
+                               adcount, k_ad, kth, hist);
+            after(KID_AD_HIST);
+        }
+        before(KID_AD_PICK);
+        hipLaunchKernelGGL((alone ? &mvk::mv_ad_pick<true> : &mvk::mv_ad_pick<false>), grid, dim3(mvk::kRowThreads), 0,
+                           st, alist, p.cap, dlist, p.cap_d, adcount, k_ad, kth, hist, cand, adbits, p.nwords_pad,
+                           p.bit_blocks, adblk, msum32, a.counts);
+        after(KID_AD_PICK);
+        before(KID_AD_EMIT);
+        hipLaunchKernelGGL(mvk::mv_ad_emit, dim3(p.N * p.bit_blocks + p.rs_blocks), dim3(mvk::kVoteThreads), 0, st,
+                           adbits, p.nwords_pad, p.bit_blocks, adblk, k_ad, a.add_idx, a.drop_idx, a.vote_bits, a.ld_bits,
                            p.N * p.bit_blocks, (const uint32_t*)msum32, p.d, lvlsets);
-        after(KID_AD_COMPACT_COUNT);
-        before(KID_AD_COMPACT_EMIT);
-        hipLaunchKernelGGL(mvk::mv_ad_compact_emit, dim3(p.bit_blocks, p.N), dim3(mvk::kVoteThreads), 0, st,
-                           adbits, p.nwords_pad, p.bit_blocks, adblk, k_ad, a.add_idx, a.drop_idx, a.vote_bits,
-                           a.ld_bits);
-        after(KID_AD_COMPACT_EMIT);
+        after(KID_AD_EMIT);
         mask_votes32 = msum32;
     }
+    uint32_t* rsbits = ws_ptr<uint32_t>(c, p.off_rsbits);
     if (random_sel) {
-        // 4''. random selection: keys of the voted coordinates, their histogram, split at the bin of the K-th
-        // soonest, exact ranking inside that bin, ordered compaction of the winners' bitmap
-        uint32_t* rshist = ws_ptr<uint32_t>(c, p.off_rshist);
+        // 3''. random selection: keys of the voted coordinates, exact select of the K soonest into a bitmap
         uint32_t* rscount = ws_ptr<uint32_t>(c, p.off_rscount);
-        uint32_t* rsbits = ws_ptr<uint32_t>(c, p.off_rsbits);
-        mvk::u32x2* rsblk = ws_ptr<mvk::u32x2>(c, p.off_rsblk);
         mvk::u32x2* rslist = ws_ptr<mvk::u32x2>(c, p.off_rslist);
         mvk::u32x2* rslist2 = ws_ptr<mvk::u32x2>(c, p.off_rslist2);
         before(KID_RS_KEYS);
         hipLaunchKernelGGL(mvk::mv_rs_keys, dim3(p.rs_blocks), dim3(mvk::kVoteThreads), 0, st, votes32, p.d,
                            a.rand_exp, rslist, p.rs_cap, rscount);
         after(KID_RS_KEYS);
-        mvk::ListSelect ls;
-        ls.list = rslist;  ls.cap = p.rs_cap;  ls.count = rscount;  ls.count_stride = 1;  ls.base = nullptr;
-        ls.shift = 20;
-        ls.want = p.K;
-        ls.hist = rshist;  ls.list2 = rslist2;  ls.count2 = rscount + 1;  ls.bin_want = rscount + 2;
-        const dim3 grid((p.rs_cap + mvk::kListPerBlock - 1) / mvk::kListPerBlock);
-        before(KID_RS_HIST);
-        hipLaunchKernelGGL(mvk::mv_rs_hist, grid, dim3(mvk::kRowThreads), 0, st, ls);
-        after(KID_RS_HIST);
-        before(KID_RS_SPLIT);
-        hipLaunchKernelGGL(mvk::mv_rs_split, grid, dim3(mvk::kRowThreads), 0, st, ls, rsbits);
-        after(KID_RS_SPLIT);
-        before(KID_RS_RANK);
-        hipLaunchKernelGGL(mvk::mv_rs_rank, dim3(1), dim3(mvk::kRowThreads), 0, st, ls, rscount, rsbits);
-        after(KID_RS_RANK);
-        before(KID_AD_COMPACT_COUNT);
-        hipLaunchKernelGGL(mvk::mv_ad_compact_count, dim3(p.bit_blocks), dim3(mvk::kVoteThreads), 0, st, rsbits,
-                           p.nwords_pad, p.bit_blocks, rsblk, (const uint32_t*)nullptr, (int64_t)0, p.bit_blocks,
-                           (const uint32_t*)nullptr, p.d, (uint32_t*)nullptr);
-        after(KID_AD_COMPACT_COUNT);
-        before(KID_AD_COMPACT_EMIT);
-        hipLaunchKernelGGL(mvk::mv_ad_compact_emit, dim3(p.bit_blocks, 1), dim3(mvk::kVoteThreads), 0, st, rsbits,
-                           p.nwords_pad, p.bit_blocks, rsblk, p.K, a.mask_idx, (uint32_t*)nullptr,
-                           (uint32_t*)nullptr, (int64_t)0);
-        after(KID_AD_COMPACT_EMIT);
+        const bool alone = p.rs_cap <= mvk::kAloneList;
+        uint32_t parts = (p.rs_cap + mvk::kListBatch - 1) / mvk::kListBatch;
+        parts = alone ? 1 : parts > 256 ? 256 : parts;
+        if (!alone) {
+            before(KID_RS_HIST);
+            hipLaunchKernelGGL(mvk::mv_rs_hist, dim3(parts), dim3(mvk::kRowThreads), 0, st, rslist, p.rs_cap, rscount,
+                               p.K, hist);
+            after(KID_RS_HIST);
+        }
+        before(KID_RS_PICK);
+        hipLaunchKernelGGL((alone ? &mvk::mv_rs_pick<true> : &mvk::mv_rs_pick<false>), dim3(parts),
+                           dim3(mvk::kRowThreads), 0, st, rslist, p.rs_cap, rscount, p.K, hist, rslist2, rsbits,
+                           (uint32_t)mvk::kMaskThreads * 16 * p.vote_q, p.n_vote_blocks, rsblk);
+        after(KID_RS_PICK);
     }
-    // 5. global mask: the vote threshold and the counts per stretch of the vote bytes (in plain voting extra
-    // workgroups scan the segment tallies for the sorted vote lists); then 6. every workgroup of the last
-    // kernel emits its part of the mask, gathers it, takes the mean and updates the error buffers; extra
-    // workgroups write the sorted vote lists beside it.  With random selection the mask is already written.
+    // 4. global mask: the vote threshold and the counts per stretch of the vote bytes (in plain voting extra
+    // workgroups scan the segment tallies for the sorted vote lists), or the winners of the
+    // random selection in order; then 5. every workgroup of the last kernel gathers its part of the mask, takes the
+    // mean and updates the error buffers; extra workgroups write the sorted vote lists beside it.
     const bool lists = sorted && !add_drop;
     {
         const dim3 grid_c(p.n_vote_blocks + (lists ? p.N : 0));
@@ -717,11 +659,12 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         const dim3 grid_g(n_gather + n_list);
 #define MV_LAUNCH_MASK(Q)                                                                                        \
         before(KID_MASK_COUNT);                                                                                  \
-        hipLaunchKernelGGL(mvk::mv_mask_count<Q>, grid_c, block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,     \
+        hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \
+                           block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
                            subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, p.scan_parts, p.scan_blocks,   \
                            p.nseg,                                                                               \
                            slow, segsel, segpre, blktotal, add_drop ? 1 : 0, lookback, emitfail, c->spin_limit,  \
-                           random_sel ? nullptr : a.mask_idx);                                                  \
+                           a.mask_idx, reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
         after(KID_MASK_COUNT);                                                                                   \
         before(KID_GATHER);                                                                                      \
         hipLaunchKernelGGL(mvk::mv_gather_update<Q>, grid_g, block, 0, st, a.err, a.ld_e, p.d, p.N, p.K,          \

@@ -21,10 +21,9 @@ constexpr int      kHistBits       = 13;     // sample histogram: exponent + 5 m
 constexpr int      kHistBins       = 1 << kHistBits;
 constexpr int      kHistShift      = 31 - kHistBits;
 constexpr int      kChunk          = 32;     // sampled chunk: 32 coordinates (one 128-byte line of fp32)
-constexpr int      kRowThreads     = 1024;   // mv_pick_threshold / mv_row_select: one workgroup per row
-constexpr int      kVoteBlock      = 16384;  // coordinates per workgroup in mv_mask_count / mv_mask_emit
-constexpr int      kVoteThreads    = 256;
-constexpr int      kGatherThreads  = 256;
+constexpr int      kRowThreads     = 1024;   // mv_row_select and the selects from lists
+constexpr int      kVoteBlock      = 16384;  // coordinates per workgroup of mv_rs_keys and of msum's level counts
+constexpr int      kVoteThreads    = 1024;   // add-drop kernels and mv_rs_keys
 constexpr int      kMaxScanBlocks  = 2048;   // blocks of 1024 segments in a row of up to 2^31 coordinates
 constexpr uint32_t kAbsMask        = 0x7FFFFFFFu;
 constexpr int      kFineBins       = 2048;   // mv_row_select: histogram of the candidates' magnitudes above tau

@@ -1,5 +1,5 @@
-// Vote casting for long lists, the global mask (counting sort over the vote levels,
-// ordered emission), the sorted vote lists, and the masked gather / mean / error update.
+// The global mask (counting sort over the vote levels, ordered emission), the sorted vote lists, and the
+// masked gather / mean / error update.
 //
 // These kernels are short (a few dependent memory round trips each), and the chip
 // starts only a few hundred workgroups per microsecond: they use workgroups of 1024
@@ -13,29 +13,6 @@ namespace mvk {
 
 constexpr int kMaskThreads = 1024;   // mv_mask_count / mv_gather_update
 constexpr int kLookBack = 256;       // earlier blocks whose totals a block of mv_mask_count adds up itself
-
-// ----------------------------------------------------------------------------
-// 4. vote casting for long candidate lists (the rows' select ran in the mv_sel_*
-//    kernels): many workgroups per row, each casting the votes of its share
-// ----------------------------------------------------------------------------
-__global__ __launch_bounds__(kRowThreads) void mv_row_votes(
-    const u32x2* __restrict__ cand, uint32_t cap, const uint32_t* __restrict__ row_count, uint32_t nseg,
-    const uint32_t* __restrict__ kth_in, const uint32_t* __restrict__ tie_cut_in,
-    const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ seg_sel,
-    uint32_t* __restrict__ votes32, uint32_t* __restrict__ lvl_sets)
-{
-    __shared__ uint32_t lvl[257];
-    const uint32_t row = blockIdx.y;
-    const uint32_t kth = kth_in[row], tie_cut = tie_cut_in[row];
-    if (slow_flag[row] == 1u) return;                              // whole workgroup
-    const uint32_t C = row_count[row];
-    for (int i = threadIdx.x; i < 257; i += kRowThreads) lvl[i] = 0;
-    __syncthreads();
-    cast_votes_of_share<kRowThreads, true>(cand + (size_t)row * cap, C, kth, tie_cut, blockIdx.x, gridDim.x, votes32, lvl,
-                                     seg_sel ? seg_sel + (size_t)row * nseg : nullptr);
-    __syncthreads();
-    merge_levels(lvl, lvl_sets, blockIdx.y * gridDim.x + blockIdx.x);
-}
 
 // ----------------------------------------------------------------------------
 // 5. global mask = the K most voted coordinates, ties to the lowest coordinate
@@ -156,12 +133,41 @@ __device__ __forceinline__ void seg_scan_part(const uint32_t* __restrict__ ssel,
     __syncthreads();                              // the LDS scratch is free for the next part
 }
 
+// Random selection: the winners are marked in a bitmap and counted per block already, so a block's
+// mask follows from the counts of the blocks before it.  `halves`: the bitmap, 16 coordinates to a
+// half-word; it is left at zero.
+template <int Q>
+__device__ __forceinline__ void write_winners(uint16_t* __restrict__ halves, const uint32_t* __restrict__ winners_per_block,
+                                              int64_t d, uint32_t K, uint64_t* scan_lds, uint32_t* __restrict__ mask_idx)
+{
+    const int64_t h0 = ((int64_t)blockIdx.x * kMaskThreads + threadIdx.x) * Q;
+    uint32_t m[Q];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        m[q] = (h0 + q) * 16 < d ? halves[h0 + q] : 0u;
+        mine += (uint32_t)__popc(m[q]);
+    }
+    uint32_t before = 0;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kMaskThreads) before += winners_per_block[b];
+    uint64_t total;
+    const uint64_t ex = block_excl_scan64<kMaskThreads>(pack2(before, mine), scan_lds, total);
+    uint32_t pos = (uint32_t)(total >> 32) + (uint32_t)ex;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        if (m[q]) halves[h0 + q] = 0;
+        for (uint32_t w = m[q]; w != 0u; w &= w - 1u, ++pos)
+            if (pos < K) mask_idx[pos] = (uint32_t)((h0 + q) * 16) + (uint32_t)__ffs((int)w) - 1u;
+    }
+}
+
 // Workgroups [0, n_vote_blocks): count the block's coordinates above and at the vote
 // threshold (also per wavefront's stretch of 1024 Q coordinates), exchange the counts
 // with the other blocks and write the block's part of the mask; optionally copy the vote
 // bytes to the caller.  Workgroups beyond (only launched when the sorted vote lists are
-// wanted): one per row, scanning the row's segment tallies.
-template <int Q>
+// wanted): one per row, scanning the row's segment tallies.  RANDOM: the mask comes from
+// the winners' bitmap.
+template <int Q, bool RANDOM>
 __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __restrict__ votes32,
                                                               int64_t d, uint32_t N, uint32_t K,
                                                               const uint32_t* __restrict__ lvl_sets,
@@ -178,7 +184,9 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
                                                               int exact_levels,
                                                               unsigned long long* __restrict__ lookback,
                                                               uint32_t* __restrict__ emit_fail, uint32_t spin_limit,
-                                                              uint32_t* __restrict__ mask_idx)
+                                                              uint32_t* __restrict__ mask_idx,
+                                                              uint16_t* __restrict__ winners,
+                                                              const uint32_t* __restrict__ winners_per_block)
 {
     __shared__ uint32_t lvl[256];
     __shared__ uint32_t thr[2];
@@ -203,8 +211,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         const u32x4 z = {0u, 0u, 0u, 0u};
         w[q] = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;   // padded to 16 bytes with zeros
     }
-    uint32_t vstar, take_eq;
-    vote_threshold(lvl_sets, N, K, lvl, thr, scan_lds, vstar, take_eq, exact_levels);
+    uint32_t vstar = 0, take_eq = 0;
+    if constexpr (!RANDOM) vote_threshold(lvl_sets, N, K, lvl, thr, scan_lds, vstar, take_eq, exact_levels);
     uint32_t ww[4 * Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -218,6 +226,10 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
                     if (j + b < d) votes_out[j + b] = (uint8_t)((ww[4 * q + (b >> 2)] >> (8 * (b & 3))) & 255u);
             }
         }
+    }
+    if constexpr (RANDOM) {
+        write_winners<Q>(winners, winners_per_block, d, K, scan_lds, mask_idx);
+        return;
     }
     uint32_t gt, eq;
     count_above_and_at<Q>(ww, j0, d, vstar, gt, eq);
@@ -249,8 +261,6 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         vote_thr[0] = vstar;
         vote_thr[1] = take_eq;
     }
-    if (!mask_idx) return;                        // random selection writes the mask elsewhere
-
     // The counts of the earlier blocks, without another kernel: every block publishes its own
     // totals at once (word 0 of its pair); its first wavefront then reads the totals of the
     // kLookBack blocks before it, all loads in flight together, and the sum over everything
@@ -473,7 +483,7 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
 
 // Workgroups [0, n_gather_blocks): each owns `rounds` times kb = 1024 / N consecutive
 // positions of the mask.
-// (a) Unless the mask is given (random selection writes it elsewhere), the workgroup
+// (a) Unless the mask is there (it is, but for a block that gave up waiting), the workgroup
 //     first finds its own positions' coordinates: the counts per block of the vote bytes
 //     and, inside the few blocks that matter, per wavefront stretch (from mv_mask_count)
 //     are scanned, which says where in the mask each stretch's coordinates go; the few

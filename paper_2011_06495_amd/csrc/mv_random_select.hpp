@@ -16,10 +16,8 @@ namespace mvk {
 // rand_exp[j] ~ Exp(1) from the caller, and the K clocks that ring first win
 // (equal times: lowest coordinate first).  The time is one correctly rounded fp32
 // division; its bit pattern, complemented, is a key for the same exact select
-// that serves the rows: list of (key, coordinate), a histogram of the key's 11
-// leading bits, the members of the bin that holds the K-th, their exact ranking.
-// Selected coordinates are marked in a bitmap that an ordered compaction turns
-// into the ascending mask.
+// that serves long lists of candidates (list_split).  Selected coordinates are marked in
+// a bitmap that the mask kernel turns into the ascending mask.
 
 // Scan of the packed vote bytes (grid as for the mask kernels): every voted
 // coordinate is appended to the list with its key.  rs_count[0] = list length.
@@ -39,7 +37,7 @@ __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __res
     constexpr int kIt = kVoteBlock / (kVoteThreads * 16);
     constexpr int kPerIt = kVoteThreads * 16;                      // coordinates per round: all may hold a vote
     __shared__ uint32_t stage[kPerIt];
-    __shared__ uint64_t scan_lds[kVoteThreads / kWave + 1];
+    __shared__ uint64_t scan_lds[kVoteThreads / kWave];
     __shared__ uint32_t base_sh;
     const int64_t base = (int64_t)blockIdx.x * kVoteBlock;
     u32x4 w[kIt];
@@ -114,33 +112,61 @@ __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __res
     }
 }
 
-// ---- random selection: one list (row 0); winners are marked in the bitmap
-__global__ __launch_bounds__(kRowThreads) void mv_rs_hist(ListSelect a)
+// ---- one list; its storage is row 0's
+__device__ __forceinline__ ListView rs_list(const u32x2* __restrict__ list, uint32_t list_cap,
+                                            const uint32_t* __restrict__ rs_count, uint32_t K,
+                                            uint32_t* __restrict__ sample_hist)
 {
-    __shared__ uint32_t hist[kSelBins];
-    list_hist_body(a, 0, hist);
+    ListView v;
+    v.list = list;
+    v.n = min(rs_count[0], list_cap);
+    v.want = K;
+    v.base = kAbsMask - 0x42800000u;              // times from 64 down: 64 bins to an octave for eight octaves, then 32
+    v.fine = 17;
+    v.coarse = 18;
+    lend_storage(v, sample_hist, 0, 0);
+    return v;
 }
-__global__ __launch_bounds__(kRowThreads) void mv_rs_split(ListSelect a, uint32_t* __restrict__ rs_bits)
+
+// Long lists only (see list_split): the histogram
+__global__ __launch_bounds__(kRowThreads) void mv_rs_hist(const u32x2* __restrict__ list, uint32_t list_cap,
+                                                          const uint32_t* __restrict__ rs_count, uint32_t K,
+                                                          uint32_t* __restrict__ sample_hist)
 {
-    __shared__ ListSplitLds lds;
-    list_split_body(a, 0, lds, rs_bits);
+    __shared__ uint32_t hist[kListBins];
+    const ListView v = rs_list(list, list_cap, rs_count, K, sample_hist);
+    list_hist(v, blockIdx.x, gridDim.x, hist);
 }
-// Also leaves the list's length at zero for the next step.
-__global__ __launch_bounds__(kRowThreads) void mv_rs_rank(ListSelect a, uint32_t* __restrict__ rs_count,
-                                                          uint32_t* __restrict__ rs_bits)
+
+// Marks the winners in the bitmap and counts them per block of the mask kernel (`per_block` coordinates).  Leaves
+// the list's length at zero for the next step.
+template <bool ALONE>
+__global__ __launch_bounds__(kRowThreads) void mv_rs_pick(const u32x2* __restrict__ list, uint32_t list_cap,
+                                                          uint32_t* __restrict__ rs_count, uint32_t K,
+                                                          uint32_t* __restrict__ sample_hist, u32x2* __restrict__ list2,
+                                                          uint32_t* __restrict__ rs_bits, uint32_t per_block, uint32_t n_blocks,
+                                                          uint32_t* __restrict__ winners_per_block)
 {
-    __shared__ SelectLds lds;
-    uint32_t kth, tie_cut, path;
-    const uint32_t C = min(a.count2[0], a.cap);
-    const bool ranked = list_rank_body(a, 0, lds, kth, tie_cut, path);
-    __syncthreads();
-    if (threadIdx.x == 0) rs_count[0] = 0;
-    if (!ranked) return;
-    const u32x2* list2 = a.list2;
-    for (uint32_t i = threadIdx.x; i < C; i += kRowThreads) {
-        const u32x2 c = list2[i];
-        if (is_taken(c, kth, tie_cut)) atomicOr(&rs_bits[c.y >> 5], 1u << (c.y & 31u));
-    }
+    __shared__ SplitLds<kMembersMost> lds;        // few workgroups, each with a compute unit to itself
+    ListView v = rs_list(list, list_cap, rs_count, K, sample_hist);
+    v.list2 = list2;
+    if (v.n < K) return;                          // whole grid; cannot happen: every row votes K coordinates
+    const BlockTally tally = {lds.tally, winners_per_block, 1, n_blocks};
+    tally.clear();                                // (list_split has barriers before it acts)
+    uint32_t kth, tie_cut;
+    const bool finished = list_split<ALONE>(
+        v, blockIdx.x, gridDim.x, lds,
+        [&](const u32x2 (&c)[kListUnroll], uint32_t taken) {
+#pragma unroll
+            for (int u = 0; u < kListUnroll; ++u) {
+                const bool mine = taken >> u & 1u;
+                if (mine) atomicOr(&rs_bits[c[u].y >> 5], 1u << (c[u].y & 31u));
+                tally.add(c[u].y / per_block, mine);
+            }
+        },
+        kth, tie_cut);
+    tally.merge();
+    if (finished && threadIdx.x == 0) rs_count[0] = 0;   // (all workgroups have read it)
 }
 
 }  // namespace mvk

@@ -1,8 +1,9 @@
 // Exact selects: the K-th largest magnitude of a row's candidate list with its tie cut
-// (one workgroup per row, or three kernels with many workgroups for long lists).
+// (one workgroup per row, or two kernels with many workgroups for long lists).
 #pragma once
 
 #include "mv_common.hpp"
+#include "mv_stream.hpp"
 
 namespace mvk {
 
@@ -12,13 +13,10 @@ namespace mvk {
 
 constexpr int kSelBins = 2048;   // radix-select digit: 11, 10, 10 bits of the 31-bit key
 constexpr int kKeyBins = 4096;   // exact magnitudes inside one fine-histogram bin (1 << kFineShift)
-constexpr int kKeep    = 32;     // candidate keys a thread of the generic select can hold in registers
 constexpr int kRep     = 8;      // copies of the candidates' fine histogram, one per lane % kRep
 constexpr int kTieCap  = 8192;   // ties with the K-th magnitude that fit the LDS list
 constexpr int kRankCap = 256;    // at most this many entries are ranked by counting (quadratic work)
-constexpr int kKeepShort = 32;   // list entries per thread of the two instances of mv_row_select
-constexpr int kKeepLong  = 160;
-constexpr int kSpec    = 32;     // list entries per thread that mv_row_select can fetch ahead of the row's count
+constexpr int kSpec    = 32;     // list entries per thread that mv_row_select keeps, fetched ahead of the row's count
 
 __device__ __forceinline__ int      sel_shift(int pass) { return pass == 0 ? 20 : pass == 1 ? 10 : 0; }
 __device__ __forceinline__ uint32_t sel_dmask(int pass) { return pass == 0 ? 2047u : 1023u; }
@@ -81,29 +79,11 @@ __device__ __forceinline__ void find_rank_bin(const uint32_t* hist, uint64_t* sc
     __syncthreads();
 }
 
-// Key sources for the selects below.  each(f) calls f(key, i, valid) the same
-// number of times in every lane of the workgroup (so f may use wave-wide
-// operations); i is the key's position in the source, valid says whether it
-// exists.
-struct KeysInRegs {                     // thread t holds key number q * kRowThreads + t in k[q]
-    static constexpr bool kCheapPasses = true;
-    const uint32_t (&k)[kKeep];
-    uint32_t count;
-    template <typename F>
-    __device__ __forceinline__ void each(F f) const
-    {
-#pragma unroll
-        for (int q = 0; q < kKeep; ++q) {
-            if ((uint32_t)q * kRowThreads < count) {              // uniform over the workgroup
-                const uint32_t i = (uint32_t)q * kRowThreads + threadIdx.x;
-                f(k[q], (uint64_t)i, i < count);
-            }
-        }
-    }
-};
+// Keys of the selects below, re-read on every pass.  each(f) calls f(key, i, valid) the
+// same number of times in every lane of the workgroup (so f may use wave-wide
+// operations); i is the key's position, valid says whether it exists.
 template <typename KeyAt>
-struct KeysInMemory {                   // re-read on every pass
-    static constexpr bool kCheapPasses = false;
+struct KeysInMemory {
     KeyAt    key_at;
     uint64_t count;
     template <typename F>
@@ -191,6 +171,24 @@ __device__ __forceinline__ uint32_t wave_slots(bool want, uint32_t* counter, uin
     return base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
 }
 
+// f(key, count) by the first lane of every group of neighbouring lanes with equal keys, count being the
+// group's lanes with `marked` set, if any.  All lanes of the wavefront must call it.
+template <typename F>
+__device__ __forceinline__ void tally_groups(uint32_t key, bool marked, F f)
+{
+    const uint32_t lane = lane_id();
+    const uint32_t prev = __shfl_up(key, 1, kWave);
+    const uint64_t heads = __ballot(lane == 0 || key != prev);
+    const uint64_t tk = __ballot(marked);
+    if (heads & (1ull << lane)) {
+        const uint64_t above = (lane == kWave - 1) ? 0ull : (heads >> (lane + 1));
+        const uint32_t len = above ? (uint32_t)__ffsll((long long)above) : (kWave - lane);
+        const uint64_t span = (len >= 64 ? ~0ull : ((1ull << len) - 1)) << lane;
+        const uint32_t n = (uint32_t)__popcll(tk & span);
+        if (n) f(key, n);
+    }
+}
+
 // A candidate (magnitude bits, coordinate) is in the row's top K iff its
 // magnitude is above the K-th largest, or equals it and its coordinate is not
 // beyond the last tie taken (ties go to the lowest coordinates).
@@ -210,17 +208,19 @@ struct SelectLds {
     uint64_t scan[kRowThreads / kWave + 1];
 };
 
-// The take-th SMALLEST of the n distinct coordinates in lds.ties[0..n): ranked by
+// The take-th SMALLEST of the n distinct coordinates in ties[0..n): ranked by
 // counting when few; else narrowed by one histogram and then ranked by counting;
 // a radix select on (0x7FFFFFFF - coordinate) if they crowd into one bin.
-__device__ __forceinline__ uint32_t smallest_coordinate(SelectLds& lds, uint32_t n, uint32_t take)
+// (Lds: the scratch of the kernel at hand; ties has room for four more entries.)
+template <typename Lds>
+__device__ __forceinline__ uint32_t smallest_coordinate(Lds& lds, uint32_t* ties, uint32_t n, uint32_t take)
 {
     if (n <= (uint32_t)kRankCap) {
-        if (threadIdx.x < 4) lds.ties[n + threadIdx.x] = 0xFFFFFFFFu;   // pad to a multiple of 4, ranked last
+        if (threadIdx.x < 4) ties[n + threadIdx.x] = 0xFFFFFFFFu;   // pad to a multiple of 4, ranked last
         __syncthreads();
         if (threadIdx.x < n) {
-            const uint32_t mine = lds.ties[threadIdx.x];
-            const u32x4* tv = reinterpret_cast<const u32x4*>(lds.ties);
+            const uint32_t mine = ties[threadIdx.x];
+            const u32x4* tv = reinterpret_cast<const u32x4*>(ties);
             uint32_t below = 0;
 #pragma unroll 4
             for (uint32_t j = 0; j < (n + 3) / 4; ++j) {
@@ -246,7 +246,7 @@ __device__ __forceinline__ uint32_t smallest_coordinate(SelectLds& lds, uint32_t
     __syncthreads();
     uint32_t mx = 0u, mn = 0xFFFFFFFFu;
     for (uint32_t i = t; i < n; i += kRowThreads) {
-        const uint32_t c = lds.ties[i];
+        const uint32_t c = ties[i];
         mx = max(mx, c);
         mn = min(mn, c);
     }
@@ -265,7 +265,7 @@ __device__ __forceinline__ uint32_t smallest_coordinate(SelectLds& lds, uint32_t
     const uint32_t shift = span < (uint32_t)kSelBins ? 0u : (32u - (uint32_t)__clz(span)) - 11u;
     // bins ordered like the select's keys: the smallest coordinates in the highest bin
     for (uint32_t i = t; i < n; i += kRowThreads)
-        atomicAdd(&lds.hist[(uint32_t)(kSelBins - 1) - ((lds.ties[i] - mn) >> shift)], 1u);
+        atomicAdd(&lds.hist[(uint32_t)(kSelBins - 1) - ((ties[i] - mn) >> shift)], 1u);
     __syncthreads();                                  // also: everyone has read bcast
     uint32_t bin, want, in_bin;
     find_rank_bin<kSelBins>(lds.hist, lds.scan, lds.bcast, take, bin, want, in_bin);
@@ -273,7 +273,7 @@ __device__ __forceinline__ uint32_t smallest_coordinate(SelectLds& lds, uint32_t
         if (t == 0) lds.n_list = 0;
         __syncthreads();
         for (uint32_t i = t; i < n; i += kRowThreads) {
-            const uint32_t c = lds.ties[i];
+            const uint32_t c = ties[i];
             if ((uint32_t)(kSelBins - 1) - ((c - mn) >> shift) == bin) lds.hist[atomicAdd(&lds.n_list, 1u)] = c;
         }
         if (t < 4) lds.hist[in_bin + t] = 0xFFFFFFFFu;
@@ -295,7 +295,6 @@ __device__ __forceinline__ uint32_t smallest_coordinate(SelectLds& lds, uint32_t
         return r;
     }
     uint32_t t_eq, n_eq;
-    const uint32_t* ties = lds.ties;
     auto at = [ties](uint64_t i) { return kAbsMask - ties[i]; };
     const KeysInMemory<decltype(at)> src{at, n};
     return kAbsMask - block_radix_select(src, take, lds.hist, lds.scan, lds.bcast, t_eq, n_eq);
@@ -387,31 +386,6 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
             tie_cut = lds.bcast[1];
             return;
         }
-        if (Keys::kCheapPasses && in_bin <= (uint32_t)kKeyBins) {   // uniform; an extra pass only where passes are cheap
-            // A crowded bin that still fits in LDS.  Values on a lattice put hundreds of
-            // EQUAL magnitudes there: if all members share one key, that key is the K-th
-            // largest and only the tie cut is left to find, among coordinates already in LDS.
-            if (t < 2) lds.bcast[t] = t ? 0xFFFFFFFFu : 0u;          // max, min of the members' keys
-            collect_bin_members(keys, crow, tau, bin, in_bin, lds);
-            for (uint32_t i = t; i < in_bin; i += kRowThreads) {
-                const uint32_t k = lds.hist[i];
-                if (k != lds.hist[0]) {                              // any writer will do: both end up != hist[0]
-                    atomicMax(&lds.bcast[0], k);
-                    atomicMin(&lds.bcast[1], k);
-                }
-            }
-            __syncthreads();
-            const bool one_key = lds.bcast[0] == 0u && lds.bcast[1] == 0xFFFFFFFFu;   // nobody differed from hist[0]
-            const uint32_t the_key = lds.hist[0];
-            __syncthreads();
-            if (one_key) {                                           // uniform
-                kth = the_key;
-                tie_cut = want < in_bin ? smallest_coordinate(lds, in_bin, want) : 0xFFFFFFFFu;
-                return;
-            }
-            if (t == 0) lds.n_list = 0;                              // distinct keys: go on below
-            __syncthreads();
-        }
         if (bin < (uint32_t)(kFineBins - 1)) {
             // a crowded bin (many equal magnitudes): it spans exactly 4096 key values,
             // so a second histogram over the exact keys inside it finds the K-th largest
@@ -444,7 +418,7 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
             __syncthreads();
             for (uint32_t p = t; p < n_eq; p += kRowThreads) lds.ties[p] = crow[lds.ties[p]].y;
             __syncthreads();
-            tie_cut = smallest_coordinate(lds, n_eq, take_eq);
+            tie_cut = smallest_coordinate(lds, lds.ties, n_eq, take_eq);
         } else {
             // more ties than the LDS list holds: select over the whole candidate list in
             // memory, entries that are not ties mapped below every tie
@@ -459,93 +433,87 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
     }
 }
 
-// Casts the votes of the list entries i with (i / kRowThreads) % parts == part:
-// a taken candidate adds one to its coordinate's vote byte and, when the sorted
-// vote lists are wanted (ssel != nullptr), is tallied in its 1024-coordinate
-// segment (ssel was zeroed by the streaming pass).  Lanes of a wavefront hold
-// consecutive list entries, which mostly share a segment (they are one run): the
-// first lane of each group of equal segments adds the group's count.  All threads of
-// the workgroup must call it.
-template <int NT, bool MERGE>
+// Casts votes for the marked ones of a batch of list entries, U per thread (bit u of `taken`: c[u]): each
+// adds one to its coordinate's vote byte and, when the sorted vote lists are wanted (ssel != nullptr), is
+// tallied in its 1024-coordinate segment (ssel was zeroed by the streaming pass).  Lanes of a wavefront
+// mostly hold consecutive list entries, which share a segment (they are one run): the first lane of each
+// group of equal segments adds the group's count.  All threads of the workgroup must call it.
+template <int U, bool MERGE>
+__device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_mask, uint32_t* __restrict__ votes32,
+                                           uint32_t* lvl, uint32_t* __restrict__ ssel)
+{
+    const uint32_t lane = lane_id();
+    // MERGE (long lists, where the atomics' rate at the memory side is what the step waits for): lanes
+    // hold consecutive list entries, ascending inside a run, and a row votes at most once per
+    // coordinate, so neighbouring taken lanes whose coordinates share a vote word (four bytes) cast
+    // their votes with ONE atomic, the sum of their byte increments, issued by the first of them;
+    // the returned word holds every byte's count before this row's vote.  Where the mask is dense
+    // that is up to four votes per atomic (measured at K = d/100: 27 -> 19 us).  Short lists
+    // wait for latency, not rate: there every taken lane issues its own.
+    uint32_t old[U];
+    uint32_t ahead[U];                            // lanes between this lane and the first of its group
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool taken = (taken_mask >> u) & 1u;
+        const uint32_t inc = taken ? 1u << ((c[u].y & 3u) * 8u) : 0u;
+        uint32_t before = 0;                      // lanes of the same group just below this one
+        uint32_t sum = inc;
+        if (MERGE) {
+            const uint32_t key = taken ? (c[u].y >> 2) : (0xFFFFFF00u | lane);   // never equal to a neighbour's
+            bool run = true;
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {
+                const uint32_t below = __shfl_up(key, k, kWave);
+                run = run && lane >= (uint32_t)k && below == key;
+                before += run ? 1u : 0u;
+            }
+            run = true;
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {
+                const uint32_t above_key = __shfl_down(key, k, kWave);
+                const uint32_t above_inc = __shfl_down(inc, k, kWave);
+                run = run && lane + (uint32_t)k < (uint32_t)kWave && above_key == key;
+                sum += run ? above_inc : 0u;
+            }
+        }
+        ahead[u] = before;
+        old[u] = 0;
+        if (taken && before == 0u) old[u] = atomicAdd(&votes32[c[u].y >> 2], sum);
+    }
+    if (MERGE) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) old[u] = __shfl(old[u], lane - ahead[u], kWave);   // the group's returned word
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const bool taken = (taken_mask >> u) & 1u;
+        if (taken) atomicAdd(&lvl[((old[u] >> ((c[u].y & 3u) * 8u)) & 255u) + 1u], 1u);
+        if (ssel) tally_groups(c[u].y / kSeg, taken, [&](uint32_t sg, uint32_t n) { atomicAdd(&ssel[sg], n); });
+    }
+}
+
+// The votes of the list entries i with (i / kRowThreads) % parts == part, those that are taken.
 __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ crow, uint32_t C, uint32_t kth,
                                                     uint32_t tie_cut, uint32_t part, uint32_t parts,
                                                     uint32_t* __restrict__ votes32, uint32_t* lvl,
                                                     uint32_t* __restrict__ ssel)
 {
+    // all the loads, then all the vote atomics, then what depends on their results: a thread's
+    // entries wait for memory together, not one after the other
     constexpr int kU = 8;                         // list entries per thread in flight together
-    const uint32_t t = threadIdx.x, lane = lane_id();
-    for (uint64_t q0 = part; q0 * NT < C; q0 += (uint64_t)parts * kU) {
-        // all the loads, then all the vote atomics, then what depends on their results: a thread's
-        // entries wait for memory together, not one after the other
+    for (uint64_t q0 = part; q0 * kRowThreads < C; q0 += (uint64_t)parts * kU) {
         u32x2 c[kU];
+        uint32_t taken = 0;
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const uint64_t i = (q0 + (uint64_t)u * parts) * NT + t;
+            const uint64_t i = (q0 + (uint64_t)u * parts) * kRowThreads + threadIdx.x;
             const u32x2 none = {0u, 0xFFFFFFFFu};
             c[u] = (i < C) ? crow[i] : none;
         }
-        // MERGE (long lists, where the atomics' rate at the memory side is what the step waits for): lanes
-        // hold consecutive list entries, ascending inside a run, and a row votes at most once per
-        // coordinate, so neighbouring taken lanes whose coordinates share a vote word (four bytes) cast
-        // their votes with ONE atomic, the sum of their byte increments, issued by the first of them;
-        // the returned word holds every byte's count before this row's vote.  Where the mask is dense
-        // that is up to four votes per atomic (measured at K = d/100: 27 -> 19 us).  Short lists
-        // wait for latency, not rate: there every taken lane issues its own.
-        uint32_t old[kU];
-        uint32_t taken_mask = 0;
-        uint32_t ahead[kU];                           // lanes between this lane and the first of its group
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const bool taken = c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut);
-            if (taken) taken_mask |= 1u << u;
-            const uint32_t inc = taken ? 1u << ((c[u].y & 3u) * 8u) : 0u;
-            uint32_t before = 0;                      // lanes of the same group just below this one
-            uint32_t sum = inc;
-            if (MERGE) {
-                const uint32_t key = taken ? (c[u].y >> 2) : (0xFFFFFF00u | lane);   // never equal to a neighbour's
-                bool run = true;
-#pragma unroll
-                for (int k = 1; k < 4; ++k) {
-                    const uint32_t below = __shfl_up(key, k, kWave);
-                    run = run && lane >= (uint32_t)k && below == key;
-                    before += run ? 1u : 0u;
-                }
-                run = true;
-#pragma unroll
-                for (int k = 1; k < 4; ++k) {
-                    const uint32_t above_key = __shfl_down(key, k, kWave);
-                    const uint32_t above_inc = __shfl_down(inc, k, kWave);
-                    run = run && lane + (uint32_t)k < (uint32_t)kWave && above_key == key;
-                    sum += run ? above_inc : 0u;
-                }
-            }
-            ahead[u] = before;
-            old[u] = 0;
-            if (taken && before == 0u) old[u] = atomicAdd(&votes32[c[u].y >> 2], sum);
-        }
-        if (MERGE) {
-#pragma unroll
-            for (int u = 0; u < kU; ++u) old[u] = __shfl(old[u], lane - ahead[u], kWave);   // the group's returned word
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            if ((q0 + (uint64_t)u * parts) * NT >= C) break;        // uniform over the workgroup
-            const bool taken = (taken_mask >> u) & 1u;
-            if (taken) atomicAdd(&lvl[((old[u] >> ((c[u].y & 3u) * 8u)) & 255u) + 1u], 1u);
-            if (ssel) {
-                const uint32_t sg = c[u].y / kSeg;
-                const uint32_t prev = __shfl_up(sg, 1, kWave);
-                const uint64_t heads = __ballot(lane == 0 || sg != prev);
-                const uint64_t tk = __ballot(taken);
-                if (heads & (1ull << lane)) {
-                    const uint64_t above = (lane == kWave - 1) ? 0ull : (heads >> (lane + 1));
-                    const uint32_t len = above ? (uint32_t)__ffsll((long long)above) : (kWave - lane);
-                    const uint64_t span = (len >= 64 ? ~0ull : ((1ull << len) - 1)) << lane;
-                    const uint32_t n = (uint32_t)__popcll(tk & span);
-                    if (n) atomicAdd(&ssel[sg], n);
-                }
-            }
-        }
+        for (int u = 0; u < kU; ++u)
+            taken |= (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
+        cast_votes<kU, false>(c, taken, votes32, lvl, ssel);
     }
 }
 
@@ -676,7 +644,7 @@ __device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, c
     if (lds.bcast[2] == 0) {                      // uniform
         kth = mkey[0];
         __syncthreads();                          // everyone has read bcast and mkey
-        tie_cut = want < in_bin ? smallest_coordinate(lds, in_bin, want) : 0xFFFFFFFFu;
+        tie_cut = want < in_bin ? smallest_coordinate(lds, lds.ties, in_bin, want) : 0xFFFFFFFFu;
         return true;
     }
     // up to 4096 members: the bin spans exactly 4096 key values, so a histogram over the
@@ -704,145 +672,22 @@ __device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, c
             if (mine) lds.ties[s] = mpos[p];
         }
         __syncthreads();
-        tie_cut = smallest_coordinate(lds, n_eq, take_eq);
+        tie_cut = smallest_coordinate(lds, lds.ties, n_eq, take_eq);
     }
     return true;
 }
 
-// parts workgroups per row; the grid is one-dimensional and workgroup ids are laid
-// out so that the workgroups of one row have equal id % 8: consecutive ids go to
-// different XCDs (each with an L2 of its own), so a row's list is then read from
-// memory once and served to the row's other workgroups from that L2.
-// Usual case: EVERY workgroup of a row runs the same exact select over the row's
-// candidate list (the work is repeated rather than shared so that no workgroup
-// waits for another): the K-th largest magnitude kth[row] and tie_cut[row], the
-// largest coordinate taken among the candidates tied with it (0xFFFFFFFF: all ties
-// taken).  Each workgroup then casts the votes of its share of the list.  With
-// thresholds_only (add-drop voting) no vote is cast; with slow_rows_only the
-// candidate lists are selected by the mv_sel_* kernels and their votes cast by
-// mv_row_votes.
-// If the candidate count is < K or overflowed the list (for instance a row of
-// equal magnitudes), the row's first workgroup selects it exactly from memory (e
-// already holds a = g + e), emits and casts its vote; slow_flag[row] = 1 tells the
-// later kernels to skip the row.
-// n_spec (<= kSpec): how many of a thread's list entries are fetched before the
-// row's count is known (the list's storage holds cap entries; what lies at or
-// beyond the count is ignored), so that the two loads do not queue up.
-template <int KEEP>
-__global__ __launch_bounds__(kRowThreads) void mv_row_select(
-    const float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N, uint32_t K,
-    const u32x2* __restrict__ cand, uint32_t cap, const uint32_t* __restrict__ row_count_sets,
-    uint32_t row_count_set_words, const uint32_t* __restrict__ step_no,
-    const unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ row_poison,
-    uint32_t* __restrict__ cand_count, uint32_t* __restrict__ tau_bits, uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out,
-    uint32_t* __restrict__ worker_idx, uint32_t* __restrict__ votes32,
-    uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
-    uint32_t* __restrict__ slow_flag, uint32_t parts, uint32_t n_spec, int thresholds_only, int slow_rows_only)
+// Exact select of a whole row from memory by one workgroup: the K-th largest magnitude by a radix select,
+// then the row's vote in ascending order (out, may be null) and its votes; with thresholds_only the tie cut
+// instead.  (Lds: the scratch of the kernel at hand.)
+template <typename Lds>
+__device__ __forceinline__ void select_row_from_memory(Lds& lds, const float* __restrict__ arow, int64_t d, uint32_t K,
+                                                       uint32_t* __restrict__ out, uint32_t* __restrict__ votes32,
+                                                       uint32_t* __restrict__ lvl_sets, uint32_t* __restrict__ kth_out,
+                                                       uint32_t* __restrict__ tie_cut_out, int thresholds_only)
 {
-    __shared__ SelectLds lds;
     const uint32_t t = threadIdx.x;
-    const uint32_t within = blockIdx.x % (8u * parts);
-    const uint32_t row = (blockIdx.x / (8u * parts)) * 8u + within % 8u, part = within / 8u;
-    if (row >= N) return;                         // whole workgroup
-    const u32x2* crow = cand + (size_t)row * cap;
-    uint32_t raw[kSpec];
-#pragma unroll
-    for (int q = 0; q < kSpec; ++q) {
-        raw[q] = 0;
-        if ((uint32_t)q < n_spec) raw[q] = crow[min((uint32_t)q * kRowThreads + t, cap - 1)].x;
-        if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);   // keep address arithmetic from piling up
-    }
-    // (the streaming kernel counted into the counter set of this step's parity)
-    const uint32_t epoch = step_no[0] + 1u;
-    uint32_t C = row_count_sets[(epoch & 1u) * row_count_set_words + row * kCounterStride];
-    const uint32_t tau = (uint32_t)tau_pub[row * (kCounterStride / 2)];   // with the count, not after it
-    // a row whose streaming wavefronts did not all see tau in time: its list is incomplete
-    const bool poisoned = row_poison[row] == epoch;
-    // the fine histogram is cleared while those loads are under way
-    {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        u32x4* rz = reinterpret_cast<u32x4*>(lds.rhist);
-        for (int b = t; b < kFineBins * kRep / 4; b += kRowThreads) rz[b] = z;
-        if (t == 0) lds.n_list = 0;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    if (poisoned) C = kRowPoison | C;             // reads as overflowed, here and for every later reader
-    if (part == 0 && t == 0) {                    // for the kernels that follow, and the row statistics
-        cand_count[row] = C;
-        tau_bits[row] = tau;
-        slow_flag[row] = 0;
-    }
-    const bool from_list = C >= K && C <= cap;
-    if (slow_rows_only && from_list) return;      // whole workgroup
-    if (!from_list && part != 0) return;          // whole workgroup
-
-    if (from_list) {
-        uint32_t kth = 0, tie_cut = 0, path = 0;
-        bool done = false;
-        if (tau != 0 && C <= (uint32_t)KEEP * kRowThreads) {
-            PackedBins<KEEP> bins;
-            bins.clear();
-            auto pack = [&](auto qc, uint32_t key) {
-                constexpr int Q = decltype(qc)::value;
-                const uint32_t i = (uint32_t)Q * kRowThreads + t;
-                bins.template set<Q>(i < C ? fine_bin(key, tau) : 0xFFFFu);
-            };
-            // what was fetched ahead, then the rest of the list
-            static_for<0, (KEEP < kSpec ? KEEP : kSpec)>([&](auto qc) {
-                constexpr int Q = decltype(qc)::value;
-                if ((uint32_t)Q < n_spec && (uint32_t)Q * kRowThreads < C) pack(qc, raw[Q]);
-            });
-            // (sixteen loads at a time, all issued before the first is used: used one by one, each load
-            // would wait for the one before)
-            static_for<0, KEEP / 16>([&](auto gc) {
-                constexpr int G = decltype(gc)::value;
-                if ((uint32_t)(G * 16 + 15) >= n_spec && (uint32_t)(G * 16) * kRowThreads < C) {   // uniform
-                    uint32_t more[16];
-#pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        more[q] = 0;
-                        if ((uint32_t)(G * 16 + q) >= n_spec && (uint32_t)(G * 16 + q) * kRowThreads < C)   // uniform
-                            more[q] = crow[min((uint32_t)(G * 16 + q) * kRowThreads + t, cap - 1)].x;
-                    }
-                    static_for<0, 16>([&](auto qc) {
-                        constexpr int Q = G * 16 + decltype(qc)::value;
-                        if ((uint32_t)Q >= n_spec && (uint32_t)Q * kRowThreads < C)
-                            pack(std::integral_constant<int, Q>{}, more[decltype(qc)::value]);
-                    });
-                }
-            });
-            done = select_from_bins<KEEP>(bins, crow, C, K, tau, lds, kth, tie_cut);
-        }
-        if (!done) {                              // uniform
-            __syncthreads();
-            path = 2;
-            auto at = [crow](uint64_t i) { return crow[i].x; };
-            const KeysInMemory<decltype(at)> src{at, C};
-            uint32_t p2;
-            select_among_candidates(src, crow, C, K, tau, lds, kth, tie_cut, p2);
-        }
-        if (part == 0 && t == 0) {
-            kth_out[row] = kth;
-            tie_cut_out[row] = tie_cut;
-            if (path) slow_flag[row] = path;      // diagnostic only
-        }
-        if (!thresholds_only) {
-            for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;
-            __syncthreads();
-            cast_votes_of_share<kRowThreads, (KEEP > kKeepShort)>(crow, C, kth, tie_cut, part, parts, votes32, lds.lvl,
-                                             seg_sel ? seg_sel + (size_t)row * nseg : nullptr);
-            __syncthreads();
-            merge_levels(lds.lvl, lvl_sets, blockIdx.x);
-        }
-        return;
-    }
-
-    // ---- exact path from memory
-    if (t == 0) slow_flag[row] = 1;
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;   // ordered by the select's first barrier
-    uint32_t* out = worker_idx ? worker_idx + (size_t)row * K : nullptr;
-    const float* arow = e + (int64_t)row * ld_e;
     uint32_t take_eq, n_eq;
     auto at = [arow](uint64_t i) { return __float_as_uint(arow[i]) & kAbsMask; };
     const KeysInMemory<decltype(at)> src{at, (uint64_t)d};
@@ -860,8 +705,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
             tie_cut = kAbsMask - block_radix_select(ties_src, take_eq, lds.hist, lds.scan, lds.bcast, t_eq, t_n);
         }
         if (t == 0) {
-            kth_out[row] = kth;
-            tie_cut_out[row] = tie_cut;
+            *kth_out = kth;
+            *tie_cut_out = tie_cut;
         }
         return;
     }
@@ -900,188 +745,589 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     merge_levels(lds.lvl, lvl_sets, blockIdx.x);
 }
 
+// parts workgroups per row; the grid is one-dimensional and workgroup ids are laid
+// out so that the workgroups of one row have equal id % 8: consecutive ids go to
+// different XCDs (each with an L2 of its own), so a row's list is then read from
+// memory once and served to the row's other workgroups from that L2.
+// Usual case: EVERY workgroup of a row runs the same exact select over the row's
+// candidate list (the work is repeated rather than shared so that no workgroup
+// waits for another): the K-th largest magnitude kth[row] and tie_cut[row], the
+// largest coordinate taken among the candidates tied with it (0xFFFFFFFF: all ties
+// taken).  Each workgroup then casts the votes of its share of the list.  With
+// thresholds_only (add-drop voting) no vote is cast.  Longer lists go through
+// mv_sel_hist and mv_sel_split.
+// If the candidate count is < K or overflowed the list (for instance a row of
+// equal magnitudes), the row's first workgroup selects it exactly from memory (e
+// already holds a = g + e), emits and casts its vote; slow_flag[row] = 1 tells the
+// later kernels to skip the row.
+// n_spec (<= kSpec): how many of a thread's list entries are fetched before the
+// row's count is known (the list's storage holds cap entries; what lies at or
+// beyond the count is ignored), so that the two loads do not queue up.
+__global__ __launch_bounds__(kRowThreads) void mv_row_select(
+    const float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N, uint32_t K,
+    const u32x2* __restrict__ cand, uint32_t cap, const uint32_t* __restrict__ row_count_sets,
+    uint32_t row_count_set_words, const uint32_t* __restrict__ step_no,
+    const unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ row_poison,
+    uint32_t* __restrict__ cand_count, uint32_t* __restrict__ tau_bits, uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out,
+    uint32_t* __restrict__ worker_idx, uint32_t* __restrict__ votes32,
+    uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
+    uint32_t* __restrict__ slow_flag, uint32_t parts, uint32_t n_spec, int thresholds_only)
+{
+    __shared__ SelectLds lds;
+    const uint32_t t = threadIdx.x;
+    const uint32_t within = blockIdx.x % (8u * parts);
+    const uint32_t row = (blockIdx.x / (8u * parts)) * 8u + within % 8u, part = within / 8u;
+    if (row >= N) return;                         // whole workgroup
+    const u32x2* crow = cand + (size_t)row * cap;
+    uint32_t raw[kSpec];
+#pragma unroll
+    for (int q = 0; q < kSpec; ++q) {
+        raw[q] = 0;
+        if ((uint32_t)q < n_spec) raw[q] = crow[min((uint32_t)q * kRowThreads + t, cap - 1)].x;
+        if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);   // keep address arithmetic from piling up
+    }
+    // (the streaming kernel counted into the counter set of this step's parity)
+    const uint32_t epoch = step_no[0] + 1u;
+    uint32_t C = row_count_sets[(epoch & 1u) * row_count_set_words + row * kCounterStride];
+    const uint32_t tau = (uint32_t)tau_pub[row * (kCounterStride / 2)];   // with the count, not after it
+    // a row whose streaming wavefronts did not all see tau in time: its list is incomplete
+    const bool poisoned = row_poison[row] == epoch;
+    // the fine histogram is cleared while those loads are under way
+    {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        u32x4* rz = reinterpret_cast<u32x4*>(lds.rhist);
+        for (int b = t; b < kFineBins * kRep / 4; b += kRowThreads) rz[b] = z;
+        if (t == 0) lds.n_list = 0;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    if (poisoned) C = kRowPoison | C;             // reads as overflowed, here and for every later reader
+    if (part == 0 && t == 0) {                    // for the kernels that follow, and the row statistics
+        cand_count[row] = C;
+        tau_bits[row] = tau;
+        slow_flag[row] = 0;
+    }
+    const bool from_list = C >= K && C <= cap;
+    if (!from_list && part != 0) return;          // whole workgroup
+
+    if (from_list) {
+        uint32_t kth = 0, tie_cut = 0, path = 0;
+        bool done = false;
+        if (tau != 0 && C <= (uint32_t)kSpec * kRowThreads) {
+            PackedBins<kSpec> bins;
+            bins.clear();
+            auto pack = [&](auto qc, uint32_t key) {
+                constexpr int Q = decltype(qc)::value;
+                const uint32_t i = (uint32_t)Q * kRowThreads + t;
+                bins.template set<Q>(i < C ? fine_bin(key, tau) : 0xFFFFu);
+            };
+            static_for<0, kSpec>([&](auto qc) {
+                constexpr int Q = decltype(qc)::value;
+                if ((uint32_t)Q * kRowThreads < C) pack(qc, (uint32_t)Q < n_spec ? raw[Q] : crow[min((uint32_t)Q * kRowThreads + t, cap - 1)].x);
+            });
+            done = select_from_bins<kSpec>(bins, crow, C, K, tau, lds, kth, tie_cut);
+        }
+        if (!done) {                              // uniform
+            __syncthreads();
+            path = 2;
+            auto at = [crow](uint64_t i) { return crow[i].x; };
+            const KeysInMemory<decltype(at)> src{at, C};
+            uint32_t p2;
+            select_among_candidates(src, crow, C, K, tau, lds, kth, tie_cut, p2);
+        }
+        if (part == 0 && t == 0) {
+            kth_out[row] = kth;
+            tie_cut_out[row] = tie_cut;
+            if (path) slow_flag[row] = path;      // diagnostic only
+        }
+        if (!thresholds_only) {
+            for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;
+            __syncthreads();
+            cast_votes_of_share(crow, C, kth, tie_cut, part, parts, votes32, lds.lvl,
+                                seg_sel ? seg_sel + (size_t)row * nseg : nullptr);
+            __syncthreads();
+            merge_levels(lds.lvl, lvl_sets, blockIdx.x);
+        }
+        return;
+    }
+
+    if (t == 0) slow_flag[row] = 1;
+    select_row_from_memory(lds, e + (int64_t)row * ld_e, d, K, worker_idx ? worker_idx + (size_t)row * K : nullptr,
+                           votes32, lvl_sets, kth_out + row, tie_cut_out + row, thresholds_only);
+}
+
 // ---- exact select over a long list with many workgroups ----------------------
-// Three kernels find the `want` largest keys of lists too long for one workgroup
-// to read more than once: (1) a histogram of kSelBins bins of (key - base) >> shift
-// over the list, (2) every workgroup locates the bin of the want-th largest and
-// moves that bin's members to a second list (and, with a bitmap, marks the
-// entries of higher bins), (3) one workgroup per list ranks the second list
-// exactly.  They serve the random selection (one list, base 0, shift 20: the 11
-// leading key bits) and the rows' top-K when K is large (one list per row, base =
-// the row's threshold estimate, shift = kFineShift).
-constexpr int kListPerThread = 4;
-constexpr int kListPerBlock = kRowThreads * kListPerThread;
+// Finds the `want` largest keys of a list and does something with them, in two
+// launches when the list is long: (1) a histogram of the keys over the list (see
+// list_bin), (2) every workgroup locates the bin of the
+// want-th largest, acts on its entries of higher bins, and moves that bin's members
+// to a second list; the last of a list's workgroups ranks these exactly and acts on
+// those that are taken.  Lists that one workgroup reads in a moment take one launch,
+// with the histogram in LDS.  The rows' top K when K is large (to act = cast the
+// vote), the add and drop candidates of add-drop voting, and the random selection all
+// come this way.
+//
+// What the last workgroup reads of the others -- the second list and its length -- goes
+// through atomics, which are performed in memory; the workgroups count themselves done
+// behind them, and nobody waits.
+// 10 lists of 145,000, K = 111,740, with the votes: 59 us in five launches (select, histogram,
+// split, rank, votes), 44 us so; random selection and add-drop voting lost three and two
+// launches of at least 4 us each.
+constexpr int kListUnroll = 4;                    // entries per thread in flight together
+constexpr int kListBatch = kRowThreads * kListUnroll;
+// members of the want-th largest's bin that are ranked in LDS: the first lets two workgroups share a compute unit
+constexpr int kMembers = 3072, kMembersMost = 8192;
+constexpr int kTallyBlocks = 1024;
+constexpr uint32_t kAloneList = 4 * kListBatch;   // lists of up to so many entries are left to one workgroup
 
-struct ListSelect {
-    const u32x2* list;        // rows of `cap` entries
-    uint32_t     cap;
-    const uint32_t* count;    // entries per row (clamped to cap), row r at count[r * count_stride]
-    uint32_t     count_stride;
-    const uint32_t* base;     // per row, or null: 0
-    uint32_t     shift;
-    uint32_t     want;        // K
-    uint32_t*    hist;        // rows of kSelBins counters, zero between steps
-    u32x2*       list2;       // rows of `cap` entries: members of the want-th largest's bin
-    uint32_t*    count2;      // per row, zero between steps
-    uint32_t*    bin_want;    // per row: the bin, and how many of its members are wanted
+struct ListView {
+    const u32x2* list;
+    uint32_t  n;              // entries, at least `want`
+    uint32_t  want;
+    uint32_t  base, fine, coarse;   // the histogram's bins, see list_bin
+    uint32_t* hist;           // kListBins counters, zero between steps
+    uint32_t* count2;         // length of the second list, zero between steps
+    uint32_t* done;           // workgroups that have passed, zero between steps (on a line of its own)
+    u32x2*    list2;          // room for n entries; step2 = -1: growing downwards
+    int       step2;
 };
 
-__device__ __forceinline__ uint32_t list_bin(uint32_t key, uint32_t base, uint32_t shift)
-{
-    return min((key - base) >> shift, (uint32_t)(kSelBins - 1));
-}
-// a row takes part when its list holds at least `want` entries and did not overflow
-__device__ __forceinline__ bool list_row_ok(const ListSelect& a, uint32_t row, uint32_t& n)
-{
-    n = a.count[row * a.count_stride];
-    return n >= a.want && n <= a.cap;
-}
-
-__device__ __forceinline__ void list_hist_body(const ListSelect& a, uint32_t row, uint32_t* hist_lds)
-{
-    const uint32_t t = threadIdx.x;
-    uint32_t n;
-    if (!list_row_ok(a, row, n)) return;                             // whole workgroup
-    const uint32_t i0 = blockIdx.x * (uint32_t)kListPerBlock;
-    if (i0 >= n) return;                                             // whole workgroup
-    const u32x2* list = a.list + (size_t)row * a.cap;
-    const uint32_t base = a.base ? a.base[row] : 0u;
-    uint32_t k[kListPerThread];
-#pragma unroll
-    for (int u = 0; u < kListPerThread; ++u) {
-        const uint32_t i = i0 + (uint32_t)u * kRowThreads + t;
-        k[u] = (i < n) ? list[i].x : 0xFFFFFFFFu;                   // keys are at most 0x7FFFFFFF
-    }
-    for (int b = t; b < kSelBins; b += kRowThreads) hist_lds[b] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < kListPerThread; ++u)
-        if (k[u] != 0xFFFFFFFFu) atomicAdd(&hist_lds[list_bin(k[u], base, a.shift)], 1u);
-    __syncthreads();
-    uint32_t* hrow = a.hist + (size_t)row * kSelBins;
-    for (int b = t; b < kSelBins; b += kRowThreads) {
-        const uint32_t c = hist_lds[b];
-        if (c) atomicAdd(&hrow[b], c);
-    }
-}
-
-struct ListSplitLds {
-    uint32_t hist[kSelBins];
-    uint64_t scan[kRowThreads / kWave + 1];
+template <int MEMBERS>
+struct SplitLds {
+    static constexpr uint32_t kMost = MEMBERS;
+    __attribute__((aligned(16))) uint32_t hist[kKeyBins];
+    __attribute__((aligned(16))) uint32_t key[2][MEMBERS + 4];
+    __attribute__((aligned(16))) uint32_t at[2][MEMBERS + 4];
+    union {
+        uint32_t lvl[257];                        // the rows' votes: see merge_levels
+        uint32_t tally[kTallyBlocks];             // the other lists: see BlockTally
+    };
     uint32_t bcast[3];
-    uint32_t base_sh;
+    uint32_t n_list, last;
+    uint64_t scan[kRowThreads / kWave];
 };
 
-__device__ __forceinline__ void list_split_body(const ListSelect& a, uint32_t row, ListSplitLds& lds,
-                                                uint32_t* __restrict__ bits)
+// Counts taken entries per block of coordinates: in LDS and merged at the end, since the taken ones concentrate in
+// few blocks and their counters in memory would be the bottleneck (counted there one group of lanes at a time, the
+// random selection's pick took 31 us instead of 14); in memory when there are more blocks than LDS has
+// counters.
+struct BlockTally {
+    uint32_t* lds;
+    uint32_t* counters;       // of block b at counters[b * stride]
+    uint32_t  stride, n_blocks;
+    __device__ __forceinline__ void clear() const       // a barrier must follow before the first add
+    {
+        for (uint32_t b = threadIdx.x; b < n_blocks && b < (uint32_t)kTallyBlocks; b += kRowThreads) lds[b] = 0;
+    }
+    __device__ __forceinline__ void add(uint32_t block, bool marked) const
+    {
+        if (n_blocks <= (uint32_t)kTallyBlocks)          // uniform
+            tally_groups(block, marked, [&](uint32_t b, uint32_t n) { atomicAdd(&lds[b], n); });
+        else
+            tally_groups(block, marked, [&](uint32_t b, uint32_t n) { atomicAdd(&counters[b * stride], n); });
+    }
+    __device__ __forceinline__ void merge() const        // all threads of the workgroup
+    {
+        if (n_blocks > (uint32_t)kTallyBlocks) return;
+        __syncthreads();
+        for (uint32_t b = threadIdx.x; b < n_blocks; b += kRowThreads) {
+            const uint32_t c = lds[b];
+            if (c) atomicAdd(&counters[b * stride], c);
+        }
+    }
+};
+
+// Bins of a list's histogram, ordered like the keys: kListBins / 2 of 2^fine keys from `base` on (keys below
+// count there as well), then as many of 2^coarse keys, the last one open-ended.  Where the wanted key is expected
+// the bins are narrow, and a workgroup's share of a list still meets few of them: every one it meets is an atomic
+// in the merge (10 lists of 145,000: 9.4 us, with 2048 equal bins 10.9).
+constexpr int kListBins = 1024;
+__device__ __forceinline__ uint32_t list_bin(const ListView& v, uint32_t key)
+{
+    const uint32_t x = key > v.base ? key - v.base : 0u, half = kListBins / 2;
+    const uint32_t in_fine = x >> v.fine;
+    return in_fine < half ? in_fine : half + min((x - (half << v.fine)) >> v.coarse, half - 1u);
+}
+// the keys of bin b: from lo on, 2^bits of them at most
+__device__ __forceinline__ void list_bin_range(const ListView& v, uint32_t b, uint32_t& lo, uint32_t& bits)
+{
+    const uint32_t half = kListBins / 2;
+    lo = v.base + (b < half ? b << v.fine : (half << v.fine) + ((b - half) << v.coarse));
+    bits = b < half ? v.fine : v.coarse;
+    if (b == 0) lo = 0;
+    if (b == 0 || b == (uint32_t)(kListBins - 1)) bits = 31;
+}
+
+__device__ __forceinline__ u32x2 load_past_caches(const u32x2* p)
+{
+    const unsigned long long w = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    return u32x2{(uint32_t)w, (uint32_t)(w >> 32)};
+}
+__device__ __forceinline__ void store_past_caches(u32x2* p, u32x2 v)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)v.y << 32 | v.x, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The histogram of the list's share of workgroup `part` of `parts`
+__device__ __forceinline__ void list_hist(const ListView& v, uint32_t part, uint32_t parts, uint32_t* hist_lds)
 {
     const uint32_t t = threadIdx.x;
-    uint32_t n;
-    if (!list_row_ok(a, row, n)) return;                             // whole workgroup
-    const uint32_t i0 = blockIdx.x * (uint32_t)kListPerBlock;
-    if (i0 >= n && blockIdx.x != 0) return;                          // whole workgroup
-    const u32x2* list = a.list + (size_t)row * a.cap;
-    const uint32_t base = a.base ? a.base[row] : 0u;
-    u32x2 c[kListPerThread];
+    if (part * (uint32_t)kListBatch >= v.n) return;                 // whole workgroup
+    hist_lds[t] = 0;
+    __syncthreads();
+    for (uint64_t i0 = (uint64_t)part * kListBatch; i0 < v.n; i0 += (uint64_t)parts * kListBatch) {
+        uint32_t k[kListUnroll];
 #pragma unroll
-    for (int u = 0; u < kListPerThread; ++u) {
-        const uint32_t i = i0 + (uint32_t)u * kRowThreads + t;
-        const u32x2 none = {0u, 0xFFFFFFFFu};
-        c[u] = (i < n) ? list[i] : none;
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint64_t i = i0 + (uint32_t)u * kRowThreads + t;
+            k[u] = (i < v.n) ? v.list[i].x : 0xFFFFFFFFu;           // keys are at most 0x7FFFFFFF
+        }
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u)
+            if (k[u] != 0xFFFFFFFFu) atomicAdd(&hist_lds[list_bin(v, k[u])], 1u);
     }
-    const uint32_t* hrow = a.hist + (size_t)row * kSelBins;
-    for (int b = t; b < kSelBins; b += kRowThreads) lds.hist[b] = hrow[b];
+    __syncthreads();
+    const uint32_t c = hist_lds[t];
+    if (c) atomicAdd(&v.hist[t], c);
+}
+
+// The want-th of n members (key[0], at[0] in LDS, a barrier behind them), whose keys lie in
+// [lo, lo + 2^bits), under (key descending, coordinate ascending): its key and its coordinate, or
+// 0xFFFFFFFF when all with that key are taken.  Ranked by counting when few; else narrowed by
+// histograms of the next 12 bits until they are few or all equal.
+template <typename Lds>
+__device__ __forceinline__ void rank_members(Lds& lds, uint32_t n, uint32_t want, uint32_t lo, uint32_t bits,
+                                             uint32_t& kth, uint32_t& tie_cut)
+{
+    const uint32_t t = threadIdx.x, lane = lane_id();
+    for (int cur = 0;; cur ^= 1) {                // uniform
+        uint32_t* key = lds.key[cur];
+        uint32_t* at = lds.at[cur];
+        if (n <= (uint32_t)kRankCap) {
+            if (t < 4) {                          // pad to a multiple of 4 with entries ranked last
+                key[n + t] = 0;
+                at[n + t] = 0xFFFFFFFFu;
+            }
+            __syncthreads();
+            if (t < n) {
+                const uint32_t mk = key[t], mi = at[t];
+                const u32x4* hk = reinterpret_cast<const u32x4*>(key);
+                const u32x4* hi = reinterpret_cast<const u32x4*>(at);
+                uint32_t ahead = 0;
+#pragma unroll 4
+                for (uint32_t j = 0; j < (n + 3) / 4; ++j) {
+                    const u32x4 ok = hk[j], oi = hi[j];
+                    ahead += (ok.x > mk) || (ok.x == mk && oi.x < mi);
+                    ahead += (ok.y > mk) || (ok.y == mk && oi.y < mi);
+                    ahead += (ok.z > mk) || (ok.z == mk && oi.z < mi);
+                    ahead += (ok.w > mk) || (ok.w == mk && oi.w < mi);
+                }
+                if (ahead == want - 1) {
+                    lds.bcast[0] = mk;
+                    lds.bcast[1] = mi;
+                }
+            }
+            __syncthreads();
+            kth = lds.bcast[0];
+            tie_cut = lds.bcast[1];
+            __syncthreads();
+            return;
+        }
+        if (bits == 0) {
+            kth = lo;
+            tie_cut = want < n ? smallest_coordinate(lds, at, n, want) : 0xFFFFFFFFu;
+            return;
+        }
+        const uint32_t rest = bits > 12u ? bits - 12u : 0u;
+        for (int b = t; b < kKeyBins; b += kRowThreads) lds.hist[b] = 0;
+        if (t == 0) lds.n_list = 0;
+        __syncthreads();
+        for (uint32_t p0 = 0; p0 < n; p0 += kRowThreads) {           // wave-wide grouping: many keys may be equal
+            const uint32_t p = p0 + t;
+            tally_digit(lds.hist, p < n, p < n ? (key[p] - lo) >> rest : 0u, lane);
+        }
+        __syncthreads();
+        uint32_t sub, in_sub;
+        find_rank_bin<kKeyBins>(lds.hist, lds.scan, lds.bcast, want, sub, want, in_sub);
+        for (uint32_t p0 = 0; p0 < n; p0 += kRowThreads) {
+            const uint32_t p = p0 + t;
+            const bool mine = p < n && (key[p] - lo) >> rest == sub;
+            const uint32_t s = wave_slots(mine, &lds.n_list, lane);
+            if (mine) {
+                lds.key[cur ^ 1][s] = key[p];
+                lds.at[cur ^ 1][s] = at[p];
+            }
+        }
+        __syncthreads();
+        n = in_sub;
+        lo += sub << rest;
+        bits = rest;
+    }
+}
+
+// The same over n entries in memory, entry(i) = (key, coordinate): those in [lo, lo + 2^bits) are `count`
+// members, more than LDS holds.  Narrowed by histograms of the next 12 bits until they fit (or are all equal).
+template <typename Lds, typename Entry>
+__device__ __forceinline__ void rank_in_memory(Lds& lds, Entry entry, uint32_t n, uint32_t count, uint32_t want,
+                                               uint32_t lo, uint32_t bits, uint32_t& kth, uint32_t& tie_cut)
+{
+    const uint32_t t = threadIdx.x, lane = lane_id();
+    // f(entry, member) the same number of times in every lane, eight loads in flight
+    auto each = [&](auto f) {
+        for (uint64_t i0 = 0; i0 < n; i0 += (uint64_t)kRowThreads * 8) {
+            u32x2 c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint64_t i = i0 + (uint32_t)u * kRowThreads + t;
+                const u32x2 none = {0u, 0u};
+                c[u] = i < n ? entry(i) : none;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                f(c[u], i0 + (uint32_t)u * kRowThreads + t < n && c[u].x - lo < 1u << bits);
+        }
+    };
+    while (count > Lds::kMost && bits != 0) {                // uniform
+        const uint32_t rest = bits > 12u ? bits - 12u : 0u;
+        for (int b = t; b < kKeyBins; b += kRowThreads) lds.hist[b] = 0;
+        __syncthreads();
+        each([&](u32x2 c, bool member) { tally_digit(lds.hist, member, member ? (c.x - lo) >> rest : 0u, lane); });
+        __syncthreads();
+        uint32_t sub;
+        find_rank_bin<kKeyBins>(lds.hist, lds.scan, lds.bcast, want, sub, want, count);
+        lo += sub << rest;
+        bits = rest;
+    }
+    if (count <= Lds::kMost) {            // uniform
+        if (t == 0) lds.n_list = 0;
+        __syncthreads();
+        each([&](u32x2 c, bool member) {
+            const uint32_t p = wave_slots(member, &lds.n_list, lane);
+            if (member) {
+                lds.key[0][p] = c.x;
+                lds.at[0][p] = c.y;
+            }
+        });
+        __syncthreads();
+        rank_members(lds, count, want, lo, bits, kth, tie_cut);
+        return;
+    }
+    kth = lo;
+    tie_cut = 0xFFFFFFFFu;
+    if (want < count) {                           // uniform; entries that are not ties are mapped below every tie
+        auto tie_at = [&](uint64_t i) {
+            const u32x2 c = entry(i);
+            return c.x == lo ? kAbsMask - c.y : 0u;
+        };
+        const KeysInMemory<decltype(tie_at)> ties{tie_at, n};
+        uint32_t a, b;
+        tie_cut = kAbsMask - block_radix_select(ties, want, lds.hist, lds.scan, lds.bcast, a, b);
+    }
+}
+
+// Workgroup `part` of `parts` of a list.  act(c, taken): the marked ones of a batch of kListUnroll entries per
+// thread are among the `want` largest; every one of these is marked in exactly one call, by one workgroup.
+// Returns true to all threads of the one workgroup that finished the list, with kth / tie_cut (the membership
+// test is is_taken).  ALONE: parts is 1 and the histogram is taken here.
+template <bool ALONE, typename Lds, typename Act>
+__device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uint32_t parts, Lds& lds, Act act,
+                                           uint32_t& kth, uint32_t& tie_cut)
+{
+    const uint32_t t = threadIdx.x, lane = lane_id();
+    const u32x2 none = {0u, 0xFFFFFFFFu};
+    u32x2 c[kListUnroll];
+    auto load = [&](uint64_t i0) {
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint64_t i = i0 + (uint32_t)u * kRowThreads + t;
+            c[u] = i < v.n ? v.list[i] : none;
+        }
+    };
+    const uint64_t first = (uint64_t)part * kListBatch;
+    load(first);
+    if (t == 0) lds.n_list = 0;
+    if (ALONE) {
+        lds.hist[t] = 0;
+        __syncthreads();
+        for (uint64_t i0 = 0; i0 < v.n; i0 += kListBatch) {
+            if (i0) load(i0);
+#pragma unroll
+            for (int u = 0; u < kListUnroll; ++u)
+                if (c[u].y != 0xFFFFFFFFu) atomicAdd(&lds.hist[list_bin(v, c[u].x)], 1u);
+        }
+        if (v.n > (uint32_t)kListBatch) load(0);
+    } else {
+        lds.hist[t] = v.hist[t];
+    }
     __syncthreads();
     uint32_t bin, want, in_bin;
-    find_rank_bin<kSelBins>(lds.hist, lds.scan, lds.bcast, a.want, bin, want, in_bin);
-    if (blockIdx.x == 0 && t == 0) {
-        a.bin_want[2 * row] = bin;
-        a.bin_want[2 * row + 1] = want;
-    }
-    uint32_t mine = 0;
+    find_rank_bin<kListBins>(lds.hist, lds.scan, lds.bcast, v.want, bin, want, in_bin);
+    for (uint64_t i0 = first; i0 < v.n; i0 += (uint64_t)parts * kListBatch) {
+        if (i0 != first) load(i0);
+        uint32_t above = 0, member = 0;
 #pragma unroll
-    for (int u = 0; u < kListPerThread; ++u) {
-        const bool valid = c[u].y != 0xFFFFFFFFu;
-        const uint32_t b = list_bin(c[u].x, base, a.shift);
-        if (bits && valid && b > bin) atomicOr(&bits[c[u].y >> 5], 1u << (c[u].y & 31u));
-        mine += (valid && b == bin);
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint32_t b = list_bin(v, c[u].x);
+            const bool there = c[u].y != 0xFFFFFFFFu;
+            above |= (there && b > bin ? 1u : 0u) << u;
+            member |= (there && b == bin ? 1u : 0u) << u;
+        }
+        // the members first: the last workgroup waits for them
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u) {
+            const bool mine = member >> u & 1u;
+            if (ALONE) {
+                const uint32_t p = wave_slots(mine, &lds.n_list, lane);
+                if (mine && p < Lds::kMost) {
+                    lds.key[0][p] = c[u].x;
+                    lds.at[0][p] = c[u].y;
+                }
+            } else {
+                const uint32_t p = wave_slots(mine, v.count2, lane);
+                if (mine && p < v.n) store_past_caches(v.list2 + (int64_t)p * v.step2, c[u]);
+            }
+        }
+        act(c, above);
     }
-    uint32_t total;
-    const uint32_t ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
-    if (total == 0) return;                                          // whole workgroup
-    if (t == 0) lds.base_sh = atomicAdd(&a.count2[row], total);
+    uint32_t n_members = in_bin;
+    if (!ALONE) {
+        // every store and atomic of this workgroup has been performed before it is counted as done
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (t == 0) lds.last = atomicAdd(v.done, 1u) == parts - 1u;
+        __syncthreads();
+        if (!lds.last) return false;
+        // (the histogram counts what the list holds, so in_bin members have been stored)
+        for (uint32_t p = t; p < in_bin && p < Lds::kMost; p += kRowThreads) {
+            const u32x2 m = load_past_caches(v.list2 + (int64_t)p * v.step2);
+            lds.key[0][p] = m.x;
+            lds.at[0][p] = m.y;
+        }
+        // what the next step must find at zero
+        v.hist[t] = 0;
+        if (t == 0) {
+            *v.count2 = 0;
+            *v.done = 0;
+        }
+    }
     __syncthreads();
-    uint32_t pos = lds.base_sh + ex;
-    u32x2* list2 = a.list2 + (size_t)row * a.cap;
+    auto member_at = [&](uint64_t i) { return load_past_caches(v.list2 + (int64_t)i * v.step2); };
+    uint32_t lo, bits;
+    list_bin_range(v, bin, lo, bits);
+    if (n_members <= Lds::kMost)          // uniform
+        rank_members(lds, n_members, want, lo, bits, kth, tie_cut);
+    else if (ALONE)
+        rank_in_memory(lds,
+                       [&](uint64_t i) {          // what is no member gets a key outside every range
+                           u32x2 m = v.list[i];
+                           if (list_bin(v, m.x) != bin) m.x = 0xFFFFFFFFu;
+                           return m;
+                       },
+                       v.n, n_members, want, lo, bits, kth, tie_cut);
+    else
+        rank_in_memory(lds, member_at, n_members, n_members, want, lo, bits, kth, tie_cut);
+    // the members that are taken
+    const uint32_t n = ALONE ? v.n : n_members;
+    for (uint64_t i0 = 0; i0 < n; i0 += kListBatch) {
+        uint32_t taken = 0;
 #pragma unroll
-    for (int u = 0; u < kListPerThread; ++u) {
-        const bool valid = c[u].y != 0xFFFFFFFFu;
-        if (valid && list_bin(c[u].x, base, a.shift) == bin) {
-            if (pos < a.cap) list2[pos] = c[u];
-            ++pos;
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint64_t i = i0 + (uint32_t)u * kRowThreads + t;
+            c[u] = i < n ? (ALONE ? v.list[i] : member_at(i)) : none;
+            const bool mine = i < n && (!ALONE || list_bin(v, c[u].x) == bin);
+            taken |= (mine && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
         }
-    }
-}
-
-// Ranks the second list exactly: kth / tie_cut as for a row's candidate list.
-// Leaves the row's histogram and count2 at zero.  Returns false when the row does
-// not take part.
-__device__ __forceinline__ bool list_rank_body(const ListSelect& a, uint32_t row, SelectLds& lds, uint32_t& kth,
-                                               uint32_t& tie_cut, uint32_t& path)
-{
-    const uint32_t t = threadIdx.x;
-    uint32_t n;
-    if (!list_row_ok(a, row, n)) return false;                       // whole workgroup
-    const uint32_t C = min(a.count2[row], a.cap), bin = a.bin_want[2 * row], want = a.bin_want[2 * row + 1];
-    __syncthreads();                                                  // everyone has read the counters
-    uint32_t* hrow = a.hist + (size_t)row * kSelBins;
-    for (int b = t; b < kSelBins; b += kRowThreads) hrow[b] = 0;
-    if (t == 0) a.count2[row] = 0;
-    if (C == 0 || want == 0 || want > C) return false;                // cannot happen after the split
-    const u32x2* list2 = a.list2 + (size_t)row * a.cap;
-    const uint32_t base = (a.base ? a.base[row] : 0u) + (bin << a.shift);
-    if (C > 8u * kRowThreads && C <= (uint32_t)kKeep * kRowThreads) {   // short lists: a few loads per pass are cheaper
-        uint32_t k[kKeep];
-        const uint32_t last = C - 1;
-#pragma unroll
-        for (int q = 0; q < kKeep; ++q) {
-            k[q] = 0;
-            if ((uint32_t)q * kRowThreads < C) k[q] = list2[min((uint32_t)q * kRowThreads + t, last)].x;
-            if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);
-        }
-        const KeysInRegs src{k, C};
-        select_among_candidates(src, list2, C, want, base, lds, kth, tie_cut, path);
-    } else {
-        auto at = [list2](uint64_t i) { return list2[i].x; };
-        const KeysInMemory<decltype(at)> src{at, C};
-        select_among_candidates(src, list2, C, want, base, lds, kth, tie_cut, path);
+        act(c, taken);
     }
     return true;
 }
 
-// ---- the rows' top-K when K is large (grid: blocks of the candidate list x rows)
-__global__ __launch_bounds__(kRowThreads) void mv_sel_hist(ListSelect a)
+// ---- the rows' top-K when K is large: grid (workgroups of a list, rows)
+// A row whose list is too short or overflowed (or that was marked) is left to its first workgroup of
+// mv_sel_split, which selects it from memory.
+constexpr uint32_t kHistRow = kHistBins;          // words of a row's sample histogram, which lends its storage below
+constexpr uint32_t kCtlWords = 3 * kListBins;      // behind three histograms: the counters, a line each
+// The sample histograms are at zero when the streaming kernel has ended: list number `which` (0, 1, 2) of a
+// row keeps its histogram and its two counters there, and leaves them at zero as well.
+__device__ __forceinline__ void lend_storage(ListView& v, uint32_t* __restrict__ sample_hist, uint32_t row, uint32_t which)
 {
-    __shared__ uint32_t hist[kSelBins];
-    list_hist_body(a, blockIdx.y, hist);
+    uint32_t* h = sample_hist + (size_t)row * kHistRow;
+    v.hist = h + which * kListBins;
+    v.count2 = h + kCtlWords + (2 * which) * kCounterStride;
+    v.done = h + kCtlWords + (2 * which + 1) * kCounterStride;
+    v.step2 = 1;
 }
-__global__ __launch_bounds__(kRowThreads) void mv_sel_split(ListSelect a)
+static_assert(kListBins == kRowThreads, "a bin per thread");
+static_assert(kHistRow >= kCtlWords + 6 * kCounterStride, "three lists' storage fits a row's sample histogram");
+
+__global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
+    const u32x2* __restrict__ cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ row_count_sets,
+    uint32_t row_count_set_words, const uint32_t* __restrict__ step_no, const unsigned long long* __restrict__ tau_pub,
+    const uint32_t* __restrict__ row_poison, uint32_t* __restrict__ sample_hist, uint32_t* __restrict__ cand_count,
+    uint32_t* __restrict__ tau_bits, uint32_t* __restrict__ slow_flag)
 {
-    __shared__ ListSplitLds lds;
-    list_split_body(a, blockIdx.y, lds, nullptr);
+    __shared__ uint32_t hist[kListBins];
+    const uint32_t row = blockIdx.y;
+    const uint32_t epoch = step_no[0] + 1u;
+    uint32_t C = row_count_sets[(epoch & 1u) * row_count_set_words + row * kCounterStride];
+    const uint32_t tau = (uint32_t)tau_pub[row * (kCounterStride / 2)];
+    if (row_poison[row] == epoch) C |= kRowPoison;                   // reads as overflowed, here and for later readers
+    const bool from_list = C >= K && C <= cap;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {                       // for the kernels that follow, and the row statistics
+        cand_count[row] = C;
+        tau_bits[row] = tau;
+        slow_flag[row] = from_list ? 0u : 1u;
+    }
+    if (!from_list) return;                                          // whole workgroup
+    ListView v;
+    v.list = cand + (size_t)row * cap;  v.n = C;
+    v.want = K;
+    v.base = tau;  v.fine = 12;  v.coarse = 18;   // 2048 bins to an octave, beyond a quarter octave 32
+    lend_storage(v, sample_hist, row, 0);
+    list_hist(v, blockIdx.x, gridDim.x, hist);
 }
-__global__ __launch_bounds__(kRowThreads) void mv_sel_rank(ListSelect a, uint32_t* __restrict__ kth_out,
-                                                           uint32_t* __restrict__ tie_cut_out,
-                                                           uint32_t* __restrict__ slow_flag)
+
+__global__ __launch_bounds__(kRowThreads) void mv_sel_split(
+    const float* __restrict__ e, int64_t ld_e, int64_t d, const u32x2* __restrict__ cand, uint32_t cap, uint32_t K,
+    const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
+    const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist, u32x2* __restrict__ list2,
+    uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
+    uint32_t* __restrict__ votes32, uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
+    int thresholds_only)
 {
-    __shared__ SelectLds lds;
-    const uint32_t row = blockIdx.x;
-    uint32_t kth, tie_cut, path;
-    if (!list_rank_body(a, row, lds, kth, tie_cut, path)) return;
-    if (threadIdx.x == 0) {
+    __shared__ SplitLds<kMembers> lds;
+    const uint32_t row = blockIdx.y, t = threadIdx.x;
+    if (slow_flag[row] == 1u) {
+        if (blockIdx.x == 0)
+            select_row_from_memory(lds, e + (int64_t)row * ld_e, d, K, worker_idx ? worker_idx + (size_t)row * K : nullptr,
+                                   votes32, lvl_sets, kth_out + row, tie_cut_out + row, thresholds_only);
+        return;
+    }
+    ListView v;
+    v.list = cand + (size_t)row * cap;  v.n = cand_count[row];
+    v.want = K;
+    v.base = tau_bits[row];  v.fine = 12;  v.coarse = 18;   // as in mv_sel_hist
+    lend_storage(v, sample_hist, row, 0);
+    v.list2 = list2 + (size_t)row * cap;
+    for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
+    uint32_t* ssel = seg_sel ? seg_sel + (size_t)row * nseg : nullptr;
+    uint32_t kth, tie_cut;
+    const bool finished = list_split<false>(v, blockIdx.x, gridDim.x, lds,
+                                            [&](const u32x2 (&c)[kListUnroll], uint32_t taken) {
+                                                if (!thresholds_only)
+                                                    cast_votes<kListUnroll, true>(c, taken, votes32, lds.lvl, ssel);
+                                            },
+                                            kth, tie_cut);
+    if (finished && t == 0) {
         kth_out[row] = kth;
         tie_cut_out[row] = tie_cut;
-        if (path) slow_flag[row] = path;          // diagnostic only
+    }
+    if (!thresholds_only) {
+        __syncthreads();
+        merge_levels(lds.lvl, lvl_sets, blockIdx.y * gridDim.x + blockIdx.x);
     }
 }
 
