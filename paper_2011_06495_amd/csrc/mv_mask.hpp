@@ -77,25 +77,69 @@ __device__ __forceinline__ void vote_threshold(const uint32_t* __restrict__ lvl_
     take_eq = thr[1];
 }
 
+// The bytes of x that are >= t (1 <= t <= 255), as the low bit of each byte: the low seven bits are
+// compared by one subtraction that borrows from the eighth.
+__device__ __forceinline__ uint32_t bytes_at_least(uint32_t x, uint32_t t)
+{
+    const uint32_t top = 0x80808080u;
+    const uint32_t low = (x | top) - (t & 127u) * 0x01010101u;
+    return ((t & 128u) ? x & low : x | low) >> 7 & 0x01010101u;
+}
 // The thread's coordinates with more than / exactly vstar votes among its 16 Q bytes from j0
-// on.  Must be called by all lanes of a wavefront together: a word that holds no vote in
-// any lane is passed over by the whole wavefront (most words, where votes are sparse);
-// with vstar == 0 the coordinates without a vote count too and nothing is passed over.
+// on: bit b of marks[q] is set if coordinate j0 + 16 q + b has more, bit 16 + b if it has exactly
+// vstar; gt and eq count them.  Four bytes at a time (byte by byte, and once more for the emission, the
+// mask kernel took 18.5 us instead of 14.9 at 10 x 11.2 M, K = 111,740, and 37 instead of 32 at 32 x 25.6 M).  Must be called by all lanes of a wavefront together: a quad that holds no vote
+// in any lane is passed over by the whole wavefront (most quads, where votes are sparse); with
+// vstar == 0 the coordinates without a vote count too and nothing is passed over.
 template <int Q>
 __device__ __forceinline__ void count_above_and_at(const uint32_t (&ww)[4 * Q], int64_t j0, int64_t d,
-                                                   uint32_t vstar, uint32_t& gt, uint32_t& eq)
+                                                   uint32_t vstar, uint32_t (&marks)[Q], uint32_t& gt, uint32_t& eq)
 {
     gt = 0;
     eq = 0;
 #pragma unroll
-    for (int q = 0; q < 4 * Q; ++q) {
-        if (vstar != 0u && __ballot(ww[q] != 0u) == 0ull) continue;   // wave-uniform
+    for (int q = 0; q < Q; ++q) {
+        marks[q] = 0;
+        const uint32_t any = ww[4 * q] | ww[4 * q + 1] | ww[4 * q + 2] | ww[4 * q + 3];
+        if (vstar != 0u && __ballot(any != 0u) == 0ull) continue;     // wave-uniform
+        uint32_t above[2] = {0, 0}, from[2] = {0, 0};                 // eight coordinates each
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t v = (ww[q] >> (8 * b)) & 255u;
-            const bool inside = j0 + 4 * q + b < d;                   // matters when v* is 0
-            gt += (inside && v > vstar);
-            eq += (inside && v == vstar);
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t w = ww[4 * q + k], weights = k & 1 ? 0x80402010u : 0x08040201u;
+            if (vstar < 255u) above[k / 2] = __builtin_amdgcn_udot4(bytes_at_least(w, vstar + 1u), weights, above[k / 2], false);
+            if (vstar != 0u) from[k / 2] = __builtin_amdgcn_udot4(bytes_at_least(w, vstar), weights, from[k / 2], false);
+        }
+        const uint32_t up = above[0] | above[1] << 8;
+        uint32_t all = from[0] | from[1] << 8;
+        if (vstar == 0u) {                        // uniform: every coordinate there is
+            const int64_t there = d - (j0 + 16 * q);
+            all = there >= 16 ? 0xFFFFu : there > 0 ? (1u << there) - 1u : 0u;
+        }
+        marks[q] = up | (all & ~up) << 16;
+        gt += (uint32_t)__popc(up);
+        eq += (uint32_t)__popc(all & ~up);
+    }
+}
+
+// f(position, coordinate) for every mask coordinate among the thread's, g0 being the coordinates above the
+// threshold before it and e0 those at it.
+template <int Q, typename F>
+__device__ __forceinline__ void each_mask_position(const uint32_t (&marks)[Q], int64_t j0, uint32_t g0, uint32_t e0,
+                                                   uint32_t take_eq, F f)
+{
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t up = marks[q] & 0xFFFFu, at = marks[q] >> 16;
+        if (up == 0u && e0 >= take_eq) {
+            e0 += (uint32_t)__popc(at);
+            continue;
+        }
+        for (uint32_t m = up | at; m != 0u; m &= m - 1u) {
+            const uint32_t low = m & (0u - m);
+            const bool is_up = (up & low) != 0u;
+            if (is_up || e0 < take_eq) f(g0 + min(e0, take_eq), (uint32_t)(j0 + 16 * q) + (uint32_t)__ffs((int)low) - 1u);
+            if (is_up) ++g0;
+            else ++e0;
         }
     }
 }
@@ -231,8 +275,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         write_winners<Q>(winners, winners_per_block, d, K, scan_lds, mask_idx);
         return;
     }
-    uint32_t gt, eq;
-    count_above_and_at<Q>(ww, j0, d, vstar, gt, eq);
+    uint32_t gt, eq, marks[Q];
+    count_above_and_at<Q>(ww, j0, d, vstar, marks, gt, eq);
     const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;   // (vote_threshold ended with a barrier)
     const uint64_t both = pack2(gt, eq);
     uint64_t block_total;
@@ -325,30 +369,27 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     if (bound[0] == 0u) return;                   // whole workgroup
     const uint64_t before = before_sh;
     if ((uint32_t)(before >> 32) + min((uint32_t)before, take_eq) >= K) return;   // the mask is full before this block
-    uint32_t g0 = (uint32_t)((before + ex) >> 32), e0 = (uint32_t)(before + ex);
-#pragma unroll
-    for (int q = 0; q < 4 * Q; ++q) {
-        if (vstar != 0u && __ballot(ww[q] != 0u) == 0ull) continue;   // wave-uniform: no vote in this word
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t v = (ww[q] >> (8 * b)) & 255u;
-            const int64_t j = j0 + 4 * q + b;
-            const bool inside = j < d;
-            const bool is_gt = inside && v > vstar, is_eq = inside && v == vstar;
-            if (is_gt || (is_eq && e0 < take_eq)) {
-                const uint32_t pos = g0 + min(e0, take_eq);
-                if (pos < K) mask_idx[pos] = (uint32_t)j;
-            }
-            g0 += is_gt;
-            e0 += is_eq;
-        }
-    }
+    each_mask_position<Q>(marks, j0, (uint32_t)((before + ex) >> 32), (uint32_t)(before + ex), take_eq,
+                          [&](uint32_t pos, uint32_t j) {
+                              if (pos < K) mask_idx[pos] = j;
+                          });
 }
 
 // ----------------------------------------------------------------------------
 // 6. masked gather, ordered sum over workers, mean, error update; beside it, the
 //    sorted vote lists
 // ----------------------------------------------------------------------------
+
+constexpr int kMaskWaves = kMaskThreads / kWave;
+constexpr int kEmitUnroll = 4;                    // list entries per thread in flight together
+constexpr int kEmitBatch = kMaskThreads * kEmitUnroll;
+static_assert(kEmitUnroll * kMaskWaves == kWave, "a lane per wavefront's part of a batch");
+struct EmitLds {
+    uint32_t blk_pre[kMaxScanBlocks];
+    uint32_t wave_taken[kEmitUnroll * kMaskWaves];
+    uint32_t wave_earlier[kMaskWaves];
+    uint16_t number[kEmitBatch];                  // taken entries of the batch before each of its entries
+};
 
 // A row's vote list in ascending coordinate order, without a sort: a taken
 // candidate's rank is (taken candidates in earlier blocks of 1024 segments, from
@@ -359,10 +400,11 @@ __device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, u
                                                const uint32_t* __restrict__ prow,
                                                const uint32_t* __restrict__ blk_total, uint32_t scan_blocks,
                                                uint32_t K, uint32_t kth, uint32_t tie_cut, uint32_t blk,
-                                               uint32_t nblk, uint32_t* __restrict__ out,
-                                               uint32_t* blk_pre /*LDS, kMaxScanBlocks*/, uint64_t* scan_lds)
+                                               uint32_t nblk, uint32_t* __restrict__ out, EmitLds& lds,
+                                               uint64_t* scan_lds)
 {
-    if ((uint64_t)blk * 4 * kMaskThreads >= C) return;       // whole workgroup
+    if ((uint64_t)blk * kEmitBatch >= C) return;             // whole workgroup
+    uint32_t* blk_pre = lds.blk_pre;
     // exclusive prefix of the blocks' totals, once per workgroup
     {
         constexpr int per = kMaxScanBlocks / kMaskThreads;
@@ -383,64 +425,72 @@ __device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, u
         }
         __syncthreads();
     }
-    // Lanes of a wavefront hold consecutive list entries, so the entries of one run
-    // sit in neighbouring lanes: the rank inside the run comes from a ballot; only
-    // the part of the first lane's run that lies before the wavefront is counted
-    // from memory, by the whole wavefront together.  kU entries per thread are in
-    // flight at a time, each followed by the loads that depend on it.
-    constexpr int kU = 4;
-    const uint32_t lane = lane_id();
-    for (uint64_t i0 = (uint64_t)blk * kU * kMaskThreads; i0 < C; i0 += (uint64_t)nblk * kU * kMaskThreads) {
-        u32x2 c[kU];
+    // A workgroup takes kEmitBatch consecutive entries at a time and numbers the taken ones; an entry's rank
+    // inside its run is the difference of two such numbers.  Only the first entry's run can have begun before
+    // the batch (a run has at most kSeg entries): that part is counted by all threads together, one load each.
+    // (Counted by each wavefront for itself, 64 entries after the other, dense rows kept the kernel waiting:
+    // 4 x 2^20, K = 10,486: the last kernel took 8.2 us instead of 6.6.)
+    static_assert(kSeg <= kMaskThreads, "one load per thread covers a run");
+    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    for (uint64_t i0 = (uint64_t)blk * kEmitBatch; i0 < C; i0 += (uint64_t)nblk * kEmitBatch) {
+        u32x2 c[kEmitUnroll];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+        for (int u = 0; u < kEmitUnroll; ++u) {
             const uint64_t i = i0 + (uint64_t)u * kMaskThreads + threadIdx.x;
             const u32x2 none = {0u, 0xFFFFFFFFu};
             c[u] = (i < C) ? crow[i] : none;
         }
-        uint32_t seg_before[kU], run0[kU];
+        uint32_t seg_before[kEmitUnroll], run0[kEmitUnroll];
+        const uint32_t first_run = srow[crow[i0].y / kSeg].x;         // uniform: where the first entry's run begins
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
+        for (int u = 0; u < kEmitUnroll; ++u) {
             const uint32_t sg = c[u].y / kSeg;                // 0x3FFFFF for lanes past the end
             const bool there = c[u].y != 0xFFFFFFFFu;
             seg_before[u] = there ? prow[sg] + blk_pre[sg / 1024u] : 0u;
             run0[u] = there ? srow[sg].x : 0u;
         }
+        const uint64_t j = (uint64_t)first_run + threadIdx.x;
+        const bool earlier = j < i0 && is_taken(crow[j], kth, tie_cut);
+        const uint32_t n_earlier = (uint32_t)__popcll(__ballot(earlier));
+        uint32_t mine[kEmitUnroll];               // taken ones in the lanes below
+        uint32_t taken = 0;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * kMaskThreads + threadIdx.x;
-            const uint64_t wave_first = i - lane;
-            if (wave_first >= C) break;                           // wave-uniform
-            const bool taken = c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut);
-            const uint32_t sg = c[u].y / kSeg;
-            const uint32_t prev = __shfl_up(sg, 1, kWave);
-            const uint64_t heads = __ballot(lane == 0 || sg != prev);
-            const uint64_t tk = __ballot(taken);
-            if (tk == 0ull) continue;                             // wave-uniform
-            const uint64_t upto = (lane == 63) ? ~0ull : ((2ull << lane) - 1);      // lanes 0..lane
-            const uint32_t head_lane = 63u - (uint32_t)__clzll((long long)(heads & upto));
-            const uint64_t in_run_before = ((1ull << lane) - 1) & ~((1ull << head_lane) - 1);
-            uint32_t rank = (uint32_t)__popcll(tk & in_run_before);
-            // the run of lane 0 may have started before this wavefront
-            const uint32_t first_run = __shfl(run0[u], 0, kWave);
-            uint32_t carry = 0;
-            for (uint64_t j0 = first_run; j0 < wave_first; j0 += kWave) {
-                const uint64_t j = j0 + lane;
-                const bool tj = (j < wave_first) && is_taken(crow[j], kth, tie_cut);
-                carry += (uint32_t)__popcll(__ballot(tj));
-            }
-            if (head_lane == 0) rank += carry;
-            if (taken) {
+        for (int u = 0; u < kEmitUnroll; ++u) {
+            const bool tk = c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut);
+            const uint64_t all = __ballot(tk);
+            taken |= (tk ? 1u : 0u) << u;
+            mine[u] = (uint32_t)__popcll(all & ((1ull << lane) - 1ull));
+            if (lane == 0) lds.wave_taken[u * kMaskWaves + wave] = (uint32_t)__popcll(all);
+        }
+        if (lane == 0) lds.wave_earlier[wave] = n_earlier;
+        __syncthreads();
+        // the taken ones before each wavefront's part of the batch, in the order of the entries
+        const uint32_t part = lds.wave_taken[lane];
+        const uint32_t before = wave_incl_scan(part) - part;
+        const uint32_t carry_lanes = row_incl_scan(lane < (uint32_t)kMaskWaves ? lds.wave_earlier[lane] : 0u);
+        const uint32_t carry = from_lane(carry_lanes, kMaskWaves - 1);
+#pragma unroll
+        for (int u = 0; u < kEmitUnroll; ++u) {
+            mine[u] += from_lane(before, (uint32_t)u * kMaskWaves + wave);
+            lds.number[u * kMaskThreads + threadIdx.x] = (uint16_t)mine[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kEmitUnroll; ++u)
+            if (taken >> u & 1u) {
+                const uint32_t rank = run0[u] >= i0 ? mine[u] - lds.number[run0[u] - i0] : mine[u] + carry;
                 const uint32_t pos = seg_before[u] + rank;
                 if (pos < K) out[pos] = c[u].y;
             }
-        }
+        __syncthreads();                          // the scratch is free for the next batch
     }
 }
 
 // Positions [k0, k1) of the mask, whose coordinates are in slice[0 .. k1 - k0), at most `rounds` times
-// kMaskThreads / N of them: thread (kl, n) reads a[n][j], stores +0.0 there, and parks the value in LDS;
-// one thread per coordinate then adds the N values in worker order.
+// kMaskThreads / N of them: thread (n, kl) reads a[n][j], stores +0.0 there, and parks the value in LDS;
+// one thread per coordinate then adds the N values in worker order.  Neighbouring lanes have neighbouring
+// positions of one row: masks crowd where gradients are large, so lanes share cache lines (10 x 11.2 M,
+// K = 111,740: 48.6 -> 47.0 us).
 constexpr int kGatherRounds = 4;                  // at most this many rounds of kb positions per workgroup
 
 __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint32_t* slice /*LDS*/,
@@ -449,14 +499,14 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
                                                  int apply_scale, float* __restrict__ agg)
 {
     const uint32_t t = threadIdx.x, kb = kMaskThreads / N;
-    const uint32_t kl = t / N, n = t % N;
+    const uint32_t n = t / kb, kl = t % kb;           // threads from N kb on have n >= N: idle
     const uint32_t pitch = N + 1;                     // kb * (N + 1) <= 1024 + kb <= 1536
     // a thread's loads of all rounds are in flight together
     float v[kGatherRounds];
 #pragma unroll
     for (int r = 0; r < kGatherRounds; ++r) {
         const uint32_t k = k0 + (uint32_t)r * kb + kl;
-        const uint32_t j = ((uint32_t)r < rounds && kl < kb && k < k1) ? slice[k - k0] : 0xFFFFFFFFu;
+        const uint32_t j = ((uint32_t)r < rounds && n < N && k < k1) ? slice[k - k0] : 0xFFFFFFFFu;
         v[r] = 0.0f;
         if ((int64_t)j < d) {                         // always true for a mask built above
             float* p = e + (int64_t)n * ld_e + j;
@@ -467,7 +517,7 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
 #pragma unroll
     for (int r = 0; r < kGatherRounds; ++r) {
         if ((uint32_t)r >= rounds) break;             // uniform over the workgroup
-        if (kl < kb) tile[kl * pitch + n] = v[r];
+        if (n < N) tile[kl * pitch + n] = v[r];
         __syncthreads();
         if (t < kb) {
             const uint32_t kk = k0 + (uint32_t)r * kb + t;
@@ -502,8 +552,8 @@ struct GatherLds {
     uint32_t need[3 * (kMaskThreads + 2)];                     // stretches to read: (stretch, above before, at before)
     uint32_t blocks[3 * (kMaskThreads + 2)];                   // blocks whose stretches are looked at
     uint32_t n_need, n_blocks;
-    uint32_t blk_pre[kMaxScanBlocks];
-    uint64_t scan[kMaskThreads / kWave + 1];
+    EmitLds  emit;
+    uint64_t scan[kMaskThreads / kWave];
 };
 
 template <int Q>
@@ -538,7 +588,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
         row_emit_block(cand + (size_t)row * cap, row_count[row], seg + (size_t)row * nseg,
                        seg_pre + (size_t)row * nseg, blk_total + (size_t)row * scan_blocks, scan_blocks, K,
                        kth_in[row], tie_cut_in[row], b % emit_blocks, emit_blocks,
-                       worker_idx + (size_t)row * K, lds.blk_pre, lds.scan);
+                       worker_idx + (size_t)row * K, lds.emit, lds.scan);
         return;
     }
     const uint32_t kb = kMaskThreads / N;             // N <= 255, so kb >= 4
@@ -618,31 +668,17 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
                     const u32x4 w = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;
                     ww[4 * q + 0] = w.x; ww[4 * q + 1] = w.y; ww[4 * q + 2] = w.z; ww[4 * q + 3] = w.w;
                 }
-                uint32_t gt, eq;
-                count_above_and_at<Q>(ww, j0, d, vstar, gt, eq);
+                uint32_t gt, eq, marks[Q];
+                count_above_and_at<Q>(ww, j0, d, vstar, marks, gt, eq);
                 const uint64_t both = pack2(gt, eq);
                 const uint64_t ex = wave_incl_scan64(both) - both;
-                uint32_t g0 = lds.need[3 * i + 1] + (uint32_t)(ex >> 32), e0 = lds.need[3 * i + 2] + (uint32_t)ex;
-#pragma unroll
-                for (int q = 0; q < 4 * Q; ++q) {
-                    if (vstar != 0u && __ballot(ww[q] != 0u) == 0ull) continue;   // wave-uniform: no vote in this word
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const uint32_t v = (ww[q] >> (8 * b)) & 255u;
-                        const int64_t j = j0 + 4 * q + b;
-                        const bool inside = j < d;
-                        const bool is_gt = inside && v > vstar, is_eq = inside && v == vstar;
-                        if (is_gt || (is_eq && e0 < take_eq)) {
-                            const uint32_t pos = g0 + min(e0, take_eq);
-                            if (pos >= q0 && pos < q1) {
-                                lds.slice[pos - k0] = (uint32_t)j;
-                                mask_idx[pos] = (uint32_t)j;
-                            }
-                        }
-                        g0 += is_gt;
-                        e0 += is_eq;
-                    }
-                }
+                each_mask_position<Q>(marks, j0, lds.need[3 * i + 1] + (uint32_t)(ex >> 32),
+                                      lds.need[3 * i + 2] + (uint32_t)ex, take_eq, [&](uint32_t pos, uint32_t j) {
+                                          if (pos >= q0 && pos < q1) {
+                                              lds.slice[pos - k0] = j;
+                                              mask_idx[pos] = j;
+                                          }
+                                      });
             }
             __syncthreads();                          // the lists are reused by the next round
         }
