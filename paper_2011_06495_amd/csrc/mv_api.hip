@@ -41,6 +41,7 @@ const char* const kKernelNames[KID_COUNT] = {
     "mv_rs_pick",        "mv_small_rows", "mv_small_mask"};
 
 constexpr size_t kAlign = 256;
+constexpr int64_t kOneSamplerD = 1 << 20;   // see make_plan
 constexpr int kEventRing = 64;   // steps whose kernel durations stay readable
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -109,37 +110,45 @@ Plan make_plan(const mv_config* c)
     p.d = c->d;
     p.nseg = (uint32_t)((p.d + mvk::kSeg - 1) / mvk::kSeg);
 
-    // Sample about d/128 coordinates of each row, but at least ~32K when the row has them.
+    // A row with exactly K coordinates above the threshold shows K * frac of them in a sample of frac * d
+    // coordinates on average.  Ask for m sampled ones with m - 7 sqrt(m) = K * frac, never fewer than 128:
+    // falling short of K is then a 7-sigma event of the sample count, and the candidates exceed K by about
+    // 7 sqrt(m) / frac (a factor 2 at K = d/1000, 1.3 at d/100).
+    auto sampled_above = [&](double frac) {
+        const double root_m = 3.5 + sqrt(12.25 + (double)p.K * frac), m = ceil(root_m * root_m);
+        return m < 128.0 ? 128.0 : m;
+    };
+    // Sample about d/128 coordinates of each row, at least 32K, by up to 16 workgroups (kSampleQuads quads per
+    // thread and round) -- or, in short rows, 8K by ONE workgroup in one round, whose histogram need not be merged in
+    // memory: the step of a short row waits for the estimate.  The list is longer for it; the line is where that
+    // begins to cost more than the wait (one round against 32K samples: 16 x 100,003, K = 1000: 35.6 against
+    // 40.3 us, 4 x 2^20, K = 10,486: 48.9 against 51.7; but 16 x 2^20, K = 17,000, a list of 31K entries for 23K:
+    // 87.8 against 86.5, and K = 270, 16K entries for 4K: 86 against 67; two rounds of one workgroup lie between).
     const uint64_t nchunks = (uint64_t)(p.d + mvk::kChunk - 1) / mvk::kChunk;
-    uint64_t want = (uint64_t)p.d / 128;
-    if (want < 32768) want = 32768;
-    uint64_t stride = nchunks / ((want + mvk::kChunk - 1) / mvk::kChunk);
-    if (stride < 1) stride = 1;
-    if (stride > 128) stride = 128;
+    const uint64_t per_round = (uint64_t)mvk::kSampleQuads * mvk::kStreamThreads;      // quads
+    const uint64_t want = (uint64_t)p.d / 128 > 32768 ? (uint64_t)p.d / 128 : 32768;
+    const double one = 4.0 * (double)per_round / (double)p.d, many = (double)want / (double)p.d;   // fractions
+    const double list_one = sampled_above(one) / one, list_many = sampled_above(many) / many;
+    uint64_t stride;
+    if (p.d <= kOneSamplerD && (list_one <= 8192.0 || (list_one <= 1.5 * list_many && list_one <= 24576.0))) {
+        const uint64_t chunks = per_round / (mvk::kChunk / 4);
+        stride = (nchunks + chunks - 1) / chunks;
+        p.sample_wgs = 1;
+    } else {
+        stride = nchunks / ((want + mvk::kChunk - 1) / mvk::kChunk);
+        if (stride < 1) stride = 1;
+        if (stride > 128) stride = 128;
+        const uint64_t bx = ((nchunks + stride - 1) / stride * (mvk::kChunk / 4) + per_round - 1) / per_round;
+        p.sample_wgs = (uint32_t)(bx > 16 ? 16 : bx);
+    }
     p.stride = (uint32_t)stride;
     p.n_sampled_chunks = (uint32_t)((nchunks + stride - 1) / stride);
     // all sampled chunks are full except possibly the row's last chunk
     p.n_sampled = (uint64_t)p.n_sampled_chunks * mvk::kChunk;
-    {
-        // kSampleQuads quads per thread and round; at most 16 sampling workgroups of 512 threads per row
-        const uint64_t nquads = (uint64_t)p.n_sampled_chunks * (mvk::kChunk / 4);
-        const uint64_t per_wg = (uint64_t)mvk::kSampleQuads * mvk::kStreamThreads;
-        uint64_t bx = (nquads + per_wg - 1) / per_wg;
-        if (bx > 16) bx = 16;
-        if (bx < 1) bx = 1;
-        p.sample_wgs = (uint32_t)bx;
-    }
     if (((nchunks - 1) % stride) == 0) p.n_sampled -= (uint64_t)(nchunks * mvk::kChunk - (uint64_t)p.d);
 
-    // A row with exactly K coordinates above the threshold shows K * frac of them in the
-    // sample on average.  Ask for m sampled ones with m - 7 sqrt(m) = K * frac, never fewer
-    // than 128: falling short of K is then a 7-sigma event of the sample count, and the
-    // candidates exceed K by about 7 sqrt(m) / frac (a factor 2 at K = d/1000, 1.3 at d/100).
     const double frac = (double)p.n_sampled / (double)p.d;
-    const double root_m = 3.5 + sqrt(12.25 + (double)p.K * frac);
-    double m = ceil(root_m * root_m);
-    if (m < 128.0) m = 128.0;
-    m += 1.0;
+    const double m = sampled_above(frac) + 1.0;
     p.m_target = (m >= 4294967295.0) ? 0xFFFFFFFFu : (uint32_t)m;
 
     uint64_t cap = 16ull * p.K;

@@ -55,7 +55,7 @@ constexpr int      kSampleQuads = 4;              // quads of samples a sampling
 constexpr uint32_t kRowPoison = 0x80000000u;      // set in a marked row's candidate counter by mv_row_select
 
 struct StreamLds {
-    uint32_t h[kHistBins];                        // sampling workgroups only
+    __attribute__((aligned(16))) uint32_t h[kHistBins];   // sampling workgroups only
     uint64_t scan[kStreamThreads / kWave + 1];
     uint32_t found, is_last;
     uint32_t wave_total[kSegPerBlock];
@@ -75,7 +75,11 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
                                                 uint32_t* __restrict__ ad_count)
 {
     const uint32_t t = threadIdx.x;
-    for (int b = t; b < kHistBins; b += kStreamThreads) lds.h[b] = 0;
+    {
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        u32x4* hz = reinterpret_cast<u32x4*>(lds.h);
+        for (int b = t; b < kHistBins / 4; b += kStreamThreads) hz[b] = z;
+    }
     __syncthreads();
     const GT*    grow = g + (int64_t)row * ld_g;
     const float* erow = e + (int64_t)row * ld_e;
@@ -119,27 +123,37 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     // wavefronts may overwrite e as far as this workgroup is concerned
     if (t == 0) atomicAdd(&reads_done[row * kCounterStride], 1u);
     uint32_t* hrow = hist + (size_t)row * kHistBins;
-    for (int b = t; b < kHistBins; b += kStreamThreads) {
-        const uint32_t c = lds.h[b];
-        if (c) atomicAdd(&hrow[b], c);
-    }
-    // every atomic of this workgroup has been performed before it is counted as done
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (t == 0) lds.is_last = atomicAdd(&sample_done[row * kCounterStride], 1u) == spr - 1u;
-    __syncthreads();
-    if (!lds.is_last) return;                     // whole workgroup
-
-    // ---- the row's last sampling workgroup: histogram -> tau
     constexpr int per = kHistBins / kStreamThreads;   // bins per thread, descending bin order
     uint32_t c[per];
-    uint32_t sum = 0;
+    if (spr == 1u) {
+        // Short rows: the row's only sampling workgroup has the whole histogram in LDS.
+        const u32x4* hv = reinterpret_cast<const u32x4*>(lds.h);
 #pragma unroll
-    for (int q = 0; q < per; ++q) {               // read from memory, where the others' atomics went
-        const int bin = kHistBins - 1 - ((int)t * per + q);
-        c[q] = __hip_atomic_load(&hrow[bin], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int q = 0; q < per; q += 4) {
+            const u32x4 w = hv[(kHistBins - (int)t * per - q) / 4 - 1];
+            c[q] = w.w;  c[q + 1] = w.z;  c[q + 2] = w.y;  c[q + 3] = w.x;
+        }
+    } else {
+        for (int b = t; b < kHistBins; b += kStreamThreads) {
+            const uint32_t n = lds.h[b];
+            if (n) atomicAdd(&hrow[b], n);
+        }
+        // every atomic of this workgroup has been performed before it is counted as done
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (t == 0) lds.is_last = atomicAdd(&sample_done[row * kCounterStride], 1u) == spr - 1u;
+        __syncthreads();
+        if (!lds.is_last) return;                 // whole workgroup
+        // the row's last sampling workgroup reads the sum from memory, where the others' atomics went
+#pragma unroll
+        for (int q = 0; q < per; ++q)
+            c[q] = __hip_atomic_load(&hrow[kHistBins - 1 - ((int)t * per + q)], __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
     }
+
+    // ---- histogram -> tau
+    uint32_t sum = 0;
 #pragma unroll
     for (int q = 0; q < per; ++q) sum += c[q];
     if (t == 0) lds.found = 0;
@@ -164,8 +178,10 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     // are in memory when this kernel has ended): the histogram, the sampling counter, the row's
     // candidate counter of the other parity (this step's streaming workgroups bump row_count; the
     // next step's bump next_row_count), the add / drop list lengths, the vote-level counters.
+    if (spr != 1u) {
 #pragma unroll
-    for (int q = 0; q < per; ++q) hrow[kHistBins - 1 - ((int)t * per + q)] = 0;
+        for (int q = 0; q < per; ++q) hrow[kHistBins - 1 - ((int)t * per + q)] = 0;
+    }
     if (t == 0) {
         sample_done[row * kCounterStride] = 0;
         next_row_count[row * kCounterStride] = 0;

@@ -115,3 +115,23 @@ def test_captured_short_step_replays(oracle, scheme):
             ref = oracle.vote_step(g, e, K) if scheme == "plain" else oracle.rs_vote_step(g, e, K, r)
             assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (scheme, t))
             e = ref.err
+
+
+@pytest.mark.parametrize("kind", ["normal", "lattice", "equal"])
+@pytest.mark.parametrize("N,d,K", [(3, 32769, 3), (2, 262145, 2600), (2, 524288, 100), (2, 524289, 100),
+                                   (2, 524320, 524320), (1, 1 << 20, 10486), (2, (1 << 20) + 1, 10486)])
+def test_rows_sampled_by_one_workgroup(oracle, kind, N, d, K):
+    """Beyond the short vectors a row's threshold is estimated by one workgroup up to a size that depends on K, then
+    by several: both sides of the lines, with K from a handful to all of the row."""
+    print("[case] one sampling workgroup N=%d d=%d K=%d %s" % (N, d, K, kind), flush=True)
+    rng = np.random.default_rng(d + K)
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        gs.set_error(e)
+        for t in range(2):
+            g = values(rng, kind, N, d)
+            gs.set_grads(g)
+            gs.step()
+            ref = oracle.vote_step(g, e, K, threads=8)
+            assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (kind, t))
+            e = ref.err
