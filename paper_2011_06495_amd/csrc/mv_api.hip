@@ -183,14 +183,14 @@ Plan make_plan(const mv_config* c)
         const uint64_t in_cap = ((uint64_t)p.cap + mvk::kRowThreads - 1) / mvk::kRowThreads;
         if (slots > in_cap) slots = in_cap;
         if (slots < 1) slots = 1;
-        p.n_spec = (uint32_t)(slots < (uint64_t)mvk::kSpec ? slots : (uint64_t)mvk::kSpec);
+        p.n_spec = (uint32_t)(slots < (uint64_t)mvk::kKeepMost ? slots : (uint64_t)mvk::kKeepMost);
         uint64_t parts = (slots + 3) / 4;
         if (parts > 16) parts = 16;
         if (parts * p.N > 240) parts = 240 / p.N;      // all at once: with its registers a workgroup has a unit to itself
         if (parts < 1) parts = 1;
         p.select_parts = (uint32_t)parts;
         // beyond what one workgroup keeps in registers the lists go through the many-workgroup select
-        p.multi_select = slots > (uint64_t)mvk::kSpec;
+        p.multi_select = slots > (uint64_t)mvk::kKeepMost;
         // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
         uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
         if (sb > 256) sb = 256;
@@ -573,7 +573,9 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     } else {
         const uint32_t parts = add_drop ? 1 : p.select_parts;
         before(KID_ROW_SELECT);
-        hipLaunchKernelGGL(mvk::mv_row_select, dim3((p.N + 7) / 8 * 8 * parts), dim3(mvk::kRowThreads), 0, st, a.err,
+        auto* kernel = p.n_spec <= 8 ? &mvk::mv_row_select<8> : p.n_spec <= 16 ? &mvk::mv_row_select<16>
+                                                                               : &mvk::mv_row_select<mvk::kKeepMost>;
+        hipLaunchKernelGGL(kernel, dim3((p.N + 7) / 8 * 8 * parts), dim3(mvk::kRowThreads), 0, st, a.err,
                            a.ld_e, p.d, p.N, p.K, cand, p.cap, rowcnt_sets, rowcnt_set_words, stepno, taupub, poison,
                            rowcnt, tau, kth, tiecut, a.worker_idx, votes32, ssel, p.nseg, lvlsets, slow, parts, p.n_spec,
                            thresholds_only);

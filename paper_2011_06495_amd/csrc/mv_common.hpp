@@ -3,7 +3,6 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <type_traits>
 
 namespace mvk {
 
@@ -107,16 +106,6 @@ __device__ __forceinline__ uint64_t block_excl_scan64(uint64_t v, uint64_t* lds,
     total = pack2(from_lane(hi, NW - 1), from_lane(lo, NW - 1));
     const uint64_t before = wave ? pack2(from_lane(hi, wave - 1), from_lane(lo, wave - 1)) : 0u;
     return before + incl - v;
-}
-
-// f(std::integral_constant<int, I>) for I = A .. B-1, unrolled at compile time
-template <int A, int B, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (A < B) {
-        f(std::integral_constant<int, A>{});
-        static_for<A + 1, B>(f);
-    }
 }
 
 // bin of a candidate's magnitude key (>= tau) in the row's fine histogram; order preserving

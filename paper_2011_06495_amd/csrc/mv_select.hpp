@@ -16,7 +16,7 @@ constexpr int kKeyBins = 4096;   // exact magnitudes inside one fine-histogram b
 constexpr int kRep     = 8;      // copies of the candidates' fine histogram, one per lane % kRep
 constexpr int kTieCap  = 8192;   // ties with the K-th magnitude that fit the LDS list
 constexpr int kRankCap = 256;    // at most this many entries are ranked by counting (quadratic work)
-constexpr int kSpec    = 32;     // list entries per thread that mv_row_select keeps, fetched ahead of the row's count
+constexpr int kKeepMost = 32;    // list entries per thread of the largest instance of mv_row_select (8, 16, 32)
 
 __device__ __forceinline__ int      sel_shift(int pass) { return pass == 0 ? 20 : pass == 1 ? 10 : 0; }
 __device__ __forceinline__ uint32_t sel_dmask(int pass) { return pass == 0 ? 2047u : 1023u; }
@@ -518,49 +518,58 @@ __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ cr
 }
 
 // ---- the rows' select from registers ------------------------------------------
-// A thread keeps, for each of its list entries, only the number of the entry's bin
-// in the fine histogram (16 bits, two to a register; 0xFFFF: no entry): that is all
-// the histogram pass and the search for the bin's members need, and it lets one
-// workgroup hold lists of KEEP * 1024 entries.  The members of the bin that holds
-// the K-th largest are then fetched from the list by position, all lanes together.
+// A thread keeps its list entries from the first load to the votes; entry number q of
+// thread t is at q * kRowThreads + t of the list.  That is two round trips less than
+// reading the members of the K-th's bin and the entries to vote for again -- while the
+// unrolled code stays short: every launch fetches it anew.  So there are instances for 8
+// and 16 entries, the votes from registers only in the first (7 x 272,475, K = 2725:
+// 38.0 us with one instance for 32, 34.5 so), and beyond 16 a thread keeps only the
+// number of each entry's bin (16 bits, two to a register; 0xFFFF: no entry), which is
+// all the histogram pass and the search for the bin's members need (with whole entries
+// 4 x 2^20, K = 10,486 took 50.7 us instead of 48.8; left to mv_sel_split, 50.1).
 template <int KEEP>
-struct PackedBins {
-    uint32_t b[KEEP / 2];
-    __device__ __forceinline__ void clear()
-    {
-#pragma unroll
-        for (int q = 0; q < KEEP / 2; ++q) b[q] = 0xFFFFFFFFu;
-    }
-    template <int Q>
-    __device__ __forceinline__ void set(uint32_t bin)
-    {
-        if (Q & 1) b[Q / 2] = (b[Q / 2] & 0x0000FFFFu) | (bin << 16);
-        else       b[Q / 2] = (b[Q / 2] & 0xFFFF0000u) | bin;
-    }
-    // f(bin, list position) for every entry slot below `count`, the same number of
-    // times in every lane of the workgroup
+struct KeptEntries {
+    static constexpr bool kWhole = true;
+    u32x2 entry[KEEP];
+    // f(bin, q) for every entry slot below `count`, the same number of times in every lane of the workgroup;
+    // bin = 0xFFFF: no entry
     template <typename F>
-    __device__ __forceinline__ void each(uint32_t count, F f) const
+    __device__ __forceinline__ void each(uint32_t count, uint32_t tau, F f) const
     {
 #pragma unroll
-        for (int q = 0; q < KEEP; ++q) {
-            if ((uint32_t)q * kRowThreads < count) {              // uniform over the workgroup
-                const uint32_t bin = (q & 1) ? (b[q / 2] >> 16) : (b[q / 2] & 0xFFFFu);
-                f(bin, (uint32_t)q * kRowThreads + threadIdx.x);
-            }
-        }
+        for (int q = 0; q < KEEP; ++q)
+            if ((uint32_t)q * kRowThreads < count)                   // uniform over the workgroup
+                f((uint32_t)q * kRowThreads + threadIdx.x < count ? fine_bin(entry[q].x, tau) : 0xFFFFu, q);
+    }
+};
+template <int KEEP>
+struct KeptBins {
+    static constexpr bool kWhole = false;
+    uint32_t b[KEEP / 2];
+    __device__ __forceinline__ void set(int q, uint32_t bin)
+    {
+        if (q & 1) b[q / 2] = (b[q / 2] & 0x0000FFFFu) | (bin << 16);
+        else       b[q / 2] = bin;
+    }
+    template <typename F>
+    __device__ __forceinline__ void each(uint32_t count, uint32_t, F f) const
+    {
+#pragma unroll
+        for (int q = 0; q < KEEP; ++q)
+            if ((uint32_t)q * kRowThreads < count)                   // uniform over the workgroup
+                f((q & 1) ? (b[q / 2] >> 16) : (b[q / 2] & 0xFFFFu), q);
     }
 };
 
-// Exact K-th largest magnitude and tie cut of a candidate list whose entries' bins
-// are in registers.  Returns false when the bin of the K-th largest holds more
-// members than the LDS lists take (the caller then runs the generic select).
+// Exact K-th largest magnitude and tie cut of a candidate list that is kept in registers.  Returns false
+// when the bin of the K-th largest holds more members than the LDS lists take (the caller then runs the generic
+// select).
 // LDS use: rhist holds the histogram, then (words [0, 4096)) the members' magnitudes,
 // ([4096, 8192)) their coordinates, ([8192, 12288)) the histogram of their exact keys.
-template <int KEEP>
-__device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, const u32x2* __restrict__ crow,
-                                                 uint32_t C, uint32_t K, uint32_t tau, SelectLds& lds,
-                                                 uint32_t& kth, uint32_t& tie_cut)
+template <typename Kept>
+__device__ __forceinline__ bool select_from_registers(const Kept& kept, const u32x2* __restrict__ crow, uint32_t C,
+                                                      uint32_t K, uint32_t tau, SelectLds& lds, uint32_t& kth,
+                                                      uint32_t& tie_cut)
 {
     static_assert(kFineBins * kRep >= 3 * kKeyBins, "the members' lists reuse the histogram's storage");
     const uint32_t lane = lane_id(), t = threadIdx.x;
@@ -568,7 +577,7 @@ __device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, c
     // Values on a lattice put thousands of candidates on a few dozen keys, and LDS
     // atomics of one instruction that meet on one address are served one after the
     // other: lane l adds to copy l % kRep of the histogram, which divides those queues.
-    bins.each(C, [&](uint32_t bin, uint32_t) {
+    kept.each(C, tau, [&](uint32_t bin, int) {
         if (bin != 0xFFFFu) atomicAdd(&lds.rhist[bin * kRep + (lane & (kRep - 1))], 1u);
     });
     __syncthreads();
@@ -581,20 +590,32 @@ __device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, c
     uint32_t* mkey = lds.rhist;                   // find_rank_bin ended with a barrier: the histogram is free
     uint32_t* mpos = lds.rhist + kKeyBins;
     {
-        // the members' list positions, in no particular order: count, scan, place
+        // the members, in no particular order: count, scan, place
         uint32_t mine = 0;
-        bins.each(C, [&](uint32_t b, uint32_t) { mine += (b == bin); });
+        kept.each(C, tau, [&](uint32_t b, int) { mine += (b == bin); });
         uint32_t total;
         uint32_t p = block_excl_scan<kRowThreads>(mine, lds.scan, total);
-        if (mine) bins.each(C, [&](uint32_t b, uint32_t i) { if (b == bin) mpos[p++] = i; });
+        if (mine)
+            kept.each(C, tau, [&](uint32_t b, int q) {
+                if (b == bin) {
+                    if constexpr (Kept::kWhole) {
+                        mkey[p] = kept.entry[q].x;
+                        mpos[p++] = kept.entry[q].y;
+                    } else {
+                        mpos[p++] = (uint32_t)q * kRowThreads + t;   // for now its place in the list
+                    }
+                }
+            });
     }
     __syncthreads();
-    for (uint32_t p = t; p < in_bin; p += kRowThreads) {             // all lanes together: one round trip
-        const u32x2 c = crow[mpos[p]];
-        mkey[p] = c.x;
-        mpos[p] = c.y;                            // from here on: the member's coordinate
+    if constexpr (!Kept::kWhole) {
+        for (uint32_t p = t; p < in_bin; p += kRowThreads) {         // all lanes together: one round trip
+            const u32x2 c = crow[mpos[p]];
+            mkey[p] = c.x;
+            mpos[p] = c.y;
+        }
+        __syncthreads();
     }
-    __syncthreads();
     if (in_bin <= (uint32_t)kRankCap) {           // uniform
         // few members: ranked by counting under (magnitude desc, coordinate asc);
         // the one with exactly want-1 others ahead is the last of the top K
@@ -675,6 +696,37 @@ __device__ __forceinline__ bool select_from_bins(const PackedBins<KEEP>& bins, c
         tie_cut = smallest_coordinate(lds, lds.ties, n_eq, take_eq);
     }
     return true;
+}
+
+// The votes of the entries q with q % parts == part, those that are taken: all the atomics, then what depends on
+// their results (see cast_votes).
+template <int KEEP>
+__device__ __forceinline__ void cast_votes_from_registers(u32x2 (&entry)[KEEP], uint32_t C, uint32_t kth, uint32_t tie_cut,
+                                                          uint32_t part, uint32_t parts, uint32_t* __restrict__ votes32,
+                                                          uint32_t* lvl, uint32_t* __restrict__ ssel)
+{
+    uint32_t taken = 0;
+    uint32_t next = part;                         // the workgroup's next q
+#pragma unroll
+    for (int q = 0; q < KEEP; ++q)
+        if ((uint32_t)q == next && (uint32_t)q * kRowThreads < C) {                // uniform
+            next += parts;
+            if ((uint32_t)q * kRowThreads + threadIdx.x < C && is_taken(entry[q], kth, tie_cut)) {
+                taken |= 1u << q;
+                entry[q].x = atomicAdd(&votes32[entry[q].y >> 2], 1u << ((entry[q].y & 3u) * 8u));   // key done with
+            }
+        }
+    next = part;
+#pragma unroll
+    for (int q = 0; q < KEEP; ++q)
+        if ((uint32_t)q == next && (uint32_t)q * kRowThreads < C) {                // uniform
+            next += parts;
+            const bool mine = taken >> q & 1u;
+            if (mine) atomicAdd(&lvl[((entry[q].x >> ((entry[q].y & 3u) * 8u)) & 255u) + 1u], 1u);
+            if (ssel)
+                tally_groups((uint32_t)q * kRowThreads + threadIdx.x < C ? entry[q].y / kSeg : 0xFFFFFFFFu, mine,
+                             [&](uint32_t sg, uint32_t n) { atomicAdd(&ssel[sg], n); });
+        }
 }
 
 // Exact select of a whole row from memory by one workgroup: the K-th largest magnitude by a radix select,
@@ -760,9 +812,10 @@ __device__ __forceinline__ void select_row_from_memory(Lds& lds, const float* __
 // equal magnitudes), the row's first workgroup selects it exactly from memory (e
 // already holds a = g + e), emits and casts its vote; slow_flag[row] = 1 tells the
 // later kernels to skip the row.
-// n_spec (<= kSpec): how many of a thread's list entries are fetched before the
+// n_spec (<= KEEP): how many of a thread's list entries are fetched before the
 // row's count is known (the list's storage holds cap entries; what lies at or
 // beyond the count is ignored), so that the two loads do not queue up.
+template <int KEEP>
 __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     const float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N, uint32_t K,
     const u32x2* __restrict__ cand, uint32_t cap, const uint32_t* __restrict__ row_count_sets,
@@ -779,11 +832,17 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     const uint32_t row = (blockIdx.x / (8u * parts)) * 8u + within % 8u, part = within / 8u;
     if (row >= N) return;                         // whole workgroup
     const u32x2* crow = cand + (size_t)row * cap;
-    uint32_t raw[kSpec];
+    constexpr bool kWhole = KEEP <= 16;           // whole entries are kept, else bins
+    KeptEntries<kWhole ? KEEP : 1> whole;
+    uint32_t key[kWhole ? 1 : KEEP];
+    auto fetch = [&](int q) {
+        const u32x2* at = &crow[min((uint32_t)q * kRowThreads + t, cap - 1)];
+        if constexpr (kWhole) whole.entry[q] = *at;
+        else                  key[q] = at->x;
+    };
 #pragma unroll
-    for (int q = 0; q < kSpec; ++q) {
-        raw[q] = 0;
-        if ((uint32_t)q < n_spec) raw[q] = crow[min((uint32_t)q * kRowThreads + t, cap - 1)].x;
+    for (int q = 0; q < KEEP; ++q) {
+        if ((uint32_t)q < n_spec) fetch(q);
         if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);   // keep address arithmetic from piling up
     }
     // (the streaming kernel counted into the counter set of this step's parity)
@@ -813,19 +872,19 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     if (from_list) {
         uint32_t kth = 0, tie_cut = 0, path = 0;
         bool done = false;
-        if (tau != 0 && C <= (uint32_t)kSpec * kRowThreads) {
-            PackedBins<kSpec> bins;
-            bins.clear();
-            auto pack = [&](auto qc, uint32_t key) {
-                constexpr int Q = decltype(qc)::value;
-                const uint32_t i = (uint32_t)Q * kRowThreads + t;
-                bins.template set<Q>(i < C ? fine_bin(key, tau) : 0xFFFFu);
-            };
-            static_for<0, kSpec>([&](auto qc) {
-                constexpr int Q = decltype(qc)::value;
-                if ((uint32_t)Q * kRowThreads < C) pack(qc, (uint32_t)Q < n_spec ? raw[Q] : crow[min((uint32_t)Q * kRowThreads + t, cap - 1)].x);
-            });
-            done = select_from_bins<kSpec>(bins, crow, C, K, tau, lds, kth, tie_cut);
+        if (tau != 0 && C <= (uint32_t)KEEP * kRowThreads) {
+#pragma unroll
+            for (int q = 0; q < KEEP; ++q)        // longer than expected
+                if ((uint32_t)q >= n_spec && (uint32_t)q * kRowThreads < C) fetch(q);      // uniform
+            if constexpr (kWhole) {
+                done = select_from_registers(whole, crow, C, K, tau, lds, kth, tie_cut);
+            } else {
+                KeptBins<KEEP> bins;
+#pragma unroll
+                for (int q = 0; q < KEEP; ++q)
+                    bins.set(q, (uint32_t)q * kRowThreads + t < C ? fine_bin(key[q], tau) : 0xFFFFu);
+                done = select_from_registers(bins, crow, C, K, tau, lds, kth, tie_cut);
+            }
         }
         if (!done) {                              // uniform
             __syncthreads();
@@ -843,8 +902,13 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
         if (!thresholds_only) {
             for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;
             __syncthreads();
-            cast_votes_of_share(crow, C, kth, tie_cut, part, parts, votes32, lds.lvl,
-                                seg_sel ? seg_sel + (size_t)row * nseg : nullptr);
+            uint32_t* ssel = seg_sel ? seg_sel + (size_t)row * nseg : nullptr;
+            bool cast = false;
+            if constexpr (KEEP <= 8) {
+                cast = done;
+                if (done) cast_votes_from_registers(whole.entry, C, kth, tie_cut, part, parts, votes32, lds.lvl, ssel);
+            }
+            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, part, parts, votes32, lds.lvl, ssel);
             __syncthreads();
             merge_levels(lds.lvl, lvl_sets, blockIdx.x);
         }
