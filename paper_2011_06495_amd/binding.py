@@ -141,20 +141,38 @@ def _dev_ptr(t) -> int:
     return 0 if t is None else t.data_ptr()
 
 
+_raw_stream = None      # torch's own getter of the current stream's handle, once torch is there
+
+
+def _stream_handle(stream, t) -> int:
+    """The hipStream_t of `stream` (a torch.cuda.Stream), or of the current stream of t's device.
+    The short calls of this library take a few microseconds on the GPU, less than building a
+    torch.cuda.Stream object and the rest of a call took on the host (a loop of mv_quant_decode
+    calls: 7.0 us each, 5.0 us so)."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    device = t.get_device()
+    if device < 0:                       # not on a GPU: torch's own error
+        import torch
+        return torch.cuda.current_stream(t.device).cuda_stream
+    if _raw_stream is None:
+        import torch
+        _raw_stream = torch._C._cuda_getCurrentRawStream
+    return _raw_stream(device)
+
+
 def mv_vote_step(ctx: int, grads, err, worker_idx, votes, mask_idx, agg_vals, stream=None,
                  ld_g: Optional[int] = None, ld_e: Optional[int] = None) -> None:
     """Enqueues one vote step on `stream` (a torch.cuda.Stream; None = torch's
     current stream).  Tensors are torch device tensors; `grads` and `err` are
     2-D with unit column stride (the row stride is taken from the tensor unless
     given).  worker_idx and votes may be None."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(err.device)
     st = load().mv_vote_step(
         ctx, _dev_ptr(grads), grads.stride(0) if ld_g is None else ld_g,
         _dev_ptr(err), err.stride(0) if ld_e is None else ld_e,
         _dev_ptr(worker_idx), _dev_ptr(votes), _dev_ptr(mask_idx), _dev_ptr(agg_vals),
-        stream.cuda_stream)
+        _stream_handle(stream, err))
     if st != MV_OK:
         raise MvError(st, "mv_vote_step")
 
@@ -164,14 +182,11 @@ def mv_rs_vote_step(ctx: int, grads, err, rand_exp, worker_idx, votes, mask_idx,
     """Enqueues one step of majority voting with random selection: as mv_vote_step,
     the mask drawn in proportion to the votes with the caller's Exp(1) numbers
     `rand_exp` (d float32 on the device)."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(err.device)
     st = load().mv_rs_vote_step(
         ctx, _dev_ptr(grads), grads.stride(0) if ld_g is None else ld_g,
         _dev_ptr(err), err.stride(0) if ld_e is None else ld_e, _dev_ptr(rand_exp),
         _dev_ptr(worker_idx), _dev_ptr(votes), _dev_ptr(mask_idx), _dev_ptr(agg_vals),
-        stream.cuda_stream)
+        _stream_handle(stream, err))
     if st != MV_OK:
         raise MvError(st, "mv_rs_vote_step")
 
@@ -180,14 +195,11 @@ def mv_ad_vote_step(ctx: int, grads, err, k_ad: int, vote_bits, msum, add_idx, d
                     agg_vals, stream=None, ld_g: Optional[int] = None, ld_e: Optional[int] = None) -> None:
     """Enqueues one add-drop vote step (Algorithm 2).  vote_bits: N x ld_bits int32
     device tensor (the standing votes' bitmaps), msum: uint8 device tensor."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(err.device)
     st = load().mv_ad_vote_step(
         ctx, _dev_ptr(grads), grads.stride(0) if ld_g is None else ld_g,
         _dev_ptr(err), err.stride(0) if ld_e is None else ld_e, int(k_ad),
         _dev_ptr(vote_bits), vote_bits.stride(0), _dev_ptr(msum), _dev_ptr(add_idx), _dev_ptr(drop_idx),
-        _dev_ptr(counts), _dev_ptr(mask_idx), _dev_ptr(agg_vals), stream.cuda_stream)
+        _dev_ptr(counts), _dev_ptr(mask_idx), _dev_ptr(agg_vals), _stream_handle(stream, err))
     if st != MV_OK:
         raise MvError(st, "mv_ad_vote_step")
 
@@ -238,12 +250,9 @@ def mv_last_step_row_stats(ctx: int, n_workers: int):
 
 def mv_probe_copy(dst, src, stream=None) -> None:
     """Plain streaming copy src -> dst (torch device tensors of equal byte size)."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(src.device)
     nbytes = src.numel() * src.element_size()
     assert dst.numel() * dst.element_size() == nbytes
-    st = load().mv_probe_copy(dst.data_ptr(), src.data_ptr(), nbytes, stream.cuda_stream)
+    st = load().mv_probe_copy(dst.data_ptr(), src.data_ptr(), nbytes, _stream_handle(stream, src))
     if st != MV_OK:
         raise MvError(st, "mv_probe_copy")
 
@@ -261,24 +270,18 @@ def mv_codec_encode(idx, n: int, d: int, block_len: int, streams, n_bits, counts
     """idx: rows x ld int32 device tensor of ascending coordinates; streams: rows x ld_words
     int32 device tensor (out); n_bits: rows int64 device tensor (out); counts: optional
     int32 device tensor with the rows' lengths at stride counts_stride."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(idx.device)
     st = load().mv_codec_encode(_dev_ptr(idx), idx.stride(0), _dev_ptr(counts), counts_stride, n, idx.shape[0], d,
                                 block_len, _dev_ptr(streams), streams.stride(0), _dev_ptr(n_bits),
-                                stream.cuda_stream)
+                                _stream_handle(stream, idx))
     if st != MV_OK:
         raise MvError(st, "mv_codec_encode")
 
 
 def mv_codec_decode(streams, n_bits, max_bits: int, d: int, block_len: int, idx_out, max_n: int, counts_out,
                     scratch, stream=None) -> None:
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(streams.device)
     st = load().mv_codec_decode(_dev_ptr(streams), streams.stride(0), _dev_ptr(n_bits), max_bits, streams.shape[0],
                                 d, block_len, _dev_ptr(idx_out), idx_out.stride(0), max_n, _dev_ptr(counts_out),
-                                _dev_ptr(scratch), scratch.numel() * scratch.element_size(), stream.cuda_stream)
+                                _dev_ptr(scratch), scratch.numel() * scratch.element_size(), _stream_handle(stream, streams))
     if st != MV_OK:
         raise MvError(st, "mv_codec_decode")
 
@@ -289,12 +292,9 @@ MV_CODEC_STATIC_SCRATCH_BYTES = 16 << 20
 def mv_codec_decode_static(streams, n_bits, max_bits: int, d: int, block_len: int, idx_out, max_n: int, counts_out,
                            stream=None) -> None:
     """mv_codec_decode on the library's own scratch array: allocates nothing."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(streams.device)
     st = load().mv_codec_decode_static(_dev_ptr(streams), streams.stride(0), _dev_ptr(n_bits), max_bits,
                                        streams.shape[0], d, block_len, _dev_ptr(idx_out), idx_out.stride(0), max_n,
-                                       _dev_ptr(counts_out), stream.cuda_stream)
+                                       _dev_ptr(counts_out), _stream_handle(stream, streams))
     if st != MV_OK:
         raise MvError(st, "mv_codec_decode_static")
 
@@ -306,21 +306,15 @@ def mv_quant_scratch_bytes(n: int, rows: int, q: int) -> int:
 def mv_quant_encode(vals, q: int, streams, means, scratch, stream=None) -> None:
     """vals: rows x n float32 device tensor; streams: rows x ld_words int32 (out);
     means: rows x 2**(q-1) float32 (out)."""
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(vals.device)
     st = load().mv_quant_encode(_dev_ptr(vals), vals.stride(0), vals.shape[1], vals.shape[0], q, _dev_ptr(streams),
                                 streams.stride(0), _dev_ptr(means), _dev_ptr(scratch),
-                                scratch.numel() * scratch.element_size(), stream.cuda_stream)
+                                scratch.numel() * scratch.element_size(), _stream_handle(stream, vals))
     if st != MV_OK:
         raise MvError(st, "mv_quant_encode")
 
 
 def mv_quant_decode(streams, n: int, q: int, means, out, stream=None) -> None:
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream(out.device)
     st = load().mv_quant_decode(_dev_ptr(streams), streams.stride(0), n, streams.shape[0], q, _dev_ptr(means),
-                                _dev_ptr(out), out.stride(0), stream.cuda_stream)
+                                _dev_ptr(out), out.stride(0), _stream_handle(stream, out))
     if st != MV_OK:
         raise MvError(st, "mv_quant_decode")
