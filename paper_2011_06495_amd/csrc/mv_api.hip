@@ -72,7 +72,6 @@ struct Plan {
     uint32_t bit_blocks;          // workgroups of kBitBlockWords bitmap words per row
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
-    size_t   off_sellist2;
     // random selection
     uint32_t rs_cap;              // most coordinates that can hold a vote: min(N K, d)
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
@@ -248,9 +247,6 @@ Plan make_plan(const mv_config* c)
         p.off_dlist = off;   off += align_up((size_t)p.N * p.cap_d * 8);
         p.off_adcount = off; off += align_up((size_t)p.N * 2 * mvk::kCounterStride * 4);
         p.off_adbits = off;  off += align_up((size_t)p.N * p.nwords_pad * 4);
-    }
-    if (p.multi_select) {
-        p.off_sellist2 = off; off += align_up((size_t)p.N * p.cap * 8);
     }
     const uint64_t voted_max = (uint64_t)p.N * p.K;
     p.rs_cap = (uint32_t)(voted_max < (uint64_t)p.d ? voted_max : (uint64_t)p.d);
@@ -567,7 +563,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         before(KID_SEL_SPLIT);
         hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
-                           ws_ptr<mvk::u32x2>(c, p.off_sellist2), kth, tiecut, a.worker_idx, votes32, ssel, p.nseg,
+                           kth, tiecut, a.worker_idx, votes32, ssel, p.nseg,
                            lvlsets, thresholds_only);
         after(KID_SEL_SPLIT);
     } else {

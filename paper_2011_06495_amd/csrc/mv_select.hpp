@@ -952,8 +952,9 @@ struct ListView {
     uint32_t* hist;           // kListBins counters, zero between steps
     uint32_t* count2;         // length of the second list, zero between steps
     uint32_t* done;           // workgroups that have passed, zero between steps (on a line of its own)
-    u32x2*    list2;          // room for n entries; step2 = -1: growing downwards
+    u32x2*    list2;          // room for `room` members; step2 = -1: growing downwards
     int       step2;
+    uint32_t  room;
 };
 
 template <int MEMBERS>
@@ -1250,12 +1251,15 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
                 }
             } else {
                 const uint32_t p = wave_slots(mine, v.count2, lane);
-                if (mine && p < v.n) store_past_caches(v.list2 + (int64_t)p * v.step2, c[u]);
+                if (mine && p < v.room) store_past_caches(v.list2 + (int64_t)p * v.step2, c[u]);
             }
         }
         act(c, above);
     }
-    uint32_t n_members = in_bin;
+    const uint32_t n_members = in_bin;            // (the histogram counts what the list holds)
+    // members that the second list has no room for are found in the first one again
+    const bool stored = !ALONE && n_members <= v.room;
+    auto member_at = [&](uint64_t i) { return load_past_caches(v.list2 + (int64_t)i * v.step2); };
     if (!ALONE) {
         // every store and atomic of this workgroup has been performed before it is counted as done
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1264,9 +1268,8 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
         if (t == 0) lds.last = atomicAdd(v.done, 1u) == parts - 1u;
         __syncthreads();
         if (!lds.last) return false;
-        // (the histogram counts what the list holds, so in_bin members have been stored)
-        for (uint32_t p = t; p < in_bin && p < Lds::kMost; p += kRowThreads) {
-            const u32x2 m = load_past_caches(v.list2 + (int64_t)p * v.step2);
+        for (uint32_t p = t; stored && p < n_members && p < Lds::kMost; p += kRowThreads) {
+            const u32x2 m = member_at(p);
             lds.key[0][p] = m.x;
             lds.at[0][p] = m.y;
         }
@@ -1278,12 +1281,11 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
         }
     }
     __syncthreads();
-    auto member_at = [&](uint64_t i) { return load_past_caches(v.list2 + (int64_t)i * v.step2); };
     uint32_t lo, bits;
     list_bin_range(v, bin, lo, bits);
-    if (n_members <= Lds::kMost)          // uniform
+    if (n_members <= Lds::kMost && (ALONE || stored))   // uniform
         rank_members(lds, n_members, want, lo, bits, kth, tie_cut);
-    else if (ALONE)
+    else if (!stored)
         rank_in_memory(lds,
                        [&](uint64_t i) {          // what is no member gets a key outside every range
                            u32x2 m = v.list[i];
@@ -1294,14 +1296,14 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
     else
         rank_in_memory(lds, member_at, n_members, n_members, want, lo, bits, kth, tie_cut);
     // the members that are taken
-    const uint32_t n = ALONE ? v.n : n_members;
+    const uint32_t n = stored ? n_members : v.n;
     for (uint64_t i0 = 0; i0 < n; i0 += kListBatch) {
         uint32_t taken = 0;
 #pragma unroll
         for (int u = 0; u < kListUnroll; ++u) {
             const uint64_t i = i0 + (uint32_t)u * kRowThreads + t;
-            c[u] = i < n ? (ALONE ? v.list[i] : member_at(i)) : none;
-            const bool mine = i < n && (!ALONE || list_bin(v, c[u].x) == bin);
+            c[u] = i < n ? (stored ? member_at(i) : v.list[i]) : none;
+            const bool mine = i < n && (stored || list_bin(v, c[u].x) == bin);
             taken |= (mine && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
         }
         act(c, taken);
@@ -1323,6 +1325,7 @@ __device__ __forceinline__ void lend_storage(ListView& v, uint32_t* __restrict__
     v.count2 = h + kCtlWords + (2 * which) * kCounterStride;
     v.done = h + kCtlWords + (2 * which + 1) * kCounterStride;
     v.step2 = 1;
+    v.room = v.n;
 }
 static_assert(kListBins == kRowThreads, "a bin per thread");
 static_assert(kHistRow >= kCtlWords + 6 * kCounterStride, "three lists' storage fits a row's sample histogram");
@@ -1355,9 +1358,9 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
 }
 
 __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
-    const float* __restrict__ e, int64_t ld_e, int64_t d, const u32x2* __restrict__ cand, uint32_t cap, uint32_t K,
+    const float* __restrict__ e, int64_t ld_e, int64_t d, u32x2* cand, uint32_t cap, uint32_t K,
     const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
-    const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist, u32x2* __restrict__ list2,
+    const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist,
     uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
     uint32_t* __restrict__ votes32, uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
     int thresholds_only)
@@ -1375,7 +1378,9 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     v.want = K;
     v.base = tau_bits[row];  v.fine = 12;  v.coarse = 18;   // as in mv_sel_hist
     lend_storage(v, sample_hist, row, 0);
-    v.list2 = list2 + (size_t)row * cap;
+    v.list2 = cand + (size_t)row * cap + (cap - 1);                 // the end of the row's storage, downwards
+    v.step2 = -1;
+    v.room = cap - v.n;
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
     uint32_t* ssel = seg_sel ? seg_sel + (size_t)row * nseg : nullptr;
     uint32_t kth, tie_cut;
