@@ -493,6 +493,18 @@ __device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, u
 // K = 111,740: 48.6 -> 47.0 us).
 constexpr int kGatherRounds = 4;                  // at most this many rounds of kb positions per workgroup
 
+// The N values of a position lie together, positions an odd number of words apart: the threads that add them up,
+// one per position, hit different banks.
+constexpr uint32_t tile_pitch(uint32_t N) { return N | 1u; }
+constexpr uint32_t kTileFloats = kMaskThreads + kMaskThreads / 2;     // two workers need the most
+constexpr bool tile_holds_every_n()
+{
+    for (uint32_t N = 1; N <= 255; ++N)
+        if ((kMaskThreads / N - 1) * tile_pitch(N) + N > kTileFloats) return false;
+    return true;
+}
+static_assert(tile_holds_every_n(), "a round's values fit the tile for every number of workers");
+
 __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint32_t* slice /*LDS*/,
                                                  float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N,
                                                  uint32_t k0, uint32_t k1, uint32_t rounds, float scale,
@@ -500,7 +512,7 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
 {
     const uint32_t t = threadIdx.x, kb = kMaskThreads / N;
     const uint32_t n = t / kb, kl = t % kb;           // threads from N kb on have n >= N: idle
-    const uint32_t pitch = N + 1;                     // kb * (N + 1) <= 1024 + kb <= 1536
+    const uint32_t pitch = tile_pitch(N);
     // a thread's loads of all rounds are in flight together
     float v[kGatherRounds];
 #pragma unroll
@@ -547,7 +559,7 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
 // row (b / emit_blocks)'s vote list; they start after the gather's workgroups and
 // run beside them.
 struct GatherLds {
-    float    tile[kMaskThreads + kMaskThreads / 2 + 8];
+    float    tile[kTileFloats];
     uint32_t slice[kGatherRounds * kMaskThreads];              // the workgroup's positions' coordinates
     uint32_t need[3 * (kMaskThreads + 2)];                     // stretches to read: (stretch, above before, at before)
     uint32_t blocks[3 * (kMaskThreads + 2)];                   // blocks whose stretches are looked at

@@ -347,7 +347,7 @@ struct SmallMaskLds {
         };
         struct {                                              // then, for the gather:
             uint32_t slice[kGatherRounds * kSmallThreads];    // the workgroup's positions' coordinates
-            float    tile[kSmallThreads + kSmallThreads / 2 + 8];
+            float    tile[kTileFloats];
         };
     };
     uint64_t scan[2][kSmallThreads / kWave];

@@ -11,6 +11,7 @@ import torch
 from paper_2011_06495_amd import binding as B
 from paper_2011_06495_amd import workloads as W
 from tests.gpu_util import GpuStepper, assert_matches_oracle
+from tests.test_gpu_add_drop import GpuAdStepper
 
 pytestmark = pytest.mark.gpu
 
@@ -425,3 +426,38 @@ def test_tie_cut_inside_a_run_of_neighbouring_ties(oracle):
     say("  candidates %s path %s" % (cand, path))
     assert all(p != 1 for p in path), "meant for the candidate-list routes"
     assert_matches_oracle(got, oracle.vote_step(g, e, K), "neighbouring ties")
+
+
+@pytest.mark.parametrize("d,K", [(40009, 1), (40009, 400), (40009, 700), (40009, 1500), (40009, 33000),
+                                 (400003, 300000)])
+def test_one_worker_of_a_long_vector(oracle, d, K):
+    """One worker: a round of the gather has 1024 positions, whose values and coordinates lie side by side in LDS; with
+    a workgroup's positions below, at and far beyond a round, in all three schemes."""
+    say("one worker d=%d K=%d" % (d, K))
+    rng = np.random.default_rng(d + K)
+    e = (rng.standard_normal((1, d)) * 0.1).astype(np.float32)
+    with GpuStepper(1, d, K) as gs:
+        gs.set_error(e)
+        for t in range(4):
+            g = rng.standard_normal((1, d)).astype(np.float32)
+            gs.set_grads(g)
+            if t % 2 == 0:
+                gs.step()
+                ref = oracle.vote_step(g, e, K, threads=8)
+            else:
+                r = rng.standard_exponential(d).astype(np.float32)
+                gs.step_rs(r)
+                ref = oracle.rs_vote_step(g, e, K, r, threads=8)
+            assert_matches_oracle(gs.fetch(), ref, "step %d" % t)
+            e = ref.err
+    gs = GpuAdStepper(1, d, K, K)
+    try:
+        vote, msum, e = np.zeros((1, d), np.uint8), np.zeros(d, np.uint8), np.zeros((1, d), np.float32)
+        for t, k_ad in enumerate([K, max(1, K // 10)]):
+            g = rng.standard_normal((1, d)).astype(np.float32)
+            ref = oracle.ad_vote_step(g, e, K, k_ad, vote, msum, threads=8)
+            gs.step(g, k_ad)
+            gs.compare(ref, "add-drop step %d" % t)
+            vote, msum, e = ref.vote, ref.msum, ref.err
+    finally:
+        gs.close()
