@@ -1229,6 +1229,11 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
     __syncthreads();
     uint32_t bin, want, in_bin;
     find_rank_bin<kListBins>(lds.hist, lds.scan, lds.bcast, v.want, bin, want, in_bin);
+    // Space in the second list is reserved once per workgroup, or per workgroup and batch when the members are many:
+    // reservations of one list follow each other at the memory side, about 9 ns apart (once per wavefront
+    // instead, random selection took 452 us at 16 x 11.2 M, K = 11,174, for 441 so, and at 3 x 10 M, K = 150,000,
+    // 207 for 169).
+    const bool few = in_bin <= Lds::kMost;        // uniform
     for (uint64_t i0 = first; i0 < v.n; i0 += (uint64_t)parts * kListBatch) {
         if (i0 != first) load(i0);
         uint32_t above = 0, member = 0;
@@ -1239,22 +1244,46 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
             above |= (there && b > bin ? 1u : 0u) << u;
             member |= (there && b == bin ? 1u : 0u) << u;
         }
-        // the members first: the last workgroup waits for them
+        if (ALONE || few) {
+            // (few members in the whole list: they all fit; in a list alone, as many as fit)
 #pragma unroll
-        for (int u = 0; u < kListUnroll; ++u) {
-            const bool mine = member >> u & 1u;
-            if (ALONE) {
+            for (int u = 0; u < kListUnroll; ++u) {
+                const bool mine = member >> u & 1u;
                 const uint32_t p = wave_slots(mine, &lds.n_list, lane);
                 if (mine && p < Lds::kMost) {
                     lds.key[0][p] = c[u].x;
                     lds.at[0][p] = c[u].y;
                 }
-            } else {
-                const uint32_t p = wave_slots(mine, v.count2, lane);
-                if (mine && p < v.room) store_past_caches(v.list2 + (int64_t)p * v.step2, c[u]);
             }
+            act(c, above);
+        } else {
+            uint32_t total;
+            uint32_t p = block_excl_scan<kRowThreads>((uint32_t)__popc(member), lds.scan, total);
+            uint32_t base = 0;
+            if (t == 0 && total != 0u) base = atomicAdd(v.count2, total);
+            act(c, above);
+            if (t == 0) lds.n_list = base;
+            __syncthreads();
+            p += lds.n_list;
+#pragma unroll
+            for (int u = 0; u < kListUnroll; ++u)
+                if (member >> u & 1u) {
+                    if (p < v.room) store_past_caches(v.list2 + (int64_t)p * v.step2, c[u]);
+                    ++p;
+                }
+            __syncthreads();                      // (lds.n_list has been read)
         }
-        act(c, above);
+    }
+    if (!ALONE && few) {                          // uniform
+        __syncthreads();
+        const uint32_t n = lds.n_list;
+        if (t == 0 && n != 0u) lds.bcast[0] = atomicAdd(v.count2, n);
+        __syncthreads();
+        for (uint32_t p = t; p < n; p += kRowThreads) {
+            const uint32_t to = lds.bcast[0] + p;
+            const u32x2 m = {lds.key[0][p], lds.at[0][p]};
+            if (to < v.room) store_past_caches(v.list2 + (int64_t)to * v.step2, m);
+        }
     }
     const uint32_t n_members = in_bin;            // (the histogram counts what the list holds)
     // members that the second list has no room for are found in the first one again

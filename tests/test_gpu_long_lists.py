@@ -92,3 +92,33 @@ def test_random_selection_around_one_workgroups_list(oracle, N, K, votes):
             gs.set_grads(g)
             gs.step_rs(r)
             assert_matches_oracle(gs.fetch(), oracle.rs_vote_step(g, e, K, r), "N=%d K=%d" % (N, K))
+
+
+@pytest.mark.parametrize("m", [3071, 3072, 3073, 8191, 8192, 8193])
+def test_groups_around_what_fits_on_chip(oracle, m):
+    """The boundary lies in a group of m equal magnitudes (m equal times): 3072 members of a bin are kept in LDS in the
+    rows' select and for the add and drop lists, 8192 in the random selection."""
+    N, d, K = 2, 300007, 32000
+    print("[case] groups around what fits on chip m=%d" % m, flush=True)
+    rng = np.random.default_rng(m)
+    above = K - m // 2
+    g = rng.uniform(0.1, 0.9, (N, d)).astype(np.float32)
+    for n in range(N):
+        at = rng.permutation(d)
+        g[n, at[:above]] = rng.uniform(2.0, 3.0, above)
+        g[n, at[above:above + m]] = 1.0
+    e = np.zeros_like(g)
+    with GpuStepper(N, d, K) as gs:
+        gs.set_grads(g)
+        gs.set_error(e)
+        gs.step()
+        ref = oracle.vote_step(g, e, K, threads=8)
+        assert_matches_oracle(gs.fetch(), ref, "plain")
+        once = rng.permutation(np.flatnonzero(ref.votes == 1))
+        r = np.full(d, 3.0, np.float32)
+        r[once[:above]] = rng.uniform(0.1, 0.4, above)
+        r[once[above:above + m]] = 1.0
+        gs.set_grads(g)
+        gs.set_error(e)
+        gs.step_rs(r)
+        assert_matches_oracle(gs.fetch(), oracle.rs_vote_step(g, e, K, r, threads=8), "random")
