@@ -304,7 +304,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_ad_pick(
         }
     } else {
         uint32_t kth, tie_cut;
-        (void)list_split<ALONE>(v, blockIdx.x, gridDim.x, lds, apply, kth, tie_cut);
+        ListRest rest;
+        (void)list_split<ALONE ? SplitEnd::Alone : SplitEnd::Last>(v, blockIdx.x, gridDim.x, lds, apply, kth, tie_cut, rest);
     }
     tally.merge();
 }

@@ -19,6 +19,7 @@ enum KernelId {
     // rows' select with many workgroups (large K) in place of the one above
     KID_SEL_HIST,
     KID_SEL_SPLIT,
+    KID_SEL_FINISH,
     KID_MASK_COUNT,
     KID_GATHER,
     // add-drop voting only
@@ -36,7 +37,7 @@ enum KernelId {
     KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
-    "mv_stream_collect", "mv_row_select", "mv_sel_hist", "mv_sel_split", "mv_mask_count", "mv_gather_update",
+    "mv_stream_collect", "mv_row_select", "mv_sel_hist", "mv_sel_split", "mv_sel_finish", "mv_mask_count", "mv_gather_update",
     "mv_ad_collect",     "mv_ad_hist",    "mv_ad_pick",  "mv_ad_emit",   "mv_rs_keys",    "mv_rs_hist",
     "mv_rs_pick",        "mv_small_rows", "mv_small_mask"};
 
@@ -72,6 +73,7 @@ struct Plan {
     uint32_t bit_blocks;          // workgroups of kBitBlockWords bitmap words per row
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
+    uint32_t block_shift;         // its blocks of coordinates: 2^block_shift, at most kCoordBlocks of them
     // random selection
     uint32_t rs_cap;              // most coordinates that can hold a vote: min(N K, d)
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
@@ -190,6 +192,8 @@ Plan make_plan(const mv_config* c)
         p.select_parts = (uint32_t)parts;
         // beyond what one workgroup keeps in registers the lists go through the many-workgroup select
         p.multi_select = slots > (uint64_t)mvk::kKeepMost;
+        p.block_shift = 10;
+        while (((p.d - 1) >> p.block_shift) >= mvk::kCoordBlocks) ++p.block_shift;
         // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
         uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
         if (sb > 256) sb = 256;
@@ -564,8 +568,15 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
                            kth, tiecut, a.worker_idx, votes32, ssel, p.nseg,
-                           lvlsets, thresholds_only);
+                           lvlsets, thresholds_only, taupub, p.block_shift);
         after(KID_SEL_SPLIT);
+        uint32_t parts = add_drop ? 1 : 256 / p.N;
+        parts = parts > 16 ? 16 : parts < 1 ? 1 : parts;
+        before(KID_SEL_FINISH);
+        hipLaunchKernelGGL(mvk::mv_sel_finish, dim3(parts, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
+                           (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist, kth, tiecut,
+                           votes32, ssel, p.nseg, lvlsets, thresholds_only, taupub, (const mvk::u32x2*)seg, p.block_shift);
+        after(KID_SEL_FINISH);
     } else {
         const uint32_t parts = add_drop ? 1 : p.select_parts;
         before(KID_ROW_SELECT);

@@ -27,8 +27,8 @@
 //                         the row is selected exactly from memory instead) and of
 //                         the largest coordinate taken among its ties; then every
 //                         workgroup casts the votes of its share of the list.
-//                         Long lists (large K) go through mv_sel_hist and
-//                         mv_sel_split, many workgroups per row
+//                         Long lists (large K) go through mv_sel_hist,
+//                         mv_sel_split and mv_sel_finish, many workgroups per row
 //   3. mv_mask_count      counting-sort selection of the K most voted
 //                         coordinates, ties to the lowest coordinate: the vote
 //                         threshold from the level counters, the counts of every

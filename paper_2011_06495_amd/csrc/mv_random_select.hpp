@@ -154,7 +154,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_rs_pick(const u32x2* __restric
     const BlockTally tally = {lds.tally, winners_per_block, 1, n_blocks};
     tally.clear();                                // (list_split has barriers before it acts)
     uint32_t kth, tie_cut;
-    const bool finished = list_split<ALONE>(
+    ListRest rest;
+    const bool finished = list_split<ALONE ? SplitEnd::Alone : SplitEnd::Last>(
         v, blockIdx.x, gridDim.x, lds,
         [&](const u32x2 (&c)[kListUnroll], uint32_t taken) {
 #pragma unroll
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_rs_pick(const u32x2* __restric
                 tally.add(c[u].y / per_block, mine);
             }
         },
-        kth, tie_cut);
+        kth, tie_cut, rest);
     tally.merge();
     if (finished && threadIdx.x == 0) rs_count[0] = 0;   // (all workgroups have read it)
 }

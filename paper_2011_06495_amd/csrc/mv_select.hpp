@@ -807,7 +807,7 @@ __device__ __forceinline__ void select_row_from_memory(Lds& lds, const float* __
 // largest coordinate taken among the candidates tied with it (0xFFFFFFFF: all ties
 // taken).  Each workgroup then casts the votes of its share of the list.  With
 // thresholds_only (add-drop voting) no vote is cast.  Longer lists go through
-// mv_sel_hist and mv_sel_split.
+// mv_sel_hist, mv_sel_split and mv_sel_finish.
 // If the candidate count is < K or overflowed the list (for instance a row of
 // equal magnitudes), the row's first workgroup selects it exactly from memory (e
 // already holds a = g + e), emits and casts its vote; slow_flag[row] = 1 tells the
@@ -921,22 +921,23 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
 }
 
 // ---- exact select over a long list with many workgroups ----------------------
-// Finds the `want` largest keys of a list and does something with them, in two
-// launches when the list is long: (1) a histogram of the keys over the list (see
-// list_bin), (2) every workgroup locates the bin of the
+// Finds the `want` largest keys of a list and does something with them: (1) a histogram
+// of the keys over the list (see list_bin), (2) every workgroup locates the bin of the
 // want-th largest, acts on its entries of higher bins, and moves that bin's members
-// to a second list; the last of a list's workgroups ranks these exactly and acts on
-// those that are taken.  Lists that one workgroup reads in a moment take one launch,
-// with the histogram in LDS.  The rows' top K when K is large (to act = cast the
-// vote), the add and drop candidates of add-drop voting, and the random selection all
-// come this way.
+// to a second list, (3) these are ranked exactly and those that are taken are acted on.
+// The rows' top K when K is large (to act = cast the vote), the add and drop candidates of
+// add-drop voting, and the random selection all come this way.
+//
+// (3) for the rows' top K is a launch of its own: several workgroups rank the same members, each
+// acts on its share.  It costs an ordinary row nothing (10 x 11.2 M, K = 111,740: 332 us with it and
+// without), and a tie group of a hundred thousand members, which values on a lattice have, is no
+// longer one workgroup's to act on (4 x 10 M, K = 300,000 on a lattice: 297 us, so 193; 2 x 10^6 equal values,
+// K = 500,001: 4040 and 159).  The other lists are shorter: their last workgroup ranks and acts, or
+// the only one, with the histogram in LDS, where one workgroup reads the list in a moment.
 //
 // What the last workgroup reads of the others -- the second list and its length -- goes
 // through atomics, which are performed in memory; the workgroups count themselves done
 // behind them, and nobody waits.
-// 10 lists of 145,000, K = 111,740, with the votes: 59 us in five launches (select, histogram,
-// split, rank, votes), 44 us so; random selection and add-drop voting lost three and two
-// launches of at least 4 us each.
 constexpr int kListUnroll = 4;                    // entries per thread in flight together
 constexpr int kListBatch = kRowThreads * kListUnroll;
 // members of the want-th largest's bin that are ranked in LDS: the first lets two workgroups share a compute unit
@@ -955,7 +956,12 @@ struct ListView {
     u32x2*    list2;          // room for `room` members; step2 = -1: growing downwards
     int       step2;
     uint32_t  room;
+    // the rows' lists only: counters of the members per block of 2^block_shift coordinates and, at count2[1] and
+    // [2], the largest of their keys and of the keys' complements (see BigGroup); zero between steps
+    uint32_t* blocks;
+    uint32_t  block_shift;
 };
+constexpr int kCoordBlocks = 2048;                // block_shift is such that there are at most so many
 
 template <int MEMBERS>
 struct SplitLds {
@@ -1192,14 +1198,199 @@ __device__ __forceinline__ void rank_in_memory(Lds& lds, Entry entry, uint32_t n
     }
 }
 
-// Workgroup `part` of `parts` of a list.  act(c, taken): the marked ones of a batch of kListUnroll entries per
-// thread are among the `want` largest; every one of these is marked in exactly one call, by one workgroup.
-// Returns true to all threads of the one workgroup that finished the list, with kth / tie_cut (the membership
-// test is is_taken).  ALONE: parts is 1 and the histogram is taken here.
-template <bool ALONE, typename Lds, typename Act>
-__device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uint32_t parts, Lds& lds, Act act,
-                                           uint32_t& kth, uint32_t& tie_cut)
+// What of a list is still to be decided when its histogram has been read and every entry of a higher bin has been
+// acted on: the members of one bin, of which the first `want` under (key descending, coordinate ascending) are taken.
+struct ListRest {
+    uint32_t bin, want, n;
+};
+
+// Members that the second list has no room for are found in the first one again.
+__device__ __forceinline__ bool members_stored(const ListView& v, const ListRest& r) { return r.n <= v.room; }
+
+// A member; PAST: past the caches, as this launch's other workgroups have stored it.
+template <bool PAST>
+__device__ __forceinline__ u32x2 member_at(const ListView& v, uint64_t i)
 {
+    const u32x2* at = v.list2 + (int64_t)i * v.step2;
+    if constexpr (PAST) return load_past_caches(at);
+    return *at;
+}
+
+// By one workgroup, with the members in the second list (or in the first): their ranking, ...
+template <bool PAST, typename Lds>
+__device__ __forceinline__ void rank_rest(const ListView& v, const ListRest& r, Lds& lds, uint32_t& kth, uint32_t& tie_cut)
+{
+    uint32_t lo, bits;
+    list_bin_range(v, r.bin, lo, bits);
+    if (r.want == r.n) {                          // uniform: all of them are taken
+        kth = lo;
+        tie_cut = 0xFFFFFFFFu;
+        return;
+    }
+    const bool stored = members_stored(v, r);
+    if (stored && r.n <= Lds::kMost) {            // uniform
+        for (uint32_t p = threadIdx.x; p < r.n; p += kRowThreads) {
+            const u32x2 m = member_at<PAST>(v, p);
+            lds.key[0][p] = m.x;
+            lds.at[0][p] = m.y;
+        }
+        __syncthreads();
+        rank_members(lds, r.n, r.want, lo, bits, kth, tie_cut);
+    } else if (stored) {
+        rank_in_memory(lds, [&](uint64_t i) { return member_at<PAST>(v, i); }, r.n, r.n, r.want, lo, bits, kth, tie_cut);
+    } else {
+        rank_in_memory(lds,
+                       [&](uint64_t i) {          // what is no member gets a key outside every range
+                           u32x2 m = v.list[i];
+                           if (list_bin(v, m.x) != r.bin) m.x = 0xFFFFFFFFu;
+                           return m;
+                       },
+                       v.n, r.n, r.want, lo, bits, kth, tie_cut);
+    }
+}
+
+// ... and act for the taken ones among the share of workgroup `part` of `parts`.
+template <bool PAST, typename Act>
+__device__ __forceinline__ void act_on_rest(const ListView& v, const ListRest& r, uint32_t kth, uint32_t tie_cut,
+                                            uint32_t part, uint32_t parts, Act act)
+{
+    const bool stored = members_stored(v, r);
+    const uint32_t n = stored ? r.n : v.n;
+    for (uint64_t i0 = (uint64_t)part * kListBatch; i0 < n; i0 += (uint64_t)parts * kListBatch) {
+        u32x2 c[kListUnroll];
+        uint32_t taken = 0;
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint64_t i = i0 + (uint32_t)u * kRowThreads + threadIdx.x;
+            const u32x2 none = {0u, 0xFFFFFFFFu};
+            c[u] = i < n ? (stored ? member_at<PAST>(v, i) : v.list[i]) : none;
+        }
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u)
+            taken |= (c[u].y != 0xFFFFFFFFu && (stored || list_bin(v, c[u].x) == r.bin) && is_taken(c[u], kth, tie_cut)
+                          ? 1u : 0u) << u;
+        if (__ballot(taken != 0u) != 0ull) act(c, taken);            // wave-uniform
+    }
+}
+
+// A bin with more members than LDS holds: nearly always a tie group (values on a lattice, a row of equal values),
+// of which the lowest coordinates are taken.  Read member by member by one workgroup such a group of a million costs
+// milliseconds, so the workgroups that find the members also count them per block of coordinates and note
+// whether all keys are the same.
+template <typename Lds>
+struct BigGroup {
+    Lds&     lds;
+    uint32_t largest = 0, largest_not = 0;
+    __device__ __forceinline__ void clear()       // a barrier must follow before the first add
+    {
+        for (uint32_t b = threadIdx.x; b < (uint32_t)kCoordBlocks; b += kRowThreads) lds.hist[b] = 0;
+        if (threadIdx.x < 2) lds.bcast[threadIdx.x] = 0;
+    }
+    __device__ __forceinline__ void add(const ListView& v, u32x2 c, bool member)
+    {
+        if (member) {
+            largest = max(largest, c.x);
+            largest_not = max(largest_not, ~c.x);
+        }
+        tally_groups(c.y >> v.block_shift, member, [&](uint32_t b, uint32_t n) { atomicAdd(&lds.hist[b], n); });
+    }
+    __device__ __forceinline__ void merge(const ListView& v)         // all threads of the workgroup
+    {
+        for (int o = 1; o < kWave; o <<= 1) {
+            largest = max(largest, (uint32_t)__shfl_xor(largest, o, kWave));
+            largest_not = max(largest_not, (uint32_t)__shfl_xor(largest_not, o, kWave));
+        }
+        if (lane_id() == 0) {
+            atomicMax(&lds.bcast[0], largest);
+            atomicMax(&lds.bcast[1], largest_not);
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) atomicMax(&v.count2[1 + threadIdx.x], lds.bcast[threadIdx.x]);
+        for (uint32_t b = threadIdx.x; b < (uint32_t)kCoordBlocks; b += kRowThreads) {
+            const uint32_t n = lds.hist[b];
+            if (n) atomicAdd(&v.blocks[b], n);
+        }
+    }
+};
+
+// The coordinate of the want-th of a row's candidates with this key, in coordinate order, `count` being the
+// thread's two counters of v.blocks: the block it lies in, its segment among the block's, its place in the
+// segment's run (runs are ascending).
+template <typename Lds>
+__device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const uint32_t (&count)[2], uint32_t key,
+                                                      uint32_t want, const u32x2* __restrict__ srow, uint32_t nseg, Lds& lds)
+{
+    static_assert(kCoordBlocks == 2 * kRowThreads && kSeg == kRowThreads, "two blocks to a thread, a thread per entry of a run");
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    uint32_t total;
+    uint32_t ex = block_excl_scan<kRowThreads>(count[0] + count[1], lds.scan, total);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (ex < want && want <= ex + count[q]) {
+            lds.bcast[0] = 2u * t + q;
+            lds.bcast[1] = want - ex;
+        }
+        ex += count[q];
+    }
+    __syncthreads();
+    const uint32_t per_block = 1u << (v.block_shift - 10);           // segments: at most 1024
+    const uint32_t s0 = lds.bcast[0] * per_block, n_segs = min(per_block, nseg - s0);
+    want = lds.bcast[1];
+    __syncthreads();
+    if (n_segs > 1) {                             // uniform: a wavefront per segment counts
+        for (uint32_t i = wave; i < n_segs; i += kRowThreads / kWave) {
+            const u32x2 run = srow[s0 + i];
+            uint32_t k[kSeg / kWave];
+            uint32_t n = 0;
+#pragma unroll
+            for (int q = 0; q < kSeg / kWave; ++q) {
+                const uint32_t j = (uint32_t)q * kWave + lane;
+                k[q] = j < run.y ? v.list[run.x + j].x : 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int q = 0; q < kSeg / kWave; ++q) n += (uint32_t)__popcll(__ballot(k[q] == key));
+            if (lane == 0) lds.hist[i] = n;
+        }
+        __syncthreads();
+        const uint32_t mine = t < n_segs ? lds.hist[t] : 0u;
+        ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
+        if (ex < want && want <= ex + mine) {
+            lds.bcast[0] = t;
+            lds.bcast[1] = want - ex;
+        }
+        __syncthreads();
+        want = lds.bcast[1];
+    } else if (t == 0) {
+        lds.bcast[0] = 0;
+    }
+    __syncthreads();
+    const u32x2 run = srow[s0 + lds.bcast[0]];
+    __syncthreads();
+    const u32x2 none = {0u, 0u};
+    const u32x2 c = t < run.y ? v.list[run.x + t] : none;
+    const bool tie = t < run.y && c.x == key;
+    ex = block_excl_scan<kRowThreads>(tie ? 1u : 0u, lds.scan, total);
+    if (tie && ex == want - 1) lds.bcast[0] = c.y;
+    __syncthreads();
+    const uint32_t cut = lds.bcast[0];
+    __syncthreads();
+    return cut;
+}
+
+// How list_split ends: with the histogram taken here by the list's only workgroup; by the last of the list's
+// workgroups; or not at all -- the next launch ranks the members and acts on them.
+enum class SplitEnd { Alone, Last, Later };
+
+// Workgroup `part` of `parts` of a list.  act(c, taken): the marked ones of a batch of kListUnroll entries per
+// thread are among the `want` largest; every one of these is marked in exactly one call, by one workgroup.  A
+// wavefront calls it for the batches in which it has marked ones; it must hold no barrier.
+// Returns true to all threads of the one workgroup that finished the list, with kth / tie_cut (the membership
+// test is is_taken).  SplitEnd::Later: false to all, with `rest`.
+template <SplitEnd END, typename Lds, typename Act>
+__device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uint32_t parts, Lds& lds, Act act,
+                                           uint32_t& kth, uint32_t& tie_cut, ListRest& rest)
+{
+    constexpr bool ALONE = END == SplitEnd::Alone, LATER = END == SplitEnd::Later;
     const uint32_t t = threadIdx.x, lane = lane_id();
     const u32x2 none = {0u, 0xFFFFFFFFu};
     u32x2 c[kListUnroll];
@@ -1227,13 +1418,14 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
         lds.hist[t] = v.hist[t];
     }
     __syncthreads();
-    uint32_t bin, want, in_bin;
-    find_rank_bin<kListBins>(lds.hist, lds.scan, lds.bcast, v.want, bin, want, in_bin);
+    find_rank_bin<kListBins>(lds.hist, lds.scan, lds.bcast, v.want, rest.bin, rest.want, rest.n);
     // Space in the second list is reserved once per workgroup, or per workgroup and batch when the members are many:
     // reservations of one list follow each other at the memory side, about 9 ns apart (once per wavefront
     // instead, random selection took 452 us at 16 x 11.2 M, K = 11,174, for 441 so, and at 3 x 10 M, K = 150,000,
     // 207 for 169).
-    const bool few = in_bin <= Lds::kMost;        // uniform
+    const bool few = rest.n <= Lds::kMost;        // uniform
+    BigGroup<Lds> group = {lds};
+    if (LATER && !few) group.clear();             // (a barrier follows before the first add)
     for (uint64_t i0 = first; i0 < v.n; i0 += (uint64_t)parts * kListBatch) {
         if (i0 != first) load(i0);
         uint32_t above = 0, member = 0;
@@ -1241,8 +1433,8 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
         for (int u = 0; u < kListUnroll; ++u) {
             const uint32_t b = list_bin(v, c[u].x);
             const bool there = c[u].y != 0xFFFFFFFFu;
-            above |= (there && b > bin ? 1u : 0u) << u;
-            member |= (there && b == bin ? 1u : 0u) << u;
+            above |= (there && b > rest.bin ? 1u : 0u) << u;
+            member |= (there && b == rest.bin ? 1u : 0u) << u;
         }
         if (ALONE || few) {
             // (few members in the whole list: they all fit; in a list alone, as many as fit)
@@ -1255,13 +1447,16 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
                     lds.at[0][p] = c[u].y;
                 }
             }
-            act(c, above);
+            if (__ballot(above != 0u) != 0ull) act(c, above);        // wave-uniform
         } else {
             uint32_t total;
             uint32_t p = block_excl_scan<kRowThreads>((uint32_t)__popc(member), lds.scan, total);
             uint32_t base = 0;
             if (t == 0 && total != 0u) base = atomicAdd(v.count2, total);
-            act(c, above);
+            if (__ballot(above != 0u) != 0ull) act(c, above);        // wave-uniform
+            if (LATER)
+#pragma unroll
+                for (int u = 0; u < kListUnroll; ++u) group.add(v, c[u], member >> u & 1u);
             if (t == 0) lds.n_list = base;
             __syncthreads();
             p += lds.n_list;
@@ -1285,57 +1480,44 @@ __device__ __forceinline__ bool list_split(const ListView& v, uint32_t part, uin
             if (to < v.room) store_past_caches(v.list2 + (int64_t)to * v.step2, m);
         }
     }
-    const uint32_t n_members = in_bin;            // (the histogram counts what the list holds)
-    // members that the second list has no room for are found in the first one again
-    const bool stored = !ALONE && n_members <= v.room;
-    auto member_at = [&](uint64_t i) { return load_past_caches(v.list2 + (int64_t)i * v.step2); };
-    if (!ALONE) {
-        // every store and atomic of this workgroup has been performed before it is counted as done
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (t == 0) lds.last = atomicAdd(v.done, 1u) == parts - 1u;
-        __syncthreads();
-        if (!lds.last) return false;
-        for (uint32_t p = t; stored && p < n_members && p < Lds::kMost; p += kRowThreads) {
-            const u32x2 m = member_at(p);
-            lds.key[0][p] = m.x;
-            lds.at[0][p] = m.y;
-        }
-        // what the next step must find at zero
-        v.hist[t] = 0;
-        if (t == 0) {
-            *v.count2 = 0;
-            *v.done = 0;
-        }
+    if (LATER) {
+        if (!few && first < v.n) group.merge(v);
+        return false;
     }
+    if (ALONE) {
+        __syncthreads();
+        uint32_t lo, bits;
+        list_bin_range(v, rest.bin, lo, bits);
+        ListView again = v;                       // more members than LDS holds are found in the list again
+        again.room = 0;
+        if (rest.n <= Lds::kMost) rank_members(lds, rest.n, rest.want, lo, bits, kth, tie_cut);   // uniform
+        else                      rank_rest<false>(again, rest, lds, kth, tie_cut);
+        act_on_rest<false>(again, rest, kth, tie_cut, 0, 1, act);
+        return true;
+    }
+    // every store and atomic of this workgroup has been performed before it is counted as done
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    uint32_t lo, bits;
-    list_bin_range(v, bin, lo, bits);
-    if (n_members <= Lds::kMost && (ALONE || stored))   // uniform
-        rank_members(lds, n_members, want, lo, bits, kth, tie_cut);
-    else if (!stored)
-        rank_in_memory(lds,
-                       [&](uint64_t i) {          // what is no member gets a key outside every range
-                           u32x2 m = v.list[i];
-                           if (list_bin(v, m.x) != bin) m.x = 0xFFFFFFFFu;
-                           return m;
-                       },
-                       v.n, n_members, want, lo, bits, kth, tie_cut);
-    else
-        rank_in_memory(lds, member_at, n_members, n_members, want, lo, bits, kth, tie_cut);
-    // the members that are taken
-    const uint32_t n = stored ? n_members : v.n;
-    for (uint64_t i0 = 0; i0 < n; i0 += kListBatch) {
-        uint32_t taken = 0;
-#pragma unroll
-        for (int u = 0; u < kListUnroll; ++u) {
-            const uint64_t i = i0 + (uint32_t)u * kRowThreads + t;
-            c[u] = i < n ? (stored ? member_at(i) : v.list[i]) : none;
-            const bool mine = i < n && (stored || list_bin(v, c[u].x) == bin);
-            taken |= (mine && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
-        }
-        act(c, taken);
+    if (t == 0) lds.last = atomicAdd(v.done, 1u) == parts - 1u;
+    __syncthreads();
+    if (!lds.last) return false;
+    // what the next step must find at zero
+    v.hist[t] = 0;
+    if (t == 0) {
+        *v.count2 = 0;
+        *v.done = 0;
+    }
+    if (few) {                                    // uniform
+        rank_rest<true>(v, rest, lds, kth, tie_cut);
+        act_on_rest<true>(v, rest, kth, tie_cut, 0, 1, act);
+    } else {
+        // many members are read several times: with this unit's and its L2's copies dropped, plain loads find what
+        // was stored past the caches, and find it in the cache the next time (dropped by the last workgroup of
+        // every list, a step of 16 x 300,001, K = 30,000, K_ad = 3000 took 139 us instead of 118)
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        rank_rest<false>(v, rest, lds, kth, tie_cut);
+        act_on_rest<false>(v, rest, kth, tie_cut, 0, 1, act);
     }
     return true;
 }
@@ -1355,12 +1537,35 @@ __device__ __forceinline__ void lend_storage(ListView& v, uint32_t* __restrict__
     v.done = h + kCtlWords + (2 * which + 1) * kCounterStride;
     v.step2 = 1;
     v.room = v.n;
+    v.blocks = nullptr;
+    v.block_shift = 0;
 }
 static_assert(kListBins == kRowThreads, "a bin per thread");
 static_assert(kHistRow >= kCtlWords + 6 * kCounterStride, "three lists' storage fits a row's sample histogram");
 
+// A row's list as mv_sel_hist, mv_sel_split and mv_sel_finish see it.  2048 bins to an octave above the row's
+// threshold, beyond a quarter octave 32; without a threshold (nearly all of the row is wanted) 4 to an octave.
+__device__ __forceinline__ ListView row_list(u32x2* __restrict__ cand, uint32_t cap, uint32_t row, uint32_t n, uint32_t K,
+                                             uint32_t tau, uint32_t* __restrict__ sample_hist, uint32_t block_shift)
+{
+    ListView v;
+    v.list = cand + (size_t)row * cap;  v.n = n;
+    v.want = K;
+    v.base = tau;
+    v.fine = tau ? 12 : 21;
+    v.coarse = tau ? 18 : 21;
+    lend_storage(v, sample_hist, row, 0);
+    v.list2 = cand + (size_t)row * cap + (cap - 1);                 // the end of the row's storage, downwards
+    v.step2 = -1;
+    v.room = cap - v.n;
+    v.blocks = v.hist + kListBins;                // (the other two lists' storage: add-drop voting uses it later)
+    v.block_shift = block_shift;
+    return v;
+}
+static_assert(kCoordBlocks <= 2 * kListBins, "the blocks' counters fit two lists' histograms");
+
 __global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
-    const u32x2* __restrict__ cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ row_count_sets,
+    u32x2* __restrict__ cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ row_count_sets,
     uint32_t row_count_set_words, const uint32_t* __restrict__ step_no, const unsigned long long* __restrict__ tau_pub,
     const uint32_t* __restrict__ row_poison, uint32_t* __restrict__ sample_hist, uint32_t* __restrict__ cand_count,
     uint32_t* __restrict__ tau_bits, uint32_t* __restrict__ slow_flag)
@@ -1378,21 +1583,34 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
         slow_flag[row] = from_list ? 0u : 1u;
     }
     if (!from_list) return;                                          // whole workgroup
-    ListView v;
-    v.list = cand + (size_t)row * cap;  v.n = C;
-    v.want = K;
-    v.base = tau;  v.fine = 12;  v.coarse = 18;   // 2048 bins to an octave, beyond a quarter octave 32
-    lend_storage(v, sample_hist, row, 0);
-    list_hist(v, blockIdx.x, gridDim.x, hist);
+    list_hist(row_list(cand, cap, row, C, K, tau, sample_hist, 0), blockIdx.x, gridDim.x, hist);
 }
 
+// Votes for the marked entries of a batch; with thresholds_only (add-drop voting) none are cast.
+struct CastVotes {
+    uint32_t *votes32, *lvl, *ssel;
+    int thresholds_only;
+    __device__ __forceinline__ void operator()(const u32x2 (&c)[kListUnroll], uint32_t taken) const
+    {
+        if (!thresholds_only) cast_votes<kListUnroll, true>(c, taken, votes32, lvl, ssel);
+    }
+};
+
+// What mv_sel_split leaves of a row to mv_sel_finish: behind the row's published threshold, on the line it has
+// to itself.
+__device__ __forceinline__ uint32_t* row_rest(unsigned long long* tau_pub, uint32_t row)
+{
+    return reinterpret_cast<uint32_t*>(tau_pub + row * (kCounterStride / 2) + 1);
+}
+
+// The members of the K-th's bin are left to mv_sel_finish.
 __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     const float* __restrict__ e, int64_t ld_e, int64_t d, u32x2* cand, uint32_t cap, uint32_t K,
     const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist,
     uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
     uint32_t* __restrict__ votes32, uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
-    int thresholds_only)
+    int thresholds_only, unsigned long long* __restrict__ tau_pub, uint32_t block_shift)
 {
     __shared__ SplitLds<kMembers> lds;
     const uint32_t row = blockIdx.y, t = threadIdx.x;
@@ -1402,31 +1620,112 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
                                    votes32, lvl_sets, kth_out + row, tie_cut_out + row, thresholds_only);
         return;
     }
-    ListView v;
-    v.list = cand + (size_t)row * cap;  v.n = cand_count[row];
-    v.want = K;
-    v.base = tau_bits[row];  v.fine = 12;  v.coarse = 18;   // as in mv_sel_hist
-    lend_storage(v, sample_hist, row, 0);
-    v.list2 = cand + (size_t)row * cap + (cap - 1);                 // the end of the row's storage, downwards
-    v.step2 = -1;
-    v.room = cap - v.n;
+    const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift);
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
-    uint32_t* ssel = seg_sel ? seg_sel + (size_t)row * nseg : nullptr;
+    const CastVotes act = {votes32, lds.lvl, seg_sel ? seg_sel + (size_t)row * nseg : nullptr, thresholds_only};
     uint32_t kth, tie_cut;
-    const bool finished = list_split<false>(v, blockIdx.x, gridDim.x, lds,
-                                            [&](const u32x2 (&c)[kListUnroll], uint32_t taken) {
-                                                if (!thresholds_only)
-                                                    cast_votes<kListUnroll, true>(c, taken, votes32, lds.lvl, ssel);
-                                            },
-                                            kth, tie_cut);
-    if (finished && t == 0) {
-        kth_out[row] = kth;
-        tie_cut_out[row] = tie_cut;
+    ListRest rest;
+    (void)list_split<SplitEnd::Later>(v, blockIdx.x, gridDim.x, lds, act, kth, tie_cut, rest);
+    if (blockIdx.x == 0 && t == 0) {
+        uint32_t* r = row_rest(tau_pub, row);
+        r[0] = rest.bin;
+        r[1] = rest.want;
+        r[2] = rest.n;
     }
     if (!thresholds_only) {
         __syncthreads();
         merge_levels(lds.lvl, lvl_sets, blockIdx.y * gridDim.x + blockIdx.x);
     }
+}
+
+// The end of the rows' select: grid (parts, rows).  Every workgroup of a row ranks the members -- the work
+// is repeated rather than shared so that no workgroup waits for another -- and casts the votes of its share.
+__global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
+    u32x2* cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
+    const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist, uint32_t* __restrict__ kth_out,
+    uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ votes32, uint32_t* __restrict__ seg_sel, uint32_t nseg,
+    uint32_t* __restrict__ lvl_sets, int thresholds_only, unsigned long long* __restrict__ tau_pub,
+    const u32x2* __restrict__ seg, uint32_t block_shift)
+{
+    __shared__ SplitLds<kMembers> lds;
+    const uint32_t row = blockIdx.y, t = threadIdx.x;
+    if (slow_flag[row] == 1u) return;
+    const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift);
+    const uint32_t* left = row_rest(tau_pub, row);
+    const ListRest rest = {left[0], left[1], left[2]};
+    const uint32_t share = members_stored(v, rest) ? rest.n : v.n;
+    if (blockIdx.x != 0 && blockIdx.x * (uint32_t)kListBatch >= share) return;      // nothing to act on
+    if (blockIdx.x == 0) {                        // what the next step must find at zero
+        v.hist[t] = 0;
+        if (t == 0) *v.count2 = 0;
+    }
+    for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
+    const CastVotes act = {votes32, lds.lvl, seg_sel ? seg_sel + (size_t)row * nseg : nullptr, thresholds_only};
+    uint32_t kth, tie_cut;
+    if (rest.n <= (uint32_t)kMembers && members_stored(v, rest)) {   // uniform; usual: this is the row's only workgroup
+        static_assert(kMembers <= kListBatch, "a batch holds them");
+        u32x2 c[kListUnroll];
+        const u32x2 none = {0u, 0xFFFFFFFFu};
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint32_t i = (uint32_t)u * kRowThreads + t;
+            c[u] = i < rest.n ? member_at<false>(v, i) : none;
+        }
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u)
+            if (c[u].y != 0xFFFFFFFFu) {
+                lds.key[0][u * kRowThreads + t] = c[u].x;
+                lds.at[0][u * kRowThreads + t] = c[u].y;
+            }
+        __syncthreads();
+        uint32_t lo, bits;
+        list_bin_range(v, rest.bin, lo, bits);
+        rank_members(lds, rest.n, rest.want, lo, bits, kth, tie_cut);
+        if (t == 0) {
+            kth_out[row] = kth;
+            tie_cut_out[row] = tie_cut;
+        }
+        if (thresholds_only) return;
+        uint32_t taken = 0;
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u)
+            taken |= (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
+        if (__ballot(taken != 0u) != 0ull) act(c, taken);            // wave-uniform
+        __syncthreads();
+        merge_levels(lds.lvl, lvl_sets, row);
+        return;
+    }
+    bool ranked = false;
+    if (rest.n > (uint32_t)kMembers) {            // uniform: a big group
+        const uint32_t count[2] = {v.blocks[2 * t], v.blocks[2 * t + 1]};
+        const uint32_t largest = v.count2[1], smallest = ~v.count2[2];
+        // these values are there before the workgroup is counted
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (t == 0) lds.last = atomicAdd(v.done, 1u) + 1u == min(gridDim.x, (share + kListBatch - 1) / kListBatch);
+        __syncthreads();
+        if (lds.last) {                           // every workgroup of the row has read them
+            v.blocks[2 * t] = 0;
+            v.blocks[2 * t + 1] = 0;
+            if (t < 2) v.count2[1 + t] = 0;
+            if (t == 0) *v.done = 0;
+        }
+        if (largest == smallest && rest.want < rest.n) {
+            kth = largest;
+            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, seg + (size_t)row * nseg, nseg, lds);
+            ranked = true;
+        }
+    }
+    if (!ranked) rank_rest<false>(v, rest, lds, kth, tie_cut);
+    if (blockIdx.x == 0 && t == 0) {
+        kth_out[row] = kth;
+        tie_cut_out[row] = tie_cut;
+    }
+    if (thresholds_only) return;
+    act_on_rest<false>(v, rest, kth, tie_cut, blockIdx.x, gridDim.x, act);
+    __syncthreads();
+    merge_levels(lds.lvl, lvl_sets, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 }  // namespace mvk

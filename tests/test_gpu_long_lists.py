@@ -94,6 +94,82 @@ def test_random_selection_around_one_workgroups_list(oracle, N, K, votes):
             assert_matches_oracle(gs.fetch(), oracle.rs_vote_step(g, e, K, r), "N=%d K=%d" % (N, K))
 
 
+def tied_values(rng, kind, N, d):
+    if kind == "equal":              # one magnitude: the candidate list is the row, with no room behind it
+        g = np.where(rng.random((N, d)) < 0.5, -2.5, 2.5)
+    elif kind == "lattice":
+        g = np.round(rng.standard_normal((N, d)) * 6.0) / 64.0
+    elif kind == "zeros":            # the boundary lies among zeros
+        g = np.where(rng.random((N, d)) < 0.05, rng.standard_normal((N, d)), 0.0)
+    elif kind == "one_bin":          # thousands of different keys within one bin, many of them several times
+        g = 1.0 + rng.integers(0, 3000, (N, d)) * 2.0 ** -23
+    else:                            # "two_bins": a tie group in a wide bin far above the estimate's, beside another key
+        g = np.where(rng.random((N, d)) < 0.3, 8.0 + np.round(rng.random((N, d))) * 2.0 ** -8,
+                     rng.standard_normal((N, d)) * 1e-2)
+    return g.astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ["equal", "lattice", "zeros", "one_bin", "two_bins"])
+@pytest.mark.parametrize("N,d,K", [(3, 200003, 40000), (3, 200003, 150002), (2, 200003, 200002), (2, 200003, 200003),
+                                   (2, 60001, 57000), (2, 2500003, 500000), (2, 2097153, 1900000)])
+def test_large_tie_groups(oracle, kind, N, d, K):
+    """Tie groups far larger than what is ranked in on-chip memory, with room for them behind the list and without, in
+    rows whose blocks of coordinates have one segment and two; several steps of one context."""
+    print("[case] large tie groups %s N=%d d=%d K=%d" % (kind, N, d, K), flush=True)
+    rng = np.random.default_rng(sum(map(ord, kind)) + K)
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        gs.set_error(e)
+        for t in range(3):
+            g = tied_values(rng, kind, N, d)
+            gs.set_grads(g)
+            if t != 1:
+                gs.step()
+                ref = oracle.vote_step(g, e, K, threads=8)
+            else:
+                r = rng.standard_exponential(d).astype(np.float32)
+                gs.step_rs(r)
+                ref = oracle.rs_vote_step(g, e, K, r, threads=8)
+            assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (kind, t))
+            e = ref.err
+    gs = GpuAdStepper(N, d, K, K)
+    try:
+        vote, msum, e = np.zeros((N, d), np.uint8), np.zeros(d, np.uint8), np.zeros((N, d), np.float32)
+        for t, k_ad in enumerate([K, K // 3, 100]):
+            g = tied_values(rng, kind, N, d)
+            ref = oracle.ad_vote_step(g, e, K, k_ad, vote, msum, threads=8)
+            gs.step(g, k_ad)
+            gs.compare(ref, "%s add-drop step %d k_ad %d" % (kind, t, k_ad))
+            vote, msum, e = ref.vote, ref.msum, ref.err
+    finally:
+        gs.close()
+
+
+def test_large_tie_groups_are_not_left_to_one_workgroup():
+    """A row of equal magnitudes costs about what an ordinary row does: its tie group is neither ranked nor voted for
+    by one workgroup member by member (which took 50 times as long)."""
+    N, d, K = 2, 1000003, 500001
+    print("[case] time of large tie groups N=%d d=%d K=%d" % (N, d, K), flush=True)
+
+    def milliseconds(kind):
+        best = 1e9
+        with GpuStepper(N, d, K) as gs:
+            gs.set_grads(np.random.default_rng(1).standard_normal((N, d)) if kind == "normal" else np.full((N, d), 2.5))
+            for _ in range(6):
+                gs.set_error(np.zeros((N, d), np.float32))
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                gs.step()
+                end.record()
+                torch.cuda.synchronize()
+                best = min(best, start.elapsed_time(end))
+        return best
+
+    ordinary, equal = milliseconds("normal"), milliseconds("equal")
+    print("  ordinary %.3f ms, equal %.3f ms" % (ordinary, equal), flush=True)
+    assert equal < 8 * ordinary
+
+
 @pytest.mark.parametrize("m", [3071, 3072, 3073, 8191, 8192, 8193])
 def test_groups_around_what_fits_on_chip(oracle, m):
     """The boundary lies in a group of m equal magnitudes (m equal times): 3072 members of a bin are kept in LDS in the
