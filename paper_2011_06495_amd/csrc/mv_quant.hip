@@ -17,10 +17,10 @@
 //
 // Encoding is latency, not bandwidth (a row of 111,740 values is 447 KB): what counts is
 // how many compute units share a row and how long the dependent chain is.  Rows of up to
-// kTile values are done whole by one workgroup in one launch; longer rows are cut into
-// tiles of kTile values over up to kMaxBlocks workgroups, in three launches: the blocks'
-// largest and smallest magnitudes; codes and the blocks' sums per interval; the means.
-// 10 rows of 111,740 values, q = 4: 188 us with one workgroup per row, 14.6 us so (3.8 + 6.8 + 2.7
+// kTile values, and of up to row_most(q), are done whole by one workgroup in one launch; longer
+// rows are cut into tiles of kTile values over up to kMaxBlocks workgroups, in three launches: the
+// blocks' largest and smallest magnitudes; codes and the blocks' sums per interval; the means.
+// 10 rows of 111,740 values, q = 4: 188 us with one workgroup per row, 12.6 us so (3.8 + 6.8 + 2.7
 // us in the kernels).
 #include "../../include/mv.h"
 
@@ -45,6 +45,13 @@ __host__ __device__ constexpr int group_size(int q)
 // Wavefronts per workgroup of quant_codes_kernel: every wavefront has a table of L x 64 sums
 // (8 bytes) and counts (4 bytes) in LDS, 96 KB of tables at most.
 constexpr int code_waves(int q) { return q <= 6 ? 4 : q == 7 ? 2 : 1; }
+
+// The values of a row that one workgroup of kRowWaves wavefronts takes whole.  The three launches take 12 us however
+// short the row is: 10 rows of 2049 values, q = 2, 3, 4: 12.8, 12.5, 13.3 us, so 5.3, 5.9, 5.5; of 8192 values 12.9, 13.2,
+// 12.9, so 5.8, 7.0, 6.9; of 16,384, q = 2, 3: 12.9, 12.7, so 7.3, 8.7.  With more intervals the tables of so many
+// wavefronts would not fit.
+constexpr int kRowWaves = 16;
+__host__ __device__ constexpr int row_most(int q) { return q <= 3 ? 16384 : q == 4 ? 8192 : 0; }
 
 struct Range {                      // of the non-zero magnitudes, as bit patterns (same order as the values)
     uint32_t vmax, vmin;            // 0 and 0xFFFFFFFF: none
@@ -104,17 +111,20 @@ __global__ __launch_bounds__(kRangeThreads) void quant_range_kernel(const float*
 //  * A lane adds its magnitudes to sums of its own, table[interval][lane] of its wavefront: every
 //    sum is formed in one order whatever the timing, and equal intervals do not queue up.
 //  * Codes go through LDS bytes, so that loads are coalesced and a thread packs whole words.
-// ALONE: the workgroup has the whole row (n <= kTile): range, codes and means in this one launch.
+// Alone and Row: the workgroup has the whole row: range, codes and means in this one launch.
 // Bound by its dependent chain: q - 1 square roots and L divisions in fp64 before the first code
 // (about 1 us at q = 4), LDS round trips behind it.
-template <int q, bool ALONE>
-__global__ __launch_bounds__(64 * code_waves(q)) void quant_codes_kernel(
+enum class Work { Tiles, Alone, Row };           // many workgroups to a row; rows of up to kTile; of up to row_most(q)
+template <int q, Work WORK>
+__global__ __launch_bounds__(64 * (WORK == Work::Row ? kRowWaves : code_waves(q))) void quant_codes_kernel(
     const float* __restrict__ vals, int64_t ld_vals, int64_t n, uint32_t* __restrict__ streams, int64_t ld_words,
     const Range* __restrict__ ranges, double* __restrict__ partial, uint32_t* __restrict__ pcount,
     float* __restrict__ means)
 {
     constexpr int L = 1 << (q - 1);
-    constexpr int kWaves = code_waves(q), kThreads = 64 * kWaves;
+    constexpr bool ALONE = WORK != Work::Tiles;
+    constexpr int kWaves = WORK == Work::Row ? kRowWaves : code_waves(q), kThreads = 64 * kWaves;
+    constexpr int kTile = WORK == Work::Row ? row_most(q) : mvq::kTile;
     constexpr int kPer = kTile / kThreads;
     __shared__ double   sums[kWaves * L * 64];
     __shared__ uint32_t count[kWaves * L * 64];
@@ -181,6 +191,7 @@ __global__ __launch_bounds__(64 * code_waves(q)) void quant_codes_kernel(
     for (;;) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
+            if (WORK == Work::Row && k0 + i * kThreads >= n) break;            // uniform
             const bool live = k0 + i * kThreads + t < n;
             const double m = (double)fabsf(x[i]);
             uint32_t l = 0;                       // interval - 1 = #{ j in 1 .. L-1 : m <= edges[j] }
@@ -312,7 +323,8 @@ mv_status mv_quant_encode(const float* vals, int64_t ld_vals, int64_t n, int32_t
     if (scratch_bytes < mv_quant_scratch_bytes(n, rows, q)) return MV_ERR_INVALID_ARG;
     const int L = 1 << (q - 1);
     const int64_t tiles = (n + mvq::kTile - 1) / mvq::kTile;
-    const uint32_t blocks = (uint32_t)(tiles < mvq::kMaxBlocks ? tiles : mvq::kMaxBlocks);
+    const bool row_alone = n > mvq::kTile && n <= mvq::row_most(q);
+    const uint32_t blocks = row_alone ? 1u : (uint32_t)(tiles < mvq::kMaxBlocks ? tiles : mvq::kMaxBlocks);
     // Per row and block L sums, L counts and a range, 12 L + 8 bytes: b > 1 blocks have more than
     // 64 (b - 1) >= 2 b packing groups (of at most 32 values), for each of which mv_quant_scratch_bytes counts 12 L.
     static_assert(mvq::kTile >= 64 * 32, "the blocks' records fit the scratch");
@@ -325,22 +337,28 @@ mv_status mv_quant_encode(const float* vals, int64_t ld_vals, int64_t n, int32_t
     const dim3 grid(blocks, (uint32_t)rows);
     if (blocks > 1)
         hipLaunchKernelGGL(mvq::quant_range_kernel, grid, dim3(mvq::kRangeThreads), 0, st, vals, ld_vals, n, ranges);
-#define MV_QUANT_LAUNCH(Q)                                                                                        \
-    case Q:                                                                                                       \
-        if (blocks > 1)                                                                                           \
-            hipLaunchKernelGGL((mvq::quant_codes_kernel<Q, false>), grid, dim3(64 * mvq::code_waves(Q)), 0, st,   \
-                               vals, ld_vals, n, streams, ld_words, (const mvq::Range*)ranges, partial, pcount, means); \
-        else                                                                                                      \
-            hipLaunchKernelGGL((mvq::quant_codes_kernel<Q, true>), grid, dim3(64 * mvq::code_waves(Q)), 0, st,    \
-                               vals, ld_vals, n, streams, ld_words, (const mvq::Range*)nullptr, (double*)nullptr, \
-                               (uint32_t*)nullptr, means);                                                        \
+#define MV_QUANT_KERNEL(Q, W, THREADS)                                                                             \
+    hipLaunchKernelGGL((mvq::quant_codes_kernel<Q, mvq::Work::W>), grid, dim3(THREADS), 0, st, vals, ld_vals, n,   \
+                       streams, ld_words, (const mvq::Range*)ranges, partial, pcount, means)
+#define MV_QUANT_LAUNCH(Q)                                                                                         \
+    case Q:                                                                                                        \
+        if (blocks > 1) MV_QUANT_KERNEL(Q, Tiles, 64 * mvq::code_waves(Q));                                        \
+        else MV_QUANT_KERNEL(Q, Alone, 64 * mvq::code_waves(Q));                                                   \
+        break;
+#define MV_QUANT_LAUNCH_ROW(Q)                                                                                     \
+    case Q:                                                                                                        \
+        if (row_alone) MV_QUANT_KERNEL(Q, Row, 64 * mvq::kRowWaves);                                               \
+        else if (blocks > 1) MV_QUANT_KERNEL(Q, Tiles, 64 * mvq::code_waves(Q));                                   \
+        else MV_QUANT_KERNEL(Q, Alone, 64 * mvq::code_waves(Q));                                                   \
         break;
     switch (q) {
-        MV_QUANT_LAUNCH(2) MV_QUANT_LAUNCH(3) MV_QUANT_LAUNCH(4) MV_QUANT_LAUNCH(5)
+        MV_QUANT_LAUNCH_ROW(2) MV_QUANT_LAUNCH_ROW(3) MV_QUANT_LAUNCH_ROW(4) MV_QUANT_LAUNCH(5)
         MV_QUANT_LAUNCH(6) MV_QUANT_LAUNCH(7) MV_QUANT_LAUNCH(8)
         default: return MV_ERR_INVALID_ARG;
     }
+#undef MV_QUANT_LAUNCH_ROW
 #undef MV_QUANT_LAUNCH
+#undef MV_QUANT_KERNEL
     if (blocks > 1)
         hipLaunchKernelGGL(mvq::quant_means_kernel, dim3((uint32_t)rows), dim3(mvq::kMeanThreads), 0, st,
                            (const double*)partial, (const uint32_t*)pcount, blocks, L, means);

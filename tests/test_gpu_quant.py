@@ -74,6 +74,20 @@ def test_quant_tiles(oracle, q, n, rows):
     gpu_quant(oracle, vals, q)
 
 
+@pytest.mark.parametrize("q,n,rows", [(2, 2049, 3), (3, 3071, 2), (4, 4097, 2), (4, 8191, 2), (4, 8192, 1), (4, 8193, 2),
+                                      (2, 16383, 1), (2, 16384, 2), (3, 16384, 2), (2, 16385, 2), (3, 16385, 1),
+                                      (5, 8192, 2)])
+def test_quant_rows_of_one_workgroup(oracle, q, n, rows):
+    """Rows longer than a tile that one workgroup takes whole at few bits: both sides of where that ends, and values
+    of the rows' last threads."""
+    say("quant rows of one workgroup q=%d n=%d rows=%d" % (q, n, rows))
+    rng = np.random.default_rng(q * 1000 + n)
+    vals = (rng.standard_normal((rows, n)) * np.exp(rng.standard_normal((rows, n)))).astype(np.float32)
+    vals[:, ::509] = 0.0
+    vals[0, n - 1], vals[0, n - 2] = 1e30, -1e-30
+    gpu_quant(oracle, vals, q)
+
+
 def test_quant_degenerate_rows(oracle):
     say("quant degenerate")
     n = 300
