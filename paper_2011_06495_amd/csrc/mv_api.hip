@@ -42,7 +42,6 @@ const char* const kKernelNames[KID_COUNT] = {
     "mv_rs_pick",        "mv_small_rows", "mv_small_mask"};
 
 constexpr size_t kAlign = 256;
-constexpr int64_t kOneSamplerD = 1 << 20;   // see make_plan
 constexpr int kEventRing = 64;   // steps whose kernel durations stay readable
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -119,19 +118,24 @@ Plan make_plan(const mv_config* c)
         const double root_m = 3.5 + sqrt(12.25 + (double)p.K * frac), m = ceil(root_m * root_m);
         return m < 128.0 ? 128.0 : m;
     };
+    // list entries to be ready for when so many are expected
+    auto with_room = [](double expected) { return expected * 1.25 + 1.0; };
     // Sample about d/128 coordinates of each row, at least 32K, by up to 16 workgroups (kSampleQuads quads per
-    // thread and round) -- or, in short rows, 8K by ONE workgroup in one round, whose histogram need not be merged in
-    // memory: the step of a short row waits for the estimate.  The list is longer for it; the line is where that
-    // begins to cost more than the wait (one round against 32K samples: 16 x 100,003, K = 1000: 35.6 against
-    // 40.3 us, 4 x 2^20, K = 10,486: 48.9 against 51.7; but 16 x 2^20, K = 17,000, a list of 31K entries for 23K:
-    // 87.8 against 86.5, and K = 270, 16K entries for 4K: 86 against 67; two rounds of one workgroup lie between).
+    // thread and round) -- or, where the list does not grow too long for it, 8K by ONE workgroup in one round, whose
+    // histogram need not be merged in memory: the step of a short row waits for the estimate.  The line follows the
+    // lists, one workgroup's against several's (steps of 2, 4 and 16 rows, time with several : time with one):
+    //   up to 8192 entries, whatever the others':   2.7K for 0.9K 1.04 1.04 1.02; 6.3K for 1.6K 1.04 1.04 0.99;
+    //                        beyond it, at four times theirs:   14K for 3.5K 0.92 0.90 0.93
+    //   up to half as long again, as far as mv_row_select serves them: 20K for 13K 1.05 1.03 1.02; 25K for 17K 1.07 1.03
+    //                        1.02; beyond, where several workgroups have to select: 27K for 20K 1.08 1.02 1.04, but
+    //                        with 40 rows and add-drop voting 0.90
     const uint64_t nchunks = (uint64_t)(p.d + mvk::kChunk - 1) / mvk::kChunk;
     const uint64_t per_round = (uint64_t)mvk::kSampleQuads * mvk::kStreamThreads;      // quads
     const uint64_t want = (uint64_t)p.d / 128 > 32768 ? (uint64_t)p.d / 128 : 32768;
     const double one = 4.0 * (double)per_round / (double)p.d, many = (double)want / (double)p.d;   // fractions
     const double list_one = sampled_above(one) / one, list_many = sampled_above(many) / many;
     uint64_t stride;
-    if (p.d <= kOneSamplerD && (list_one <= 8192.0 || (list_one <= 1.5 * list_many && list_one <= 24576.0))) {
+    if (list_one <= 8192.0 || (list_one <= 1.5 * list_many && with_room(list_one) <= (double)mvk::kKeepMost * mvk::kRowThreads)) {
         const uint64_t chunks = per_round / (mvk::kChunk / 4);
         stride = (nchunks + chunks - 1) / chunks;
         p.sample_wgs = 1;
@@ -179,7 +183,7 @@ Plan make_plan(const mv_config* c)
     {
         // about 2K candidates are expected; fetch 3K per row ahead (never beyond the list's storage),
         // and give every workgroup of a row about four list entries per thread to cast votes for
-        const uint64_t expect = (uint64_t)((double)p.m_target / frac * 1.25) + 1;   // candidates per row, with room
+        const uint64_t expect = (uint64_t)with_room((double)p.m_target / frac);      // candidates per row
         uint64_t slots = (expect + mvk::kRowThreads - 1) / mvk::kRowThreads;        // list entries per thread
         const uint64_t in_cap = ((uint64_t)p.cap + mvk::kRowThreads - 1) / mvk::kRowThreads;
         if (slots > in_cap) slots = in_cap;

@@ -135,3 +135,22 @@ def test_rows_sampled_by_one_workgroup(oracle, kind, N, d, K):
             ref = oracle.vote_step(g, e, K, threads=8)
             assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (kind, t))
             e = ref.err
+
+
+@pytest.mark.parametrize("kind", ["normal", "lattice"])
+@pytest.mark.parametrize("N,d,K", [(3, 1150003, 11500), (2, 1200007, 12000), (2, 1200007, 13500), (2, 1200007, 6000)])
+def test_longer_rows_sampled_by_one_workgroup(oracle, kind, N, d, K):
+    """Rows beyond 2^20 coordinates whose lists are short enough for one sampling workgroup, and such whose are not:
+    too long, and too long against what several sampling workgroups would give."""
+    print("[case] longer rows, one sampling workgroup N=%d d=%d K=%d %s" % (N, d, K, kind), flush=True)
+    rng = np.random.default_rng(d + K)
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        gs.set_error(e)
+        for t in range(2):
+            g = values(rng, kind, N, d)
+            gs.set_grads(g)
+            gs.step()
+            ref = oracle.vote_step(g, e, K, threads=8)
+            assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (kind, t))
+            e = ref.err
