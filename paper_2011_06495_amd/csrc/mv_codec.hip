@@ -138,12 +138,16 @@ __global__ __launch_bounds__(kThreads) void codec_encode_kernel(
 // tile takes one launch and no scratch.  10 lists of 111,740 positions, B = 7: 140 us when one
 // workgroup per row composed all chunks, 15 us so (maps 6.2, emission 9.8).
 //
-// A map entry is exit state | codes begun << 8: 16 bits for a chunk (at most 64 codes), 32
-// for a group, a tile or a row's tiles.
+// A map entry is exit state | codes begun << kStateBits: 16 bits for a chunk (at most 64 codes), 32
+// for a group or a tile.  27 bits of codes hold a tile of any stream of up to 2^35 bits; more than 2^32
+// codes counts_out could not say.
 
-__device__ __forceinline__ uint32_t map_exit(uint32_t m) { return m & 255u; }
+constexpr int kStateBits = 5;
+static_assert(kMaxB < 1 << kStateBits, "a state fits its bits");
+__device__ __forceinline__ uint32_t map_exit(uint32_t m) { return m & ((1u << kStateBits) - 1u); }
+__device__ __forceinline__ uint32_t map_codes(uint32_t m) { return m >> kStateBits; }
 // entry `m` (state reached, codes so far) carried on through `next`, the map's value at that state
-__device__ __forceinline__ uint32_t carry(uint32_t m, uint32_t next) { return (m & ~255u) + next; }
+__device__ __forceinline__ uint32_t carry(uint32_t m, uint32_t next) { return m - map_exit(m) + next; }
 
 // stream words i, i + 1, i + 2 with the bits at or beyond `total` read as zero
 struct ChunkBits {
@@ -175,7 +179,7 @@ __device__ __forceinline__ void chunk_map(uint64_t bits, uint16_t* tab, uint32_t
 #pragma unroll
     for (int j = kChunkBits - 1; j >= 0; --j) {
         const uint32_t word = j >= 32 ? (uint32_t)(bits >> 32) : (uint32_t)bits;
-        f[j] = (word >> (j & 31)) & 1u ? f[j + 1 + B] + 256u : f[j + 1];
+        f[j] = (word >> (j & 31)) & 1u ? f[j + 1 + B] + (1u << kStateBits) : f[j + 1];
     }
 #pragma unroll
     for (int s = 0; s <= B; ++s) tab[s * pitch] = (uint16_t)f[s];
@@ -200,12 +204,12 @@ __device__ __forceinline__ void compose_groups(TileLds& lds, uint32_t n_chunks, 
 }
 
 struct WalkLds {
-    uint32_t group_entry[kGroups + 1];            // state | codes << 8, codes from the start of the run
+    uint32_t group_entry[kGroups + 1];            // as a map's entries: state, codes from the start of the run
     uint32_t chunk_entry[kTileChunks];
 };
 
 // Entries of the run's groups and chunks from `state`, the run's entry state; returns (to all) the run's
-// exit: state | codes << 8.  The maps must be in LDS, a barrier behind them.
+// exit, as a map's entry.  The maps must be in LDS, a barrier behind them.
 __device__ __forceinline__ uint32_t walk_run(const TileLds& lds, WalkLds& walk, uint32_t n_chunks, uint32_t state)
 {
     const uint32_t t = threadIdx.x;
@@ -309,10 +313,10 @@ __global__ __launch_bounds__(kThreads) void codec_maps_kernel(
             const uint32_t end = walk_run(lds, walk, n, 0);
             if (t < n) {
                 const uint32_t m = walk.chunk_entry[t];
-                emit_chunk(bits, (uint64_t)t * kChunkBits, map_exit(m), m >> 8, B, d, block_len,
+                emit_chunk(bits, (uint64_t)t * kChunkBits, map_exit(m), map_codes(m), B, d, block_len,
                            idx_out + (int64_t)row * ld_idx, max_n);
             }
-            if (t == 0) counts_out[row] = end >> 8;
+            if (t == 0) counts_out[row] = map_codes(end);
             return;
         }
         uint32_t* to = scratch.groups(row, run, n_states);
@@ -327,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void codec_maps_kernel(
 struct EmitLds {
     TileLds  tile;
     WalkLds  walk;
-    // 16 tiles composed: exit states, codes (which need not fit the 24 bits of a map entry)
+    // 16 tiles composed: exit states, codes (which need not fit the bits of a map entry)
     uint8_t  tg_exit[kMaxTiles / kTileGroup][kMaxB + 1];
     uint32_t tg_codes[kMaxTiles / kTileGroup][kMaxB + 1];
     uint32_t entry_state, entry_codes;
@@ -374,7 +378,7 @@ __global__ __launch_bounds__(kThreads) void codec_emit_kernel(
         uint32_t st = s, sum = 0;
         for (uint32_t k = g * kTileGroup; k < (g + 1) * kTileGroup; ++k) {
             const uint32_t m = tile_maps[k * n_states + st];
-            sum += m >> 8;
+            sum += map_codes(m);
             st = map_exit(m);
         }
         lds.tg_exit[g][s] = (uint8_t)st;
@@ -389,7 +393,7 @@ __global__ __launch_bounds__(kThreads) void codec_emit_kernel(
         }
         for (uint32_t k = n_tile_groups * kTileGroup; k < tile; ++k) {
             const uint32_t m = tile_maps[k * n_states + st];
-            sum += m >> 8;
+            sum += map_codes(m);
             st = map_exit(m);
         }
         lds.entry_state = st;
@@ -401,11 +405,11 @@ __global__ __launch_bounds__(kThreads) void codec_emit_kernel(
         const uint32_t end = walk_run(lds.tile, lds.walk, n, state);
         if (t < n) {
             const uint32_t m = lds.walk.chunk_entry[t];
-            emit_chunk(bits, (run * kTileChunks + t) * kChunkBits, map_exit(m), codes + (m >> 8), B, d, block_len,
+            emit_chunk(bits, (run * kTileChunks + t) * kChunkBits, map_exit(m), codes + map_codes(m), B, d, block_len,
                        idx_out + (int64_t)row * ld_idx, max_n);
         }
         state = map_exit(end);
-        codes += end >> 8;
+        codes += map_codes(end);
         if (++run >= n_runs) {
             if (t == 0) counts_out[row] = codes;
             return;

@@ -159,3 +159,21 @@ def test_codec_lengths_from_the_wire_are_clamped(oracle):
 
 
 GUARD_COUNTS = 8
+
+
+@pytest.mark.parametrize("pattern,codes,first", [(-1, 2**32 - 2, 0), (0x55555555, 2**31 - 1, 1)])
+def test_decode_streams_of_half_a_gigabyte(pattern, codes, first):
+    """A tile of the longest streams begins 2^24 codes when every bit is a flag (no offset bits, no block ever
+    closed: not what the encoder writes, but counted all the same), half as many in an ascending list."""
+    say("decode half a gigabyte, pattern %x" % (pattern & 0xFFFFFFFF))
+    dev, bits, max_n = torch.device("cuda:0"), 2**32 - 2, 4096
+    streams = torch.full((1, 2**27), pattern, dtype=torch.int32, device=dev)
+    n_bits = torch.full((1,), bits, dtype=torch.int64, device=dev)
+    out = torch.full((1, max_n + 8), -1, dtype=torch.int32, device=dev)
+    cnt = torch.zeros(1, dtype=torch.int32, device=dev)
+    scratch = torch.empty(B.mv_codec_scratch_bytes(bits, 1), dtype=torch.uint8, device=dev)
+    B.mv_codec_decode(streams, n_bits, bits, 2**31 - 1, 1, out, max_n, cnt, scratch)
+    torch.cuda.synchronize()
+    assert int(cnt.cpu().numpy().view(np.uint32)[0]) == codes
+    assert np.array_equal(out.cpu().numpy()[0, :max_n], first * np.arange(max_n))     # a 1 bit stays in block 0
+    assert np.all(out.cpu().numpy()[0, max_n:] == -1)
