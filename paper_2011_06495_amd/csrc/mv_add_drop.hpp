@@ -23,6 +23,11 @@ namespace mvk {
 // coordinate order into the sorted add / drop lists while the standing vote is
 // updated.
 
+// Threads of mv_ad_collect's workgroups: with 1024 a unit holds two, whose barriers leave it idle where rows and votes
+// are many (128 x 400,003, K = 33,333, K_ad = 3333: 472 us, with 512 threads 377); with 256 a
+// row's reservations are more (255 x 100,003, K = 8333: 202 and 195).
+constexpr int kCollectThreads = 512;
+
 // One workgroup-wide reservation: every thread brings `n_mine` entries; returns the
 // position of the thread's first entry in the row's list (the list counter is bumped
 // once per workgroup).  All threads of the workgroup must call it.
@@ -30,7 +35,7 @@ __device__ __forceinline__ uint32_t reserve_in_list(uint32_t n_mine, uint32_t* _
                                                     uint64_t* scan_lds, uint32_t* bcast)
 {
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kVoteThreads>(n_mine, scan_lds, total);
+    const uint32_t ex = block_excl_scan<kCollectThreads>(n_mine, scan_lds, total);
     if (threadIdx.x == 0) bcast[0] = total ? atomicAdd(counter, total) : 0u;
     __syncthreads();
     const uint32_t base = bcast[0];
@@ -44,7 +49,7 @@ __device__ __forceinline__ bool vote_bit(const uint32_t* __restrict__ bits_row, 
 }
 
 constexpr int kAddUnroll = 4;                     // candidates per thread and reservation
-constexpr int kAddBatch = kVoteThreads * kAddUnroll;
+constexpr int kAddBatch = kCollectThreads * kAddUnroll;
 // A-lists.  Rows whose top-K came from the candidate list: a thread takes kAddUnroll candidates.
 // Rows selected from memory (slow_flag == 1): the whole row is read.
 __device__ __forceinline__ void ad_collect_add_block(
@@ -62,7 +67,7 @@ __device__ __forceinline__ void ad_collect_add_block(
     uint32_t* counter = ad_count + ad_counter(row, 0);
     if (slow_flag[row] == 1u) {
         const float* xrow = e + (int64_t)row * ld_e;
-        for (int64_t j0 = (int64_t)bx * kVoteThreads; j0 < d; j0 += (int64_t)nbx * kVoteThreads) {
+        for (int64_t j0 = (int64_t)bx * kCollectThreads; j0 < d; j0 += (int64_t)nbx * kCollectThreads) {
             const int64_t j = j0 + t;
             u32x2 c = {0u, 0u};
             bool in_a = false;
@@ -83,7 +88,7 @@ __device__ __forceinline__ void ad_collect_add_block(
         uint32_t in_a = 0;
 #pragma unroll
         for (int u = 0; u < kAddUnroll; ++u) {
-            const uint64_t i = i0 + (uint32_t)u * kVoteThreads + t;
+            const uint64_t i = i0 + (uint32_t)u * kCollectThreads + t;
             const u32x2 none = {0u, 0xFFFFFFFFu};
             c[u] = i < C ? crow[i] : none;
         }
@@ -103,9 +108,12 @@ __device__ __forceinline__ void ad_collect_add_block(
 // D-lists: the standing vote's bitmap is scanned, 4 words per thread; a set
 // coordinate that is not in the row's top-K goes to the list with the
 // complemented magnitude, so that "largest first" selects the smallest magnitudes.
-constexpr int kDropStage = 4096;   // set bits of one workgroup's stretch staged in LDS per round
+// Set bits of one workgroup's stretch staged in LDS per round, 16 loads in flight per thread: rounds follow each other, and
+// a stretch may be crowded (2 x 4 M, K = 400,000: 195 us with 4096, 181 so; 2 x 1 M, K = 33,333: 101 and 97).
+constexpr int kDropStage = 16 * kCollectThreads;
 constexpr int kBitIt = 1;          // quads of bitmap words per thread in the bitmap kernels (more per thread measured no faster)
-constexpr int kBitBlockWords = kVoteThreads * 4 * kBitIt;   // bitmap words per workgroup
+constexpr int kCollectWords = kCollectThreads * 4 * kBitIt;   // bitmap words per workgroup of mv_ad_collect
+constexpr int kBitBlockWords = kVoteThreads * 4 * kBitIt;     // and of mv_ad_emit
 __device__ __forceinline__ void ad_collect_drop_block(
     uint32_t bx, uint64_t* scan_lds, uint32_t* bcast, uint32_t* stage,
     const float* __restrict__ e, int64_t ld_e, int64_t d,
@@ -121,7 +129,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
     uint32_t n_bits = 0;
 #pragma unroll
     for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + t) * 4;
+        const uint32_t w0 = bx * kCollectWords + ((uint32_t)it * kCollectThreads + t) * 4;
         w[it][0] = w[it][1] = w[it][2] = w[it][3] = 0;
         if (w0 < nwords) {                        // rows are padded to a multiple of 4 words
             const u32x4 v = *reinterpret_cast<const u32x4*>(vote_bits + (int64_t)row * ld_bits + w0);
@@ -136,7 +144,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
         n_bits += __popc(w[it][0]) + __popc(w[it][1]) + __popc(w[it][2]) + __popc(w[it][3]);
     }
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kVoteThreads>(n_bits, scan_lds, total);
+    const uint32_t ex = block_excl_scan<kCollectThreads>(n_bits, scan_lds, total);
     if (total == 0) return;                                  // whole workgroup
     u32x2* drow = d_list + (size_t)row * cap_d;
     // The members' coordinates are parked in LDS (kDropStage at a time; one round unless the
@@ -146,7 +154,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
         uint32_t sp = ex;
 #pragma unroll
         for (int it = 0; it < kBitIt; ++it) {
-            const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + t) * 4;
+            const uint32_t w0 = bx * kCollectWords + ((uint32_t)it * kCollectThreads + t) * 4;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 uint32_t m = w[it][q];
@@ -160,12 +168,12 @@ __device__ __forceinline__ void ad_collect_drop_block(
         }
         __syncthreads();
         const uint32_t cnt = min((uint32_t)kDropStage, total - c0);
-        constexpr int kRounds = kDropStage / kVoteThreads;
+        constexpr int kRounds = kDropStage / kCollectThreads;
         u32x2 c[kRounds];
         uint32_t n_keep = 0, keep = 0;
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t i = (uint32_t)r * kVoteThreads + t;
+            const uint32_t i = (uint32_t)r * kCollectThreads + t;
             if (i < cnt) {
                 const uint32_t j = stage[i];
                 c[r].x = __float_as_uint(xrow[j]) & kAbsMask;
@@ -199,7 +207,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
 
 // One launch for both lists: the first add_blocks workgroups of a row walk its
 // candidate list (A-list), the others its standing vote's bitmap (D-list).
-__global__ __launch_bounds__(kVoteThreads) void mv_ad_collect(
+__global__ __launch_bounds__(kCollectThreads) void mv_ad_collect(
     const float* __restrict__ e, int64_t ld_e, int64_t d,
     const u32x2* __restrict__ cand, uint32_t cap, const uint32_t* __restrict__ row_count,
     const uint32_t* __restrict__ kth_in, const uint32_t* __restrict__ tie_cut_in,
@@ -207,7 +215,7 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_collect(
     uint32_t nwords, u32x2* __restrict__ a_list, u32x2* __restrict__ d_list, uint32_t cap_d,
     uint32_t* __restrict__ ad_count, uint32_t add_blocks)
 {
-    __shared__ uint64_t scan_lds[kVoteThreads / kWave];
+    __shared__ uint64_t scan_lds[kCollectThreads / kWave];
     __shared__ uint32_t bcast[1];
     __shared__ uint32_t stage[kDropStage];
     if (blockIdx.x < add_blocks)

@@ -600,7 +600,9 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         const uint32_t k_ad = (uint32_t)a.k_ad;
         uint32_t* msum32 = reinterpret_cast<uint32_t*>(a.msum);
         before(KID_AD_COLLECT);
-        hipLaunchKernelGGL(mvk::mv_ad_collect, dim3(p.list_blocks + p.bit_blocks, p.N), dim3(mvk::kVoteThreads), 0,
+        hipLaunchKernelGGL(mvk::mv_ad_collect,
+                           dim3(p.list_blocks + (p.nwords_pad + mvk::kCollectWords - 1) / mvk::kCollectWords, p.N),
+                           dim3(mvk::kCollectThreads), 0,
                            st, a.err, a.ld_e, p.d, cand, p.cap, rowcnt, kth, tiecut, slow, a.vote_bits, a.ld_bits,
                            p.nwords_pad, alist, dlist, p.cap_d, adcount, p.list_blocks);
         after(KID_AD_COLLECT);

@@ -22,7 +22,7 @@ constexpr int      kHistShift      = 31 - kHistBits;
 constexpr int      kChunk          = 32;     // sampled chunk: 32 coordinates (one 128-byte line of fp32)
 constexpr int      kRowThreads     = 1024;   // mv_row_select and the selects from lists
 constexpr int      kVoteBlock      = 16384;  // coordinates per workgroup of mv_rs_keys and of msum's level counts
-constexpr int      kVoteThreads    = 1024;   // add-drop kernels and mv_rs_keys
+constexpr int      kVoteThreads    = 1024;   // mv_ad_emit and mv_rs_keys
 constexpr int      kMaxScanBlocks  = 2048;   // blocks of 1024 segments in a row of up to 2^31 coordinates
 constexpr uint32_t kAbsMask        = 0x7FFFFFFFu;
 constexpr int      kFineBins       = 2048;   // mv_row_select: histogram of the candidates' magnitudes above tau
