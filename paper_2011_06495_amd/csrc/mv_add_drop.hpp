@@ -111,9 +111,9 @@ __device__ __forceinline__ void ad_collect_add_block(
 // Set bits of one workgroup's stretch staged in LDS per round, 16 loads in flight per thread: rounds follow each other, and
 // a stretch may be crowded (2 x 4 M, K = 400,000: 195 us with 4096, 181 so; 2 x 1 M, K = 33,333: 101 and 97).
 constexpr int kDropStage = 16 * kCollectThreads;
-constexpr int kBitIt = 1;          // quads of bitmap words per thread in the bitmap kernels (more per thread measured no faster)
-constexpr int kCollectWords = kCollectThreads * 4 * kBitIt;   // bitmap words per workgroup of mv_ad_collect
-constexpr int kBitBlockWords = kVoteThreads * 4 * kBitIt;     // and of mv_ad_emit
+// bitmap words per workgroup of mv_ad_collect and of mv_ad_emit, four to a thread (more measured no faster)
+constexpr int kCollectWords = kCollectThreads * 4;
+constexpr int kBitBlockWords = kVoteThreads * 4;
 __device__ __forceinline__ void ad_collect_drop_block(
     uint32_t bx, uint64_t* scan_lds, uint32_t* bcast, uint32_t* stage,
     const float* __restrict__ e, int64_t ld_e, int64_t d,
@@ -124,25 +124,20 @@ __device__ __forceinline__ void ad_collect_drop_block(
     const uint32_t row = blockIdx.y, t = threadIdx.x;
     const uint32_t kth = kth_in[row], tie_cut = tie_cut_in[row];
     const float* xrow = e + (int64_t)row * ld_e;
-    // the workgroup's stretch of the bitmap: kBitIt quads of words per thread
-    uint32_t w[kBitIt][4];
-    uint32_t n_bits = 0;
+    // the workgroup's stretch of the bitmap: four words per thread
+    const uint32_t w0 = bx * kCollectWords + t * 4;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (w0 < nwords) {                            // rows are padded to a multiple of 4 words
+        const u32x4 v = *reinterpret_cast<const u32x4*>(vote_bits + (int64_t)row * ld_bits + w0);
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        if ((uint64_t)w0 * 32 + 128 > (uint64_t)d) {             // bits at or beyond d do not exist
 #pragma unroll
-    for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = bx * kCollectWords + ((uint32_t)it * kCollectThreads + t) * 4;
-        w[it][0] = w[it][1] = w[it][2] = w[it][3] = 0;
-        if (w0 < nwords) {                        // rows are padded to a multiple of 4 words
-            const u32x4 v = *reinterpret_cast<const u32x4*>(vote_bits + (int64_t)row * ld_bits + w0);
-            w[it][0] = v.x; w[it][1] = v.y; w[it][2] = v.z; w[it][3] = v.w;
-            if ((uint64_t)w0 * 32 + 128 > (uint64_t)d) {        // bits at or beyond d do not exist
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    for (int b = 0; b < 32; ++b)
-                        if ((int64_t)(w0 + q) * 32 + b >= d) w[it][q] &= ~(1u << b);
-            }
+            for (int q = 0; q < 4; ++q)
+                for (int b = 0; b < 32; ++b)
+                    if ((int64_t)(w0 + q) * 32 + b >= d) w[q] &= ~(1u << b);
         }
-        n_bits += __popc(w[it][0]) + __popc(w[it][1]) + __popc(w[it][2]) + __popc(w[it][3]);
     }
+    const uint32_t n_bits = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
     uint32_t total;
     const uint32_t ex = block_excl_scan<kCollectThreads>(n_bits, scan_lds, total);
     if (total == 0) return;                                  // whole workgroup
@@ -153,19 +148,12 @@ __device__ __forceinline__ void ad_collect_drop_block(
     auto one_round = [&](const uint32_t c0) {
         uint32_t sp = ex;
 #pragma unroll
-        for (int it = 0; it < kBitIt; ++it) {
-            const uint32_t w0 = bx * kCollectWords + ((uint32_t)it * kCollectThreads + t) * 4;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t m = w[it][q];
-                while (m) {
-                    const uint32_t b = __ffs((int)m) - 1;
-                    m &= m - 1;
-                    if (sp - c0 < (uint32_t)kDropStage) stage[sp - c0] = (w0 + q) * 32 + b;   // sp < c0 wraps: not staged
-                    ++sp;
-                }
+        for (int q = 0; q < 4; ++q)
+            for (uint32_t m = w[q]; m != 0u; m &= m - 1) {
+                const uint32_t b = __ffs((int)m) - 1;
+                if (sp - c0 < (uint32_t)kDropStage) stage[sp - c0] = (w0 + q) * 32 + b;       // sp < c0 wraps: not staged
+                ++sp;
             }
-        }
         __syncthreads();
         const uint32_t cnt = min((uint32_t)kDropStage, total - c0);
         constexpr int kRounds = kDropStage / kCollectThreads;
@@ -323,31 +311,18 @@ __global__ __launch_bounds__(kRowThreads) void mv_ad_pick(
 __device__ __forceinline__ void ad_levels_block(const uint32_t* __restrict__ msum32, int64_t d,
                                                 uint32_t* __restrict__ lvl_sets, uint32_t bx, uint32_t* h /*256*/)
 {
-    // all of the block's words first: a load placed after the LDS atomics of the previous
-    // round would wait for its full latency every round
-    constexpr int kIt = kVoteBlock / (kVoteThreads * 16);
-    const int64_t base = (int64_t)bx * kVoteBlock;
-    u32x4 w[kIt];
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int64_t j = base + ((int64_t)it * kVoteThreads + threadIdx.x) * 16;
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        w[it] = (j < d) ? *reinterpret_cast<const u32x4*>(msum32 + (j >> 2)) : z;
-    }
+    static_assert(kVoteBlock == kVoteThreads * 16, "16 coordinates per thread");
+    const int64_t j = (int64_t)bx * kVoteBlock + (int64_t)threadIdx.x * 16;
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    const u32x4 w = j < d ? *reinterpret_cast<const u32x4*>(msum32 + (j >> 2)) : z;
     if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
+    if ((w.x | w.y | w.z | w.w) != 0u) {          // most coordinates have no vote
+        const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int64_t j = base + ((int64_t)it * kVoteThreads + threadIdx.x) * 16;
-        if (j < d) {
-            const uint32_t ww[4] = {w[it].x, w[it].y, w[it].z, w[it].w};
-            if ((ww[0] | ww[1] | ww[2] | ww[3]) != 0u) {     // most coordinates have no vote
-#pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const uint32_t v = (ww[q >> 2] >> (8 * (q & 3))) & 255u;
-                    if (v && j + q < d) atomicAdd(&h[v], 1u);
-                }
-            }
+        for (int q = 0; q < 16; ++q) {
+            const uint32_t v = (ww[q >> 2] >> (8 * (q & 3))) & 255u;
+            if (v && j + q < d) atomicAdd(&h[v], 1u);
         }
     }
     __syncthreads();
@@ -375,24 +350,19 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_emit(uint32_t* __restrict_
     }
     const uint32_t row = blockIdx.x / nblk, bx = blockIdx.x % nblk;
     uint32_t* vrow = vote_bits + (int64_t)row * ld_bits;
-    // the block's words first (cleared behind): their latency overlaps the prefix's loads
-    uint32_t w[kBitIt][4], in_vote[kBitIt][4];
+    // the thread's words first (cleared behind): their latency overlaps the prefix's loads
+    const uint32_t w0 = bx * kBitBlockWords + threadIdx.x * 4;
+    uint32_t w[4] = {0, 0, 0, 0}, in_vote[4] = {0, 0, 0, 0};
+    if (w0 < nwords_pad) {
+        u32x4* p = reinterpret_cast<u32x4*>(ad_bits + (size_t)row * nwords_pad + w0);
+        const u32x4 v = *p;
+        w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+        if ((v.x | v.y | v.z | v.w) != 0u) {
+            const u32x4 z = {0u, 0u, 0u, 0u};
+            *p = z;
 #pragma unroll
-    for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[it][q] = in_vote[it][q] = 0;
-        if (w0 < nwords_pad) {
-            u32x4* p = reinterpret_cast<u32x4*>(ad_bits + (size_t)row * nwords_pad + w0);
-            const u32x4 v = *p;
-            w[it][0] = v.x; w[it][1] = v.y; w[it][2] = v.z; w[it][3] = v.w;
-            if ((v.x | v.y | v.z | v.w) != 0u) {
-                const u32x4 z = {0u, 0u, 0u, 0u};
-                *p = z;
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (w[it][q]) in_vote[it][q] = vrow[w0 + q];
-            }
+            for (int q = 0; q < 4; ++q)
+                if (w[q]) in_vote[q] = vrow[w0 + q];
         }
     }
     uint64_t mine = 0;
@@ -405,38 +375,28 @@ __global__ __launch_bounds__(kVoteThreads) void mv_ad_emit(uint32_t* __restrict_
     __syncthreads();
     uint32_t* out_add = add_idx + (size_t)row * k_ad;
     uint32_t* out_drop = drop_idx + (size_t)row * k_ad;
-    uint64_t done = before;                       // (additions, removals) before the current quad row
+    uint32_t n_add = 0, n_drop = 0;
 #pragma unroll
-    for (int it = 0; it < kBitIt; ++it) {
-        const uint32_t w0 = bx * kBitBlockWords + ((uint32_t)it * kVoteThreads + threadIdx.x) * 4;
-        uint32_t n_add = 0, n_drop = 0;
+    for (int q = 0; q < 4; ++q) {
+        n_add += __popc(w[q] & ~in_vote[q]);
+        n_drop += __popc(w[q] & in_vote[q]);
+    }
+    uint64_t total;
+    const uint64_t at = before + block_excl_scan64<kVoteThreads>(pack2(n_add, n_drop), scan_lds, total);
+    uint32_t pos_add = (uint32_t)(at >> 32), pos_drop = (uint32_t)at;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            n_add += __popc(w[it][q] & ~in_vote[it][q]);
-            n_drop += __popc(w[it][q] & in_vote[it][q]);
-        }
-        uint64_t total;
-        const uint64_t at = done + block_excl_scan64<kVoteThreads>(pack2(n_add, n_drop), scan_lds, total);
-        uint32_t pos_add = (uint32_t)(at >> 32), pos_drop = (uint32_t)at;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint32_t m = w[it][q];
-            if (m) atomicXor(&vrow[w0 + q], m);     // additions enter the standing vote, removals leave it
-            while (m) {
-                const uint32_t b = __ffs((int)m) - 1;
-                m &= m - 1;
-                const uint32_t j = (w0 + q) * 32 + b;
-                if ((in_vote[it][q] >> b) & 1u) {
-                    if (pos_drop < k_ad) out_drop[pos_drop] = j;
-                    ++pos_drop;
-                } else {
-                    if (pos_add < k_ad) out_add[pos_add] = j;
-                    ++pos_add;
-                }
+    for (int q = 0; q < 4; ++q) {
+        if (w[q]) atomicXor(&vrow[w0 + q], w[q]);   // additions enter the standing vote, removals leave it
+        for (uint32_t m = w[q]; m != 0u; m &= m - 1) {
+            const uint32_t b = __ffs((int)m) - 1, j = (w0 + q) * 32 + b;
+            if ((in_vote[q] >> b) & 1u) {
+                if (pos_drop < k_ad) out_drop[pos_drop] = j;
+                ++pos_drop;
+            } else {
+                if (pos_add < k_ad) out_add[pos_add] = j;
+                ++pos_add;
             }
         }
-        done += total;
-        __syncthreads();
     }
 }
 

@@ -29,86 +29,40 @@ __device__ __forceinline__ u32x2 rs_entry(const float* __restrict__ rand_exp, ui
     c.y = j;
     return c;
 }
+// The voted coordinates are parked in LDS as (offset, votes) and their random numbers then fetched by all
+// lanes together: one dependent load per entry inside each thread's own loop made this kernel 2.5x
+// slower, and 8x slower on crowded blocks.
 __global__ __launch_bounds__(kVoteThreads) void mv_rs_keys(const uint32_t* __restrict__ votes32, int64_t d,
                                                            const float* __restrict__ rand_exp,
                                                            u32x2* __restrict__ list, uint32_t list_cap,
                                                            uint32_t* __restrict__ rs_count)
 {
-    constexpr int kIt = kVoteBlock / (kVoteThreads * 16);
-    constexpr int kPerIt = kVoteThreads * 16;                      // coordinates per round: all may hold a vote
-    __shared__ uint32_t stage[kPerIt];
+    static_assert(kVoteBlock == kVoteThreads * 16, "16 coordinates per thread");
+    __shared__ uint32_t stage[kVoteBlock];                         // all of the block's coordinates may hold a vote
     __shared__ uint64_t scan_lds[kVoteThreads / kWave];
     __shared__ uint32_t base_sh;
     const int64_t base = (int64_t)blockIdx.x * kVoteBlock;
-    u32x4 w[kIt];
+    const uint32_t off0 = threadIdx.x * 16;
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    const u32x4 w = base + off0 < d ? *reinterpret_cast<const u32x4*>(votes32 + ((base + off0) >> 2)) : z;   // zero past d
+    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
     uint32_t n = 0;
 #pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const int64_t j = base + ((int64_t)it * kVoteThreads + threadIdx.x) * 16;
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        w[it] = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;   // bytes past d are zero
-    }
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const uint32_t ww[4] = {w[it].x, w[it].y, w[it].z, w[it].w};
-#pragma unroll
-        for (int q = 0; q < 16; ++q) n += ((ww[q >> 2] >> (8 * (q & 3))) & 255u) != 0u;
-    }
+    for (int q = 0; q < 16; ++q) n += ((ww[q >> 2] >> (8 * (q & 3))) & 255u) != 0u;
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kVoteThreads>(n, scan_lds, total);
+    uint32_t sp = block_excl_scan<kVoteThreads>(n, scan_lds, total);
     if (total == 0) return;                                        // whole workgroup
     if (threadIdx.x == 0) base_sh = atomicAdd(&rs_count[0], total);
-    if (total <= (uint32_t)kPerIt) {                               // uniform; usual case: one round for the whole block
-        uint32_t sp = ex;
-        if (n) {
-#pragma unroll
-            for (int it = 0; it < kIt; ++it) {
-                if ((w[it].x | w[it].y | w[it].z | w[it].w) == 0u) continue;
-                const uint32_t off0 = ((uint32_t)it * kVoteThreads + threadIdx.x) * 16;
-                const uint32_t ww[4] = {w[it].x, w[it].y, w[it].z, w[it].w};
-                for (int q = 0; q < 16; ++q) {
-                    const uint32_t v = (ww[q >> 2] >> (8 * (q & 3))) & 255u;
-                    if (v) stage[sp++] = ((off0 + (uint32_t)q) << 8) | v;
-                }
-            }
+    if (n)
+        for (int q = 0; q < 16; ++q) {
+            const uint32_t v = (ww[q >> 2] >> (8 * (q & 3))) & 255u;
+            if (v) stage[sp++] = ((off0 + (uint32_t)q) << 8) | v;
         }
-        __syncthreads();
-        const uint32_t at = base_sh;
-        for (uint32_t i = threadIdx.x; i < total; i += kVoteThreads) {
-            const uint32_t s = stage[i];
-            if (at + i < list_cap) list[at + i] = rs_entry(rand_exp, (uint32_t)base + (s >> 8), s & 255u);
-        }
-        return;
-    }
     __syncthreads();
-    uint32_t first = base_sh;                                      // list position of the round's first entry
-    // A block crowded with votes (the mask concentrates in few tensors), round by round of
-    // 4096 coordinates.  Either way the voted coordinates are parked in LDS as (offset,
-    // votes) and their random numbers then fetched by all lanes together: one dependent load
-    // per entry inside each thread's own loop made this kernel 2.5x slower, and 8x slower
-    // on crowded blocks.
-#pragma unroll
-    for (int it = 0; it < kIt; ++it) {
-        const uint32_t ww[4] = {w[it].x, w[it].y, w[it].z, w[it].w};
-        uint32_t n_it = 0;
-#pragma unroll
-        for (int q = 0; q < 16; ++q) n_it += ((ww[q >> 2] >> (8 * (q & 3))) & 255u) != 0u;
-        uint32_t round_total;
-        uint32_t sp = block_excl_scan<kVoteThreads>(n_it, scan_lds, round_total);
-        if (n_it) {
-            const uint32_t off0 = ((uint32_t)it * kVoteThreads + threadIdx.x) * 16;   // offset in the block
-            for (int q = 0; q < 16; ++q) {
-                const uint32_t v = (ww[q >> 2] >> (8 * (q & 3))) & 255u;
-                if (v) stage[sp++] = ((off0 + (uint32_t)q) << 8) | v;
-            }
-        }
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < round_total; i += kVoteThreads) {
-            const uint32_t s = stage[i];
-            if (first + i < list_cap) list[first + i] = rs_entry(rand_exp, (uint32_t)base + (s >> 8), s & 255u);
-        }
-        first += round_total;
-        __syncthreads();
+    const uint32_t at = base_sh;
+    for (uint32_t i = threadIdx.x; i < total; i += kVoteThreads) {
+        const uint32_t s = stage[i];
+        if (at + i < list_cap) list[at + i] = rs_entry(rand_exp, (uint32_t)base + (s >> 8), s & 255u);
     }
 }
 
