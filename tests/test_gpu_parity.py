@@ -375,9 +375,9 @@ def test_every_route_of_the_row_select(oracle, case):
 
 @pytest.mark.parametrize("case", ["normal", "lattice_ties", "kth_far_above_threshold"])
 def test_long_candidate_lists_are_selected_by_many_workgroups(oracle, case):
-    """Candidate lists longer than a workgroup of mv_row_select keeps in registers
-    (about 240,000 per row here): selected by the histogram / split / rank kernels,
-    many workgroups per row, their votes cast by mv_row_votes."""
+    """Candidate lists far longer than a workgroup of mv_row_select keeps in registers
+    (32 x 1024 entries; about 240,000 per row here): selected, and their votes cast, by
+    mv_sel_hist, mv_sel_split and mv_sel_finish, many workgroups per row."""
     rng = np.random.default_rng(sum(map(ord, case)))
     N, d, K = 3, 1500007, 220000
     if case == "normal":
@@ -397,7 +397,7 @@ def test_long_candidate_lists_are_selected_by_many_workgroups(oracle, case):
     say("  candidates %s path %s" % (cand, path))
     assert_matches_oracle(got, oracle.vote_step(g, e, K), case)
     assert all(p != 1 for p in path), "these rows are meant for the candidate-list routes"
-    assert min(cand) > 160 * 1024, "these lists are meant to be longer than one workgroup keeps"
+    assert min(cand) > 160 * 1024, "these lists are meant to be far longer than one workgroup keeps"
 
 
 def test_tie_cut_inside_a_run_of_neighbouring_ties(oracle):

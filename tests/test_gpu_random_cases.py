@@ -31,7 +31,7 @@ def draw_case(rng):
     elif dist == 3:
         g = rng.standard_normal((N, d)) * (rng.random((1, d)) < 0.01)               # mostly zeros
     elif dist == 4:
-        g = rng.standard_normal((N, d)) * 10.0 ** rng.uniform(-20, 10, (1, d))     # down to denormals
+        g = rng.standard_normal((N, d)) * 10.0 ** rng.uniform(-20, 10, (1, d))     # thirty decades
     else:
         g = np.tile(rng.standard_normal((1, d)), (N, 1))                            # identical rows
     g = g.astype(np.float32)
