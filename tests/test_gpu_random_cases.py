@@ -1,6 +1,6 @@
 """Seeded random problems (shapes from 1 coordinate to 400,003, 1 to 255 workers, K from
-1 to d, six value distributions incl. heavy ties, mostly zeros, a range down to
-denormals, identical rows; fp32 and bf16 gradients) through all three kinds of step,
+1 to d, six value distributions incl. heavy ties, mostly zeros, a range of thirty
+decades, identical rows; fp32 and bf16 gradients) through all three kinds of step,
 each compared with the oracle element by element over consecutive steps."""
 import sys
 
