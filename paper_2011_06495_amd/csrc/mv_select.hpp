@@ -980,7 +980,8 @@ struct SplitLds {
 
 // Counts taken entries per block of coordinates: in LDS and merged at the end, since the taken ones concentrate in
 // few blocks and their counters in memory would be the bottleneck (counted there one group of lanes at a time, the
-// random selection's pick took 31 us instead of 14); in memory when there are more blocks than LDS has
+// random selection's pick took 19.8 us instead of 12.7 at 16 x 11.2 M, K = 11,174, the add-drop pick 63 instead of 27 at
+// 10 x 11.2 M, K = 111,740); in memory when there are more blocks than LDS has
 // counters.
 struct BlockTally {
     uint32_t* lds;
