@@ -1660,7 +1660,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         v.hist[t] = 0;
         if (t == 0) *v.count2 = 0;
     }
-    for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
+    for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the next barrier
     const CastVotes act = {votes32, lds.lvl, seg_sel ? seg_sel + (size_t)row * nseg : nullptr, thresholds_only};
     uint32_t kth, tie_cut;
     if (rest.n <= (uint32_t)kMembers && members_stored(v, rest)) {   // uniform; usual: this is the row's only workgroup
@@ -1696,6 +1696,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         merge_levels(lds.lvl, lvl_sets, row);
         return;
     }
+    __syncthreads();                              // (a bin that is wanted whole is acted on without another)
     bool ranked = false;
     if (rest.n > (uint32_t)kMembers) {            // uniform: a big group
         const uint32_t count[2] = {v.blocks[2 * t], v.blocks[2 * t + 1]};
@@ -1719,6 +1720,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         }
     }
     if (!ranked) rank_rest<false>(v, rest, lds, kth, tie_cut);
+    kth = max(kth, v.base);                       // (where a bin is wanted whole: what is not in the list stays outside)
     if (blockIdx.x == 0 && t == 0) {
         kth_out[row] = kth;
         tie_cut_out[row] = tie_cut;

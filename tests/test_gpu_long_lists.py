@@ -198,3 +198,27 @@ def test_groups_around_what_fits_on_chip(oracle, m):
         gs.set_error(e)
         gs.step_rs(r)
         assert_matches_oracle(gs.fetch(), oracle.rs_vote_step(g, e, K, r, threads=8), "random")
+
+
+@pytest.mark.parametrize("N,d,K", [(2, 300007, 40000), (1, 150001, 30000), (3, 90001, 41000)])
+@pytest.mark.parametrize("magnitudes", ["equal", "one_bin", "spread"])
+def test_lists_of_exactly_k(oracle, N, d, K, magnitudes):
+    """Rows with exactly K coordinates that are not zero, elsewhere in every step: the list is the vote, and what left
+    it -- zeros now -- is outside the top K.  (All workers have the same support, so every step transmits all of it.)"""
+    print("[case] lists of exactly K %s N=%d d=%d K=%d" % (magnitudes, N, d, K), flush=True)
+    rng = np.random.default_rng(K + len(magnitudes))
+    gs = GpuAdStepper(N, d, K, K)
+    try:
+        vote, msum, e = np.zeros((N, d), np.uint8), np.zeros(d, np.uint8), np.zeros((N, d), np.float32)
+        for t, k_ad in enumerate([K, K, K // 2, K]):
+            g = np.zeros((N, d), np.float32)
+            at = rng.permutation(d)[:K]
+            v = {"equal": np.ones((N, K)), "one_bin": 1.0 + rng.integers(0, 4000, (N, K)) * 2.0 ** -23,
+                 "spread": 1.0 + rng.random((N, K))}[magnitudes]
+            g[:, at] = v
+            ref = oracle.ad_vote_step(g, e, K, k_ad, vote, msum, threads=8)
+            gs.step(g, k_ad)
+            gs.compare(ref, "step %d" % t)
+            vote, msum, e = ref.vote, ref.msum, ref.err
+    finally:
+        gs.close()
