@@ -24,18 +24,19 @@ namespace mvk {
 // updated.
 
 // Threads of mv_ad_collect's workgroups: with 1024 a unit holds two, whose barriers leave it idle where rows and votes
-// are many (128 x 400,003, K = 33,333, K_ad = 3333: 472 us, with 512 threads 377); with 256 a
-// row's reservations are more (255 x 100,003, K = 8333: 202 and 195).
-constexpr int kCollectThreads = 512;
+// are many (128 x 400,003, K = 33,333, K_ad = 3333: 472 us, with 512 threads 375); a row whose bitmap is one workgroup's
+// anyway is done sooner by more threads (255 x 33,001, K = 2750: 99 us, with 512 threads 105; 2 x 33,001: 47.6 and 49.5).
+constexpr int kCollectThreads = 512, kCollectThreadsShort = 1024;
 
 // One workgroup-wide reservation: every thread brings `n_mine` entries; returns the
 // position of the thread's first entry in the row's list (the list counter is bumped
 // once per workgroup).  All threads of the workgroup must call it.
+template <int THREADS>
 __device__ __forceinline__ uint32_t reserve_in_list(uint32_t n_mine, uint32_t* __restrict__ counter,
                                                     uint64_t* scan_lds, uint32_t* bcast)
 {
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kCollectThreads>(n_mine, scan_lds, total);
+    const uint32_t ex = block_excl_scan<THREADS>(n_mine, scan_lds, total);
     if (threadIdx.x == 0) bcast[0] = total ? atomicAdd(counter, total) : 0u;
     __syncthreads();
     const uint32_t base = bcast[0];
@@ -49,9 +50,10 @@ __device__ __forceinline__ bool vote_bit(const uint32_t* __restrict__ bits_row, 
 }
 
 constexpr int kAddUnroll = 4;                     // candidates per thread and reservation
-constexpr int kAddBatch = kCollectThreads * kAddUnroll;
+__host__ __device__ constexpr int add_batch(int threads) { return threads * kAddUnroll; }
 // A-lists.  Rows whose top-K came from the candidate list: a thread takes kAddUnroll candidates.
 // Rows selected from memory (slow_flag == 1): the whole row is read.
+template <int THREADS>
 __device__ __forceinline__ void ad_collect_add_block(
     uint32_t bx, uint32_t nbx, uint64_t* scan_lds, uint32_t* bcast,
     const float* __restrict__ e, int64_t ld_e, int64_t d,
@@ -67,7 +69,7 @@ __device__ __forceinline__ void ad_collect_add_block(
     uint32_t* counter = ad_count + ad_counter(row, 0);
     if (slow_flag[row] == 1u) {
         const float* xrow = e + (int64_t)row * ld_e;
-        for (int64_t j0 = (int64_t)bx * kCollectThreads; j0 < d; j0 += (int64_t)nbx * kCollectThreads) {
+        for (int64_t j0 = (int64_t)bx * THREADS; j0 < d; j0 += (int64_t)nbx * THREADS) {
             const int64_t j = j0 + t;
             u32x2 c = {0u, 0u};
             bool in_a = false;
@@ -76,26 +78,26 @@ __device__ __forceinline__ void ad_collect_add_block(
                 c.y = (uint32_t)j;
                 in_a = is_taken(c, kth, tie_cut) && !vote_bit(bits, c.y);
             }
-            const uint32_t pos = reserve_in_list(in_a ? 1u : 0u, counter, scan_lds, bcast);
+            const uint32_t pos = reserve_in_list<THREADS>(in_a ? 1u : 0u, counter, scan_lds, bcast);
             if (in_a && pos < cap) arow[pos] = c;
         }
         return;
     }
     const uint32_t C = row_count[row];
     const u32x2* crow = cand + (size_t)row * cap;
-    for (uint64_t i0 = (uint64_t)bx * kAddBatch; i0 < C; i0 += (uint64_t)nbx * kAddBatch) {
+    for (uint64_t i0 = (uint64_t)bx * add_batch(THREADS); i0 < C; i0 += (uint64_t)nbx * add_batch(THREADS)) {
         u32x2 c[kAddUnroll];
         uint32_t in_a = 0;
 #pragma unroll
         for (int u = 0; u < kAddUnroll; ++u) {
-            const uint64_t i = i0 + (uint32_t)u * kCollectThreads + t;
+            const uint64_t i = i0 + (uint32_t)u * THREADS + t;
             const u32x2 none = {0u, 0xFFFFFFFFu};
             c[u] = i < C ? crow[i] : none;
         }
 #pragma unroll
         for (int u = 0; u < kAddUnroll; ++u)
             if (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) && !vote_bit(bits, c[u].y)) in_a |= 1u << u;
-        uint32_t pos = reserve_in_list((uint32_t)__popc(in_a), counter, scan_lds, bcast);
+        uint32_t pos = reserve_in_list<THREADS>((uint32_t)__popc(in_a), counter, scan_lds, bcast);
 #pragma unroll
         for (int u = 0; u < kAddUnroll; ++u)
             if (in_a >> u & 1u) {
@@ -105,15 +107,16 @@ __device__ __forceinline__ void ad_collect_add_block(
     }
 }
 
+// Set bits of one workgroup's stretch staged in LDS per round, 16 (8) loads in flight per thread: rounds follow each
+// other, and a stretch may be crowded (2 x 4 M, K = 400,000: 195 us with 4096, 181 so; 2 x 1 M, K = 33,333: 101 and 97).
+constexpr int kDropStage = 8192;
+// bitmap words per workgroup of mv_ad_collect and of mv_ad_emit, four to a thread (more measured no faster)
+__host__ __device__ constexpr int collect_words(int threads) { return threads * 4; }
+constexpr int kBitBlockWords = kVoteThreads * 4;
 // D-lists: the standing vote's bitmap is scanned, 4 words per thread; a set
 // coordinate that is not in the row's top-K goes to the list with the
 // complemented magnitude, so that "largest first" selects the smallest magnitudes.
-// Set bits of one workgroup's stretch staged in LDS per round, 16 loads in flight per thread: rounds follow each other, and
-// a stretch may be crowded (2 x 4 M, K = 400,000: 195 us with 4096, 181 so; 2 x 1 M, K = 33,333: 101 and 97).
-constexpr int kDropStage = 16 * kCollectThreads;
-// bitmap words per workgroup of mv_ad_collect and of mv_ad_emit, four to a thread (more measured no faster)
-constexpr int kCollectWords = kCollectThreads * 4;
-constexpr int kBitBlockWords = kVoteThreads * 4;
+template <int THREADS>
 __device__ __forceinline__ void ad_collect_drop_block(
     uint32_t bx, uint64_t* scan_lds, uint32_t* bcast, uint32_t* stage,
     const float* __restrict__ e, int64_t ld_e, int64_t d,
@@ -125,7 +128,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
     const uint32_t kth = kth_in[row], tie_cut = tie_cut_in[row];
     const float* xrow = e + (int64_t)row * ld_e;
     // the workgroup's stretch of the bitmap: four words per thread
-    const uint32_t w0 = bx * kCollectWords + t * 4;
+    const uint32_t w0 = bx * collect_words(THREADS) + t * 4;
     uint32_t w[4] = {0, 0, 0, 0};
     if (w0 < nwords) {                            // rows are padded to a multiple of 4 words
         const u32x4 v = *reinterpret_cast<const u32x4*>(vote_bits + (int64_t)row * ld_bits + w0);
@@ -139,7 +142,7 @@ __device__ __forceinline__ void ad_collect_drop_block(
     }
     const uint32_t n_bits = __popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]);
     uint32_t total;
-    const uint32_t ex = block_excl_scan<kCollectThreads>(n_bits, scan_lds, total);
+    const uint32_t ex = block_excl_scan<THREADS>(n_bits, scan_lds, total);
     if (total == 0) return;                                  // whole workgroup
     u32x2* drow = d_list + (size_t)row * cap_d;
     // The members' coordinates are parked in LDS (kDropStage at a time; one round unless the
@@ -156,30 +159,29 @@ __device__ __forceinline__ void ad_collect_drop_block(
             }
         __syncthreads();
         const uint32_t cnt = min((uint32_t)kDropStage, total - c0);
-        constexpr int kRounds = kDropStage / kCollectThreads;
-        u32x2 c[kRounds];
+        constexpr int kRounds = kDropStage / THREADS;
+        uint32_t x[kRounds];
         uint32_t n_keep = 0, keep = 0;
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            const uint32_t i = (uint32_t)r * kCollectThreads + t;
+            const uint32_t i = (uint32_t)r * THREADS + t;
             if (i < cnt) {
-                const uint32_t j = stage[i];
-                c[r].x = __float_as_uint(xrow[j]) & kAbsMask;
-                c[r].y = j;
-                if (!is_taken(c[r], kth, tie_cut)) {         // left the top-K: a drop candidate
+                const u32x2 c = {__float_as_uint(xrow[stage[i]]) & kAbsMask, stage[i]};
+                x[r] = c.x;
+                if (!is_taken(c, kth, tie_cut)) {            // left the top-K: a drop candidate
                     keep |= 1u << r;
                     ++n_keep;
                 }
             }
         }
-        uint32_t pos = reserve_in_list(n_keep, ad_count + ad_counter(row, 1), scan_lds, bcast);
+        uint32_t pos = reserve_in_list<THREADS>(n_keep, ad_count + ad_counter(row, 1), scan_lds, bcast);
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
             if (keep & (1u << r)) {
                 if (pos < cap_d) {
                     u32x2 o;
-                    o.x = kAbsMask - c[r].x;
-                    o.y = c[r].y;
+                    o.x = kAbsMask - x[r];
+                    o.y = stage[(uint32_t)r * THREADS + t];   // (in LDS and not in a register: units hold more workgroups)
                     drow[pos] = o;
                 }
                 ++pos;
@@ -189,13 +191,18 @@ __device__ __forceinline__ void ad_collect_drop_block(
     if (total <= (uint32_t)kDropStage) {                     // uniform; the usual case
         one_round(0u);
     } else {
-        for (uint32_t c0 = 0; c0 < total; c0 += kDropStage) one_round(c0);
+        for (uint32_t c0 = 0; c0 < total; c0 += kDropStage) {
+            if (c0) __syncthreads();                         // the stage is free again
+            one_round(c0);
+        }
     }
 }
 
 // One launch for both lists: the first add_blocks workgroups of a row walk its
 // candidate list (A-list), the others its standing vote's bitmap (D-list).
-__global__ __launch_bounds__(kCollectThreads) void mv_ad_collect(
+// (the second bound: 64 registers, so that a unit holds 2048 threads)
+template <int THREADS>
+__global__ __launch_bounds__(THREADS, 8) void mv_ad_collect(
     const float* __restrict__ e, int64_t ld_e, int64_t d,
     const u32x2* __restrict__ cand, uint32_t cap, const uint32_t* __restrict__ row_count,
     const uint32_t* __restrict__ kth_in, const uint32_t* __restrict__ tie_cut_in,
@@ -203,15 +210,15 @@ __global__ __launch_bounds__(kCollectThreads) void mv_ad_collect(
     uint32_t nwords, u32x2* __restrict__ a_list, u32x2* __restrict__ d_list, uint32_t cap_d,
     uint32_t* __restrict__ ad_count, uint32_t add_blocks)
 {
-    __shared__ uint64_t scan_lds[kCollectThreads / kWave];
+    __shared__ uint64_t scan_lds[THREADS / kWave];
     __shared__ uint32_t bcast[1];
     __shared__ uint32_t stage[kDropStage];
     if (blockIdx.x < add_blocks)
-        ad_collect_add_block(blockIdx.x, add_blocks, scan_lds, bcast, e, ld_e, d, cand, cap, row_count, kth_in,
-                             tie_cut_in, slow_flag, vote_bits, ld_bits, a_list, ad_count);
+        ad_collect_add_block<THREADS>(blockIdx.x, add_blocks, scan_lds, bcast, e, ld_e, d, cand, cap, row_count, kth_in,
+                                      tie_cut_in, slow_flag, vote_bits, ld_bits, a_list, ad_count);
     else
-        ad_collect_drop_block(blockIdx.x - add_blocks, scan_lds, bcast, stage, e, ld_e, d, kth_in, tie_cut_in,
-                              vote_bits, ld_bits, nwords, d_list, cap_d, ad_count);
+        ad_collect_drop_block<THREADS>(blockIdx.x - add_blocks, scan_lds, bcast, stage, e, ld_e, d, kth_in, tie_cut_in,
+                                       vote_bits, ld_bits, nwords, d_list, cap_d, ad_count);
 }
 
 // The K_ad first of row n's A-list under (magnitude desc, coordinate asc), and the same for the D-list, whose

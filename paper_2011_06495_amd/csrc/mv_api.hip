@@ -70,6 +70,7 @@ struct Plan {
     uint32_t nwords, nwords_pad;  // 32-bit words of a row's vote bitmap, and padded to a multiple of 4
     uint32_t cap_d;               // capacity of a row's list of removal candidates
     uint32_t bit_blocks;          // workgroups of kBitBlockWords bitmap words per row
+    uint32_t collect_threads, collect_blocks;   // of mv_ad_collect: threads per workgroup, workgroups per row for the bitmap
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
     uint32_t block_shift;         // its blocks of coordinates: 2^block_shift, at most kCoordBlocks of them
@@ -205,7 +206,11 @@ Plan make_plan(const mv_config* c)
         if (eb2 < 1) eb2 = 1;
         p.split_blocks = (uint32_t)sb;
         // likewise in mv_ad_collect
-        uint64_t lb = (expect + mvk::kAddBatch - 1) / mvk::kAddBatch;
+        // (a row's bitmap in one workgroup of more threads, where it fits)
+        const bool one = (uint64_t)p.d <= 32ull * mvk::collect_words(mvk::kCollectThreadsShort);
+        p.collect_threads = one ? mvk::kCollectThreadsShort : mvk::kCollectThreads;
+        const uint64_t batch = mvk::add_batch((int)p.collect_threads);
+        uint64_t lb = (expect + batch - 1) / batch;
         if (lb > 256) lb = 256;
         p.list_blocks = (uint32_t)lb;
         p.emit_blocks = (uint32_t)eb2;
@@ -234,6 +239,8 @@ Plan make_plan(const mv_config* c)
     p.nwords = (uint32_t)((p.d + 31) / 32);
     p.nwords_pad = (p.nwords + 3) / 4 * 4;
     p.cap_d = p.K;
+    const uint32_t stretch = mvk::collect_words((int)p.collect_threads);
+    p.collect_blocks = (p.nwords_pad + stretch - 1) / stretch;
     p.bit_blocks = (p.nwords_pad + mvk::kBitBlockWords - 1) / mvk::kBitBlockWords;
     if (p.add_drop) {
         p.off_adblk = off; off += (size_t)p.N * p.bit_blocks * 8;
@@ -600,9 +607,10 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         const uint32_t k_ad = (uint32_t)a.k_ad;
         uint32_t* msum32 = reinterpret_cast<uint32_t*>(a.msum);
         before(KID_AD_COLLECT);
-        hipLaunchKernelGGL(mvk::mv_ad_collect,
-                           dim3(p.list_blocks + (p.nwords_pad + mvk::kCollectWords - 1) / mvk::kCollectWords, p.N),
-                           dim3(mvk::kCollectThreads), 0,
+        hipLaunchKernelGGL((p.collect_threads == (uint32_t)mvk::kCollectThreads
+                                ? &mvk::mv_ad_collect<mvk::kCollectThreads>
+                                : &mvk::mv_ad_collect<mvk::kCollectThreadsShort>),
+                           dim3(p.list_blocks + p.collect_blocks, p.N), dim3(p.collect_threads), 0,
                            st, a.err, a.ld_e, p.d, cand, p.cap, rowcnt, kth, tiecut, slow, a.vote_bits, a.ld_bits,
                            p.nwords_pad, alist, dlist, p.cap_d, adcount, p.list_blocks);
         after(KID_AD_COLLECT);
