@@ -79,6 +79,7 @@ struct Plan {
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
     // scratch offsets (bytes)
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
+    uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
     size_t off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_seg, off_segsel,
         off_segpre,
@@ -147,6 +148,12 @@ Plan make_plan(const mv_config* c)
         const uint64_t bx = ((nchunks + stride - 1) / stride * (mvk::kChunk / 4) + per_round - 1) / per_round;
         p.sample_wgs = (uint32_t)(bx > 16 ? 16 : bx);
     }
+    // Loads of the grid's head beside the sampling bring a short grid's data earlier and the estimate later.  One
+    // sampling workgroup per row has little to fetch: no loads are held back (7 x 272,475 bf16: 33.7 -> 33.0 us;
+    // 4 x 2^20, K = 10,486: 49.9 -> 48.9; 40 x 1,000,003, K = 10,000: 132.7 -> 131.9).  Several do better with the
+    // memory to themselves, in any grid: two rounds of resident workgroups wait (2 x 1,000,003, K = 1000: 39.5 us, 39.9
+    // if none did; 16 x 2,000,003: 99.5 and 100.7; only from 40 x 300,001, K = 300 known otherwise: 56.0 and 54.1).
+    p.head_wgs = p.sample_wgs == 1 ? 0 : 2048;
     p.stride = (uint32_t)stride;
     p.n_sampled_chunks = (uint32_t)((nchunks + stride - 1) / stride);
     // all sampled chunks are full except possibly the row's last chunk
@@ -288,7 +295,6 @@ struct mv_ctx {
     bool       ev_recorded[kEventRing][KID_COUNT];
     uint64_t   steps_done;
     uint32_t   spin_limit;  // polls a streaming wavefront makes for its row's threshold before it gives up
-    uint32_t   head_wgs;    // streaming workgroups at the head of the grid that wait for the sampling before loading
     hipStream_t last_stream;
 };
 
@@ -335,7 +341,6 @@ mv_status mv_begin(const mv_config* cfg, mv_ctx** out_ctx)
     memset(c, 0, sizeof *c);
     c->cfg = *cfg;
     c->plan = plan;
-    c->head_wgs = 2048;         // about two rounds of resident workgroups
     c->spin_limit = 1u << 20;   // of about a microsecond each; a threshold is normally there within ten
 
     DeviceGuard guard(cfg->device);
@@ -553,14 +558,14 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, seg, segsel, p.nseg, wpr, c->head_wgs,
+                               rowcnt_sets, rowcnt_set_words, seg, segsel, p.nseg, wpr, p.head_wgs,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, seg, segsel, p.nseg, wpr, c->head_wgs,
+                               rowcnt_sets, rowcnt_set_words, seg, segsel, p.nseg, wpr, p.head_wgs,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }

@@ -241,7 +241,8 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     };
 
     // The kernel's first streaming workgroups would compete with the sampling for the memory
-    // system and delay the estimate for everybody: they hold back even their loads.
+    // system and delay the estimate for everybody: they hold back even their loads (none where one
+    // workgroup samples a row, see make_plan).
     if (sb < head_wgs) samples_are_in();
 
     uint32_t key[16];
