@@ -41,7 +41,8 @@ __device__ __forceinline__ void tally_digit(uint32_t* hist, bool active, uint32_
 // bin that holds the `want`-th largest entry.  `bin` receives it, `want_in_bin`
 // the rank inside the bin counted from its top (>= 1), `in_bin` the bin's count.
 // Requires 1 <= want <= total count.  All kRowThreads threads must call it.
-// With REP > 1 the histogram is kept in REP copies, bin b's counters at hist[b * REP .. b * REP + REP).
+// With REP > 1 the histogram is kept in REP copies, each copy_pitch(BINS) words behind the one before.
+constexpr int copy_pitch(int bins) { return bins + 8; }
 template <int BINS, int REP = 1>
 __device__ __forceinline__ void find_rank_bin(const uint32_t* hist, uint64_t* scan_lds, uint32_t* bcast,
                                               uint32_t want, uint32_t& bin, uint32_t& want_in_bin,
@@ -55,7 +56,7 @@ __device__ __forceinline__ void find_rank_bin(const uint32_t* hist, uint64_t* sc
         const int b = BINS - 1 - ((int)threadIdx.x * per + q);
         h[q] = 0;
 #pragma unroll
-        for (int r = 0; r < REP; ++r) h[q] += hist[b * REP + r];
+        for (int r = 0; r < REP; ++r) h[q] += hist[r * copy_pitch(BINS) + b];
         s += h[q];
     }
     uint32_t total;
@@ -201,12 +202,26 @@ __device__ __forceinline__ bool is_taken(u32x2 c, uint32_t kth, uint32_t tie_cut
 struct SelectLds {
     __attribute__((aligned(16))) uint32_t hist[kKeyBins];   // histograms; then magnitudes of a bin's members
     __attribute__((aligned(16))) uint32_t ties[kTieCap];    // coordinates of a bin's members / of the ties
-    __attribute__((aligned(16))) uint32_t rhist[kFineBins * kRep];   // the candidates' fine histogram, kRep copies
+    __attribute__((aligned(16))) uint32_t rhist[copy_pitch(kFineBins) * kRep];   // the candidates' fine histogram, kRep copies
     uint32_t lvl[257];
     uint32_t bcast[3];
     uint32_t n_list;
     uint64_t scan[kRowThreads / kWave + 1];
 };
+
+__device__ __forceinline__ void clear_fine_histogram(SelectLds& lds)
+{
+    const u32x4 z = {0u, 0u, 0u, 0u};
+    u32x4* rz = reinterpret_cast<u32x4*>(lds.rhist);
+    for (int b = threadIdx.x; b < copy_pitch(kFineBins) * kRep / 4; b += kRowThreads) rz[b] = z;
+}
+// the lane's counter of a bin.  A bin's copies lie in different banks, eight words apart, and neighbouring bins of a
+// copy in neighbouring words: the adds of a crowd do not queue up, nor the reads that sum the copies (with a bin's
+// copies in neighbouring words every thread read 64 bytes in a row: 4 x 2^20, K = 10,486: 49.3 us, so 48.7).
+__device__ __forceinline__ uint32_t* fine_counter(SelectLds& lds, uint32_t bin)
+{
+    return &lds.rhist[(lane_id() % kRep) * copy_pitch(kFineBins) + bin];
+}
 
 // The take-th SMALLEST of the n distinct coordinates in ties[0..n): ranked by
 // counting when few; else narrowed by one histogram and then ranked by counting;
@@ -342,14 +357,10 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
         // Values on a lattice put thousands of candidates on a few dozen keys, and LDS
         // atomics of one instruction that meet on one address are served one after the
         // other: lane l adds to copy l % kRep of the histogram, which divides those queues.
-        {
-            const u32x4 z = {0u, 0u, 0u, 0u};
-            u32x4* rz = reinterpret_cast<u32x4*>(lds.rhist);
-            for (int b = t; b < kFineBins * kRep / 4; b += kRowThreads) rz[b] = z;
-        }
+        clear_fine_histogram(lds);
         __syncthreads();
         keys.each([&](uint32_t k, uint64_t, bool valid) {
-            if (valid) atomicAdd(&lds.rhist[fine_bin(k, tau) * kRep + (lane & (kRep - 1))], 1u);
+            if (valid) atomicAdd(fine_counter(lds, fine_bin(k, tau)), 1u);
         });
         __syncthreads();
         uint32_t bin, want, in_bin;
@@ -578,7 +589,7 @@ __device__ __forceinline__ bool select_from_registers(const Kept& kept, const u3
     // atomics of one instruction that meet on one address are served one after the
     // other: lane l adds to copy l % kRep of the histogram, which divides those queues.
     kept.each(C, tau, [&](uint32_t bin, int) {
-        if (bin != 0xFFFFu) atomicAdd(&lds.rhist[bin * kRep + (lane & (kRep - 1))], 1u);
+        if (bin != 0xFFFFu) atomicAdd(fine_counter(lds, bin), 1u);
     });
     __syncthreads();
     uint32_t bin, want, in_bin;
@@ -590,11 +601,15 @@ __device__ __forceinline__ bool select_from_registers(const Kept& kept, const u3
     uint32_t* mkey = lds.rhist;                   // find_rank_bin ended with a barrier: the histogram is free
     uint32_t* mpos = lds.rhist + kKeyBins;
     {
-        // the members, in no particular order: count, scan, place
+        // the members, in no particular order: a wavefront takes room for its own with one atomic, and nobody waits
         uint32_t mine = 0;
         kept.each(C, tau, [&](uint32_t b, int) { mine += (b == bin); });
-        uint32_t total;
-        uint32_t p = block_excl_scan<kRowThreads>(mine, lds.scan, total);
+        uint32_t p = 0;
+        if (__ballot(mine != 0u) != 0ull) {       // wave-uniform
+            const uint32_t incl = wave_incl_scan(mine);
+            if (lane == kWave - 1) p = atomicAdd(&lds.n_list, incl);
+            p = from_lane(p, kWave - 1) + incl - mine;
+        }
         if (mine)
             kept.each(C, tau, [&](uint32_t b, int q) {
                 if (b == bin) {
@@ -845,6 +860,14 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
         if ((uint32_t)q < n_spec) fetch(q);
         if ((q & 7) == 7) __builtin_amdgcn_sched_barrier(0);   // keep address arithmetic from piling up
     }
+    // where bins are kept, the first whole entries of the workgroup's share as well, for the votes (4 x 2^20, K =
+    // 10,486: 48.7 -> 48.1 us)
+    constexpr int kOwn = kWhole ? 1 : 4;
+    u32x2 own[kOwn];
+    if constexpr (!kWhole) {
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) own[i] = crow[min((part + i * parts) * kRowThreads + t, cap - 1)];
+    }
     // (the streaming kernel counted into the counter set of this step's parity)
     const uint32_t epoch = step_no[0] + 1u;
     uint32_t C = row_count_sets[(epoch & 1u) * row_count_set_words + row * kCounterStride];
@@ -852,12 +875,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     // a row whose streaming wavefronts did not all see tau in time: its list is incomplete
     const bool poisoned = row_poison[row] == epoch;
     // the fine histogram is cleared while those loads are under way
-    {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        u32x4* rz = reinterpret_cast<u32x4*>(lds.rhist);
-        for (int b = t; b < kFineBins * kRep / 4; b += kRowThreads) rz[b] = z;
-        if (t == 0) lds.n_list = 0;
-    }
+    clear_fine_histogram(lds);
+    if (t == 0) lds.n_list = 0;
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     if (poisoned) C = kRowPoison | C;             // reads as overflowed, here and for every later reader
@@ -904,11 +923,20 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
             __syncthreads();
             uint32_t* ssel = seg_sel ? seg_sel + (size_t)row * nseg : nullptr;
             bool cast = false;
+            uint32_t first = part;
             if constexpr (KEEP <= 8) {
                 cast = done;
                 if (done) cast_votes_from_registers(whole.entry, C, kth, tie_cut, part, parts, votes32, lds.lvl, ssel);
             }
-            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, part, parts, votes32, lds.lvl, ssel);
+            if constexpr (!kWhole) {
+                uint32_t taken = 0;
+#pragma unroll
+                for (int i = 0; i < kOwn; ++i)
+                    taken |= ((part + i * parts) * kRowThreads + t < C && is_taken(own[i], kth, tie_cut) ? 1u : 0u) << i;
+                cast_votes<kOwn, false>(own, taken, votes32, lds.lvl, ssel);
+                first = part + kOwn * parts;
+            }
+            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, first, parts, votes32, lds.lvl, ssel);
             __syncthreads();
             merge_levels(lds.lvl, lvl_sets, blockIdx.x);
         }
