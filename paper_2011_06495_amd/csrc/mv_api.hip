@@ -50,6 +50,7 @@ struct Plan {
     uint32_t N, K;
     int64_t  d;
     uint32_t nseg;              // segments of 1024 coordinates per row
+    uint32_t n_runs;            // streaming workgroups per row, of 8 segments each
     uint32_t stride;            // every stride-th 32-coordinate chunk is sampled
     uint32_t n_sampled_chunks;  // per row
     uint64_t n_sampled;         // sampled coordinates per row
@@ -61,10 +62,8 @@ struct Plan {
     uint32_t list_blocks;       // workgroups per row of mv_ad_collect that walk the candidate list
     uint32_t split_blocks;      // workgroups per row of the many-workgroup select
     uint32_t emit_blocks;       // workgroups per row that write the sorted vote list
-    uint32_t scan_parts;        // workgroups per row that scan the segment tallies (4096 segments each)
     uint32_t select_parts;      // workgroups per row of mv_row_select when they also cast the votes
     uint32_t n_spec;            // list entries per thread that mv_row_select fetches ahead of the row's count
-    uint32_t scan_blocks;       // workgroups per row that scan the segment tallies
     // add-drop voting (only with MV_FLAG_ADD_DROP)
     bool     add_drop;
     uint32_t nwords, nwords_pad;  // 32-bit words of a row's vote bitmap, and padded to a multiple of 4
@@ -81,9 +80,8 @@ struct Plan {
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
     size_t off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
-    size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_seg, off_segsel,
-        off_segpre,
-        off_blktotal, off_alist, off_dlist, off_adcount, off_adbits, off_adblk, off_cand, off_votes, off_blockcnt, off_subcnt, off_votethr, off_emitfail,
+    size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_runs, off_runtaken,
+        off_alist, off_dlist, off_adcount, off_adbits, off_adblk, off_cand, off_votes, off_blockcnt, off_subcnt, off_votethr, off_emitfail,
         off_lookback;
     uint32_t n_zero_words;      // words from off_lvlsets on that a step's first kernel zeroes
     size_t total_bytes;
@@ -111,6 +109,7 @@ Plan make_plan(const mv_config* c)
     p.K = (uint32_t)c->k;
     p.d = c->d;
     p.nseg = (uint32_t)((p.d + mvk::kSeg - 1) / mvk::kSeg);
+    p.n_runs = (uint32_t)((p.d + mvk::kRun - 1) / mvk::kRun);
 
     // A row with exactly K coordinates above the threshold shows K * frac of them in a sample of frac * d
     // coordinates on average.  Ask for m sampled ones with m - 7 sqrt(m) = K * frac, never fewer than 128:
@@ -171,8 +170,8 @@ Plan make_plan(const mv_config* c)
 
     p.rs_blocks = (uint32_t)((p.d + mvk::kVoteBlock - 1) / mvk::kVoteBlock);
     {
-        // the mask kernels: as few vote bytes per thread as keep the grid, with one more workgroup per row for
-        // the segment scans, at two workgroups per compute unit: all resident at once, which the exchange of
+        // the mask kernels: as few vote bytes per thread as keep the grid, with one more workgroup per row, at two
+        // workgroups per compute unit: all resident at once, which the exchange of
         // counts between the blocks likes (measured: a limit of 500 beats 250 by 3 us on C4 and 13 us on C5;
         // 750 and more lose again on d = 11 M)
         static const uint32_t kQs[] = {1, 2, 3, 4, 6, 8};
@@ -186,8 +185,6 @@ Plan make_plan(const mv_config* c)
         const uint64_t per = (uint64_t)mvk::kMaskThreads * 16 * q;
         p.n_vote_blocks = (uint32_t)(((uint64_t)p.d + per - 1) / per);
     }
-    p.scan_blocks = (p.nseg + 1023) / 1024;
-    p.scan_parts = (p.nseg + 4095) / 4096;
     {
         // about 2K candidates are expected; fetch 3K per row ahead (never beyond the list's storage),
         // and give every workgroup of a row about four list entries per thread to cast votes for
@@ -204,7 +201,7 @@ Plan make_plan(const mv_config* c)
         p.select_parts = (uint32_t)parts;
         // beyond what one workgroup keeps in registers the lists go through the many-workgroup select
         p.multi_select = slots > (uint64_t)mvk::kKeepMost;
-        p.block_shift = 10;
+        p.block_shift = 13;                       // a run at least
         while (((p.d - 1) >> p.block_shift) >= mvk::kCoordBlocks) ++p.block_shift;
         // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
         uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
@@ -255,10 +252,8 @@ Plan make_plan(const mv_config* c)
     p.off_rsblk = off;    off += align_up((size_t)p.n_vote_blocks * 4);
     p.n_zero_words = (uint32_t)((off - p.off_lvlsets) / 4);
     off = align_up(off);
-    p.off_seg = off;      off += align_up((size_t)p.N * p.nseg * 8);
-    p.off_segsel = off;   off += align_up((size_t)p.N * p.nseg * 4);
-    p.off_segpre = off;   off += align_up((size_t)p.N * p.nseg * 4);
-    p.off_blktotal = off; off += align_up((size_t)p.N * ((p.nseg + 1023) / 1024) * 4);
+    p.off_runs = off;     off += align_up((size_t)p.N * p.n_runs * 8);
+    p.off_runtaken = off; off += align_up((size_t)p.N * p.n_runs * 4);
     p.off_cand = off;     off += align_up((size_t)p.N * p.cap * 8);
     p.off_votes = off;    off += align_up(((size_t)p.d + 15) / 16 * 16);
     p.off_blockcnt = off; off += align_up((size_t)p.n_vote_blocks * 8);
@@ -365,7 +360,7 @@ mv_status mv_begin(const mv_config* cfg, mv_ctx** out_ctx)
     // leave them at zero after every step.
     bool ok = hipMemset(c->ws + plan.off_hist, 0, plan.off_tau - plan.off_hist) == hipSuccess &&
               hipMemset(c->ws + plan.off_votes, 0, ((size_t)plan.d + 15) / 16 * 16) == hipSuccess &&
-              hipMemset(c->ws + plan.off_tau, 0, plan.off_seg - plan.off_tau) == hipSuccess;
+              hipMemset(c->ws + plan.off_tau, 0, plan.off_runs - plan.off_tau) == hipSuccess;
     if (ok && plan.add_drop)   // the scratch bitmaps start at zero and are left at zero by every step
         ok = hipMemset(c->ws + plan.off_adcount, 0,
                        plan.off_adbits - plan.off_adcount + (size_t)plan.N * plan.nwords_pad * 4) == hipSuccess;
@@ -450,10 +445,8 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     uint32_t* lvlsets = ws_ptr<uint32_t>(c, p.off_lvlsets);
     uint32_t* kth = ws_ptr<uint32_t>(c, p.off_kth);
     uint32_t* tiecut = ws_ptr<uint32_t>(c, p.off_tiecut);
-    uint32_t* segsel = ws_ptr<uint32_t>(c, p.off_segsel);
-    uint32_t* segpre = ws_ptr<uint32_t>(c, p.off_segpre);
-    uint32_t* blktotal = ws_ptr<uint32_t>(c, p.off_blktotal);
-    mvk::u32x2* seg = ws_ptr<mvk::u32x2>(c, p.off_seg);
+    mvk::u32x2* runs = ws_ptr<mvk::u32x2>(c, p.off_runs);
+    uint32_t* run_taken = ws_ptr<uint32_t>(c, p.off_runtaken);
     mvk::u32x2* cand = ws_ptr<mvk::u32x2>(c, p.off_cand);
     uint32_t* votes32 = ws_ptr<uint32_t>(c, p.off_votes);
     mvk::u32x2* blockcnt = ws_ptr<mvk::u32x2>(c, p.off_blockcnt);
@@ -550,29 +543,28 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
     {
-        const uint32_t wpr = (p.nseg + mvk::kSegPerBlock - 1) / mvk::kSegPerBlock;
-        const dim3 grid(p.N * p.sample_wgs + p.N * wpr);
+        const dim3 grid(p.N * p.sample_wgs + p.N * p.n_runs);
         before(KID_STREAM);
         if (bf16)
             hipLaunchKernelGGL(mvk::mv_stream_collect<uint16_t>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, seg, segsel, p.nseg, wpr, p.head_wgs,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.nseg, p.n_runs, p.head_wgs,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, seg, segsel, p.nseg, wpr, p.head_wgs,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.nseg, p.n_runs, p.head_wgs,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }
     // 2. exact per-row select; in plain voting and random selection the votes are cast in the same launch (short
     // lists: every workgroup of a row casts those of its share; long lists: many workgroups per row)
     const bool sorted = a.worker_idx != nullptr;
-    uint32_t* ssel = sorted ? segsel : nullptr;
+    uint32_t* tallies = sorted ? run_taken : nullptr;
     const int thresholds_only = add_drop ? 1 : 0;
     if (p.multi_select) {
         const dim3 grid(p.split_blocks, p.N);
@@ -583,7 +575,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         before(KID_SEL_SPLIT);
         hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
-                           kth, tiecut, a.worker_idx, votes32, ssel, p.nseg,
+                           kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs,
                            lvlsets, thresholds_only, taupub, p.block_shift);
         after(KID_SEL_SPLIT);
         uint32_t parts = add_drop ? 1 : 256 / p.N;
@@ -591,7 +583,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         before(KID_SEL_FINISH);
         hipLaunchKernelGGL(mvk::mv_sel_finish, dim3(parts, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist, kth, tiecut,
-                           votes32, ssel, p.nseg, lvlsets, thresholds_only, taupub, (const mvk::u32x2*)seg, p.block_shift);
+                           votes32, tallies, p.n_runs, lvlsets, thresholds_only, taupub, (const mvk::u32x2*)runs, p.block_shift);
         after(KID_SEL_FINISH);
     } else {
         const uint32_t parts = add_drop ? 1 : p.select_parts;
@@ -600,7 +592,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                                                                : &mvk::mv_row_select<mvk::kKeepMost>;
         hipLaunchKernelGGL(kernel, dim3((p.N + 7) / 8 * 8 * parts), dim3(mvk::kRowThreads), 0, st, a.err,
                            a.ld_e, p.d, p.N, p.K, cand, p.cap, rowcnt_sets, rowcnt_set_words, stepno, taupub, poison,
-                           rowcnt, tau, kth, tiecut, a.worker_idx, votes32, ssel, p.nseg, lvlsets, slow, parts, p.n_spec,
+                           rowcnt, tau, kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs, lvlsets, slow, parts, p.n_spec,
                            thresholds_only);
         after(KID_ROW_SELECT);
     }
@@ -667,41 +659,38 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                            (uint32_t)mvk::kMaskThreads * 16 * p.vote_q, p.n_vote_blocks, rsblk);
         after(KID_RS_PICK);
     }
-    // 4. global mask: the vote threshold and the counts per stretch of the vote bytes (in plain voting extra
-    // workgroups scan the segment tallies for the sorted vote lists), or the winners of the
-    // random selection in order; then 5. every workgroup of the last kernel gathers its part of the mask, takes the
-    // mean and updates the error buffers; extra workgroups write the sorted vote lists beside it.
+    // 4. global mask: the vote threshold, the counts per stretch of the vote bytes and the mask's coordinates, or the
+    // winners of the random selection in order (extra workgroups write the sorted vote lists beside it); then 5. every
+    // workgroup of the last kernel gathers its part of the mask, takes the mean and updates the error buffers.
     const bool lists = sorted && !add_drop;
     {
-        const dim3 grid_c(p.n_vote_blocks + (lists ? p.N : 0));
+        const dim3 grid_c(p.n_vote_blocks + (lists ? p.N * p.emit_blocks : 0));
         const dim3 block(mvk::kMaskThreads);
         uint8_t* votes_out = add_drop ? nullptr : a.votes;
         const float inv_n = 1.0f / (float)p.N;
         const uint32_t kb = mvk::kMaskThreads / p.N;
         // Up to kGatherRounds rounds of kb mask positions per gathering workgroup.  When one or two rounds keep
-        // the grid, with the sorted lists' workgroups, at about one workgroup per compute unit, that is best
-        // (C4: 216 workgroups); when they do not (large K, many rows), many short workgroups beat few long
-        // ones: two rounds and a grid of up to a thousand measured 4 us faster at K = d/100 than four rounds.
-        const uint32_t eb = p.emit_blocks;
-        const uint32_t n_list = lists ? p.N * eb : 0;
+        // the grid at about one workgroup per compute unit, that is best; when they do not (large K, many rows),
+        // many short workgroups beat few long ones: two rounds and a grid of up to a thousand measured 4 us
+        // faster at K = d/100 than four rounds.
         auto rounds_for = [&](uint32_t limit) {
-            const uint32_t room = n_list + 64 <= limit ? limit - n_list : 64;
-            uint32_t r = (uint32_t)(((uint64_t)p.K + (uint64_t)room * kb - 1) / ((uint64_t)room * kb));
+            uint32_t r = (uint32_t)(((uint64_t)p.K + (uint64_t)limit * kb - 1) / ((uint64_t)limit * kb));
             if (r > (uint32_t)mvk::kGatherRounds) r = mvk::kGatherRounds;
             return r < 1 ? 1u : r;
         };
         uint32_t rounds = rounds_for(250);
         if (rounds > 2) rounds = rounds_for(1000);
-        const uint32_t n_gather = (p.K + kb * rounds - 1) / (kb * rounds);
-        const dim3 grid_g(n_gather + n_list);
+        const dim3 grid_g((p.K + kb * rounds - 1) / (kb * rounds));
 #define MV_LAUNCH_MASK(Q)                                                                                        \
         before(KID_MASK_COUNT);                                                                                  \
         hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \
                            block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
-                           subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, p.scan_parts, p.scan_blocks,   \
-                           p.nseg,                                                                               \
-                           slow, segsel, segpre, blktotal, add_drop ? 1 : 0, lookback, emitfail, c->spin_limit,  \
-                           a.mask_idx, reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
+                           subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, p.emit_blocks,                 \
+                           (const mvk::u32x2*)cand, p.cap, (const uint32_t*)rowcnt, (const mvk::u32x2*)runs,     \
+                           (const uint32_t*)run_taken, p.n_runs, (const uint32_t*)kth, (const uint32_t*)tiecut,  \
+                           (const uint32_t*)slow, a.worker_idx,                                                  \
+                           add_drop ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
+                           reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
         after(KID_MASK_COUNT);                                                                                   \
         before(KID_GATHER);                                                                                      \
         hipLaunchKernelGGL(mvk::mv_gather_update<Q>, grid_g, block, 0, st, a.err, a.ld_e, p.d, p.N, p.K,          \
@@ -709,9 +698,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                            (const mvk::u32x2*)blockcnt, p.n_vote_blocks,                                         \
                            (const uint32_t*)votethr, a.mask_idx, random_sel ? 1 : 0,                             \
                            (const uint32_t*)emitfail, inv_n,                                                     \
-                           c->cfg.reduce == MV_REDUCE_MEAN ? 1 : 0, a.agg_vals, rounds, n_gather, eb,            \
-                           cand, p.cap, rowcnt, seg, p.nseg, segpre, blktotal, p.scan_blocks, kth, tiecut, slow, \
-                           a.worker_idx, stepno);                                                                \
+                           c->cfg.reduce == MV_REDUCE_MEAN ? 1 : 0, a.agg_vals, rounds, stepno);                                                            \
         after(KID_GATHER);
         switch (p.vote_q) {
             case 1: { MV_LAUNCH_MASK(1) } break;

@@ -16,6 +16,7 @@ constexpr int      kWave           = 64;
 constexpr int      kSeg            = 1024;   // coordinates per wavefront segment in the streaming pass
 constexpr int      kStreamThreads  = 512;    // 8 segments per workgroup
 constexpr int      kSegPerBlock    = kStreamThreads / kWave;
+constexpr int      kRun            = kSeg * kSegPerBlock;   // coordinates per streaming workgroup, whose candidates lie together
 constexpr int      kHistBits       = 13;     // sample histogram: exponent + 5 mantissa bits
 constexpr int      kHistBins       = 1 << kHistBits;
 constexpr int      kHistShift      = 31 - kHistBits;
@@ -23,7 +24,6 @@ constexpr int      kChunk          = 32;     // sampled chunk: 32 coordinates (o
 constexpr int      kRowThreads     = 1024;   // mv_row_select and the selects from lists
 constexpr int      kVoteBlock      = 16384;  // coordinates per workgroup of mv_rs_keys and of msum's level counts
 constexpr int      kVoteThreads    = 1024;   // mv_ad_emit and mv_rs_keys
-constexpr int      kMaxScanBlocks  = 2048;   // blocks of 1024 segments in a row of up to 2^31 coordinates
 constexpr uint32_t kAbsMask        = 0x7FFFFFFFu;
 constexpr int      kFineBins       = 2048;   // mv_row_select: histogram of the candidates' magnitudes above tau
 constexpr int      kFineShift      = 12;     // 2048 bins of 4096 bit patterns = one octave above tau

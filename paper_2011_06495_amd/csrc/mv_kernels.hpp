@@ -15,8 +15,8 @@
 //                         trusted) and publishes it.  The other workgroups
 //                         stream: a = g + e is written over e, and every
 //                         coordinate with |a| >= tau is appended to the row's
-//                         candidate list; each wavefront's 1024-coordinate
-//                         segment records where its run of candidates went.  A
+//                         candidate list; each workgroup
+//                         records where its run of candidates went.  A
 //                         streaming wavefront looks for its row's tau while its
 //                         loads are in flight and polls a bounded number of
 //                         times; a row whose wavefronts did not all see tau is
@@ -34,11 +34,10 @@
 //                         threshold from the level counters, the counts of every
 //                         block of the vote bytes, their sums across blocks
 //                         (published between the workgroups), and the mask's
-//                         coordinates written in place.  Extra workgroups scan
-//                         the segment tallies for the sorted vote lists
-//   4. mv_gather_update   masked gather, sum over workers in order, mean, and
-//                         the error update (zero on the mask); extra workgroups
+//                         coordinates written in place.  Extra workgroups
 //                         write each row's vote in ascending coordinate order
+//   4. mv_gather_update   masked gather, sum over workers in order, mean, and
+//                         the error update (zero on the mask)
 //   5. mv_ad_*            majority voting with add-drop (Algorithm 2): replaces
 //                         the vote casting by the update of the workers'
 //                         standing votes

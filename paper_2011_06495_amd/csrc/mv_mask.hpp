@@ -1,5 +1,5 @@
-// The global mask (counting sort over the vote levels, ordered emission), the sorted vote lists, and the
-// masked gather / mean / error update.
+// The global mask (counting sort over the vote levels, ordered emission) and beside it the sorted vote lists, then
+// the masked gather / mean / error update.
 //
 // These kernels are short (a few dependent memory round trips each), and the chip
 // starts only a few hundred workgroups per microsecond: they use workgroups of 1024
@@ -144,37 +144,127 @@ __device__ __forceinline__ void each_mask_position(const uint32_t (&marks)[Q], i
     }
 }
 
-// Exclusive scan of a row's segment tallies for the sorted vote lists, 4096 segments
-// at a time: seg_pre[s] = taken candidates in the earlier segments of s's block of
-// 1024 segments, and blk_total[blk] = taken candidates in the whole block.
-__device__ __forceinline__ void seg_scan_part(const uint32_t* __restrict__ ssel, uint32_t nseg,
-                                              uint32_t part, uint32_t* __restrict__ spre,
-                                              uint32_t* __restrict__ blk_total, uint64_t* scan_lds,
-                                              uint32_t* bound /*LDS, 5*/)
+// ---- the sorted vote lists
+constexpr int kMaskWaves = kMaskThreads / kWave;
+constexpr int kEmitUnroll = 4;                    // list entries per thread in flight together
+constexpr int kEmitBatch = kMaskThreads * kEmitUnroll;
+constexpr int kListRuns = 4 * kMaskThreads;       // prefixes of a row's tallies in LDS, four to a thread
+static_assert(kEmitUnroll * kMaskWaves == kWave, "a lane per wavefront's part of a batch");
+struct EmitLds {
+    uint32_t before[kListRuns];                   // taken entries in the runs before
+    uint32_t wave_taken[kEmitUnroll * kMaskWaves];
+    uint32_t wave_earlier[kMaskWaves];
+    uint16_t number[kEmitBatch];                  // taken entries of the batch before each of its entries
+};
+
+// A row's vote list in ascending coordinate order, without a sort: a taken candidate's rank is (taken
+// candidates in the runs before its own, from the tallies) + (before it in its own run; runs are ascending).
+// A few workgroups per row (`part` of `parts`); each adds up the row's tallies for itself, which are few (1364 for
+// 11.2 M coordinates) and arrive beside the entries.  Run beside the mask kernel's blocks, which mostly wait, and not
+// beside the gather, the lists cost a step less (1 x 16 M, K = 16,000: 97.5 -> 93.4 us, 4 x 2,000,003, K = 20,000: 69.7 -> 68.8;
+// where the scattered traffic of the gather is the bound, nothing: 10 x 11.2 M, K = 111,740).
+__device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, uint32_t C,
+                                               const u32x2* __restrict__ runs, const uint32_t* __restrict__ run_taken,
+                                               uint32_t n_runs, uint32_t K, uint32_t kth, uint32_t tie_cut,
+                                               uint32_t part, uint32_t parts, uint32_t* __restrict__ out, EmitLds& lds,
+                                               uint64_t* scan_lds)
 {
-    const uint32_t t = threadIdx.x;
-    const uint32_t s0 = part * 4096u + t * 4u;
-    uint32_t v[4];
-    uint32_t sum = 0;
+    if ((uint64_t)part * kEmitBatch >= C) return;            // whole workgroup
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    u32x2 c[kEmitUnroll];
+    uint32_t run0[kEmitUnroll], first_run = 0;    // where the entries' runs begin, and the first entry's of the batch
+    auto load = [&](uint64_t i0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        v[q] = (s0 + q < nseg) ? ssel[s0 + q] : 0u;
-        sum += v[q];
+        for (int u = 0; u < kEmitUnroll; ++u) {
+            const uint64_t i = i0 + (uint64_t)u * kMaskThreads + t;
+            const u32x2 none = {0u, 0xFFFFFFFFu};
+            c[u] = (i < C) ? crow[i] : none;
+        }
+        first_run = crow[i0].y / kRun;            // uniform
+    };
+    auto load_runs = [&]() {
+#pragma unroll
+        for (int u = 0; u < kEmitUnroll; ++u) run0[u] = c[u].y != 0xFFFFFFFFu ? runs[c[u].y / kRun].x : 0u;
+        first_run = runs[first_run].x;
+    };
+    load((uint64_t)part * kEmitBatch);
+    // `per` runs to a prefix: one, in rows of up to 33.5 M coordinates
+    const uint32_t per = (n_runs + kListRuns - 1) / kListRuns;
+    {
+        uint32_t v[4];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t r0 = (4u * t + q) * per;
+            v[q] = r0 < n_runs ? run_taken[r0] : 0u;
+            for (uint32_t r = r0 + 1; r < min(r0 + per, n_runs); ++r) v[q] += run_taken[r];
+        }
+        load_runs();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sum += v[q];
+        uint32_t total;
+        uint32_t ex = block_excl_scan<kMaskThreads>(sum, scan_lds, total);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            lds.before[4u * t + q] = ex;
+            ex += v[q];
+        }
     }
-    uint32_t total;
-    uint32_t ex = block_excl_scan<kMaskThreads>(sum, scan_lds, total);
-    if ((t & 255u) == 0u) bound[t >> 8] = ex;                // threads 256 k .. 256 k + 255 hold block k of the four
-    if (t == 0) bound[4] = total;
     __syncthreads();
-    const uint32_t k = t >> 8;
-    ex -= bound[k];
+    // A workgroup takes kEmitBatch consecutive entries at a time and numbers the taken ones; an entry's rank
+    // inside its run is the difference of two such numbers.  Only the first entry's run can have begun before
+    // the batch: that part (fewer than kRun entries) is counted by all threads together.
+    for (uint64_t i0 = (uint64_t)part * kEmitBatch; i0 < C; i0 += (uint64_t)parts * kEmitBatch) {
+        if (i0 != (uint64_t)part * kEmitBatch) {
+            load(i0);
+            load_runs();
+        }
+        uint32_t n_earlier = 0;
+        {
+            constexpr uint32_t kStride = kMaskThreads * 4;
+            for (uint64_t j0 = first_run; j0 < i0; j0 += kStride) {  // uniform: twice at most
+                u32x2 x[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (s0 + q < nseg) spre[s0 + q] = ex;
-        ex += v[q];
+                for (int q = 0; q < 4; ++q) x[q] = crow[min(j0 + (uint32_t)q * kMaskThreads + t, i0 - 1)];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    n_earlier += (uint32_t)__popcll(
+                        __ballot(j0 + (uint32_t)q * kMaskThreads + t < i0 && is_taken(x[q], kth, tie_cut)));
+            }
+        }
+        uint32_t mine[kEmitUnroll];               // taken ones in the lanes below
+        uint32_t taken = 0;
+#pragma unroll
+        for (int u = 0; u < kEmitUnroll; ++u) {
+            const bool tk = c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut);
+            const uint64_t all = __ballot(tk);
+            taken |= (tk ? 1u : 0u) << u;
+            mine[u] = (uint32_t)__popcll(all & ((1ull << lane) - 1ull));
+            if (lane == 0) lds.wave_taken[u * kMaskWaves + wave] = (uint32_t)__popcll(all);
+        }
+        if (lane == 0) lds.wave_earlier[wave] = n_earlier;
+        __syncthreads();
+        // the taken ones before each wavefront's part of the batch, in the order of the entries
+        const uint32_t batch_part = lds.wave_taken[lane];
+        const uint32_t before = wave_incl_scan(batch_part) - batch_part;
+        const uint32_t carry_lanes = row_incl_scan(lane < (uint32_t)kMaskWaves ? lds.wave_earlier[lane] : 0u);
+        const uint32_t carry = from_lane(carry_lanes, kMaskWaves - 1);
+#pragma unroll
+        for (int u = 0; u < kEmitUnroll; ++u) {
+            mine[u] += from_lane(before, (uint32_t)u * kMaskWaves + wave);
+            lds.number[u * kMaskThreads + t] = (uint16_t)mine[u];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kEmitUnroll; ++u)
+            if (taken >> u & 1u) {
+                const uint32_t r = c[u].y / kRun, p = r / per;
+                uint32_t pos = lds.before[p] + (run0[u] >= i0 ? mine[u] - lds.number[run0[u] - i0] : mine[u] + carry);
+                for (uint32_t q = p * per; q < r; ++q) pos += run_taken[q];
+                if (pos < K) out[pos] = c[u].y;
+            }
+        __syncthreads();                          // the scratch is free for the next batch
     }
-    if ((t & 255u) == 0u && part * 4u + k < (nseg + 1023u) / 1024u) blk_total[part * 4u + k] = bound[k + 1] - bound[k];
-    __syncthreads();                              // the LDS scratch is free for the next part
 }
 
 // Random selection: the winners are marked in a bitmap and counted per block already, so a block's
@@ -209,7 +299,7 @@ __device__ __forceinline__ void write_winners(uint16_t* __restrict__ halves, con
 // threshold (also per wavefront's stretch of 1024 Q coordinates), exchange the counts
 // with the other blocks and write the block's part of the mask; optionally copy the vote
 // bytes to the caller.  Workgroups beyond (only launched when the sorted vote lists are
-// wanted): one per row, scanning the row's segment tallies.  RANDOM: the mask comes from
+// wanted): emit_blocks per row, writing the row's list.  RANDOM: the mask comes from
 // the winners' bitmap.
 template <int Q, bool RANDOM>
 __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __restrict__ votes32,
@@ -219,12 +309,15 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
                                                               u32x2* __restrict__ block_cnt,
                                                               uint32_t* __restrict__ vote_thr,
                                                               uint8_t* __restrict__ votes_out,
-                                                              uint32_t n_vote_blocks, uint32_t scan_parts,
-                                                              uint32_t scan_blocks, uint32_t nseg,
+                                                              uint32_t n_vote_blocks, uint32_t emit_blocks,
+                                                              const u32x2* __restrict__ cand, uint32_t cap,
+                                                              const uint32_t* __restrict__ row_count,
+                                                              const u32x2* __restrict__ runs,
+                                                              const uint32_t* __restrict__ run_taken, uint32_t n_runs,
+                                                              const uint32_t* __restrict__ kth_in,
+                                                              const uint32_t* __restrict__ tie_cut_in,
                                                               const uint32_t* __restrict__ slow_flag,
-                                                              const uint32_t* __restrict__ seg_sel,
-                                                              uint32_t* __restrict__ seg_pre,
-                                                              uint32_t* __restrict__ blk_total,
+                                                              uint32_t* __restrict__ worker_idx,
                                                               int exact_levels,
                                                               unsigned long long* __restrict__ lookback,
                                                               uint32_t* __restrict__ emit_fail, uint32_t spin_limit,
@@ -235,14 +328,15 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     __shared__ uint32_t lvl[256];
     __shared__ uint32_t thr[2];
     __shared__ uint64_t scan_lds[kMaskThreads / kWave + 1];
-    __shared__ uint32_t bound[5];
+    __shared__ uint32_t mask_found;
     __shared__ uint64_t before_sh;
     if (blockIdx.x >= n_vote_blocks) {
-        const uint32_t row = blockIdx.x - n_vote_blocks;       // one workgroup per row
-        if (slow_flag[row] == 1u) return;
-        for (uint32_t part = 0; part < scan_parts; ++part)
-            seg_scan_part(seg_sel + (size_t)row * nseg, nseg, part, seg_pre + (size_t)row * nseg,
-                          blk_total + (size_t)row * scan_blocks, scan_lds, bound);
+        __shared__ EmitLds emit;
+        const uint32_t row = (blockIdx.x - n_vote_blocks) / emit_blocks, part = (blockIdx.x - n_vote_blocks) % emit_blocks;
+        if (slow_flag[row] == 1u) return;                      // its list is written already
+        write_row_list(cand + (size_t)row * cap, row_count[row], runs + (size_t)row * n_runs,
+                       run_taken + (size_t)row * n_runs, n_runs, K, kth_in[row], tie_cut_in[row], part, emit_blocks,
+                       worker_idx + (size_t)row * K, emit, scan_lds);
         return;
     }
     // the block's vote words first: their latency overlaps the level counters' loads.
@@ -362,11 +456,11 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
             else
                 __hip_atomic_store(emit_fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             before_sh = before;
-            bound[0] = found ? 1u : 0u;
+            mask_found = found ? 1u : 0u;
         }
     }
     __syncthreads();
-    if (bound[0] == 0u) return;                   // whole workgroup
+    if (mask_found == 0u) return;                   // whole workgroup
     const uint64_t before = before_sh;
     if ((uint32_t)(before >> 32) + min((uint32_t)before, take_eq) >= K) return;   // the mask is full before this block
     each_mask_position<Q>(marks, j0, (uint32_t)((before + ex) >> 32), (uint32_t)(before + ex), take_eq,
@@ -376,115 +470,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
 }
 
 // ----------------------------------------------------------------------------
-// 6. masked gather, ordered sum over workers, mean, error update; beside it, the
-//    sorted vote lists
+// 6. masked gather, ordered sum over workers, mean, error update
 // ----------------------------------------------------------------------------
-
-constexpr int kMaskWaves = kMaskThreads / kWave;
-constexpr int kEmitUnroll = 4;                    // list entries per thread in flight together
-constexpr int kEmitBatch = kMaskThreads * kEmitUnroll;
-static_assert(kEmitUnroll * kMaskWaves == kWave, "a lane per wavefront's part of a batch");
-struct EmitLds {
-    uint32_t blk_pre[kMaxScanBlocks];
-    uint32_t wave_taken[kEmitUnroll * kMaskWaves];
-    uint32_t wave_earlier[kMaskWaves];
-    uint16_t number[kEmitBatch];                  // taken entries of the batch before each of its entries
-};
-
-// A row's vote list in ascending coordinate order, without a sort: a taken
-// candidate's rank is (taken candidates in earlier blocks of 1024 segments, from
-// blk_total) + (in earlier segments of its block, from seg_pre) + (before it in its
-// own segment's run; runs are ascending).
-__device__ __forceinline__ void row_emit_block(const u32x2* __restrict__ crow, uint32_t C,
-                                               const u32x2* __restrict__ srow,
-                                               const uint32_t* __restrict__ prow,
-                                               const uint32_t* __restrict__ blk_total, uint32_t scan_blocks,
-                                               uint32_t K, uint32_t kth, uint32_t tie_cut, uint32_t blk,
-                                               uint32_t nblk, uint32_t* __restrict__ out, EmitLds& lds,
-                                               uint64_t* scan_lds)
-{
-    if ((uint64_t)blk * kEmitBatch >= C) return;             // whole workgroup
-    uint32_t* blk_pre = lds.blk_pre;
-    // exclusive prefix of the blocks' totals, once per workgroup
-    {
-        constexpr int per = kMaxScanBlocks / kMaskThreads;
-        uint32_t v[per];
-        uint32_t sum = 0;
-#pragma unroll
-        for (int q = 0; q < per; ++q) {
-            const uint32_t b = threadIdx.x * per + q;
-            v[q] = (b < scan_blocks) ? blk_total[b] : 0u;
-            sum += v[q];
-        }
-        uint32_t total;
-        uint32_t ex = block_excl_scan<kMaskThreads>(sum, scan_lds, total);
-#pragma unroll
-        for (int q = 0; q < per; ++q) {
-            blk_pre[threadIdx.x * per + q] = ex;
-            ex += v[q];
-        }
-        __syncthreads();
-    }
-    // A workgroup takes kEmitBatch consecutive entries at a time and numbers the taken ones; an entry's rank
-    // inside its run is the difference of two such numbers.  Only the first entry's run can have begun before
-    // the batch (a run has at most kSeg entries): that part is counted by all threads together, one load each.
-    // (Counted by each wavefront for itself, 64 entries after the other, dense rows kept the kernel waiting:
-    // 4 x 2^20, K = 10,486: the last kernel took 8.2 us instead of 6.6.)
-    static_assert(kSeg <= kMaskThreads, "one load per thread covers a run");
-    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (uint64_t i0 = (uint64_t)blk * kEmitBatch; i0 < C; i0 += (uint64_t)nblk * kEmitBatch) {
-        u32x2 c[kEmitUnroll];
-#pragma unroll
-        for (int u = 0; u < kEmitUnroll; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * kMaskThreads + threadIdx.x;
-            const u32x2 none = {0u, 0xFFFFFFFFu};
-            c[u] = (i < C) ? crow[i] : none;
-        }
-        uint32_t seg_before[kEmitUnroll], run0[kEmitUnroll];
-        const uint32_t first_run = srow[crow[i0].y / kSeg].x;         // uniform: where the first entry's run begins
-#pragma unroll
-        for (int u = 0; u < kEmitUnroll; ++u) {
-            const uint32_t sg = c[u].y / kSeg;                // 0x3FFFFF for lanes past the end
-            const bool there = c[u].y != 0xFFFFFFFFu;
-            seg_before[u] = there ? prow[sg] + blk_pre[sg / 1024u] : 0u;
-            run0[u] = there ? srow[sg].x : 0u;
-        }
-        const uint64_t j = (uint64_t)first_run + threadIdx.x;
-        const bool earlier = j < i0 && is_taken(crow[j], kth, tie_cut);
-        const uint32_t n_earlier = (uint32_t)__popcll(__ballot(earlier));
-        uint32_t mine[kEmitUnroll];               // taken ones in the lanes below
-        uint32_t taken = 0;
-#pragma unroll
-        for (int u = 0; u < kEmitUnroll; ++u) {
-            const bool tk = c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut);
-            const uint64_t all = __ballot(tk);
-            taken |= (tk ? 1u : 0u) << u;
-            mine[u] = (uint32_t)__popcll(all & ((1ull << lane) - 1ull));
-            if (lane == 0) lds.wave_taken[u * kMaskWaves + wave] = (uint32_t)__popcll(all);
-        }
-        if (lane == 0) lds.wave_earlier[wave] = n_earlier;
-        __syncthreads();
-        // the taken ones before each wavefront's part of the batch, in the order of the entries
-        const uint32_t part = lds.wave_taken[lane];
-        const uint32_t before = wave_incl_scan(part) - part;
-        const uint32_t carry_lanes = row_incl_scan(lane < (uint32_t)kMaskWaves ? lds.wave_earlier[lane] : 0u);
-        const uint32_t carry = from_lane(carry_lanes, kMaskWaves - 1);
-#pragma unroll
-        for (int u = 0; u < kEmitUnroll; ++u) {
-            mine[u] += from_lane(before, (uint32_t)u * kMaskWaves + wave);
-            lds.number[u * kMaskThreads + threadIdx.x] = (uint16_t)mine[u];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < kEmitUnroll; ++u)
-            if (taken >> u & 1u) {
-                const uint32_t rank = run0[u] >= i0 ? mine[u] - lds.number[run0[u] - i0] : mine[u] + carry;
-                const uint32_t pos = seg_before[u] + rank;
-                if (pos < K) out[pos] = c[u].y;
-            }
-        __syncthreads();                          // the scratch is free for the next batch
-    }
-}
 
 // Positions [k0, k1) of the mask, whose coordinates are in slice[0 .. k1 - k0), at most `rounds` times
 // kMaskThreads / N of them: thread (n, kl) reads a[n][j], stores +0.0 there, and parks the value in LDS;
@@ -543,8 +530,7 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
     }
 }
 
-// Workgroups [0, n_gather_blocks): each owns `rounds` times kb = 1024 / N consecutive
-// positions of the mask.
+// A workgroup owns `rounds` times kb = 1024 / N consecutive positions of the mask.
 // (a) Unless the mask is there (it is, but for a block that gave up waiting), the workgroup
 //     first finds its own positions' coordinates: the counts per block of the vote bytes
 //     and, inside the few blocks that matter, per wavefront stretch (from mv_mask_count)
@@ -555,16 +541,12 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
 // (b) gather_positions reads a[n][mask[k]] (held in e), stores +0.0 there (the error
 //     update: the residual of a transmitted coordinate is zero), adds the N values in
 //     worker order 0..N-1 in fp32 and applies the 1/N of the mean once.
-// Workgroups beyond (only launched when the sorted vote lists are wanted): write
-// row (b / emit_blocks)'s vote list; they start after the gather's workgroups and
-// run beside them.
 struct GatherLds {
     float    tile[kTileFloats];
     uint32_t slice[kGatherRounds * kMaskThreads];              // the workgroup's positions' coordinates
     uint32_t need[3 * (kMaskThreads + 2)];                     // stretches to read: (stretch, above before, at before)
     uint32_t blocks[3 * (kMaskThreads + 2)];                   // blocks whose stretches are looked at
     uint32_t n_need, n_blocks;
-    EmitLds  emit;
     uint64_t scan[kMaskThreads / kWave];
 };
 
@@ -579,30 +561,9 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
                                                                  const uint32_t* __restrict__ emit_fail,
                                                                  float scale, int apply_scale,
                                                                  float* __restrict__ agg, uint32_t rounds,
-                                                                 uint32_t n_gather_blocks, uint32_t emit_blocks,
-                                                                 const u32x2* __restrict__ cand, uint32_t cap,
-                                                                 const uint32_t* __restrict__ row_count,
-                                                                 const u32x2* __restrict__ seg, uint32_t nseg,
-                                                                 const uint32_t* __restrict__ seg_pre,
-                                                                 const uint32_t* __restrict__ blk_total,
-                                                                 uint32_t scan_blocks,
-                                                                 const uint32_t* __restrict__ kth_in,
-                                                                 const uint32_t* __restrict__ tie_cut_in,
-                                                                 const uint32_t* __restrict__ slow_flag,
-                                                                 uint32_t* __restrict__ worker_idx,
                                                                  uint32_t* __restrict__ step_no)
 {
     __shared__ GatherLds lds;
-    if (blockIdx.x >= n_gather_blocks) {
-        const uint32_t b = blockIdx.x - n_gather_blocks;
-        const uint32_t row = b / emit_blocks;
-        if (slow_flag[row] == 1u) return;
-        row_emit_block(cand + (size_t)row * cap, row_count[row], seg + (size_t)row * nseg,
-                       seg_pre + (size_t)row * nseg, blk_total + (size_t)row * scan_blocks, scan_blocks, K,
-                       kth_in[row], tie_cut_in[row], b % emit_blocks, emit_blocks,
-                       worker_idx + (size_t)row * K, lds.emit, lds.scan);
-        return;
-    }
     const uint32_t kb = kMaskThreads / N;             // N <= 255, so kb >= 4
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
     // This is the step's last kernel and nothing in it reads the step's number: the next step

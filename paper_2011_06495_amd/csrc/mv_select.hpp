@@ -445,13 +445,13 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
 }
 
 // Casts votes for the marked ones of a batch of list entries, U per thread (bit u of `taken`: c[u]): each
-// adds one to its coordinate's vote byte and, when the sorted vote lists are wanted (ssel != nullptr), is
-// tallied in its 1024-coordinate segment (ssel was zeroed by the streaming pass).  Lanes of a wavefront
-// mostly hold consecutive list entries, which share a segment (they are one run): the first lane of each
-// group of equal segments adds the group's count.  All threads of the workgroup must call it.
+// adds one to its coordinate's vote byte and, when the sorted vote lists are wanted (run_taken != nullptr), is
+// tallied in its run (run_taken was zeroed by the streaming pass).  Lanes of a wavefront
+// mostly hold consecutive list entries, which share a run: the first lane of each
+// group of equal runs adds the group's count.  All threads of the workgroup must call it.
 template <int U, bool MERGE>
 __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_mask, uint32_t* __restrict__ votes32,
-                                           uint32_t* lvl, uint32_t* __restrict__ ssel)
+                                           uint32_t* lvl, uint32_t* __restrict__ run_taken)
 {
     const uint32_t lane = lane_id();
     // MERGE (long lists, where the atomics' rate at the memory side is what the step waits for): lanes
@@ -499,7 +499,7 @@ __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_m
     for (int u = 0; u < U; ++u) {
         const bool taken = (taken_mask >> u) & 1u;
         if (taken) atomicAdd(&lvl[((old[u] >> ((c[u].y & 3u) * 8u)) & 255u) + 1u], 1u);
-        if (ssel) tally_groups(c[u].y / kSeg, taken, [&](uint32_t sg, uint32_t n) { atomicAdd(&ssel[sg], n); });
+        if (run_taken) tally_groups(c[u].y / kRun, taken, [&](uint32_t r, uint32_t n) { atomicAdd(&run_taken[r], n); });
     }
 }
 
@@ -507,7 +507,7 @@ __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_m
 __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ crow, uint32_t C, uint32_t kth,
                                                     uint32_t tie_cut, uint32_t part, uint32_t parts,
                                                     uint32_t* __restrict__ votes32, uint32_t* lvl,
-                                                    uint32_t* __restrict__ ssel)
+                                                    uint32_t* __restrict__ run_taken)
 {
     // all the loads, then all the vote atomics, then what depends on their results: a thread's
     // entries wait for memory together, not one after the other
@@ -524,7 +524,7 @@ __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ cr
 #pragma unroll
         for (int u = 0; u < kU; ++u)
             taken |= (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
-        cast_votes<kU, false>(c, taken, votes32, lvl, ssel);
+        cast_votes<kU, false>(c, taken, votes32, lvl, run_taken);
     }
 }
 
@@ -718,7 +718,7 @@ __device__ __forceinline__ bool select_from_registers(const Kept& kept, const u3
 template <int KEEP>
 __device__ __forceinline__ void cast_votes_from_registers(u32x2 (&entry)[KEEP], uint32_t C, uint32_t kth, uint32_t tie_cut,
                                                           uint32_t part, uint32_t parts, uint32_t* __restrict__ votes32,
-                                                          uint32_t* lvl, uint32_t* __restrict__ ssel)
+                                                          uint32_t* lvl, uint32_t* __restrict__ run_taken)
 {
     uint32_t taken = 0;
     uint32_t next = part;                         // the workgroup's next q
@@ -738,9 +738,9 @@ __device__ __forceinline__ void cast_votes_from_registers(u32x2 (&entry)[KEEP], 
             next += parts;
             const bool mine = taken >> q & 1u;
             if (mine) atomicAdd(&lvl[((entry[q].x >> ((entry[q].y & 3u) * 8u)) & 255u) + 1u], 1u);
-            if (ssel)
-                tally_groups((uint32_t)q * kRowThreads + threadIdx.x < C ? entry[q].y / kSeg : 0xFFFFFFFFu, mine,
-                             [&](uint32_t sg, uint32_t n) { atomicAdd(&ssel[sg], n); });
+            if (run_taken)
+                tally_groups((uint32_t)q * kRowThreads + threadIdx.x < C ? entry[q].y / kRun : 0xFFFFFFFFu, mine,
+                             [&](uint32_t r, uint32_t n) { atomicAdd(&run_taken[r], n); });
         }
 }
 
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     const unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ row_poison,
     uint32_t* __restrict__ cand_count, uint32_t* __restrict__ tau_bits, uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out,
     uint32_t* __restrict__ worker_idx, uint32_t* __restrict__ votes32,
-    uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
+    uint32_t* __restrict__ run_tallies, uint32_t n_runs, uint32_t* __restrict__ lvl_sets,
     uint32_t* __restrict__ slow_flag, uint32_t parts, uint32_t n_spec, int thresholds_only)
 {
     __shared__ SelectLds lds;
@@ -921,22 +921,22 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
         if (!thresholds_only) {
             for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;
             __syncthreads();
-            uint32_t* ssel = seg_sel ? seg_sel + (size_t)row * nseg : nullptr;
+            uint32_t* run_taken = run_tallies ? run_tallies + (size_t)row * n_runs : nullptr;
             bool cast = false;
             uint32_t first = part;
             if constexpr (KEEP <= 8) {
                 cast = done;
-                if (done) cast_votes_from_registers(whole.entry, C, kth, tie_cut, part, parts, votes32, lds.lvl, ssel);
+                if (done) cast_votes_from_registers(whole.entry, C, kth, tie_cut, part, parts, votes32, lds.lvl, run_taken);
             }
             if constexpr (!kWhole) {
                 uint32_t taken = 0;
 #pragma unroll
                 for (int i = 0; i < kOwn; ++i)
                     taken |= ((part + i * parts) * kRowThreads + t < C && is_taken(own[i], kth, tie_cut) ? 1u : 0u) << i;
-                cast_votes<kOwn, false>(own, taken, votes32, lds.lvl, ssel);
+                cast_votes<kOwn, false>(own, taken, votes32, lds.lvl, run_taken);
                 first = part + kOwn * parts;
             }
-            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, first, parts, votes32, lds.lvl, ssel);
+            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, first, parts, votes32, lds.lvl, run_taken);
             __syncthreads();
             merge_levels(lds.lvl, lvl_sets, blockIdx.x);
         }
@@ -1343,13 +1343,13 @@ struct BigGroup {
 };
 
 // The coordinate of the want-th of a row's candidates with this key, in coordinate order, `count` being the
-// thread's two counters of v.blocks: the block it lies in, its segment among the block's, its place in the
-// segment's run (runs are ascending).
+// thread's two counters of v.blocks: the block it lies in, its run among the block's, its place in the
+// run (runs are ascending).
 template <typename Lds>
 __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const uint32_t (&count)[2], uint32_t key,
-                                                      uint32_t want, const u32x2* __restrict__ srow, uint32_t nseg, Lds& lds)
+                                                      uint32_t want, const u32x2* __restrict__ runs, uint32_t n_runs, Lds& lds)
 {
-    static_assert(kCoordBlocks == 2 * kRowThreads && kSeg == kRowThreads, "two blocks to a thread, a thread per entry of a run");
+    static_assert(kCoordBlocks == 2 * kRowThreads, "two blocks to a thread");
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
     uint32_t total;
     uint32_t ex = block_excl_scan<kRowThreads>(count[0] + count[1], lds.scan, total);
@@ -1362,26 +1362,29 @@ __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const u
         ex += count[q];
     }
     __syncthreads();
-    const uint32_t per_block = 1u << (v.block_shift - 10);           // segments: at most 1024
-    const uint32_t s0 = lds.bcast[0] * per_block, n_segs = min(per_block, nseg - s0);
+    static_assert(kCoordBlocks << 7 >= (1ll << 31) / kRun, "at most 128 runs to a block of a row of up to 2^31 coordinates");
+    const uint32_t per_block = (1u << v.block_shift) / kRun;         // runs: at most 128
+    const uint32_t r0 = lds.bcast[0] * per_block, n_here = min(per_block, n_runs - r0);
     want = lds.bcast[1];
     __syncthreads();
-    if (n_segs > 1) {                             // uniform: a wavefront per segment counts
-        for (uint32_t i = wave; i < n_segs; i += kRowThreads / kWave) {
-            const u32x2 run = srow[s0 + i];
-            uint32_t k[kSeg / kWave];
+    if (n_here > 1) {                             // uniform: a wavefront per run counts
+        for (uint32_t i = wave; i < n_here; i += kRowThreads / kWave) {
+            const u32x2 run = runs[r0 + i];
             uint32_t n = 0;
+            for (uint32_t j0 = 0; j0 < run.y; j0 += 16 * kWave) {    // (wave-uniform)
+                uint32_t k[16];
 #pragma unroll
-            for (int q = 0; q < kSeg / kWave; ++q) {
-                const uint32_t j = (uint32_t)q * kWave + lane;
-                k[q] = j < run.y ? v.list[run.x + j].x : 0xFFFFFFFFu;
+                for (int q = 0; q < 16; ++q) {
+                    const uint32_t j = j0 + (uint32_t)q * kWave + lane;
+                    k[q] = j < run.y ? v.list[run.x + j].x : 0xFFFFFFFFu;
+                }
+#pragma unroll
+                for (int q = 0; q < 16; ++q) n += (uint32_t)__popcll(__ballot(k[q] == key));
             }
-#pragma unroll
-            for (int q = 0; q < kSeg / kWave; ++q) n += (uint32_t)__popcll(__ballot(k[q] == key));
             if (lane == 0) lds.hist[i] = n;
         }
         __syncthreads();
-        const uint32_t mine = t < n_segs ? lds.hist[t] : 0u;
+        const uint32_t mine = t < n_here ? lds.hist[t] : 0u;
         ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
         if (ex < want && want <= ex + mine) {
             lds.bcast[0] = t;
@@ -1393,13 +1396,24 @@ __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const u
         lds.bcast[0] = 0;
     }
     __syncthreads();
-    const u32x2 run = srow[s0 + lds.bcast[0]];
+    const u32x2 run = runs[r0 + lds.bcast[0]];
     __syncthreads();
-    const u32x2 none = {0u, 0u};
-    const u32x2 c = t < run.y ? v.list[run.x + t] : none;
-    const bool tie = t < run.y && c.x == key;
-    ex = block_excl_scan<kRowThreads>(tie ? 1u : 0u, lds.scan, total);
-    if (tie && ex == want - 1) lds.bcast[0] = c.y;
+    // the run, kPer entries to a thread
+    constexpr int kPer = kRun / kRowThreads;
+    u32x2 c[kPer];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const uint32_t j = t * kPer + q;
+        const u32x2 none = {0xFFFFFFFFu, 0u};     // no key
+        c[q] = j < run.y ? v.list[run.x + j] : none;
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) mine += c[q].x == key;
+    ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (c[q].x == key && ++ex == want) lds.bcast[0] = c[q].y;
     __syncthreads();
     const uint32_t cut = lds.bcast[0];
     __syncthreads();
@@ -1617,11 +1631,11 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
 
 // Votes for the marked entries of a batch; with thresholds_only (add-drop voting) none are cast.
 struct CastVotes {
-    uint32_t *votes32, *lvl, *ssel;
+    uint32_t *votes32, *lvl, *run_taken;
     int thresholds_only;
     __device__ __forceinline__ void operator()(const u32x2 (&c)[kListUnroll], uint32_t taken) const
     {
-        if (!thresholds_only) cast_votes<kListUnroll, true>(c, taken, votes32, lvl, ssel);
+        if (!thresholds_only) cast_votes<kListUnroll, true>(c, taken, votes32, lvl, run_taken);
     }
 };
 
@@ -1638,7 +1652,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist,
     uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
-    uint32_t* __restrict__ votes32, uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t* __restrict__ lvl_sets,
+    uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, uint32_t n_runs, uint32_t* __restrict__ lvl_sets,
     int thresholds_only, unsigned long long* __restrict__ tau_pub, uint32_t block_shift)
 {
     __shared__ SplitLds<kMembers> lds;
@@ -1651,7 +1665,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     }
     const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift);
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
-    const CastVotes act = {votes32, lds.lvl, seg_sel ? seg_sel + (size_t)row * nseg : nullptr, thresholds_only};
+    const CastVotes act = {votes32, lds.lvl, run_tallies ? run_tallies + (size_t)row * n_runs : nullptr, thresholds_only};
     uint32_t kth, tie_cut;
     ListRest rest;
     (void)list_split<SplitEnd::Later>(v, blockIdx.x, gridDim.x, lds, act, kth, tie_cut, rest);
@@ -1672,9 +1686,9 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
 __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
     u32x2* cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist, uint32_t* __restrict__ kth_out,
-    uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ votes32, uint32_t* __restrict__ seg_sel, uint32_t nseg,
+    uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, uint32_t n_runs,
     uint32_t* __restrict__ lvl_sets, int thresholds_only, unsigned long long* __restrict__ tau_pub,
-    const u32x2* __restrict__ seg, uint32_t block_shift)
+    const u32x2* __restrict__ runs, uint32_t block_shift)
 {
     __shared__ SplitLds<kMembers> lds;
     const uint32_t row = blockIdx.y, t = threadIdx.x;
@@ -1689,7 +1703,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         if (t == 0) *v.count2 = 0;
     }
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the next barrier
-    const CastVotes act = {votes32, lds.lvl, seg_sel ? seg_sel + (size_t)row * nseg : nullptr, thresholds_only};
+    const CastVotes act = {votes32, lds.lvl, run_tallies ? run_tallies + (size_t)row * n_runs : nullptr, thresholds_only};
     uint32_t kth, tie_cut;
     if (rest.n <= (uint32_t)kMembers && members_stored(v, rest)) {   // uniform; usual: this is the row's only workgroup
         static_assert(kMembers <= kListBatch, "a batch holds them");
@@ -1743,7 +1757,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         }
         if (largest == smallest && rest.want < rest.n) {
             kth = largest;
-            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, seg + (size_t)row * nseg, nseg, lds);
+            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, runs + (size_t)row * n_runs, n_runs, lds);
             ranked = true;
         }
     }

@@ -44,10 +44,10 @@ namespace mvk {
 // read as 4 sub-blocks of 256 (lane l holds coordinates base + 256u + 4l .. +3); a
 // workgroup of 8 wavefronts covers 8 consecutive segments.  Coordinates with
 // (bits(a) & 0x7FFFFFFF) >= tau are appended to the row's candidate list as
-// (magnitude bits, coordinate), in ascending coordinate order inside the wavefront's
-// run; seg[row][s] = (start of the run, its length).  Runs land in the list in any
+// (magnitude bits, coordinate), in ascending coordinate order inside the workgroup's
+// run; runs[row][b] = (start of workgroup b's run, its length).  Runs land in the list in any
 // order; the table makes the order recoverable.  The workgroup reserves list space
-// for all its runs with ONE atomic on the row's counter (returning atomics on one
+// for its run with ONE atomic on the row's counter (returning atomics on one
 // cache line complete only every few nanoseconds chip-wide, so one per wavefront
 // would bound the whole pass when candidates are spread evenly).  Entries beyond
 // `cap` are dropped, the counter keeps counting (the overflow is detected from it).
@@ -59,7 +59,7 @@ struct StreamLds {
     uint64_t scan[kStreamThreads / kWave + 1];
     uint32_t found, is_last;
     uint32_t wave_total[kSegPerBlock];
-    uint32_t block_base;
+    uint32_t block_base, block_total;
 };
 
 template <typename GT>
@@ -198,8 +198,8 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ step_no, uint32_t spin_limit, uint32_t* __restrict__ row_poison, uint32_t* __restrict__ lvl_sets,
     uint32_t n_lvl_words, uint32_t* __restrict__ ad_count,
     u32x2* __restrict__ cand, uint32_t cap, uint32_t* __restrict__ row_count_sets, uint32_t row_count_set_words,
-    u32x2* __restrict__ seg,
-    uint32_t* __restrict__ seg_sel, uint32_t nseg, uint32_t wgs_per_row, uint32_t head_wgs,
+    u32x2* __restrict__ runs,
+    uint32_t* __restrict__ run_taken, uint32_t nseg, uint32_t wgs_per_row, uint32_t head_wgs,
     uint32_t* __restrict__ zero_votes32, int64_t votes_bytes)
 {
     __shared__ StreamLds lds;
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
             total += sums >> 16;
         }
     }
-    // one reservation for the workgroup's 8 runs
+    // one reservation for the workgroup's run
     if (lane == 0) lds.wave_total[wave] = total;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -331,6 +331,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
             lds.wave_total[w] = sum;
             sum += t;
         }
+        lds.block_total = sum;
         lds.block_base = sum ? atomicAdd(&row_count[row * kCounterStride], sum) : 0u;
     }
     __syncthreads();
@@ -358,12 +359,9 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
         const u32x4 z = {0u, 0u, 0u, 0u};
         if (j < votes_bytes) *reinterpret_cast<u32x4*>(zero_votes32 + (j >> 2)) = z;
     }
-    if (live && lane == 0) {
-        u32x2 rec;
-        rec.x = run_start;
-        rec.y = total;
-        seg[(size_t)row * nseg + s] = rec;
-        seg_sel[(size_t)row * nseg + s] = 0;     // tallied when the votes are cast
+    if (threadIdx.x == 0) {
+        runs[(size_t)row * wgs_per_row + bx] = u32x2{lds.block_base, lds.block_total};
+        run_taken[(size_t)row * wgs_per_row + bx] = 0;     // tallied when the votes are cast
     }
 }
 
