@@ -49,8 +49,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Plan {
     uint32_t N, K;
     int64_t  d;
-    uint32_t nseg;              // segments of 1024 coordinates per row
-    uint32_t n_runs;            // streaming workgroups per row, of 8 segments each
+    uint32_t n_runs;            // segments of 1024 coordinates per row, however they are shifted, in whole workgroups of 8
     uint32_t stride;            // every stride-th 32-coordinate chunk is sampled
     uint32_t n_sampled_chunks;  // per row
     uint64_t n_sampled;         // sampled coordinates per row
@@ -108,8 +107,8 @@ Plan make_plan(const mv_config* c)
     p.N = (uint32_t)c->n_workers;
     p.K = (uint32_t)c->k;
     p.d = c->d;
-    p.nseg = (uint32_t)((p.d + mvk::kSeg - 1) / mvk::kSeg);
-    p.n_runs = (uint32_t)((p.d + mvk::kRun - 1) / mvk::kRun);
+    const uint64_t per_wg = (uint64_t)mvk::kSeg * mvk::kSegPerBlock;
+    p.n_runs = (uint32_t)(((uint64_t)p.d + mvk::kMostShift + per_wg - 1) / per_wg * mvk::kSegPerBlock);
 
     // A row with exactly K coordinates above the threshold shows K * frac of them in a sample of frac * d
     // coordinates on average.  Ask for m sampled ones with m - 7 sqrt(m) = K * frac, never fewer than 128:
@@ -201,8 +200,8 @@ Plan make_plan(const mv_config* c)
         p.select_parts = (uint32_t)parts;
         // beyond what one workgroup keeps in registers the lists go through the many-workgroup select
         p.multi_select = slots > (uint64_t)mvk::kKeepMost;
-        p.block_shift = 13;                       // a run at least
-        while (((p.d - 1) >> p.block_shift) >= mvk::kCoordBlocks) ++p.block_shift;
+        p.block_shift = 10;                       // a segment at least
+        while (((p.d - 1 + mvk::kMostShift) >> p.block_shift) >= mvk::kCoordBlocks) ++p.block_shift;
         // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
         uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
         if (sb > 256) sb = 256;
@@ -253,7 +252,7 @@ Plan make_plan(const mv_config* c)
     p.n_zero_words = (uint32_t)((off - p.off_lvlsets) / 4);
     off = align_up(off);
     p.off_runs = off;     off += align_up((size_t)p.N * p.n_runs * 8);
-    p.off_runtaken = off; off += align_up((size_t)p.N * p.n_runs * 4);
+    p.off_runtaken = off; off += align_up((size_t)p.N * p.n_runs * 2);
     p.off_cand = off;     off += align_up((size_t)p.N * p.cap * 8);
     p.off_votes = off;    off += align_up(((size_t)p.d + 15) / 16 * 16);
     p.off_blockcnt = off; off += align_up((size_t)p.n_vote_blocks * 8);
@@ -427,6 +426,8 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     const bool bf16 = c->cfg.grad_dtype == MV_BF16;
     const bool add_drop = a.k_ad > 0;
     const bool random_sel = a.rand_exp != nullptr;
+    const mvk::RowSegments segs = {(uint32_t)(reinterpret_cast<uintptr_t>(a.err) / 4 % mvk::kSeg),
+                                   (uint32_t)((uint64_t)a.ld_e % mvk::kSeg), (uint32_t)p.d};
     DeviceGuard guard(c->cfg.device);
     if (!guard.ok) return MV_ERR_DEVICE;
     // an error the caller left pending is not this step's: nothing is enqueued and the context stays usable
@@ -543,21 +544,21 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
     {
-        const dim3 grid(p.N * p.sample_wgs + p.N * p.n_runs);
+        const dim3 grid(p.N * p.sample_wgs + p.N * (p.n_runs / mvk::kSegPerBlock));
         before(KID_STREAM);
         if (bf16)
             hipLaunchKernelGGL(mvk::mv_stream_collect<uint16_t>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.nseg, p.n_runs, p.head_wgs,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.nseg, p.n_runs, p.head_wgs,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }
@@ -575,7 +576,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         before(KID_SEL_SPLIT);
         hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
-                           kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs,
+                           kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs, segs,
                            lvlsets, thresholds_only, taupub, p.block_shift);
         after(KID_SEL_SPLIT);
         uint32_t parts = add_drop ? 1 : 256 / p.N;
@@ -583,7 +584,8 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         before(KID_SEL_FINISH);
         hipLaunchKernelGGL(mvk::mv_sel_finish, dim3(parts, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist, kth, tiecut,
-                           votes32, tallies, p.n_runs, lvlsets, thresholds_only, taupub, (const mvk::u32x2*)runs, p.block_shift);
+                           votes32, tallies, p.n_runs, segs, lvlsets, thresholds_only, taupub, (const mvk::u32x2*)runs,
+                           p.block_shift);
         after(KID_SEL_FINISH);
     } else {
         const uint32_t parts = add_drop ? 1 : p.select_parts;
@@ -592,8 +594,8 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                                                                : &mvk::mv_row_select<mvk::kKeepMost>;
         hipLaunchKernelGGL(kernel, dim3((p.N + 7) / 8 * 8 * parts), dim3(mvk::kRowThreads), 0, st, a.err,
                            a.ld_e, p.d, p.N, p.K, cand, p.cap, rowcnt_sets, rowcnt_set_words, stepno, taupub, poison,
-                           rowcnt, tau, kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs, lvlsets, slow, parts, p.n_spec,
-                           thresholds_only);
+                           rowcnt, tau, kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs, segs, lvlsets, slow, parts,
+                           p.n_spec, thresholds_only);
         after(KID_ROW_SELECT);
     }
 
@@ -687,7 +689,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                            block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
                            subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, p.emit_blocks,                 \
                            (const mvk::u32x2*)cand, p.cap, (const uint32_t*)rowcnt, (const mvk::u32x2*)runs,     \
-                           (const uint32_t*)run_taken, p.n_runs, (const uint32_t*)kth, (const uint32_t*)tiecut,  \
+                           (const uint32_t*)run_taken, p.n_runs, segs, (const uint32_t*)kth, (const uint32_t*)tiecut, \
                            (const uint32_t*)slow, a.worker_idx,                                                  \
                            add_drop ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
                            reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \

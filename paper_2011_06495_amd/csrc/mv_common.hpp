@@ -13,10 +13,11 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int      kWave           = 64;
-constexpr int      kSeg            = 1024;   // coordinates per wavefront segment in the streaming pass
+constexpr int      kSeg            = 1024;   // coordinates per wavefront segment in the streaming pass: 4 KB of e
 constexpr int      kStreamThreads  = 512;    // 8 segments per workgroup
 constexpr int      kSegPerBlock    = kStreamThreads / kWave;
-constexpr int      kRun            = kSeg * kSegPerBlock;   // coordinates per streaming workgroup, whose candidates lie together
+constexpr int      kXcds           = 8;      // consecutive workgroups run on as many dies, each with an L2 of its own
+constexpr int      kGroupSegs      = kXcds * kSegPerBlock;   // segments that kXcds consecutive streaming workgroups share
 constexpr int      kHistBits       = 13;     // sample histogram: exponent + 5 mantissa bits
 constexpr int      kHistBins       = 1 << kHistBits;
 constexpr int      kHistShift      = 31 - kHistBits;
@@ -106,6 +107,47 @@ __device__ __forceinline__ uint64_t block_excl_scan64(uint64_t v, uint64_t* lds,
     total = pack2(from_lane(hi, NW - 1), from_lane(lo, NW - 1));
     const uint64_t before = wave ? pack2(from_lane(hi, wave - 1), from_lane(lo, wave - 1)) : 0u;
     return before + incl - v;
+}
+
+// A row's segments begin at multiples of 4 KB of e's ADDRESS, so its first one may lack up to kMostShift coordinates:
+// segment s of a row holds the coordinates [kSeg s - shift, kSeg (s + 1) - shift) that there are.
+struct RowSegments {
+    uint32_t first, step;                         // of e and of its row stride, in floats modulo kSeg
+    uint32_t d;
+    __device__ __forceinline__ uint32_t shift(uint32_t row) const { return (first + row * step) & (uint32_t)(kSeg - 1); }
+    __device__ __forceinline__ uint32_t count(uint32_t row) const { return (d + shift(row) + kSeg - 1) / kSeg; }
+};
+constexpr int kMostShift = kSeg - 4;              // rows begin at multiples of 16 bytes
+__device__ __forceinline__ uint32_t segment_of(uint32_t j, uint32_t shift) { return (j + shift) / kSeg; }
+// A group's segments go round its workgroups, and what a workgroup notes of its segments' runs lies together: the place
+// of segment s in the row's table of runs, and just so the segment whose run has place s.  A row of n segments
+// may end with less than a group, whose workgroups take consecutive segments.
+static_assert(kXcds == 8 && kSegPerBlock == 8, "the two halves of a segment's number in its group change places");
+__device__ __forceinline__ uint32_t run_place(uint32_t s, uint32_t n)
+{
+    return s < (n & ~63u) ? (s & ~63u) | (s & 7u) << 3 | (s >> 3 & 7u) : s;
+}
+
+// The taken candidates per segment of a row, two counts to a word, counted where the sorted vote lists are wanted
+// (else null).
+struct SegmentTallies {
+    uint32_t* taken;
+    uint32_t  shift;
+    __device__ __forceinline__ void add(uint32_t s, uint32_t n) const { atomicAdd(&taken[s >> 1], n << (s & 1u) * 16u); }
+};
+constexpr int kTallyUnit = 8;                     // segments whose tallies are read at once: 16 bytes
+__device__ __forceinline__ uint32_t unit_sum(u32x4 w)
+{
+    const uint32_t s = w.x + w.y + w.z + w.w;     // two sums of four counts of at most kSeg
+    return (s & 0xFFFFu) + (s >> 16);
+}
+// the first n counts of a unit, n < kTallyUnit
+__device__ __forceinline__ uint32_t unit_sum_below(u32x4 w, uint32_t n)
+{
+    uint32_t s = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) s += n > 2 * k + 1 ? w[k] : n > 2 * k ? w[k] & 0xFFFFu : 0u;
+    return (s & 0xFFFFu) + (s >> 16);
 }
 
 // bin of a candidate's magnitude key (>= tau) in the row's fine histogram; order preserving

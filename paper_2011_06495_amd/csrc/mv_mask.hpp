@@ -148,24 +148,26 @@ __device__ __forceinline__ void each_mask_position(const uint32_t (&marks)[Q], i
 constexpr int kMaskWaves = kMaskThreads / kWave;
 constexpr int kEmitUnroll = 4;                    // list entries per thread in flight together
 constexpr int kEmitBatch = kMaskThreads * kEmitUnroll;
-constexpr int kListRuns = 4 * kMaskThreads;       // prefixes of a row's tallies in LDS, four to a thread
+constexpr int kListUnits = 4 * kMaskThreads;      // prefixes of a row's tallies in LDS, four to a thread
 static_assert(kEmitUnroll * kMaskWaves == kWave, "a lane per wavefront's part of a batch");
 struct EmitLds {
-    uint32_t before[kListRuns];                   // taken entries in the runs before
+    uint32_t before[kListUnits];                  // taken entries in the units of segments before
     uint32_t wave_taken[kEmitUnroll * kMaskWaves];
     uint32_t wave_earlier[kMaskWaves];
     uint16_t number[kEmitBatch];                  // taken entries of the batch before each of its entries
 };
 
 // A row's vote list in ascending coordinate order, without a sort: a taken candidate's rank is (taken
-// candidates in the runs before its own, from the tallies) + (before it in its own run; runs are ascending).
-// A few workgroups per row (`part` of `parts`); each adds up the row's tallies for itself, which are few (1364 for
-// 11.2 M coordinates) and arrive beside the entries.  Run beside the mask kernel's blocks, which mostly wait, and not
-// beside the gather, the lists cost a step less (1 x 16 M, K = 16,000: 97.5 -> 93.4 us, 4 x 2,000,003, K = 20,000: 69.7 -> 68.8;
-// where the scattered traffic of the gather is the bound, nothing: 10 x 11.2 M, K = 111,740).
+// candidates in the segments before its own, from the tallies) + (before it in its own run; runs are ascending).
+// A few workgroups per row (`part` of `parts`); each adds up the row's tallies for itself, eight segments to a
+// prefix (1365 for 11.2 M coordinates), which arrive beside the entries, and an entry looks at its own eight segments'
+// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).  Run beside the mask
+// kernel's blocks, which mostly wait, and not beside the gather, the lists cost a step less (1 x 16 M, K = 16,000:
+// 97.5 -> 93.4 us, 4 x 2,000,003, K = 20,000: 69.7 -> 68.8; where the scattered traffic of the gather is the bound, nothing:
+// 10 x 11.2 M, K = 111,740).
 __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, uint32_t C,
-                                               const u32x2* __restrict__ runs, const uint32_t* __restrict__ run_taken,
-                                               uint32_t n_runs, uint32_t K, uint32_t kth, uint32_t tie_cut,
+                                               const u32x2* __restrict__ runs, const u32x4* __restrict__ units,
+                                               uint32_t n_segs, uint32_t shift, uint32_t K, uint32_t kth, uint32_t tie_cut,
                                                uint32_t part, uint32_t parts, uint32_t* __restrict__ out, EmitLds& lds,
                                                uint64_t* scan_lds)
 {
@@ -173,6 +175,7 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
     u32x2 c[kEmitUnroll];
     uint32_t run0[kEmitUnroll], first_run = 0;    // where the entries' runs begin, and the first entry's of the batch
+    uint32_t below[kEmitUnroll];                  // taken in the segments of the entry's unit before its own
     auto load = [&](uint64_t i0) {
 #pragma unroll
         for (int u = 0; u < kEmitUnroll; ++u) {
@@ -180,24 +183,32 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
             const u32x2 none = {0u, 0xFFFFFFFFu};
             c[u] = (i < C) ? crow[i] : none;
         }
-        first_run = crow[i0].y / kRun;            // uniform
+        first_run = segment_of(crow[i0].y, shift);       // uniform
     };
     auto load_runs = [&]() {
 #pragma unroll
-        for (int u = 0; u < kEmitUnroll; ++u) run0[u] = c[u].y != 0xFFFFFFFFu ? runs[c[u].y / kRun].x : 0u;
-        first_run = runs[first_run].x;
+        for (int u = 0; u < kEmitUnroll; ++u) {
+            run0[u] = 0;
+            below[u] = 0;
+            if (c[u].y != 0xFFFFFFFFu) {
+                const uint32_t s = segment_of(c[u].y, shift);
+                run0[u] = runs[run_place(s, n_segs)].x;
+                below[u] = unit_sum_below(units[s / kTallyUnit], s % kTallyUnit);
+            }
+        }
+        first_run = runs[run_place(first_run, n_segs)].x;
     };
     load((uint64_t)part * kEmitBatch);
-    // `per` runs to a prefix: one, in rows of up to 33.5 M coordinates
-    const uint32_t per = (n_runs + kListRuns - 1) / kListRuns;
+    // `per` units to a prefix: one, in rows of up to 33.5 M coordinates
+    const uint32_t n_units = (n_segs + kTallyUnit - 1) / kTallyUnit, per = (n_units + kListUnits - 1) / kListUnits;
     {
         uint32_t v[4];
         uint32_t sum = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const uint32_t r0 = (4u * t + q) * per;
-            v[q] = r0 < n_runs ? run_taken[r0] : 0u;
-            for (uint32_t r = r0 + 1; r < min(r0 + per, n_runs); ++r) v[q] += run_taken[r];
+            v[q] = r0 < n_units ? unit_sum(units[r0]) : 0u;
+            for (uint32_t r = r0 + 1; r < min(r0 + per, n_units); ++r) v[q] += unit_sum(units[r]);
         }
         load_runs();
 #pragma unroll
@@ -213,7 +224,7 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
     __syncthreads();
     // A workgroup takes kEmitBatch consecutive entries at a time and numbers the taken ones; an entry's rank
     // inside its run is the difference of two such numbers.  Only the first entry's run can have begun before
-    // the batch: that part (fewer than kRun entries) is counted by all threads together.
+    // the batch: that part (fewer than kSeg entries) is counted by all threads together.
     for (uint64_t i0 = (uint64_t)part * kEmitBatch; i0 < C; i0 += (uint64_t)parts * kEmitBatch) {
         if (i0 != (uint64_t)part * kEmitBatch) {
             load(i0);
@@ -221,15 +232,10 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
         }
         uint32_t n_earlier = 0;
         {
-            constexpr uint32_t kStride = kMaskThreads * 4;
-            for (uint64_t j0 = first_run; j0 < i0; j0 += kStride) {  // uniform: twice at most
-                u32x2 x[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) x[q] = crow[min(j0 + (uint32_t)q * kMaskThreads + t, i0 - 1)];
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    n_earlier += (uint32_t)__popcll(
-                        __ballot(j0 + (uint32_t)q * kMaskThreads + t < i0 && is_taken(x[q], kth, tie_cut)));
+            static_assert(kSeg <= kMaskThreads, "a thread per entry of a run");
+            if (first_run < i0) {                                    // uniform
+                const uint64_t j = min((uint64_t)first_run + t, i0 - 1);
+                n_earlier = (uint32_t)__popcll(__ballot(first_run + t < i0 && is_taken(crow[j], kth, tie_cut)));
             }
         }
         uint32_t mine[kEmitUnroll];               // taken ones in the lanes below
@@ -258,9 +264,9 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
 #pragma unroll
         for (int u = 0; u < kEmitUnroll; ++u)
             if (taken >> u & 1u) {
-                const uint32_t r = c[u].y / kRun, p = r / per;
-                uint32_t pos = lds.before[p] + (run0[u] >= i0 ? mine[u] - lds.number[run0[u] - i0] : mine[u] + carry);
-                for (uint32_t q = p * per; q < r; ++q) pos += run_taken[q];
+                const uint32_t r = segment_of(c[u].y, shift) / kTallyUnit, p = r / per;
+                uint32_t pos = lds.before[p] + below[u] + (run0[u] >= i0 ? mine[u] - lds.number[run0[u] - i0] : mine[u] + carry);
+                for (uint32_t q = p * per; q < r; ++q) pos += unit_sum(units[q]);
                 if (pos < K) out[pos] = c[u].y;
             }
         __syncthreads();                          // the scratch is free for the next batch
@@ -314,6 +320,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
                                                               const uint32_t* __restrict__ row_count,
                                                               const u32x2* __restrict__ runs,
                                                               const uint32_t* __restrict__ run_taken, uint32_t n_runs,
+                                                              RowSegments segs,
                                                               const uint32_t* __restrict__ kth_in,
                                                               const uint32_t* __restrict__ tie_cut_in,
                                                               const uint32_t* __restrict__ slow_flag,
@@ -335,7 +342,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         const uint32_t row = (blockIdx.x - n_vote_blocks) / emit_blocks, part = (blockIdx.x - n_vote_blocks) % emit_blocks;
         if (slow_flag[row] == 1u) return;                      // its list is written already
         write_row_list(cand + (size_t)row * cap, row_count[row], runs + (size_t)row * n_runs,
-                       run_taken + (size_t)row * n_runs, n_runs, K, kth_in[row], tie_cut_in[row], part, emit_blocks,
+                       reinterpret_cast<const u32x4*>(run_taken) + (size_t)row * (n_runs / kTallyUnit), segs.count(row),
+                       segs.shift(row), K, kth_in[row], tie_cut_in[row], part, emit_blocks,
                        worker_idx + (size_t)row * K, emit, scan_lds);
         return;
     }

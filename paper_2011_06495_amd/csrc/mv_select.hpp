@@ -445,13 +445,13 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
 }
 
 // Casts votes for the marked ones of a batch of list entries, U per thread (bit u of `taken`: c[u]): each
-// adds one to its coordinate's vote byte and, when the sorted vote lists are wanted (run_taken != nullptr), is
-// tallied in its run (run_taken was zeroed by the streaming pass).  Lanes of a wavefront
-// mostly hold consecutive list entries, which share a run: the first lane of each
-// group of equal runs adds the group's count.  All threads of the workgroup must call it.
+// adds one to its coordinate's vote byte and, when the sorted vote lists are wanted, is
+// tallied in its segment (the tallies were zeroed by the streaming pass).  Lanes of a wavefront
+// mostly hold consecutive list entries, which share a segment: the first lane of each
+// group of equal segments adds the group's count.  All threads of the workgroup must call it.
 template <int U, bool MERGE>
 __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_mask, uint32_t* __restrict__ votes32,
-                                           uint32_t* lvl, uint32_t* __restrict__ run_taken)
+                                           uint32_t* lvl, SegmentTallies tallies)
 {
     const uint32_t lane = lane_id();
     // MERGE (long lists, where the atomics' rate at the memory side is what the step waits for): lanes
@@ -499,7 +499,8 @@ __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_m
     for (int u = 0; u < U; ++u) {
         const bool taken = (taken_mask >> u) & 1u;
         if (taken) atomicAdd(&lvl[((old[u] >> ((c[u].y & 3u) * 8u)) & 255u) + 1u], 1u);
-        if (run_taken) tally_groups(c[u].y / kRun, taken, [&](uint32_t r, uint32_t n) { atomicAdd(&run_taken[r], n); });
+        if (tallies.taken)
+            tally_groups(segment_of(c[u].y, tallies.shift), taken, [&](uint32_t s, uint32_t n) { tallies.add(s, n); });
     }
 }
 
@@ -507,7 +508,7 @@ __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_m
 __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ crow, uint32_t C, uint32_t kth,
                                                     uint32_t tie_cut, uint32_t part, uint32_t parts,
                                                     uint32_t* __restrict__ votes32, uint32_t* lvl,
-                                                    uint32_t* __restrict__ run_taken)
+                                                    SegmentTallies tallies)
 {
     // all the loads, then all the vote atomics, then what depends on their results: a thread's
     // entries wait for memory together, not one after the other
@@ -524,7 +525,7 @@ __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ cr
 #pragma unroll
         for (int u = 0; u < kU; ++u)
             taken |= (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
-        cast_votes<kU, false>(c, taken, votes32, lvl, run_taken);
+        cast_votes<kU, false>(c, taken, votes32, lvl, tallies);
     }
 }
 
@@ -718,7 +719,7 @@ __device__ __forceinline__ bool select_from_registers(const Kept& kept, const u3
 template <int KEEP>
 __device__ __forceinline__ void cast_votes_from_registers(u32x2 (&entry)[KEEP], uint32_t C, uint32_t kth, uint32_t tie_cut,
                                                           uint32_t part, uint32_t parts, uint32_t* __restrict__ votes32,
-                                                          uint32_t* lvl, uint32_t* __restrict__ run_taken)
+                                                          uint32_t* lvl, SegmentTallies tallies)
 {
     uint32_t taken = 0;
     uint32_t next = part;                         // the workgroup's next q
@@ -738,9 +739,9 @@ __device__ __forceinline__ void cast_votes_from_registers(u32x2 (&entry)[KEEP], 
             next += parts;
             const bool mine = taken >> q & 1u;
             if (mine) atomicAdd(&lvl[((entry[q].x >> ((entry[q].y & 3u) * 8u)) & 255u) + 1u], 1u);
-            if (run_taken)
-                tally_groups((uint32_t)q * kRowThreads + threadIdx.x < C ? entry[q].y / kRun : 0xFFFFFFFFu, mine,
-                             [&](uint32_t r, uint32_t n) { atomicAdd(&run_taken[r], n); });
+            if (tallies.taken)
+                tally_groups((uint32_t)q * kRowThreads + threadIdx.x < C ? segment_of(entry[q].y, tallies.shift) : 0xFFFFFFFFu,
+                             mine, [&](uint32_t s, uint32_t n) { tallies.add(s, n); });
         }
 }
 
@@ -838,7 +839,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
     const unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ row_poison,
     uint32_t* __restrict__ cand_count, uint32_t* __restrict__ tau_bits, uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out,
     uint32_t* __restrict__ worker_idx, uint32_t* __restrict__ votes32,
-    uint32_t* __restrict__ run_tallies, uint32_t n_runs, uint32_t* __restrict__ lvl_sets,
+    uint32_t* __restrict__ run_tallies, uint32_t n_runs, RowSegments segs, uint32_t* __restrict__ lvl_sets,
     uint32_t* __restrict__ slow_flag, uint32_t parts, uint32_t n_spec, int thresholds_only)
 {
     __shared__ SelectLds lds;
@@ -921,22 +922,22 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
         if (!thresholds_only) {
             for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;
             __syncthreads();
-            uint32_t* run_taken = run_tallies ? run_tallies + (size_t)row * n_runs : nullptr;
+            const SegmentTallies tallies = {run_tallies ? run_tallies + (size_t)row * (n_runs / 2) : nullptr, segs.shift(row)};
             bool cast = false;
             uint32_t first = part;
             if constexpr (KEEP <= 8) {
                 cast = done;
-                if (done) cast_votes_from_registers(whole.entry, C, kth, tie_cut, part, parts, votes32, lds.lvl, run_taken);
+                if (done) cast_votes_from_registers(whole.entry, C, kth, tie_cut, part, parts, votes32, lds.lvl, tallies);
             }
             if constexpr (!kWhole) {
                 uint32_t taken = 0;
 #pragma unroll
                 for (int i = 0; i < kOwn; ++i)
                     taken |= ((part + i * parts) * kRowThreads + t < C && is_taken(own[i], kth, tie_cut) ? 1u : 0u) << i;
-                cast_votes<kOwn, false>(own, taken, votes32, lds.lvl, run_taken);
+                cast_votes<kOwn, false>(own, taken, votes32, lds.lvl, tallies);
                 first = part + kOwn * parts;
             }
-            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, first, parts, votes32, lds.lvl, run_taken);
+            if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, first, parts, votes32, lds.lvl, tallies);
             __syncthreads();
             merge_levels(lds.lvl, lvl_sets, blockIdx.x);
         }
@@ -984,10 +985,10 @@ struct ListView {
     u32x2*    list2;          // room for `room` members; step2 = -1: growing downwards
     int       step2;
     uint32_t  room;
-    // the rows' lists only: counters of the members per block of 2^block_shift coordinates and, at count2[1] and
+    // the rows' lists only: counters of the members per block of 2^block_shift coordinates (segments) and, at count2[1] and
     // [2], the largest of their keys and of the keys' complements (see BigGroup); zero between steps
     uint32_t* blocks;
-    uint32_t  block_shift;
+    uint32_t  block_shift, shift;     // (of the row's segments)
 };
 constexpr int kCoordBlocks = 2048;                // block_shift is such that there are at most so many
 
@@ -1321,7 +1322,7 @@ struct BigGroup {
             largest = max(largest, c.x);
             largest_not = max(largest_not, ~c.x);
         }
-        tally_groups(c.y >> v.block_shift, member, [&](uint32_t b, uint32_t n) { atomicAdd(&lds.hist[b], n); });
+        tally_groups((c.y + v.shift) >> v.block_shift, member, [&](uint32_t b, uint32_t n) { atomicAdd(&lds.hist[b], n); });
     }
     __device__ __forceinline__ void merge(const ListView& v)         // all threads of the workgroup
     {
@@ -1347,7 +1348,7 @@ struct BigGroup {
 // run (runs are ascending).
 template <typename Lds>
 __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const uint32_t (&count)[2], uint32_t key,
-                                                      uint32_t want, const u32x2* __restrict__ runs, uint32_t n_runs, Lds& lds)
+                                                      uint32_t want, const u32x2* __restrict__ runs, uint32_t n_segs, Lds& lds)
 {
     static_assert(kCoordBlocks == 2 * kRowThreads, "two blocks to a thread");
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
@@ -1362,33 +1363,36 @@ __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const u
         ex += count[q];
     }
     __syncthreads();
-    static_assert(kCoordBlocks << 7 >= (1ll << 31) / kRun, "at most 128 runs to a block of a row of up to 2^31 coordinates");
-    const uint32_t per_block = (1u << v.block_shift) / kRun;         // runs: at most 128
-    const uint32_t r0 = lds.bcast[0] * per_block, n_here = min(per_block, n_runs - r0);
+    static_assert(((1ll << 31) + kSeg) >> 21 < kCoordBlocks && (1 << 21) / kSeg == 2 * kRowThreads,
+                  "at most two runs to a thread in a block of a row of up to 2^31 coordinates");
+    const uint32_t per_block = (1u << v.block_shift) / kSeg;         // runs: at most 2048
+    const uint32_t r0 = lds.bcast[0] * per_block, n_here = min(per_block, n_segs - r0);
     want = lds.bcast[1];
     __syncthreads();
     if (n_here > 1) {                             // uniform: a wavefront per run counts
         for (uint32_t i = wave; i < n_here; i += kRowThreads / kWave) {
-            const u32x2 run = runs[r0 + i];
+            const u32x2 run = runs[run_place(r0 + i, n_segs)];
+            uint32_t k[kSeg / kWave];
             uint32_t n = 0;
-            for (uint32_t j0 = 0; j0 < run.y; j0 += 16 * kWave) {    // (wave-uniform)
-                uint32_t k[16];
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    const uint32_t j = j0 + (uint32_t)q * kWave + lane;
-                    k[q] = j < run.y ? v.list[run.x + j].x : 0xFFFFFFFFu;
-                }
-#pragma unroll
-                for (int q = 0; q < 16; ++q) n += (uint32_t)__popcll(__ballot(k[q] == key));
+            for (int q = 0; q < kSeg / kWave; ++q) {
+                const uint32_t j = (uint32_t)q * kWave + lane;
+                k[q] = j < run.y ? v.list[run.x + j].x : 0xFFFFFFFFu;
             }
+#pragma unroll
+            for (int q = 0; q < kSeg / kWave; ++q) n += (uint32_t)__popcll(__ballot(k[q] == key));
             if (lane == 0) lds.hist[i] = n;
         }
         __syncthreads();
-        const uint32_t mine = t < n_here ? lds.hist[t] : 0u;
-        ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
-        if (ex < want && want <= ex + mine) {
-            lds.bcast[0] = t;
-            lds.bcast[1] = want - ex;
+        const uint32_t mine[2] = {2 * t < n_here ? lds.hist[2 * t] : 0u, 2 * t + 1 < n_here ? lds.hist[2 * t + 1] : 0u};
+        ex = block_excl_scan<kRowThreads>(mine[0] + mine[1], lds.scan, total);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (ex < want && want <= ex + mine[q]) {
+                lds.bcast[0] = 2 * t + q;
+                lds.bcast[1] = want - ex;
+            }
+            ex += mine[q];
         }
         __syncthreads();
         want = lds.bcast[1];
@@ -1396,24 +1400,12 @@ __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const u
         lds.bcast[0] = 0;
     }
     __syncthreads();
-    const u32x2 run = runs[r0 + lds.bcast[0]];
+    const u32x2 run = runs[run_place(r0 + lds.bcast[0], n_segs)];
     __syncthreads();
-    // the run, kPer entries to a thread
-    constexpr int kPer = kRun / kRowThreads;
-    u32x2 c[kPer];
-    uint32_t mine = 0;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-        const uint32_t j = t * kPer + q;
-        const u32x2 none = {0xFFFFFFFFu, 0u};     // no key
-        c[q] = j < run.y ? v.list[run.x + j] : none;
-    }
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) mine += c[q].x == key;
-    ex = block_excl_scan<kRowThreads>(mine, lds.scan, total);
-#pragma unroll
-    for (int q = 0; q < kPer; ++q)
-        if (c[q].x == key && ++ex == want) lds.bcast[0] = c[q].y;
+    static_assert(kSeg == kRowThreads, "a thread per entry of a run");
+    const bool tie = t < run.y && v.list[run.x + t].x == key;
+    ex = block_excl_scan<kRowThreads>(tie ? 1u : 0u, lds.scan, total);
+    if (tie && ex == want - 1) lds.bcast[0] = v.list[run.x + t].y;
     __syncthreads();
     const uint32_t cut = lds.bcast[0];
     __syncthreads();
@@ -1582,6 +1574,7 @@ __device__ __forceinline__ void lend_storage(ListView& v, uint32_t* __restrict__
     v.room = v.n;
     v.blocks = nullptr;
     v.block_shift = 0;
+    v.shift = 0;
 }
 static_assert(kListBins == kRowThreads, "a bin per thread");
 static_assert(kHistRow >= kCtlWords + 6 * kCounterStride, "three lists' storage fits a row's sample histogram");
@@ -1589,7 +1582,8 @@ static_assert(kHistRow >= kCtlWords + 6 * kCounterStride, "three lists' storage 
 // A row's list as mv_sel_hist, mv_sel_split and mv_sel_finish see it.  2048 bins to an octave above the row's
 // threshold, beyond a quarter octave 32; without a threshold (nearly all of the row is wanted) 4 to an octave.
 __device__ __forceinline__ ListView row_list(u32x2* __restrict__ cand, uint32_t cap, uint32_t row, uint32_t n, uint32_t K,
-                                             uint32_t tau, uint32_t* __restrict__ sample_hist, uint32_t block_shift)
+                                             uint32_t tau, uint32_t* __restrict__ sample_hist, uint32_t block_shift,
+                                             uint32_t shift)
 {
     ListView v;
     v.list = cand + (size_t)row * cap;  v.n = n;
@@ -1603,6 +1597,7 @@ __device__ __forceinline__ ListView row_list(u32x2* __restrict__ cand, uint32_t 
     v.room = cap - v.n;
     v.blocks = v.hist + kListBins;                // (the other two lists' storage: add-drop voting uses it later)
     v.block_shift = block_shift;
+    v.shift = shift;
     return v;
 }
 static_assert(kCoordBlocks <= 2 * kListBins, "the blocks' counters fit two lists' histograms");
@@ -1626,16 +1621,17 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
         slow_flag[row] = from_list ? 0u : 1u;
     }
     if (!from_list) return;                                          // whole workgroup
-    list_hist(row_list(cand, cap, row, C, K, tau, sample_hist, 0), blockIdx.x, gridDim.x, hist);
+    list_hist(row_list(cand, cap, row, C, K, tau, sample_hist, 0, 0), blockIdx.x, gridDim.x, hist);
 }
 
 // Votes for the marked entries of a batch; with thresholds_only (add-drop voting) none are cast.
 struct CastVotes {
-    uint32_t *votes32, *lvl, *run_taken;
+    uint32_t *votes32, *lvl;
+    SegmentTallies tallies;
     int thresholds_only;
     __device__ __forceinline__ void operator()(const u32x2 (&c)[kListUnroll], uint32_t taken) const
     {
-        if (!thresholds_only) cast_votes<kListUnroll, true>(c, taken, votes32, lvl, run_taken);
+        if (!thresholds_only) cast_votes<kListUnroll, true>(c, taken, votes32, lvl, tallies);
     }
 };
 
@@ -1652,8 +1648,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist,
     uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
-    uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, uint32_t n_runs, uint32_t* __restrict__ lvl_sets,
-    int thresholds_only, unsigned long long* __restrict__ tau_pub, uint32_t block_shift)
+    uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, uint32_t n_runs, RowSegments segs,
+    uint32_t* __restrict__ lvl_sets, int thresholds_only, unsigned long long* __restrict__ tau_pub, uint32_t block_shift)
 {
     __shared__ SplitLds<kMembers> lds;
     const uint32_t row = blockIdx.y, t = threadIdx.x;
@@ -1663,9 +1659,11 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
                                    votes32, lvl_sets, kth_out + row, tie_cut_out + row, thresholds_only);
         return;
     }
-    const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift);
+    const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift,
+                                segs.shift(row));
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
-    const CastVotes act = {votes32, lds.lvl, run_tallies ? run_tallies + (size_t)row * n_runs : nullptr, thresholds_only};
+    const CastVotes act = {votes32, lds.lvl, {run_tallies ? run_tallies + (size_t)row * (n_runs / 2) : nullptr, v.shift},
+                           thresholds_only};
     uint32_t kth, tie_cut;
     ListRest rest;
     (void)list_split<SplitEnd::Later>(v, blockIdx.x, gridDim.x, lds, act, kth, tie_cut, rest);
@@ -1687,13 +1685,14 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
     u32x2* cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist, uint32_t* __restrict__ kth_out,
     uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, uint32_t n_runs,
-    uint32_t* __restrict__ lvl_sets, int thresholds_only, unsigned long long* __restrict__ tau_pub,
+    RowSegments segs, uint32_t* __restrict__ lvl_sets, int thresholds_only, unsigned long long* __restrict__ tau_pub,
     const u32x2* __restrict__ runs, uint32_t block_shift)
 {
     __shared__ SplitLds<kMembers> lds;
     const uint32_t row = blockIdx.y, t = threadIdx.x;
     if (slow_flag[row] == 1u) return;
-    const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift);
+    const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift,
+                                segs.shift(row));
     const uint32_t* left = row_rest(tau_pub, row);
     const ListRest rest = {left[0], left[1], left[2]};
     const uint32_t share = members_stored(v, rest) ? rest.n : v.n;
@@ -1703,7 +1702,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         if (t == 0) *v.count2 = 0;
     }
     for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the next barrier
-    const CastVotes act = {votes32, lds.lvl, run_tallies ? run_tallies + (size_t)row * n_runs : nullptr, thresholds_only};
+    const CastVotes act = {votes32, lds.lvl, {run_tallies ? run_tallies + (size_t)row * (n_runs / 2) : nullptr, v.shift},
+                           thresholds_only};
     uint32_t kth, tie_cut;
     if (rest.n <= (uint32_t)kMembers && members_stored(v, rest)) {   // uniform; usual: this is the row's only workgroup
         static_assert(kMembers <= kListBatch, "a batch holds them");
@@ -1757,7 +1757,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
         }
         if (largest == smallest && rest.want < rest.n) {
             kth = largest;
-            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, runs + (size_t)row * n_runs, n_runs, lds);
+            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, runs + (size_t)row * n_runs, segs.count(row), lds);
             ranked = true;
         }
     }

@@ -41,13 +41,22 @@ namespace mvk {
 // resets the per-step counters.
 //
 // Streaming: one wavefront = one segment of 1024 consecutive coordinates of one row,
-// read as 4 sub-blocks of 256 (lane l holds coordinates base + 256u + 4l .. +3); a
-// workgroup of 8 wavefronts covers 8 consecutive segments.  Coordinates with
+// read as 4 sub-blocks of 256 (lane l holds coordinates base + 256u + 4l .. +3).  Eight
+// consecutive workgroups of 8 wavefronts share 64 consecutive segments, each taking every
+// eighth: the dies, over which consecutive workgroups are spread, then work on neighbouring
+// 4 KB of the same 32 KB, and whole, aligned ones (RowSegments).  Bare e = g + e on one box, with 8
+// consecutive segments to a workgroup / so / so and aligned:
+//   32 x 25.6 M fp32 1858 / 1630 / 1486 us, bf16 1565 / 1415 / 1268;
+//   16 x 11.2 M fp32  399 /  356 /  335 us, bf16  337 /  313 /  290 (6.4 and 6.2 TB/s);
+//   up to 4 x 2^20 no difference.
+// Neighbouring pieces of 2 KB or 1 KB are slower where rows are not aligned to them and no faster
+// where they are; segments that begin at 128-byte lines lose 1 to 3 % against 4 KB.
+// Coordinates with
 // (bits(a) & 0x7FFFFFFF) >= tau are appended to the row's candidate list as
-// (magnitude bits, coordinate), in ascending coordinate order inside the workgroup's
-// run; runs[row][b] = (start of workgroup b's run, its length).  Runs land in the list in any
+// (magnitude bits, coordinate), in ascending coordinate order inside the segment's
+// run; runs[row][run_place(s, number of segments)] = (start of segment s's run, its length).  Runs land in the list in any
 // order; the table makes the order recoverable.  The workgroup reserves list space
-// for its run with ONE atomic on the row's counter (returning atomics on one
+// for its 8 runs with ONE atomic on the row's counter (returning atomics on one
 // cache line complete only every few nanoseconds chip-wide, so one per wavefront
 // would bound the whole pass when candidates are spread evenly).  Entries beyond
 // `cap` are dropped, the counter keeps counting (the overflow is detected from it).
@@ -59,7 +68,7 @@ struct StreamLds {
     uint64_t scan[kStreamThreads / kWave + 1];
     uint32_t found, is_last;
     uint32_t wave_total[kSegPerBlock];
-    uint32_t block_base, block_total;
+    uint32_t block_base;
 };
 
 template <typename GT>
@@ -199,7 +208,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     uint32_t n_lvl_words, uint32_t* __restrict__ ad_count,
     u32x2* __restrict__ cand, uint32_t cap, uint32_t* __restrict__ row_count_sets, uint32_t row_count_set_words,
     u32x2* __restrict__ runs,
-    uint32_t* __restrict__ run_taken, uint32_t nseg, uint32_t wgs_per_row, uint32_t head_wgs,
+    uint32_t* __restrict__ run_taken, uint32_t n_runs, RowSegments segs, uint32_t head_wgs,
     uint32_t* __restrict__ zero_votes32, int64_t votes_bytes)
 {
     __shared__ StreamLds lds;
@@ -216,11 +225,13 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
         return;
     }
     const uint32_t sb = blockIdx.x - n_rows * spr;
+    const uint32_t wgs_per_row = n_runs / kSegPerBlock;
     const uint32_t row = sb / wgs_per_row, bx = sb % wgs_per_row;
-    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;
-    const uint32_t s = bx * kSegPerBlock + wave;
+    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t nseg = segs.count(row), place = bx * kSegPerBlock + wave, s = run_place(place, nseg);
+    if (bx * kSegPerBlock >= nseg) return;       // whole workgroup (a shorter shift than the longest)
     const bool live = s < nseg;                  // whole wavefront; dead ones only keep the barriers company
-    const int64_t base = (int64_t)s * kSeg;
+    const int64_t base = (int64_t)s * kSeg - segs.shift(row);
     const GT* grow = g + (int64_t)row * ld_g;
     float*    erow = e + (int64_t)row * ld_e;
     const unsigned long long* tau_at = tau_pub + row * (kCounterStride / 2);
@@ -247,7 +258,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
 
     uint32_t key[16];
     uint32_t inside = 0;                          // bit i: key[i] is a coordinate of the row
-    if (live && base + kSeg <= d) {
+    if (live && base >= 0 && base + kSeg <= d) {
         f32x4 gv[4], ev[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -270,32 +281,48 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
         }
         inside = 0xFFFFu;
     } else if (live) {
-        // last segment of the row: element-wise, nothing past d is read or written
+        // first or last segment of the row: nothing outside it is read or written.  (base is a multiple of 4, so only
+        // the row's last quad can be cut)
+        f32x4 gv[4], ev[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t j = base + u * 256 + lane * 4;
+            if (j >= 0 && j + 4 <= d) {
+                gv[u] = load4_grad(grow + j);
+                ev[u] = *reinterpret_cast<const f32x4*>(erow + j);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const bool there = j >= 0 && j + c < d;
+                    gv[u][c] = there ? load1_grad(grow + j + c) : 0.0f;
+                    ev[u][c] = there ? erow[j + c] : 0.0f;
+                }
+            }
+        }
         samples_are_in();
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) {
+            const int64_t j = base + u * 256 + lane * 4;
+            const f32x4 a = gv[u] + ev[u];
+            if (j >= 0 && j + 4 <= d) *reinterpret_cast<f32x4*>(erow + j) = a;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const int64_t j = base + u * 256 + lane * 4 + c;
-                uint32_t k = 0;
-                if (j < d) {
-                    float a = load1_grad(grow + j) + erow[j];
-                    erow[j] = a;
-                    k = __float_as_uint(a) & kAbsMask;
-                    inside |= 1u << (u * 4 + c);
-                }
-                key[u * 4 + c] = k;
+                const bool there = j >= 0 && j + c < d;
+                if (there && j + 4 > d) erow[j + c] = a[c];
+                key[u * 4 + c] = __float_as_uint(a[c]) & kAbsMask;
+                inside |= (there ? 1u : 0u) << (u * 4 + c);
             }
+        }
     }
 
     // tau: wait for it if need be (bounded), then the candidates' flags
-    while ((uint32_t)(tw >> 32) != epoch && spins < spin_limit) {
+    while (live && (uint32_t)(tw >> 32) != epoch && spins < spin_limit) {
         __builtin_amdgcn_s_sleep(16);
         tw = __hip_atomic_load(tau_at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         ++spins;
     }
     uint32_t tau = (uint32_t)tw;
-    if ((uint32_t)(tw >> 32) != epoch) {                               // not seen in time: the row goes the exact way
+    if (live && (uint32_t)(tw >> 32) != epoch) {                       // not seen in time: the row goes the exact way
         tau = 0xFFFFFFFFu;                                             // above every key
         if (lane == 0) atomicMax(&row_poison[row], epoch);             // step numbers only grow: never reset
     }
@@ -331,7 +358,6 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
             lds.wave_total[w] = sum;
             sum += t;
         }
-        lds.block_total = sum;
         lds.block_base = sum ? atomicAdd(&row_count[row * kCounterStride], sum) : 0u;
     }
     __syncthreads();
@@ -352,17 +378,17 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
                     }
                 }
     }
-    // Row 0's wavefronts pass over every coordinate once: they also clear the packed vote bytes
-    // (one per coordinate, 16 per lane), which the kernels that follow fill and read.
+    // Row 0's wavefronts also clear the packed vote bytes (one per coordinate, 16 per lane), which the kernels
+    // that follow fill and read.
     if (zero_votes32 && row == 0 && live) {
-        const int64_t j = base + (int64_t)lane * 16;
+        const int64_t j = (int64_t)s * kSeg + (int64_t)lane * 16;
         const u32x4 z = {0u, 0u, 0u, 0u};
         if (j < votes_bytes) *reinterpret_cast<u32x4*>(zero_votes32 + (j >> 2)) = z;
     }
-    if (threadIdx.x == 0) {
-        runs[(size_t)row * wgs_per_row + bx] = u32x2{lds.block_base, lds.block_total};
-        run_taken[(size_t)row * wgs_per_row + bx] = 0;     // tallied when the votes are cast
-    }
+    // the runs' table, and the tallies that are counted when the votes are cast
+    if (lane == 0) runs[(size_t)row * n_runs + place] = u32x2{run_start, total};
+    constexpr uint32_t kWords = kSegPerBlock / 2;
+    if (threadIdx.x < kWords) run_taken[((size_t)row * wgs_per_row + bx) * kWords + threadIdx.x] = 0;
 }
 
 }  // namespace mvk

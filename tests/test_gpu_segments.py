@@ -1,0 +1,94 @@
+"""The streaming pass's segments begin at multiples of 4 KB of the error buffer's address and go round groups of eight
+workgroups: error buffers that begin anywhere in 4 KB, rows whose beginnings differ in it, rows that end at the edges of a
+segment, a workgroup's share and a group, and every reader of the table of runs (sorted lists, large tie groups)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2011_06495_amd import binding as B
+from tests.gpu_util import SENTINEL_F32, GpuStepper, assert_matches_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def steps_at(oracle, what, N, d, K, offset, extra_ld, grads, bf16=False, steps=2):
+    """`steps` steps with the error buffer `offset` floats behind a 4 KB boundary."""
+    print("[case] %s N=%d d=%d K=%d offset=%d extra_ld=%d" % (what, N, d, K, offset, extra_ld), flush=True)
+    with GpuStepper(N, d, K, bf16=bf16, extra_ld=extra_ld) as gs:
+        pool = torch.full((1024 + offset + gs.e.numel(),), SENTINEL_F32, dtype=torch.float32, device=gs.dev)
+        first = -(pool.data_ptr() // 4) % 1024 + offset
+        gs.e = pool[first:first + gs.e.numel()].view(N, gs.ld_e)
+        assert gs.e.data_ptr() // 4 % 1024 == offset % 1024
+        e = np.random.default_rng(offset).standard_normal((N, d)).astype(np.float32) if offset % 8 else np.zeros((N, d), np.float32)
+        gs.set_error(e)
+        for t in range(steps):
+            g = grads(t)
+            gs.set_grads(g)
+            gs.step()
+            ref = oracle.vote_step(g, e, K, threads=8)
+            assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (what, t))
+            e = ref.err
+        outside = torch.cat([pool[:first], pool[first + gs.e.numel():]])
+        assert bool((outside == SENTINEL_F32).all()), "write outside the error buffer"
+
+
+@pytest.mark.parametrize("offset", [0, 4, 512, 1020])
+@pytest.mark.parametrize("d", [32769, 65532, 65536, 65540, 73728, 73733, 131071, 131072 + 8193])
+def test_rows_that_begin_anywhere_in_4_kb(oracle, d, offset):
+    rng = np.random.default_rng(d + offset)
+    steps_at(oracle, "normal", 3, d, d // 100, offset, 3 * offset // 4 % 7,
+             lambda t: rng.standard_normal((3, d)).astype(np.float32))
+
+
+@pytest.mark.parametrize("N,d,K,offset", [(1, 70001, 70, 4), (5, 90003, 300, 516), (2, 262144, 2621, 1020)])
+def test_bf16_gradients_beside_shifted_rows(oracle, N, d, K, offset):
+    rng = np.random.default_rng(d)
+
+    def grads(t):
+        return (rng.standard_normal((N, d)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    steps_at(oracle, "bf16", N, d, K, offset, 1, grads, bf16=True)
+
+
+@pytest.mark.parametrize("offset", [0, 8, 1016])
+@pytest.mark.parametrize("kind", ["equal", "lattice", "normal"])
+@pytest.mark.parametrize("N,d,K", [(2, 131073, 40000), (1, 2500003, 70000)])
+def test_long_lists_of_shifted_rows(oracle, N, d, K, kind, offset):
+    """Lists selected by many workgroups: with equal values the K-th lies in a tie group whose cut is found by blocks
+    of one segment (131,073 coordinates) and of two (2.5 M)."""
+    rng = np.random.default_rng(K + offset)
+    make = {"equal": lambda t: np.full((N, d), 0.5, np.float32),
+            "lattice": lambda t: (np.rint(rng.standard_normal((N, d)) * 2) / 2).astype(np.float32),
+            "normal": lambda t: rng.standard_normal((N, d)).astype(np.float32)}[kind]
+    steps_at(oracle, kind, N, d, K, offset, 5, make, steps=1)
+
+
+def test_sorted_list_of_a_row_with_several_units_to_a_prefix():
+    """Beyond 33.5 M coordinates a prefix of the tallies covers several of their units."""
+    d, K = 34_000_003, 34_000
+    print("[case] one row of %d coordinates" % d, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    ld = (d + 3) // 4 * 4
+    g = torch.zeros((1, ld), device="cuda")
+    g[:, :d] = torch.randn(d, generator=gen, device="cuda")
+    e = torch.zeros((1, ld), device="cuda")
+    widx = torch.zeros((1, K), dtype=torch.int32, device="cuda")
+    mask = torch.zeros(K, dtype=torch.int32, device="cuda")
+    agg = torch.zeros(K, device="cuda")
+    keys = g[0, :d].abs()
+    kth = torch.topk(keys, K).values[-1]
+    want = keys > kth
+    ties = torch.nonzero(keys == kth).flatten()
+    want[ties[: K - int(want.sum())]] = True
+    want = torch.nonzero(want).flatten().to(torch.int32)
+    ctx = B.mv_begin(B.make_config(1, d, K))
+    try:
+        B.mv_vote_step(ctx, g, e, widx, None, mask, agg, ld_g=ld, ld_e=ld)
+        torch.cuda.synchronize()
+    finally:
+        B.mv_end(ctx)
+        B.mv_release(ctx)
+    assert torch.equal(widx[0], want) and torch.equal(mask, want)
+    assert torch.equal(agg, g[0, want.long()])
+    g[0, want.long()] = 0.0
+    assert torch.equal(e, g)
