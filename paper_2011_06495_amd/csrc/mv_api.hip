@@ -77,6 +77,7 @@ struct Plan {
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
     // scratch offsets (bytes)
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
+    bool     through;           // the streaming pass stores past the caches
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
     size_t off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_runs, off_runtaken,
@@ -152,6 +153,12 @@ Plan make_plan(const mv_config* c)
     // memory to themselves, in any grid: two rounds of resident workgroups wait (2 x 1,000,003, K = 1000: 39.5 us, 39.9
     // if none did; 16 x 2,000,003: 99.5 and 100.7; only from 40 x 300,001, K = 300 known otherwise: 56.0 and 54.1).
     p.head_wgs = p.sample_wgs == 1 ? 0 : 2048;
+    // Where gradients and errors lie in the last-level cache (256 MB), stores past the dies' L2s spare the kernel's end
+    // the writing back of what they left there.  The line follows the bytes of both, time written back : time past the
+    // caches: 11 MB (7 x 272,475 bf16) 31.4 30.1; 34 MB 44.6 43.0; 128 MB (16 x 1 M) 63.0 59.9, (4 x 4 M) 83.5 79.8;
+    // 134 MB (8 x 2.8 M bf16) 74.9 73.4; 160 MB (2 x 10 M) 95.7 94.4, (10 x 2 M) 87.3 83.7; beyond it, 176 MB 121 127;
+    // 204 MB 124 132; 216 MB (12 x 3 M bf16) 112 116; 894 MB 332 360.
+    p.through = (uint64_t)p.N * (uint64_t)p.d * (c->grad_dtype == MV_BF16 ? 6 : 8) <= 160ull << 20;
     p.stride = (uint32_t)stride;
     p.n_sampled_chunks = (uint32_t)((nchunks + stride - 1) / stride);
     // all sampled chunks are full except possibly the row's last chunk
@@ -551,14 +558,14 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, p.through ? 1 : 0,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, p.through ? 1 : 0,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }

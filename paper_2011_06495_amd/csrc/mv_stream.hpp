@@ -199,6 +199,15 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     for (uint32_t i = row * kStreamThreads + t; i < n_lvl_words; i += n_rows * kStreamThreads) lvl_sets[i] = 0;
 }
 
+// 16 bytes to a wavefront's segment at `seg` (uniform), past the caches: nothing is left to be written back when the
+// kernel ends (see make_plan for when that pays).
+__device__ __forceinline__ void store_through(f32x4 v, float* seg, uint32_t byte)
+{
+    constexpr int kRaw = 0x00027000, kPastCaches = 17;      // a plain buffer of 32-bit data; system scope
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), __builtin_amdgcn_make_buffer_rsrc(seg, 0, kSeg * 4, kRaw),
+                                           byte, 0, kPastCaches);
+}
+
 template <typename GT>
 __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     const GT* __restrict__ g, int64_t ld_g, float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t n_rows,
@@ -208,7 +217,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     uint32_t n_lvl_words, uint32_t* __restrict__ ad_count,
     u32x2* __restrict__ cand, uint32_t cap, uint32_t* __restrict__ row_count_sets, uint32_t row_count_set_words,
     u32x2* __restrict__ runs,
-    uint32_t* __restrict__ run_taken, uint32_t n_runs, RowSegments segs, uint32_t head_wgs,
+    uint32_t* __restrict__ run_taken, uint32_t n_runs, RowSegments segs, uint32_t head_wgs, int through,
     uint32_t* __restrict__ zero_votes32, int64_t votes_bytes)
 {
     __shared__ StreamLds lds;
@@ -273,7 +282,8 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
         for (int u = 0; u < 4; ++u) {
             const int64_t j = base + u * 256 + lane * 4;
             const f32x4 a = gv[u] + ev[u];
-            __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(erow + j));
+            if (through) store_through(a, erow + base, (uint32_t)(j - base) * 4u);       // uniform
+            else         __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(erow + j));
             key[u * 4 + 0] = __float_as_uint(a.x) & kAbsMask;
             key[u * 4 + 1] = __float_as_uint(a.y) & kAbsMask;
             key[u * 4 + 2] = __float_as_uint(a.z) & kAbsMask;
