@@ -77,9 +77,10 @@ struct Plan {
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
     // scratch offsets (bytes)
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
+    bool     keep_samples;      // several sampling workgroups store what they read
     bool     through;           // the streaming pass stores past the caches
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
-    size_t off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
+    size_t off_samples, off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_runs, off_runtaken,
         off_alist, off_dlist, off_adcount, off_adbits, off_adblk, off_cand, off_votes, off_blockcnt, off_subcnt, off_votethr, off_emitfail,
         off_lookback;
@@ -159,6 +160,11 @@ Plan make_plan(const mv_config* c)
     // 134 MB (8 x 2.8 M bf16) 74.9 73.4; 160 MB (2 x 10 M) 95.7 94.4, (10 x 2 M) 87.3 83.7; beyond it, 176 MB 121 127;
     // 204 MB 124 132; 216 MB (12 x 3 M bf16) 112 116; 894 MB 332 360.
     p.through = (uint64_t)p.N * (uint64_t)p.d * (c->grad_dtype == MV_BF16 ? 6 : 8) <= 160ull << 20;
+    // With few workers the mask is nearly what each of them asked for, every coordinate grows until it is sent, and
+    // the magnitudes pile up below the K-th: there several sampling workgroups keep their samples (1 x 25.6 M: 0.8 us).
+    // With more the residuals spread (lists stay within 3K over a thousand steps of 4 to 32 rows), and it would only
+    // cost the step (10 x 11.2 M: 1.4 us, 32 x 25.6 M 9).
+    p.keep_samples = p.sample_wgs > 1 && p.N <= 4;
     p.stride = (uint32_t)stride;
     p.n_sampled_chunks = (uint32_t)((nchunks + stride - 1) / stride);
     // all sampled chunks are full except possibly the row's last chunk
@@ -260,6 +266,9 @@ Plan make_plan(const mv_config* c)
     off = align_up(off);
     p.off_runs = off;     off += align_up((size_t)p.N * p.n_runs * 8);
     p.off_runtaken = off; off += align_up((size_t)p.N * p.n_runs * 2);
+    if (p.keep_samples) {                         // their magnitudes
+        p.off_samples = off; off += align_up((size_t)p.N * p.n_sampled_chunks * mvk::kChunk * 4);
+    }
     p.off_cand = off;     off += align_up((size_t)p.N * p.cap * 8);
     p.off_votes = off;    off += align_up(((size_t)p.d + 15) / 16 * 16);
     p.off_blockcnt = off; off += align_up((size_t)p.n_vote_blocks * 8);
@@ -548,6 +557,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     // also reset the per-step counters), and the streaming pass a = g + e over e, candidates out
     uint32_t* sampledone = ws_ptr<uint32_t>(c, p.off_sampledone);
     uint32_t* readsdone = ws_ptr<uint32_t>(c, p.off_readsdone);
+    uint32_t* samples = p.keep_samples ? ws_ptr<uint32_t>(c, p.off_samples) : nullptr;
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
     {
@@ -557,14 +567,14 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
             hipLaunchKernelGGL(mvk::mv_stream_collect<uint16_t>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
-                               c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
+                               c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
                                rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, p.through ? 1 : 0,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
-                               c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, cand, p.cap,
+                               c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
                                rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, p.through ? 1 : 0,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);

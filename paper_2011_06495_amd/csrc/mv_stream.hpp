@@ -60,6 +60,18 @@ namespace mvk {
 // cache line complete only every few nanoseconds chip-wide, so one per wavefront
 // would bound the whole pass when candidates are spread evenly).  Entries beyond
 // `cap` are dropped, the counter keeps counting (the overflow is detected from it).
+//
+// A bin is 3 % of a magnitude wide.  Error buffers that a steady gradient has driven for long hold many magnitudes
+// just below the K-th, and the edge of the bin lets them all into the list: one that overflows has its row
+// selected from memory by one workgroup (1 x 16 M, after some thousand steps: 1.7 ms for 0.1).  So the samples are kept,
+// and where the bin's own make the list longer than kCrowdedOne or kCrowdedMany times what it has to be, the picking
+// workgroup goes through them once more and places tau inside the bin, at one of kSubBins edges.  One sampling workgroup
+// keeps its samples in registers; several keep them in memory, past the caches, and only with few workers (see make_plan).
+constexpr int      kSubBins = kStreamThreads;
+constexpr int      kSubShift = kHistShift - 9;
+static_assert(kSubBins == 512, "9 bits behind the bin's");
+// (several sampling workgroups have more to go through again)
+constexpr uint32_t kCrowdedOne = 2, kCrowdedMany = 3;
 constexpr int      kSampleQuads = 4;              // quads of samples a sampling thread has in flight
 constexpr uint32_t kRowPoison = 0x80000000u;      // set in a marked row's candidate counter by mv_row_select
 
@@ -67,9 +79,60 @@ struct StreamLds {
     __attribute__((aligned(16))) uint32_t h[kHistBins];   // sampling workgroups only
     uint64_t scan[kStreamThreads / kWave + 1];
     uint32_t found, is_last;
+    uint32_t crowd[3];                                    // a crowded bin: its number, the samples above it, those in it
     uint32_t wave_total[kSegPerBlock];
     uint32_t block_base;
 };
+
+// 16 bytes past the caches, at byte offset `byte` of a buffer of `bytes` bytes (both uniform but for the offset)
+constexpr int kRawBuffer = 0x00027000, kPastCaches = 17;       // plain 32-bit data; system scope
+__device__ __forceinline__ void store_through(u32x4 v, void* buffer, uint32_t bytes, uint32_t byte)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(buffer, 0, bytes, kRawBuffer), byte, 0, kPastCaches);
+}
+__device__ __forceinline__ u32x4 load_through(void* buffer, uint32_t bytes, uint32_t byte)
+{
+    return __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc(buffer, 0, bytes, kRawBuffer), byte, 0,
+                                                 kPastCaches);
+}
+
+// The lower edge of the sub-bin of the crowded bin at which `want` of its samples are covered from above.  The samples are
+// in memory or (null) the threads' kept ones.  The whole workgroup.
+__device__ __forceinline__ uint32_t edge_inside_bin(StreamLds& lds, uint32_t* samples, uint32_t nquads,
+                                                    const u32x4 (&kept)[kSampleQuads], uint32_t bin, uint32_t want)
+{
+    const uint32_t t = threadIdx.x;
+    lds.h[t] = 0;
+    __syncthreads();
+    auto tally = [&](u32x4 k) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (k[c] >> kHistShift == bin) atomicAdd(&lds.h[k[c] >> kSubShift & (uint32_t)(kSubBins - 1)], 1u);
+    };
+    if (!samples) {
+#pragma unroll
+        for (int u = 0; u < kSampleQuads; ++u) tally(kept[u]);
+    } else {
+        for (uint32_t q0 = t; q0 < nquads; q0 += kSampleQuads * kStreamThreads) {
+            u32x4 k[kSampleQuads];
+#pragma unroll
+            for (int u = 0; u < kSampleQuads; ++u) {
+                const uint32_t q = q0 + (uint32_t)u * kStreamThreads;
+                const u32x4 z = {0u, 0u, 0u, 0u};
+                k[u] = q < nquads ? load_through(samples, nquads * 16u, q * 16u) : z;
+            }
+#pragma unroll
+            for (int u = 0; u < kSampleQuads; ++u) tally(k[u]);
+        }
+    }
+    __syncthreads();
+    const uint32_t sub = (uint32_t)(kSubBins - 1) - t, n = lds.h[sub];           // from above
+    uint32_t total;
+    const uint32_t excl = block_excl_scan<kStreamThreads>(n, lds.scan, total);
+    if (excl < want && want <= excl + n) lds.found = bin << kHistShift | sub << kSubShift;
+    __syncthreads();
+    return lds.found;
+}
 
 template <typename GT>
 __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __restrict__ g, int64_t ld_g,
@@ -81,7 +144,7 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
                                                 unsigned long long* __restrict__ tau_pub, uint32_t epoch,
                                                 uint32_t* __restrict__ next_row_count, uint32_t* __restrict__ lvl_sets,
                                                 uint32_t n_lvl_words, uint32_t n_rows,
-                                                uint32_t* __restrict__ ad_count)
+                                                uint32_t* __restrict__ ad_count, uint32_t* __restrict__ all_samples)
 {
     const uint32_t t = threadIdx.x;
     {
@@ -92,20 +155,30 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     __syncthreads();
     const GT*    grow = g + (int64_t)row * ld_g;
     const float* erow = e + (int64_t)row * ld_e;
-    const uint64_t nquads = (uint64_t)n_sampled_chunks * (kChunk / 4);
-    const uint64_t step = (uint64_t)spr * kStreamThreads;
-    auto start_of = [stride](uint64_t q) {
+    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most one coordinate in 64, or 65,536
+    uint32_t* samples = all_samples ? all_samples + (size_t)row * nquads * 4 : nullptr;
+    u32x4 kept[kSampleQuads];                     // of the thread's last round: one sampling workgroup has no other
+#pragma unroll
+    for (int u = 0; u < kSampleQuads; ++u) kept[u] = u32x4{0u, 0u, 0u, 0u};
+    const uint32_t step = spr * kStreamThreads;
+    auto start_of = [stride](uint32_t q) {
         return (int64_t)(q / (kChunk / 4)) * stride * kChunk + (int64_t)(q % (kChunk / 4)) * 4;
     };
-    auto tally = [&](float a) { atomicAdd(&lds.h[(__float_as_uint(a) & kAbsMask) >> kHistShift], 1u); };
+    auto keep_and_tally = [&](uint32_t q, u32x4 key, int n, u32x4& keep) {
+        keep = key;
+        if (samples) store_through(key, samples, nquads * 16u, q * 16u);         // uniform
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (c < n) atomicAdd(&lds.h[key[c] >> kHistShift], 1u);
+    };
     // The samples lie far apart in memory and every load pays the full latency: kSampleQuads
     // quads' loads are in flight per thread and the grid is sized for one or two rounds.
-    for (uint64_t q0 = (uint64_t)part * kStreamThreads + t; q0 < nquads; q0 += kSampleQuads * step) {
+    for (uint32_t q0 = part * kStreamThreads + t; q0 < nquads; q0 += kSampleQuads * step) {
         f32x4 gv[kSampleQuads], ev[kSampleQuads];
         bool  full[kSampleQuads];
 #pragma unroll
         for (int u = 0; u < kSampleQuads; ++u) {
-            const uint64_t q = q0 + (uint64_t)u * step;
+            const uint32_t q = q0 + (uint32_t)u * step;
             const int64_t j = start_of(q);
             full[u] = q < nquads && j + 4 <= d;
             if (full[u]) {
@@ -115,15 +188,17 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
         }
 #pragma unroll
         for (int u = 0; u < kSampleQuads; ++u) {
-            const uint64_t q = q0 + (uint64_t)u * step;
+            const uint32_t q = q0 + (uint32_t)u * step;
             if (full[u]) {
                 const f32x4 a = gv[u] + ev[u];
-                tally(a.x);
-                tally(a.y);
-                tally(a.z);
-                tally(a.w);
+                keep_and_tally(q, __builtin_bit_cast(u32x4, a) & kAbsMask, 4, kept[u]);
             } else if (q < nquads) {
-                for (int64_t jj = start_of(q); jj < d; ++jj) tally(load1_grad(grow + jj) + erow[jj]);
+                const int64_t j = start_of(q);
+                u32x4 key = {0u, 0u, 0u, 0u};
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (j + c < d) key[c] = __float_as_uint(load1_grad(grow + j + c) + erow[j + c]) & kAbsMask;
+                keep_and_tally(q, key, j < d ? (int)(d - j) : 0, kept[u]);
             }
         }
     }
@@ -172,14 +247,25 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
         uint32_t acc = excl;
 #pragma unroll
         for (int q = 0; q < per; ++q) {
-            if (acc < m_target && m_target <= acc + c[q])
-                lds.found = (uint32_t)(kHistBins - 1 - ((int)t * per + q)) << kHistShift;
+            if (acc < m_target && m_target <= acc + c[q]) {
+                const uint32_t bin = (uint32_t)(kHistBins - 1 - ((int)t * per + q));
+                lds.found = bin << kHistShift;
+                lds.crowd[0] = bin;
+                lds.crowd[1] = acc;
+                lds.crowd[2] = c[q];
+            }
             acc += c[q];
         }
     }
     __syncthreads();
+    uint32_t tau = (total >= m_target) ? lds.found : 0u;
+    const uint32_t bin = lds.crowd[0], above = lds.crowd[1], in_bin = lds.crowd[2];
+    if ((spr == 1u || samples) && tau != 0u &&
+        (uint64_t)above + in_bin > (uint64_t)m_target * (spr == 1u ? kCrowdedOne : kCrowdedMany)) {               // uniform
+        __syncthreads();
+        tau = edge_inside_bin(lds, samples, nquads, kept, bin, m_target - above);
+    }
     if (t == 0) {
-        const uint32_t tau = (total >= m_target) ? lds.found : 0u;
         __hip_atomic_store(&tau_pub[row * (kCounterStride / 2)], ((unsigned long long)epoch << 32) | tau,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -199,22 +285,13 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     for (uint32_t i = row * kStreamThreads + t; i < n_lvl_words; i += n_rows * kStreamThreads) lvl_sets[i] = 0;
 }
 
-// 16 bytes to a wavefront's segment at `seg` (uniform), past the caches: nothing is left to be written back when the
-// kernel ends (see make_plan for when that pays).
-__device__ __forceinline__ void store_through(f32x4 v, float* seg, uint32_t byte)
-{
-    constexpr int kRaw = 0x00027000, kPastCaches = 17;      // a plain buffer of 32-bit data; system scope
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), __builtin_amdgcn_make_buffer_rsrc(seg, 0, kSeg * 4, kRaw),
-                                           byte, 0, kPastCaches);
-}
-
 template <typename GT>
 __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     const GT* __restrict__ g, int64_t ld_g, float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t n_rows,
     uint32_t spr, uint32_t stride, uint32_t n_sampled_chunks, uint32_t m_target,
     uint32_t* __restrict__ hist, uint32_t* __restrict__ sample_done, uint32_t* __restrict__ reads_done,
     unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ step_no, uint32_t spin_limit, uint32_t* __restrict__ row_poison, uint32_t* __restrict__ lvl_sets,
-    uint32_t n_lvl_words, uint32_t* __restrict__ ad_count,
+    uint32_t n_lvl_words, uint32_t* __restrict__ ad_count, uint32_t* __restrict__ samples,
     u32x2* __restrict__ cand, uint32_t cap, uint32_t* __restrict__ row_count_sets, uint32_t row_count_set_words,
     u32x2* __restrict__ runs,
     uint32_t* __restrict__ run_taken, uint32_t n_runs, RowSegments segs, uint32_t head_wgs, int through,
@@ -230,7 +307,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     if (blockIdx.x < n_rows * spr) {
         sample_and_pick<GT>(lds, g, ld_g, e, ld_e, d, blockIdx.x / spr, blockIdx.x % spr, spr, stride, n_sampled_chunks,
                             m_target, hist, sample_done, reads_done, tau_pub, epoch, next_row_count, lvl_sets, n_lvl_words,
-                            n_rows, ad_count);
+                            n_rows, ad_count, samples);
         return;
     }
     const uint32_t sb = blockIdx.x - n_rows * spr;
@@ -282,7 +359,8 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
         for (int u = 0; u < 4; ++u) {
             const int64_t j = base + u * 256 + lane * 4;
             const f32x4 a = gv[u] + ev[u];
-            if (through) store_through(a, erow + base, (uint32_t)(j - base) * 4u);       // uniform
+            // (uniform: stored past the caches, nothing is left to be written back when the kernel ends; see make_plan)
+            if (through) store_through(__builtin_bit_cast(u32x4, a), erow + base, kSeg * 4, (uint32_t)(j - base) * 4u);
             else         __builtin_nontemporal_store(a, reinterpret_cast<f32x4*>(erow + j));
             key[u * 4 + 0] = __float_as_uint(a.x) & kAbsMask;
             key[u * 4 + 1] = __float_as_uint(a.y) & kAbsMask;

@@ -92,3 +92,22 @@ def test_sorted_list_of_a_row_with_several_units_to_a_prefix():
     assert torch.equal(agg, g[0, want.long()])
     g[0, want.long()] = 0.0
     assert torch.equal(e, g)
+
+
+@pytest.mark.parametrize("N,d,K,width", [(2, 300_001, 300, 0.01), (2, 300_001, 300, 0.002), (1, 2_000_003, 2000, 0.01),
+                                         (3, 1_300_001, 9000, 0.01), (1, 40_000, 100, 0.02)])
+def test_threshold_inside_a_crowded_bin(oracle, N, d, K, width):
+    """All magnitudes within one bin of the sample's histogram (3 %): the threshold is placed inside it, by one sampling
+    workgroup and by several, and no row's list overflows."""
+    print("[case] crowded bin N=%d d=%d K=%d width=%g" % (N, d, K, width), flush=True)
+    rng = np.random.default_rng(d + K)
+    g = ((1.0 + width * rng.random((N, d))) * rng.choice([-1.0, 1.0], size=(N, d))).astype(np.float32)
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        for t in range(2):
+            gs.set_error(e)
+            gs.set_grads(g)
+            gs.step()
+            assert_matches_oracle(gs.fetch(), oracle.vote_step(g, e, K, threads=8), "crowded bin")
+            count, _, slow = gs.row_stats()
+            assert 1 not in slow, "rows selected from memory: %s, list lengths %s" % (slow, count)
