@@ -15,7 +15,7 @@
 //                         trusted) and publishes it.  The other workgroups
 //                         stream: a = g + e is written over e, and every
 //                         coordinate with |a| >= tau is appended to the row's
-//                         candidate list; each workgroup
+//                         candidate list; each wavefront
 //                         records where its run of candidates went.  A
 //                         streaming wavefront looks for its row's tau while its
 //                         loads are in flight and polls a bounded number of
