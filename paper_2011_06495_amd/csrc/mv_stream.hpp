@@ -157,51 +157,49 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     const float* erow = e + (int64_t)row * ld_e;
     const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most one coordinate in 64, or 65,536
     uint32_t* samples = all_samples ? all_samples + (size_t)row * nquads * 4 : nullptr;
-    u32x4 kept[kSampleQuads];                     // of the thread's last round: one sampling workgroup has no other
-#pragma unroll
-    for (int u = 0; u < kSampleQuads; ++u) kept[u] = u32x4{0u, 0u, 0u, 0u};
     const uint32_t step = spr * kStreamThreads;
     auto start_of = [stride](uint32_t q) {
         return (int64_t)(q / (kChunk / 4)) * stride * kChunk + (int64_t)(q % (kChunk / 4)) * 4;
     };
-    auto keep_and_tally = [&](uint32_t q, u32x4 key, int n, u32x4& keep) {
-        keep = key;
-        if (samples) store_through(key, samples, nquads * 16u, q * 16u);         // uniform
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            if (c < n) atomicAdd(&lds.h[key[c] >> kHistShift], 1u);
-    };
     // The samples lie far apart in memory and every load pays the full latency: kSampleQuads
-    // quads' loads are in flight per thread and the grid is sized for one or two rounds.
-    for (uint32_t q0 = part * kStreamThreads + t; q0 < nquads; q0 += kSampleQuads * step) {
+    // quads' loads are in flight per thread and the grid is sized for one or two rounds.  A round loads in every
+    // lane (past the samples: the row's first quad) and assigns all of `kept`, which is therefore not alive in the
+    // next round's loads.  The streaming workgroups have to do with the registers that this takes: 60, eight
+    // waves to a SIMD.  Where a thread only assigned what it had loaded, 78 and six (7 x 1,000,003 bf16, K = 2000:
+    // 49.5 -> 49.0 us, 1 x 80,003: 25.2 -> 24.8, 2 x 4,000,003: 70.9 -> 70.2).
+    u32x4 kept[kSampleQuads];                     // the last round's: one sampling workgroup has no other
+    uint32_t q0 = part * kStreamThreads + t;
+    do {
         f32x4 gv[kSampleQuads], ev[kSampleQuads];
-        bool  full[kSampleQuads];
+#pragma unroll
+        for (int u = 0; u < kSampleQuads; ++u) {
+            const uint32_t q = q0 + (uint32_t)u * step;
+            const int64_t j = start_of(q), at = q < nquads && j + 4 <= d ? j : 0;
+            gv[u] = load4_grad(grow + at);
+            ev[u] = *reinterpret_cast<const f32x4*>(erow + at);
+        }
 #pragma unroll
         for (int u = 0; u < kSampleQuads; ++u) {
             const uint32_t q = q0 + (uint32_t)u * step;
             const int64_t j = start_of(q);
-            full[u] = q < nquads && j + 4 <= d;
-            if (full[u]) {
-                gv[u] = load4_grad(grow + j);
-                ev[u] = *reinterpret_cast<const f32x4*>(erow + j);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kSampleQuads; ++u) {
-            const uint32_t q = q0 + (uint32_t)u * step;
-            if (full[u]) {
-                const f32x4 a = gv[u] + ev[u];
-                keep_and_tally(q, __builtin_bit_cast(u32x4, a) & kAbsMask, 4, kept[u]);
-            } else if (q < nquads) {
-                const int64_t j = start_of(q);
-                u32x4 key = {0u, 0u, 0u, 0u};
+            u32x4 key = __builtin_bit_cast(u32x4, gv[u] + ev[u]) & kAbsMask;
+            int n = q < nquads ? 4 : 0;
+            if (q < nquads && j + 4 > d) {        // the row's last quad
+                n = j < d ? (int)(d - j) : 0;
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
-                    if (j + c < d) key[c] = __float_as_uint(load1_grad(grow + j + c) + erow[j + c]) & kAbsMask;
-                keep_and_tally(q, key, j < d ? (int)(d - j) : 0, kept[u]);
+                    if (c < n) key[c] = __float_as_uint(load1_grad(grow + j + c) + erow[j + c]) & kAbsMask;
             }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                key[c] = c < n ? key[c] : 0u;
+                if (c < n) atomicAdd(&lds.h[key[c] >> kHistShift], 1u);
+            }
+            kept[u] = key;
+            if (samples && q < nquads) store_through(key, samples, nquads * 16u, q * 16u);   // (samples: uniform)
         }
-    }
+        q0 += kSampleQuads * step;
+    } while (q0 < nquads);
     __syncthreads();
     // every sample of this workgroup has been used, so it has arrived: the row's streaming
     // wavefronts may overwrite e as far as this workgroup is concerned
