@@ -182,10 +182,10 @@ Plan make_plan(const mv_config* c)
 
     p.rs_blocks = (uint32_t)((p.d + mvk::kVoteBlock - 1) / mvk::kVoteBlock);
     {
-        // the mask kernels: as few vote bytes per thread as keep the grid, with one more workgroup per row, at two
-        // workgroups per compute unit: all resident at once, which the exchange of
-        // counts between the blocks likes (measured: a limit of 500 beats 250 by 3 us on C4 and 13 us on C5;
-        // 750 and more lose again on d = 11 M)
+        // the mask kernels: as few vote bytes per thread as keep the vote blocks at two workgroups per compute unit, all
+        // resident at once, which the exchange of counts between the blocks likes (a limit of 500 beats 250 by 3 us
+        // on 16 x 11.2 M and by 13 on 32 x 25.6 M; 750 and more lose again on d = 11 M), and leave some units to the
+        // lists' workgroups, which come behind them in the grid
         static const uint32_t kQs[] = {1, 2, 3, 4, 6, 8};
         uint32_t q = 8;
         for (uint32_t cand_q : kQs)
@@ -679,11 +679,23 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         after(KID_RS_PICK);
     }
     // 4. global mask: the vote threshold, the counts per stretch of the vote bytes and the mask's coordinates, or the
-    // winners of the random selection in order (extra workgroups write the sorted vote lists beside it); then 5. every
-    // workgroup of the last kernel gathers its part of the mask, takes the mean and updates the error buffers.
+    // winners of the random selection in order; then 5. every workgroup of the last kernel gathers its part of the
+    // mask, takes the mean and updates the error buffers.  Extra workgroups of one of the two write the sorted vote lists.
     const bool lists = sorted && !add_drop;
     {
-        const dim3 grid_c(p.n_vote_blocks + (lists ? p.N * p.emit_blocks : 0));
+        const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, run_taken, p.n_runs, segs, kth, tiecut,
+                                         slow, a.worker_idx};
+        const uint32_t n_list = lists ? p.N * p.emit_blocks : 0;
+        // The lists run beside the mask kernel where its blocks wait for each other's counts anyway (steps beside the
+        // mask : beside the gather: 4 x 2^20, K = 10,486: 43.4 us 46.1; 16 x 11.2 M, K = 11,174: 389.3 392.7;
+        // 16 x 1,000,003, K = 16,000: 74.5 77.9; 3 x 20 M, K = 200,000: 207.0 209.2; 10 x 11.2 M, K = 111,740:
+        // 331.6 330.9).  Not where the blocks are short ones of one quad per thread and do not leave the lists room on
+        // the chip (16 x 6 M, K = 40,000: 267.3 263.5; 32 x 5 M, K = 20,000: 390.4 387.2; 24 x 3 M, K = 30,000:
+        // 216.3 214.1; with room, K = 20,000: 201.5 203.2), nor in random selection, whose blocks do not wait
+        // (3 x 1,467,594: 55.7 54.4; 16 x 5 M: 215.7 211.3; 10 x 11.2 M, K = 111,740: 365.2 362.8; 16 x 11.2 M t3 410.4
+        // 411.6).
+        const bool beside_mask = !random_sel && (p.vote_q > 1 || p.n_vote_blocks + n_list <= 512);
+        const dim3 grid_c(p.n_vote_blocks + (beside_mask ? n_list : 0));
         const dim3 block(mvk::kMaskThreads);
         uint8_t* votes_out = add_drop ? nullptr : a.votes;
         const float inv_n = 1.0f / (float)p.N;
@@ -699,15 +711,13 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         };
         uint32_t rounds = rounds_for(250);
         if (rounds > 2) rounds = rounds_for(1000);
-        const dim3 grid_g((p.K + kb * rounds - 1) / (kb * rounds));
+        const uint32_t n_gather = (p.K + kb * rounds - 1) / (kb * rounds);
+        const dim3 grid_g(n_gather + (beside_mask ? 0 : n_list));
 #define MV_LAUNCH_MASK(Q)                                                                                        \
         before(KID_MASK_COUNT);                                                                                  \
         hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \
                            block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
-                           subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, p.emit_blocks,                 \
-                           (const mvk::u32x2*)cand, p.cap, (const uint32_t*)rowcnt, (const mvk::u32x2*)runs,     \
-                           (const uint32_t*)run_taken, p.n_runs, segs, (const uint32_t*)kth, (const uint32_t*)tiecut, \
-                           (const uint32_t*)slow, a.worker_idx,                                                  \
+                           subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, row_lists,                     \
                            add_drop ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
                            reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
         after(KID_MASK_COUNT);                                                                                   \
@@ -717,7 +727,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                            (const mvk::u32x2*)blockcnt, p.n_vote_blocks,                                         \
                            (const uint32_t*)votethr, a.mask_idx, random_sel ? 1 : 0,                             \
                            (const uint32_t*)emitfail, inv_n,                                                     \
-                           c->cfg.reduce == MV_REDUCE_MEAN ? 1 : 0, a.agg_vals, rounds, stepno);                                                            \
+                           c->cfg.reduce == MV_REDUCE_MEAN ? 1 : 0, a.agg_vals, rounds, n_gather, row_lists, stepno);         \
         after(KID_GATHER);
         switch (p.vote_q) {
             case 1: { MV_LAUNCH_MASK(1) } break;

@@ -34,10 +34,11 @@
 //                         threshold from the level counters, the counts of every
 //                         block of the vote bytes, their sums across blocks
 //                         (published between the workgroups), and the mask's
-//                         coordinates written in place.  Extra workgroups
-//                         write each row's vote in ascending coordinate order
+//                         coordinates written in place
 //   4. mv_gather_update   masked gather, sum over workers in order, mean, and
-//                         the error update (zero on the mask)
+//                         the error update (zero on the mask).  Extra workgroups
+//                         beside this kernel or the one before write each row's
+//                         vote in ascending coordinate order
 //   5. mv_ad_*            majority voting with add-drop (Algorithm 2): replaces
 //                         the vote casting by the update of the workers'
 //                         standing votes

@@ -1,5 +1,5 @@
-// The global mask (counting sort over the vote levels, ordered emission) and beside it the sorted vote lists, then
-// the masked gather / mean / error update.
+// The global mask (counting sort over the vote levels, ordered emission), the masked gather / mean / error update,
+// and beside one of the two the sorted vote lists.
 //
 // These kernels are short (a few dependent memory round trips each), and the chip
 // starts only a few hundred workgroups per microsecond: they use workgroups of 1024
@@ -161,10 +161,7 @@ struct EmitLds {
 // candidates in the segments before its own, from the tallies) + (before it in its own run; runs are ascending).
 // A few workgroups per row (`part` of `parts`); each adds up the row's tallies for itself, eight segments to a
 // prefix (1365 for 11.2 M coordinates), which arrive beside the entries, and an entry looks at its own eight segments'
-// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).  Run beside the mask
-// kernel's blocks, which mostly wait, and not beside the gather, the lists cost a step less (1 x 16 M, K = 16,000:
-// 97.5 -> 93.4 us, 4 x 2,000,003, K = 20,000: 69.7 -> 68.8; where the scattered traffic of the gather is the bound, nothing:
-// 10 x 11.2 M, K = 111,740).
+// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).
 __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, uint32_t C,
                                                const u32x2* __restrict__ runs, const u32x4* __restrict__ units,
                                                uint32_t n_segs, uint32_t shift, uint32_t K, uint32_t kth, uint32_t tie_cut,
@@ -273,6 +270,30 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
     }
 }
 
+// The lists of all rows, by `per_row` workgroups to a row behind a kernel's own.  They run beside the mask kernel's
+// blocks where those mostly wait for each other and beside the gather otherwise (mv_api.hip has the line).
+struct RowLists {
+    uint32_t        per_row;
+    const u32x2*    cand;
+    uint32_t        cap;
+    const uint32_t* row_count;
+    const u32x2*    runs;
+    const uint32_t* run_taken;
+    uint32_t        n_runs;
+    RowSegments     segs;
+    const uint32_t *kth, *tie_cut, *slow_flag;
+    uint32_t*       worker_idx;
+};
+__device__ __forceinline__ void write_row_lists(const RowLists& l, uint32_t block, uint32_t K, EmitLds& lds, uint64_t* scan_lds)
+{
+    const uint32_t row = block / l.per_row, part = block % l.per_row;
+    if (l.slow_flag[row] == 1u) return;                        // its list is written already
+    write_row_list(l.cand + (size_t)row * l.cap, l.row_count[row], l.runs + (size_t)row * l.n_runs,
+                   reinterpret_cast<const u32x4*>(l.run_taken) + (size_t)row * (l.n_runs / kTallyUnit), l.segs.count(row),
+                   l.segs.shift(row), K, l.kth[row], l.tie_cut[row], part, l.per_row,
+                   l.worker_idx + (size_t)row * K, lds, scan_lds);
+}
+
 // Random selection: the winners are marked in a bitmap and counted per block already, so a block's
 // mask follows from the counts of the blocks before it.  `halves`: the bitmap, 16 coordinates to a
 // half-word; it is left at zero.
@@ -304,9 +325,8 @@ __device__ __forceinline__ void write_winners(uint16_t* __restrict__ halves, con
 // Workgroups [0, n_vote_blocks): count the block's coordinates above and at the vote
 // threshold (also per wavefront's stretch of 1024 Q coordinates), exchange the counts
 // with the other blocks and write the block's part of the mask; optionally copy the vote
-// bytes to the caller.  Workgroups beyond (only launched when the sorted vote lists are
-// wanted): emit_blocks per row, writing the row's list.  RANDOM: the mask comes from
-// the winners' bitmap.
+// bytes to the caller.  Workgroups beyond write the sorted vote lists, where they run
+// beside this kernel.  RANDOM: the mask comes from the winners' bitmap.
 template <int Q, bool RANDOM>
 __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __restrict__ votes32,
                                                               int64_t d, uint32_t N, uint32_t K,
@@ -315,16 +335,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
                                                               u32x2* __restrict__ block_cnt,
                                                               uint32_t* __restrict__ vote_thr,
                                                               uint8_t* __restrict__ votes_out,
-                                                              uint32_t n_vote_blocks, uint32_t emit_blocks,
-                                                              const u32x2* __restrict__ cand, uint32_t cap,
-                                                              const uint32_t* __restrict__ row_count,
-                                                              const u32x2* __restrict__ runs,
-                                                              const uint32_t* __restrict__ run_taken, uint32_t n_runs,
-                                                              RowSegments segs,
-                                                              const uint32_t* __restrict__ kth_in,
-                                                              const uint32_t* __restrict__ tie_cut_in,
-                                                              const uint32_t* __restrict__ slow_flag,
-                                                              uint32_t* __restrict__ worker_idx,
+                                                              uint32_t n_vote_blocks, RowLists lists,
                                                               int exact_levels,
                                                               unsigned long long* __restrict__ lookback,
                                                               uint32_t* __restrict__ emit_fail, uint32_t spin_limit,
@@ -339,12 +350,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     __shared__ uint64_t before_sh;
     if (blockIdx.x >= n_vote_blocks) {
         __shared__ EmitLds emit;
-        const uint32_t row = (blockIdx.x - n_vote_blocks) / emit_blocks, part = (blockIdx.x - n_vote_blocks) % emit_blocks;
-        if (slow_flag[row] == 1u) return;                      // its list is written already
-        write_row_list(cand + (size_t)row * cap, row_count[row], runs + (size_t)row * n_runs,
-                       reinterpret_cast<const u32x4*>(run_taken) + (size_t)row * (n_runs / kTallyUnit), segs.count(row),
-                       segs.shift(row), K, kth_in[row], tie_cut_in[row], part, emit_blocks,
-                       worker_idx + (size_t)row * K, emit, scan_lds);
+        write_row_lists(lists, blockIdx.x - n_vote_blocks, K, emit, scan_lds);
         return;
     }
     // the block's vote words first: their latency overlaps the level counters' loads.
@@ -478,7 +484,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
 }
 
 // ----------------------------------------------------------------------------
-// 6. masked gather, ordered sum over workers, mean, error update
+// 6. masked gather, ordered sum over workers, mean, error update; the sorted vote lists that are not written
+//    beside the mask kernel
 // ----------------------------------------------------------------------------
 
 // Positions [k0, k1) of the mask, whose coordinates are in slice[0 .. k1 - k0), at most `rounds` times
@@ -538,7 +545,7 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
     }
 }
 
-// A workgroup owns `rounds` times kb = 1024 / N consecutive positions of the mask.
+// Workgroups [0, n_gather_blocks): each owns `rounds` times kb = 1024 / N consecutive positions of the mask.
 // (a) Unless the mask is there (it is, but for a block that gave up waiting), the workgroup
 //     first finds its own positions' coordinates: the counts per block of the vote bytes
 //     and, inside the few blocks that matter, per wavefront stretch (from mv_mask_count)
@@ -549,13 +556,13 @@ __device__ __forceinline__ void gather_positions(float* tile /*LDS*/, const uint
 // (b) gather_positions reads a[n][mask[k]] (held in e), stores +0.0 there (the error
 //     update: the residual of a transmitted coordinate is zero), adds the N values in
 //     worker order 0..N-1 in fp32 and applies the 1/N of the mean once.
+// Workgroups beyond write the sorted vote lists.
 struct GatherLds {
     float    tile[kTileFloats];
     uint32_t slice[kGatherRounds * kMaskThreads];              // the workgroup's positions' coordinates
     uint32_t need[3 * (kMaskThreads + 2)];                     // stretches to read: (stretch, above before, at before)
     uint32_t blocks[3 * (kMaskThreads + 2)];                   // blocks whose stretches are looked at
     uint32_t n_need, n_blocks;
-    uint64_t scan[kMaskThreads / kWave];
 };
 
 template <int Q>
@@ -569,9 +576,16 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
                                                                  const uint32_t* __restrict__ emit_fail,
                                                                  float scale, int apply_scale,
                                                                  float* __restrict__ agg, uint32_t rounds,
+                                                                 uint32_t n_gather_blocks, RowLists lists,
                                                                  uint32_t* __restrict__ step_no)
 {
-    __shared__ GatherLds lds;
+    __shared__ union { GatherLds gather; EmitLds emit; } shared;
+    __shared__ uint64_t scan_lds[kMaskThreads / kWave];
+    if (blockIdx.x >= n_gather_blocks) {
+        write_row_lists(lists, blockIdx.x - n_gather_blocks, K, shared.emit, scan_lds);
+        return;
+    }
+    GatherLds& lds = shared.gather;
     const uint32_t kb = kMaskThreads / N;             // N <= 255, so kb >= 4
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = t / kWave;
     // This is the step's last kernel and nothing in it reads the step's number: the next step
@@ -604,7 +618,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
                 const u32x2 none = {0u, 0u};
                 const u32x2 c = b0 + t < n_blocks ? block_cnt[b0 + t] : none;
                 uint64_t total;
-                const uint64_t ex = block_excl_scan64<kMaskThreads>(pack2(c.x, c.y), lds.scan, total);
+                const uint64_t ex = block_excl_scan64<kMaskThreads>(pack2(c.x, c.y), scan_lds, total);
                 const uint32_t g = gt_before + (uint32_t)(ex >> 32), q = eq_before + (uint32_t)ex;
                 if (reaches_in(g, q, c)) {
                     const uint32_t at = atomicAdd(&lds.n_blocks, 1u);
@@ -614,7 +628,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
                 }
                 gt_before += (uint32_t)(total >> 32);
                 eq_before += (uint32_t)total;
-                __syncthreads();                          // lds.scan is reused by the next pass
+                __syncthreads();                          // the scan's scratch is reused by the next pass
                 if (gt_before + min(eq_before, take_eq) >= q1) break;   // uniform: the rest lies behind these positions
             }
             __syncthreads();

@@ -222,3 +222,19 @@ def test_lists_of_exactly_k(oracle, N, d, K, magnitudes):
             vote, msum, e = ref.vote, ref.msum, ref.err
     finally:
         gs.close()
+
+
+@pytest.mark.parametrize("kind,N,d,K", [("lattice", 128, 200_003, 20_000), ("normal", 255, 70_001, 12_000)])
+def test_sorted_lists_without_room_beside_the_vote_blocks(oracle, kind, N, d, K):
+    """More than 512 workgroups with the vote blocks' (one quad per thread): the lists are written beside the gather."""
+    print("[case] lists beside the gather %s N=%d d=%d K=%d" % (kind, N, d, K), flush=True)
+    rng = np.random.default_rng(N + d)
+    g = values(rng, kind, N, d)
+    g[1] = 0.0                                        # a row selected from memory, whose list is written by then
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        for t in range(2):
+            gs.set_error(e)
+            gs.set_grads(g)
+            gs.step()
+            assert_matches_oracle(gs.fetch(), oracle.vote_step(g, e, K, threads=8), "%s step %d" % (kind, t))
