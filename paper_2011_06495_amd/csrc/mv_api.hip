@@ -700,17 +700,13 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         uint8_t* votes_out = add_drop ? nullptr : a.votes;
         const float inv_n = 1.0f / (float)p.N;
         const uint32_t kb = mvk::kMaskThreads / p.N;
-        // Up to kGatherRounds rounds of kb mask positions per gathering workgroup.  When one or two rounds keep
-        // the grid at about one workgroup per compute unit, that is best; when they do not (large K, many rows),
-        // many short workgroups beat few long ones: two rounds and a grid of up to a thousand measured 4 us
-        // faster at K = d/100 than four rounds.
-        auto rounds_for = [&](uint32_t limit) {
-            uint32_t r = (uint32_t)(((uint64_t)p.K + (uint64_t)limit * kb - 1) / ((uint64_t)limit * kb));
-            if (r > (uint32_t)mvk::kGatherRounds) r = mvk::kGatherRounds;
-            return r < 1 ? 1u : r;
-        };
-        uint32_t rounds = rounds_for(250);
-        if (rounds > 2) rounds = rounds_for(1000);
+        // Up to kGatherRounds rounds of kb mask positions per gathering workgroup, as few as keep the grid to a
+        // thousand: many short workgroups beat few long ones (10 x 11.2 M, K = 111,740: two rounds 4 us faster than
+        // four; with two rounds where they bring 312 to 390 workgroups to half as many, and with one: 12 x 2 M,
+        // K = 33,000 104.6 us 103.4; 6 x 4 M, K = 66,000 109.9 108.4; random selection 8 x 4 M, K = 40,000 137.8 135.4;
+        // 40 x 1 M, K = 10,000 131.6 130.9; 32 x 10 M, K = 10,000 665.5 667.2).
+        uint32_t rounds = (uint32_t)(((uint64_t)p.K + 1000ull * kb - 1) / (1000ull * kb));
+        if (rounds > (uint32_t)mvk::kGatherRounds) rounds = mvk::kGatherRounds;
         const uint32_t n_gather = (p.K + kb * rounds - 1) / (kb * rounds);
         const dim3 grid_g(n_gather + (beside_mask ? 0 : n_list));
 #define MV_LAUNCH_MASK(Q)                                                                                        \
