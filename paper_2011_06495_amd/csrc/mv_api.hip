@@ -78,7 +78,8 @@ struct Plan {
     // scratch offsets (bytes)
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
     bool     keep_samples;      // several sampling workgroups store what they read
-    bool     through;           // the streaming pass stores past the caches
+    uint64_t vector_bytes;      // gradients and errors
+    uint64_t through_most;      // up to so many bytes the streaming pass stores past the caches
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
     size_t off_samples, off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_runs, off_runtaken,
@@ -154,12 +155,18 @@ Plan make_plan(const mv_config* c)
     // memory to themselves, in any grid: two rounds of resident workgroups wait (2 x 1,000,003, K = 1000: 39.5 us, 39.9
     // if none did; 16 x 2,000,003: 99.5 and 100.7; only from 40 x 300,001, K = 300 known otherwise: 56.0 and 54.1).
     p.head_wgs = p.sample_wgs == 1 ? 0 : 2048;
-    // Where gradients and errors lie in the last-level cache (256 MB), stores past the dies' L2s spare the kernel's end
-    // the writing back of what they left there.  The line follows the bytes of both, time written back : time past the
-    // caches: 11 MB (7 x 272,475 bf16) 31.4 30.1; 34 MB 44.6 43.0; 128 MB (16 x 1 M) 63.0 59.9, (4 x 4 M) 83.5 79.8;
-    // 134 MB (8 x 2.8 M bf16) 74.9 73.4; 160 MB (2 x 10 M) 95.7 94.4, (10 x 2 M) 87.3 83.7; beyond it, 176 MB 121 127;
-    // 204 MB 124 132; 216 MB (12 x 3 M bf16) 112 116; 894 MB 332 360.
-    p.through = (uint64_t)p.N * (uint64_t)p.d * (c->grad_dtype == MV_BF16 ? 6 : 8) <= 160ull << 20;
+    // Where a step's vectors lie in the last-level cache (256 MB), stores past the dies' L2s spare the kernel's end the
+    // writing back of what they left there.  The line follows the bytes of gradients and errors, in random selection with
+    // the clocks and the votes, which it reads and clears beside them (enqueue_step).  Time written back : time past the
+    // caches, fp32: 34 MB 44.6 43.0; 128 MB (16 x 1 M) 63.0 59.9, (4 x 4 M) 83.5 79.8; 160 MB (2 x 10 M) 95.7 94.4,
+    // (10 x 2 M) 87.3 83.7; beyond it 176 MB 121 127; 204 MB 124 132; 894 MB 332 360.  bf16, whose line lies lower:
+    // 11 MB (7 x 272,475) 31.4 30.1; 114 MB (16 rows) 63.1 60.1; 132 MB (2 rows) 96.7 96.9, (8) 74.1 72.1, (30) 68.0
+    // 66.0; beyond it 150 MB (2) 105.7 106.9, (8) 80.5 81.6, (30) 73.4 74.7; 162 MB 78.6 80.3; 216 MB 112 116.
+    // Random selection, with clocks and votes: 112 MB (1 x 8 M) 81.4 81.2; 154 MB (8 x 2.2 M) 87.5 86.2; 176 MB
+    // (2 x 8 M) 111.1 111.1; 198 MB (2 x 9 M) 106.9 107.8; 224 MB (1 x 16 M) 113.7 119.6; bf16 121 MB (16 rows) 79.4 78.7;
+    // 139 MB (16) 85.2 87.1; 142 MB (4) 92.6 94.1; 162 MB (2 x 9 M) 103.2 104.3; 228 MB (1 x 19 M) 113.4 120.7.
+    p.vector_bytes = (uint64_t)p.N * (uint64_t)p.d * (c->grad_dtype == MV_BF16 ? 6 : 8);
+    p.through_most = (c->grad_dtype == MV_BF16 ? 128ull : 160ull) << 20;
     // With few workers the mask is nearly what each of them asked for, every coordinate grows until it is sent, and
     // the magnitudes pile up below the K-th: there several sampling workgroups keep their samples (1 x 25.6 M: 0.8 us).
     // With more the residuals spread (lists stay within 3K over a thousand steps of 4 to 32 rows), and it would only
@@ -557,6 +564,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     // also reset the per-step counters), and the streaming pass a = g + e over e, candidates out
     uint32_t* sampledone = ws_ptr<uint32_t>(c, p.off_sampledone);
     uint32_t* readsdone = ws_ptr<uint32_t>(c, p.off_readsdone);
+    const int through = p.vector_bytes + (random_sel ? 6ull * (uint64_t)p.d : 0ull) <= p.through_most ? 1 : 0;
     uint32_t* samples = p.keep_samples ? ws_ptr<uint32_t>(c, p.off_samples) : nullptr;
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
@@ -568,14 +576,14 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, p.through ? 1 : 0,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, through,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
-                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, p.through ? 1 : 0,
+                               rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, through,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }
