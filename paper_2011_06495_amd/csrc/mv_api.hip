@@ -78,6 +78,7 @@ struct Plan {
     // scratch offsets (bytes)
     uint32_t sample_wgs;        // workgroups per row that sample it (the head of the streaming kernel's grid)
     bool     keep_samples;      // several sampling workgroups store what they read
+    uint32_t crowded;           // samples in tau's bin or above it beyond which tau is placed inside the bin
     uint64_t vector_bytes;      // gradients and errors
     uint64_t through_most;      // up to so many bytes the streaming pass stores past the caches
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
@@ -186,6 +187,18 @@ Plan make_plan(const mv_config* c)
     if (cap < 65536) cap = 65536;
     if (cap > (uint64_t)p.d) cap = (uint64_t)p.d;
     p.cap = (uint32_t)cap;
+    {
+        // A crowded bin makes the list longer than it has to be, and the search inside it holds the row's stream up:
+        // it is made where the list would be twice as long (one sampling workgroup, whose samples are at hand) or three
+        // times (several, whose samples one has to fetch: up to 32,768 quads of them), and in longer rows only where the
+        // list nears its storage.  K = d / 1000, lists of 6K to 8K entries kept : searched: 1 x 8 M 86.3 us 73.0;
+        // 1 x 14 M 100.8 99.9; 1 x 25 M 134.2 138.7, 1 x 50 M 209.3 222.8, 1 x 200 M 638 745; of 13K: 1 x 25 M 153.3 139.7,
+        // 1 x 50 M 229.1 223.5, 1 x 200 M 665 772.
+        const bool long_row = (uint64_t)p.n_sampled_chunks * (mvk::kChunk / 4) > 32768;
+        double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
+        if (long_row && 0.875 * (double)p.cap * frac > most) most = 0.875 * (double)p.cap * frac;
+        p.crowded = (p.sample_wgs > 1 && !p.keep_samples) || most >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)most;
+    }
 
     p.rs_blocks = (uint32_t)((p.d + mvk::kVoteBlock - 1) / mvk::kVoteBlock);
     {
@@ -574,14 +587,14 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         if (bf16)
             hipLaunchKernelGGL(mvk::mv_stream_collect<uint16_t>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const uint16_t*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
-                               p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
+                               p.stride, p.n_sampled_chunks, p.m_target, p.crowded, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
                                rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, through,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
-                               p.stride, p.n_sampled_chunks, p.m_target, hist, sampledone, readsdone, taupub, stepno,
+                               p.stride, p.n_sampled_chunks, p.m_target, p.crowded, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
                                rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, through,
                                add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));

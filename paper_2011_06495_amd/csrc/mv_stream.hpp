@@ -64,15 +64,14 @@ namespace mvk {
 // A bin is 3 % of a magnitude wide.  Error buffers that a steady gradient has driven for long hold many magnitudes
 // just below the K-th, and the edge of the bin lets them all into the list: one that overflows has its row
 // selected from memory by one workgroup (1 x 16 M, after some thousand steps: 1.7 ms for 0.1).  So the samples are kept,
-// and where the bin's own make the list longer than kCrowdedOne or kCrowdedMany times what it has to be, the picking
-// workgroup goes through them once more and places tau inside the bin, at one of kSubBins edges.  One sampling workgroup
-// keeps its samples in registers; several keep them in memory, past the caches, and only with few workers (see make_plan).
+// and where more than `crowded` of them lie in the bin or above it, the picking workgroup goes through them once more and
+// places tau inside the bin, at one of kSubBins edges.  One sampling workgroup keeps its samples in registers; several
+// keep them in memory, past the caches, and only with few workers (see make_plan, which also has the line).
 constexpr int      kSubBins = kStreamThreads;
 constexpr int      kSubShift = kHistShift - 9;
 static_assert(kSubBins == 512, "9 bits behind the bin's");
-// (several sampling workgroups have more to go through again)
-constexpr uint32_t kCrowdedOne = 2, kCrowdedMany = 3;
 constexpr int      kSampleQuads = 4;              // quads of samples a sampling thread has in flight
+constexpr int      kAgainQuads = 8;               // and one that goes through them once more (1 x 200 M: four 761 us, eight 738)
 constexpr uint32_t kRowPoison = 0x80000000u;      // set in a marked row's candidate counter by mv_row_select
 
 struct StreamLds {
@@ -113,16 +112,16 @@ __device__ __forceinline__ uint32_t edge_inside_bin(StreamLds& lds, uint32_t* sa
 #pragma unroll
         for (int u = 0; u < kSampleQuads; ++u) tally(kept[u]);
     } else {
-        for (uint32_t q0 = t; q0 < nquads; q0 += kSampleQuads * kStreamThreads) {
-            u32x4 k[kSampleQuads];
+        for (uint32_t q0 = t; q0 < nquads; q0 += kAgainQuads * kStreamThreads) {
+            u32x4 k[kAgainQuads];
 #pragma unroll
-            for (int u = 0; u < kSampleQuads; ++u) {
+            for (int u = 0; u < kAgainQuads; ++u) {
                 const uint32_t q = q0 + (uint32_t)u * kStreamThreads;
                 const u32x4 z = {0u, 0u, 0u, 0u};
                 k[u] = q < nquads ? load_through(samples, nquads * 16u, q * 16u) : z;
             }
 #pragma unroll
-            for (int u = 0; u < kSampleQuads; ++u) tally(k[u]);
+            for (int u = 0; u < kAgainQuads; ++u) tally(k[u]);
         }
     }
     __syncthreads();
@@ -138,7 +137,7 @@ template <typename GT>
 __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __restrict__ g, int64_t ld_g,
                                                 const float* __restrict__ e, int64_t ld_e, int64_t d,
                                                 uint32_t row, uint32_t part, uint32_t spr, uint32_t stride,
-                                                uint32_t n_sampled_chunks, uint32_t m_target,
+                                                uint32_t n_sampled_chunks, uint32_t m_target, uint32_t crowded,
                                                 uint32_t* __restrict__ hist, uint32_t* __restrict__ sample_done,
                                                 uint32_t* __restrict__ reads_done,
                                                 unsigned long long* __restrict__ tau_pub, uint32_t epoch,
@@ -258,8 +257,7 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     __syncthreads();
     uint32_t tau = (total >= m_target) ? lds.found : 0u;
     const uint32_t bin = lds.crowd[0], above = lds.crowd[1], in_bin = lds.crowd[2];
-    if ((spr == 1u || samples) && tau != 0u &&
-        (uint64_t)above + in_bin > (uint64_t)m_target * (spr == 1u ? kCrowdedOne : kCrowdedMany)) {               // uniform
+    if (tau != 0u && above + in_bin > crowded) {                       // uniform
         __syncthreads();
         tau = edge_inside_bin(lds, samples, nquads, kept, bin, m_target - above);
     }
@@ -286,7 +284,7 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
 template <typename GT>
 __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     const GT* __restrict__ g, int64_t ld_g, float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t n_rows,
-    uint32_t spr, uint32_t stride, uint32_t n_sampled_chunks, uint32_t m_target,
+    uint32_t spr, uint32_t stride, uint32_t n_sampled_chunks, uint32_t m_target, uint32_t crowded,
     uint32_t* __restrict__ hist, uint32_t* __restrict__ sample_done, uint32_t* __restrict__ reads_done,
     unsigned long long* __restrict__ tau_pub, const uint32_t* __restrict__ step_no, uint32_t spin_limit, uint32_t* __restrict__ row_poison, uint32_t* __restrict__ lvl_sets,
     uint32_t n_lvl_words, uint32_t* __restrict__ ad_count, uint32_t* __restrict__ samples,
@@ -304,7 +302,7 @@ __global__ __launch_bounds__(kStreamThreads) void mv_stream_collect(
     uint32_t* next_row_count = row_count_sets + ((epoch & 1u) ^ 1u) * row_count_set_words;
     if (blockIdx.x < n_rows * spr) {
         sample_and_pick<GT>(lds, g, ld_g, e, ld_e, d, blockIdx.x / spr, blockIdx.x % spr, spr, stride, n_sampled_chunks,
-                            m_target, hist, sample_done, reads_done, tau_pub, epoch, next_row_count, lvl_sets, n_lvl_words,
+                            m_target, crowded, hist, sample_done, reads_done, tau_pub, epoch, next_row_count, lvl_sets, n_lvl_words,
                             n_rows, ad_count, samples);
         return;
     }

@@ -63,14 +63,12 @@ def test_long_lists_of_shifted_rows(oracle, N, d, K, kind, offset):
     steps_at(oracle, kind, N, d, K, offset, 5, make, steps=1)
 
 
-def test_sorted_list_of_a_row_with_several_units_to_a_prefix():
-    """Beyond 33.5 M coordinates a prefix of the tallies covers several of their units."""
-    d, K = 34_000_003, 34_000
-    print("[case] one row of %d coordinates" % d, flush=True)
-    gen = torch.Generator(device="cuda").manual_seed(5)
+def check_one_row(d, K, magnitudes):
+    """One step of one row against torch's selection: ties go to the lowest coordinate.  Length of the row's list, and
+    whether it was selected from memory."""
     ld = (d + 3) // 4 * 4
     g = torch.zeros((1, ld), device="cuda")
-    g[:, :d] = torch.randn(d, generator=gen, device="cuda")
+    g[:, :d] = magnitudes
     e = torch.zeros((1, ld), device="cuda")
     widx = torch.zeros((1, K), dtype=torch.int32, device="cuda")
     mask = torch.zeros(K, dtype=torch.int32, device="cuda")
@@ -85,6 +83,7 @@ def test_sorted_list_of_a_row_with_several_units_to_a_prefix():
     try:
         B.mv_vote_step(ctx, g, e, widx, None, mask, agg, ld_g=ld, ld_e=ld)
         torch.cuda.synchronize()
+        count, _, slow = B.mv_last_step_row_stats(ctx, 1)
     finally:
         B.mv_end(ctx)
         B.mv_release(ctx)
@@ -92,6 +91,34 @@ def test_sorted_list_of_a_row_with_several_units_to_a_prefix():
     assert torch.equal(agg, g[0, want.long()])
     g[0, want.long()] = 0.0
     assert torch.equal(e, g)
+    return int(count[0]) & 0x7FFFFFFF, int(slow[0]) == 1
+
+
+def test_sorted_list_of_a_row_with_several_units_to_a_prefix():
+    """Beyond 33.5 M coordinates a prefix of the tallies covers several of their units."""
+    d, K = 34_000_003, 34_000
+    print("[case] one row of %d coordinates" % d, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    check_one_row(d, K, torch.randn(d, generator=gen, device="cuda"))
+
+
+@pytest.mark.parametrize("d", [16_600_000, 16_900_003])
+@pytest.mark.parametrize("crowd", [7, 11, 40])
+def test_crowded_bins_of_long_rows(d, crowd):
+    """Up to 32,768 quads of samples (16.6 M coordinates) the threshold goes inside a bin that makes the list three times
+    as long as need be; in longer rows only where the list, of `crowd` K entries, would not fit its storage of 16 K."""
+    K = d // 1000
+    print("[case] crowded bin in one row of %d coordinates, %d K" % (d, crowd), flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(crowd)
+    x = 0.1 * torch.randn(d, generator=gen, device="cuda").clamp_(-5.0, 5.0)
+    at = torch.rand(d, generator=gen, device="cuda") < crowd * K / d
+    x = torch.where(at, 1.0 + 0.02 * torch.rand(d, generator=gen, device="cuda"), x)
+    count, slow = check_one_row(d, K, x)
+    assert not slow
+    if crowd == 40 or d == 16_600_000:
+        assert count < 4 * K, count
+    else:
+        assert count > (crowd - 1) * K, count
 
 
 @pytest.mark.parametrize("N,d,K,width", [(2, 300_001, 300, 0.01), (2, 300_001, 300, 0.002), (1, 2_000_003, 2000, 0.01),
