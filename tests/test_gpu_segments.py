@@ -7,18 +7,30 @@ import torch
 
 from paper_2011_06495_amd import binding as B
 from tests.gpu_util import SENTINEL_F32, GpuStepper, assert_matches_oracle
+from tests.test_gpu_add_drop import GpuAdStepper
 
 pytestmark = pytest.mark.gpu
+
+
+def error_buffer_at(gs, offset):
+    """Moves a stepper's error buffer `offset` floats behind a 4 KB boundary; returns a check of what lies around it."""
+    pool = torch.full((1024 + offset + gs.e.numel(),), SENTINEL_F32, dtype=torch.float32, device="cuda")
+    first = -(pool.data_ptr() // 4) % 1024 + offset
+    gs.e = pool[first:first + gs.e.numel()].view(gs.N, gs.ld_e)
+    assert gs.e.data_ptr() // 4 % 1024 == offset % 1024
+
+    def check():
+        outside = torch.cat([pool[:first], pool[first + gs.e.numel():]])
+        assert bool((outside == SENTINEL_F32).all()), "write outside the error buffer"
+
+    return check
 
 
 def steps_at(oracle, what, N, d, K, offset, extra_ld, grads, bf16=False, steps=2):
     """`steps` steps with the error buffer `offset` floats behind a 4 KB boundary."""
     print("[case] %s N=%d d=%d K=%d offset=%d extra_ld=%d" % (what, N, d, K, offset, extra_ld), flush=True)
     with GpuStepper(N, d, K, bf16=bf16, extra_ld=extra_ld) as gs:
-        pool = torch.full((1024 + offset + gs.e.numel(),), SENTINEL_F32, dtype=torch.float32, device=gs.dev)
-        first = -(pool.data_ptr() // 4) % 1024 + offset
-        gs.e = pool[first:first + gs.e.numel()].view(N, gs.ld_e)
-        assert gs.e.data_ptr() // 4 % 1024 == offset % 1024
+        check_outside = error_buffer_at(gs, offset)
         e = np.random.default_rng(offset).standard_normal((N, d)).astype(np.float32) if offset % 8 else np.zeros((N, d), np.float32)
         gs.set_error(e)
         for t in range(steps):
@@ -28,8 +40,7 @@ def steps_at(oracle, what, N, d, K, offset, extra_ld, grads, bf16=False, steps=2
             ref = oracle.vote_step(g, e, K, threads=8)
             assert_matches_oracle(gs.fetch(), ref, "%s step %d" % (what, t))
             e = ref.err
-        outside = torch.cat([pool[:first], pool[first + gs.e.numel():]])
-        assert bool((outside == SENTINEL_F32).all()), "write outside the error buffer"
+        check_outside()
 
 
 @pytest.mark.parametrize("offset", [0, 4, 512, 1020])
@@ -122,7 +133,7 @@ def test_crowded_bins_of_long_rows(d, crowd):
 
 
 @pytest.mark.parametrize("N,d,K,width", [(2, 300_001, 300, 0.01), (2, 300_001, 300, 0.002), (1, 2_000_003, 2000, 0.01),
-                                         (3, 1_300_001, 9000, 0.01), (1, 40_000, 100, 0.02)])
+                                         (3, 1_300_001, 9000, 0.01), (1, 100_000, 100, 0.02)])
 def test_threshold_inside_a_crowded_bin(oracle, N, d, K, width):
     """All magnitudes within one bin of the sample's histogram (3 %): the threshold is placed inside it, by one sampling
     workgroup and by several, and no row's list overflows."""
@@ -138,3 +149,60 @@ def test_threshold_inside_a_crowded_bin(oracle, N, d, K, width):
             assert_matches_oracle(gs.fetch(), oracle.vote_step(g, e, K, threads=8), "crowded bin")
             count, _, slow = gs.row_stats()
             assert 1 not in slow, "rows selected from memory: %s, list lengths %s" % (slow, count)
+
+
+def test_crowded_bin_of_rows_whose_samples_are_not_kept(oracle):
+    """Five workers and more with several sampling workgroups each: their lists overflow and the rows are selected from
+    memory."""
+    N, d, K = 6, 1_300_001, 9000
+    print("[case] crowded bin N=%d d=%d K=%d" % (N, d, K), flush=True)
+    rng = np.random.default_rng(6)
+    g = ((1.0 + 0.01 * rng.random((N, d))) * rng.choice([-1.0, 1.0], size=(N, d))).astype(np.float32)
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        for t in range(2):
+            gs.set_error(e)
+            gs.set_grads(g)
+            gs.step()
+            assert_matches_oracle(gs.fetch(), oracle.vote_step(g, e, K, threads=8), "crowded bin")
+            assert all(int(v) == 1 for v in gs.row_stats()[2])
+
+
+@pytest.mark.parametrize("offset", [4, 512, 1020])
+@pytest.mark.parametrize("N,d,K", [(3, 70_001, 700), (2, 200_003, 30_000)])
+def test_random_selection_with_shifted_rows(oracle, N, d, K, offset):
+    print("[case] random selection N=%d d=%d K=%d offset=%d" % (N, d, K, offset), flush=True)
+    rng = np.random.default_rng(d + offset)
+    e = rng.standard_normal((N, d)).astype(np.float32)
+    with GpuStepper(N, d, K, extra_ld=3) as gs:
+        check_outside = error_buffer_at(gs, offset)
+        gs.set_error(e)
+        for t in range(2):
+            g, r = rng.standard_normal((N, d)).astype(np.float32), rng.standard_exponential(d).astype(np.float32)
+            gs.set_grads(g)
+            gs.step_rs(r)
+            ref = oracle.rs_vote_step(g, e, K, r, threads=8)
+            assert_matches_oracle(gs.fetch(), ref, "random selection step %d" % t)
+            e = ref.err
+        check_outside()
+
+
+@pytest.mark.parametrize("offset", [4, 512, 1020])
+@pytest.mark.parametrize("N,d,K", [(3, 70_001, 700), (2, 200_003, 30_000)])
+def test_add_drop_with_shifted_rows(oracle, N, d, K, offset):
+    print("[case] add-drop N=%d d=%d K=%d offset=%d" % (N, d, K, offset), flush=True)
+    rng = np.random.default_rng(d + offset)
+    gs = GpuAdStepper(N, d, K, K)
+    try:
+        check_outside = error_buffer_at(gs, offset)
+        gs.e[:, :d] = 0
+        e, vote, msum = np.zeros((N, d), np.float32), np.zeros((N, d), np.uint8), np.zeros(d, np.uint8)
+        for t, k_ad in enumerate([K, K // 10]):
+            g = rng.standard_normal((N, d)).astype(np.float32)
+            gs.step(g, k_ad)
+            ref = oracle.ad_vote_step(g, e, K, k_ad, vote, msum, threads=8)
+            gs.compare(ref, "add-drop step %d" % t)
+            vote, msum, e = ref.vote, ref.msum, ref.err
+        check_outside()
+    finally:
+        gs.close()
