@@ -153,8 +153,9 @@ Plan make_plan(const mv_config* c)
     // Loads of the grid's head beside the sampling bring a short grid's data earlier and the estimate later.  One
     // sampling workgroup per row has little to fetch: no loads are held back (7 x 272,475 bf16: 33.7 -> 33.0 us;
     // 4 x 2^20, K = 10,486: 49.9 -> 48.9; 40 x 1,000,003, K = 10,000: 132.7 -> 131.9).  Several do better with the
-    // memory to themselves, in any grid: two rounds of resident workgroups wait (2 x 1,000,003, K = 1000: 39.5 us, 39.9
-    // if none did; 16 x 2,000,003: 99.5 and 100.7; only from 40 x 300,001, K = 300 known otherwise: 56.0 and 54.1).
+    // memory to themselves, in any grid: two rounds of resident workgroups (of four to a unit) wait (2 x 1,000,003,
+    // K = 1000: 35.4 us, 36.3 if none did; 4 x 1,500,003: 44.5 and 47.0; 16 x 2,000,003: 97.5 and 99.3; 3 x 25.6 M:
+    // 217.0 and 219.3).
     p.head_wgs = p.sample_wgs == 1 ? 0 : 2048;
     // Where a step's vectors lie in the last-level cache (256 MB), stores past the dies' L2s spare the kernel's end the
     // writing back of what they left there.  The line follows the bytes of gradients and errors, in random selection with
@@ -169,9 +170,12 @@ Plan make_plan(const mv_config* c)
     p.vector_bytes = (uint64_t)p.N * (uint64_t)p.d * (c->grad_dtype == MV_BF16 ? 6 : 8);
     p.through_most = (c->grad_dtype == MV_BF16 ? 128ull : 160ull) << 20;
     // With few workers the mask is nearly what each of them asked for, every coordinate grows until it is sent, and
-    // the magnitudes pile up below the K-th: there several sampling workgroups keep their samples (1 x 25.6 M: 0.8 us).
-    // With more the residuals spread (lists stay within 3K over a thousand steps of 4 to 32 rows), and it would only
-    // cost the step (10 x 11.2 M: 1.4 us, 32 x 25.6 M 9).
+    // the magnitudes pile up below the K-th: there several sampling workgroups keep their samples.  That costs every such
+    // step a little (2 x 1,000,003 0.3 us of 35.4, 2 x 9 M 0.7 of 88.3, 1 x 16 M 1.1 of 90.1, 3 x 25.6 M 1.6 of 217) and
+    // spares a long run on the same gradients lists that overflow, at 0.1 ms per million coordinates of the row.  With
+    // more workers the residuals spread: over four thousand steps on the same normal gradients lists of 5 to 32 rows grew
+    // from 2 to 5 K entries to at most 7 K of the 16 K that fit, and keeping the samples would only cost the step
+    // (10 x 11.2 M: 1.4 us, 32 x 25.6 M 9).  Values on a lattice can overflow there after some thousand steps.
     p.keep_samples = p.sample_wgs > 1 && p.N <= 4;
     p.stride = (uint32_t)stride;
     p.n_sampled_chunks = (uint32_t)((nchunks + stride - 1) / stride);
