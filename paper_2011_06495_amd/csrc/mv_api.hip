@@ -678,6 +678,10 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         after(KID_AD_EMIT);
         mask_votes32 = msum32;
     }
+    // the sorted vote lists, written by extra workgroups of one of the kernels from here on
+    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, run_taken, p.n_runs, segs, kth, tiecut,
+                                     slow, a.worker_idx};
+    const uint32_t n_list = sorted && !add_drop ? p.N * p.emit_blocks : 0;
     uint32_t* rsbits = ws_ptr<uint32_t>(c, p.off_rsbits);
     if (random_sel) {
         // 3''. random selection: keys of the voted coordinates, exact select of the K soonest into a bitmap
@@ -697,28 +701,27 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                p.K, hist);
             after(KID_RS_HIST);
         }
+        // The sorted vote lists are written beside this kernel, however many workgroups that makes: its own are few, or
+        // long, and leave units idle, while beside the mask kernel and the gather, which fill the chip, the lists made the
+        // step longer (beside the gather : so: 2 x 1,353,211 bf16, K = 3206: 58.3 us 55.6; 12 x 1 M, K = 16,000: 84.0
+        // 80.5; 1 x 100,000, K = 1000: 34.3 33.0; 16 x 11.2 M, K = 11,174: 409.5 405.1; with 768 workgroups, 10 x 11.2 M,
+        // K = 111,740: 333.2 331.3; 24 x 3 M, K = 30,000: 225.8 224.1).
         before(KID_RS_PICK);
-        hipLaunchKernelGGL((alone ? &mvk::mv_rs_pick<true> : &mvk::mv_rs_pick<false>), dim3(parts),
+        hipLaunchKernelGGL((alone ? &mvk::mv_rs_pick<true> : &mvk::mv_rs_pick<false>), dim3(parts + n_list),
                            dim3(mvk::kRowThreads), 0, st, rslist, p.rs_cap, rscount, p.K, hist, rslist2, rsbits,
-                           (uint32_t)mvk::kMaskThreads * 16 * p.vote_q, p.n_vote_blocks, rsblk);
+                           (uint32_t)mvk::kMaskThreads * 16 * p.vote_q, p.n_vote_blocks, rsblk, parts, row_lists);
         after(KID_RS_PICK);
     }
     // 4. global mask: the vote threshold, the counts per stretch of the vote bytes and the mask's coordinates, or the
     // winners of the random selection in order; then 5. every workgroup of the last kernel gathers its part of the
     // mask, takes the mean and updates the error buffers.  Extra workgroups of one of the two write the sorted vote lists.
-    const bool lists = sorted && !add_drop;
     {
-        const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, run_taken, p.n_runs, segs, kth, tiecut,
-                                         slow, a.worker_idx};
-        const uint32_t n_list = lists ? p.N * p.emit_blocks : 0;
-        // The lists run beside the mask kernel where its blocks wait for each other's counts anyway (steps beside the
-        // mask : beside the gather: 4 x 2^20, K = 10,486: 43.4 us 46.1; 16 x 11.2 M, K = 11,174: 389.3 392.7;
-        // 16 x 1,000,003, K = 16,000: 74.5 77.9; 3 x 20 M, K = 200,000: 207.0 209.2; 10 x 11.2 M, K = 111,740:
-        // 331.6 330.9).  Not where the blocks are short ones of one quad per thread and do not leave the lists room on
-        // the chip (16 x 6 M, K = 40,000: 267.3 263.5; 32 x 5 M, K = 20,000: 390.4 387.2; 24 x 3 M, K = 30,000:
-        // 216.3 214.1; with room, K = 20,000: 201.5 203.2), nor in random selection, whose blocks do not wait
-        // (3 x 1,467,594: 55.7 54.4; 16 x 5 M: 215.7 211.3; 10 x 11.2 M, K = 111,740: 365.2 362.8; 16 x 11.2 M t3 410.4
-        // 411.6).
+        // Random selection's lists are under way beside mv_rs_pick.  The others run beside the mask kernel, whose blocks
+        // wait for each other's counts anyway (steps beside the mask : beside the gather: 4 x 2^20, K = 10,486: 43.4 us
+        // 46.1; 16 x 11.2 M, K = 11,174: 389.3 392.7; 16 x 1,000,003, K = 16,000: 74.5 77.9; 3 x 20 M, K = 200,000: 207.0
+        // 209.2; 10 x 11.2 M, K = 111,740: 331.6 330.9), but not where its blocks are short ones of one quad per thread
+        // and do not leave the lists room on the chip (16 x 6 M, K = 40,000: 267.3 263.5; 32 x 5 M, K = 20,000: 390.4
+        // 387.2; 24 x 3 M, K = 30,000: 216.3 214.1; with room, K = 20,000: 201.5 203.2).
         const bool beside_mask = !random_sel && (p.vote_q > 1 || p.n_vote_blocks + n_list <= 512);
         const dim3 grid_c(p.n_vote_blocks + (beside_mask ? n_list : 0));
         const dim3 block(mvk::kMaskThreads);
@@ -733,7 +736,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         uint32_t rounds = (uint32_t)(((uint64_t)p.K + 1000ull * kb - 1) / (1000ull * kb));
         if (rounds > (uint32_t)mvk::kGatherRounds) rounds = mvk::kGatherRounds;
         const uint32_t n_gather = (p.K + kb * rounds - 1) / (kb * rounds);
-        const dim3 grid_g(n_gather + (beside_mask ? 0 : n_list));
+        const dim3 grid_g(n_gather + (beside_mask || random_sel ? 0 : n_list));
 #define MV_LAUNCH_MASK(Q)                                                                                        \
         before(KID_MASK_COUNT);                                                                                  \
         hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \

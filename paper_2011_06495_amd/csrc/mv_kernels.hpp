@@ -37,8 +37,9 @@
 //                         coordinates written in place
 //   4. mv_gather_update   masked gather, sum over workers in order, mean, and
 //                         the error update (zero on the mask).  Extra workgroups
-//                         beside this kernel or the one before write each row's
-//                         vote in ascending coordinate order
+//                         beside this kernel or the one before (in random selection
+//                         beside mv_rs_pick) write each row's vote in ascending
+//                         coordinate order
 //   5. mv_ad_*            majority voting with add-drop (Algorithm 2): replaces
 //                         the vote casting by the update of the workers'
 //                         standing votes

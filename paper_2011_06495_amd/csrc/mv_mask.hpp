@@ -1,5 +1,5 @@
 // The global mask (counting sort over the vote levels, ordered emission), the masked gather / mean / error update,
-// and beside one of the two the sorted vote lists.
+// and beside one of the two (in random selection beside mv_rs_pick) the sorted vote lists.
 //
 // These kernels are short (a few dependent memory round trips each), and the chip
 // starts only a few hundred workgroups per microsecond: they use workgroups of 1024
@@ -271,7 +271,8 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
 }
 
 // The lists of all rows, by `per_row` workgroups to a row behind a kernel's own.  They run beside the mask kernel's
-// blocks where those mostly wait for each other and beside the gather otherwise (mv_api.hip has the line).
+// blocks where those mostly wait for each other, in random selection beside mv_rs_pick, and beside the gather otherwise
+// (mv_api.hip has the lines).
 struct RowLists {
     uint32_t        per_row;
     const u32x2*    cand;
@@ -348,10 +349,12 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     __shared__ uint64_t scan_lds[kMaskThreads / kWave + 1];
     __shared__ uint32_t mask_found;
     __shared__ uint64_t before_sh;
-    if (blockIdx.x >= n_vote_blocks) {
-        __shared__ EmitLds emit;
-        write_row_lists(lists, blockIdx.x - n_vote_blocks, K, emit, scan_lds);
-        return;
+    if constexpr (!RANDOM) {
+        if (blockIdx.x >= n_vote_blocks) {
+            __shared__ EmitLds emit;
+            write_row_lists(lists, blockIdx.x - n_vote_blocks, K, emit, scan_lds);
+            return;
+        }
     }
     // the block's vote words first: their latency overlaps the level counters' loads.
     // Thread t owns the block's bytes [16 Q t, 16 Q t + 16 Q).

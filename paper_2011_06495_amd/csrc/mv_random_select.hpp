@@ -3,6 +3,7 @@
 
 #include "mv_common.hpp"
 #include "mv_select.hpp"
+#include "mv_mask.hpp"
 
 namespace mvk {
 
@@ -92,16 +93,25 @@ __global__ __launch_bounds__(kRowThreads) void mv_rs_hist(const u32x2* __restric
     list_hist(v, blockIdx.x, gridDim.x, hist);
 }
 
-// Marks the winners in the bitmap and counts them per block of the mask kernel (`per_block` coordinates).  Leaves
-// the list's length at zero for the next step.
+// Workgroups [0, n_pick): mark the winners in the bitmap and count them per block of the mask kernel (`per_block`
+// coordinates), and leave the list's length at zero for the next step.  Workgroups beyond write the sorted vote lists,
+// where they run beside this kernel.
 template <bool ALONE>
 __global__ __launch_bounds__(kRowThreads) void mv_rs_pick(const u32x2* __restrict__ list, uint32_t list_cap,
                                                           uint32_t* __restrict__ rs_count, uint32_t K,
                                                           uint32_t* __restrict__ sample_hist, u32x2* __restrict__ list2,
                                                           uint32_t* __restrict__ rs_bits, uint32_t per_block, uint32_t n_blocks,
-                                                          uint32_t* __restrict__ winners_per_block)
+                                                          uint32_t* __restrict__ winners_per_block, uint32_t n_pick,
+                                                          RowLists lists)
 {
-    __shared__ SplitLds<kMembersMost> lds;        // few workgroups, each with a compute unit to itself
+    __shared__ union { SplitLds<kMembersMost> pick; EmitLds emit; } shared;   // few workgroups, each with a compute unit to itself
+    if (blockIdx.x >= n_pick) {
+        __shared__ uint64_t scan_lds[kMaskThreads / kWave];
+        static_assert(kMaskThreads == kRowThreads, "both kinds of workgroup have as many threads");
+        write_row_lists(lists, blockIdx.x - n_pick, K, shared.emit, scan_lds);
+        return;
+    }
+    SplitLds<kMembersMost>& lds = shared.pick;
     ListView v = rs_list(list, list_cap, rs_count, K, sample_hist);
     v.list2 = list2;
     if (v.n < K) return;                          // whole grid; cannot happen: every row votes K coordinates
@@ -110,7 +120,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_rs_pick(const u32x2* __restric
     uint32_t kth, tie_cut;
     ListRest rest;
     const bool finished = list_split<ALONE ? SplitEnd::Alone : SplitEnd::Last>(
-        v, blockIdx.x, gridDim.x, lds,
+        v, blockIdx.x, n_pick, lds,
         [&](const u32x2 (&c)[kListUnroll], uint32_t taken) {
 #pragma unroll
             for (int u = 0; u < kListUnroll; ++u) {

@@ -49,6 +49,26 @@ def test_reduced_workloads_three_steps(oracle, name):
             e_ref = ref.err
 
 
+@pytest.mark.parametrize("N,d,K", [(1, 32_769, 60), (3, 70_001, 5000), (128, 200_003, 20_000), (255, 70_001, 12_000)])
+def test_sorted_lists_beside_the_pick(oracle, N, d, K):
+    """The sorted vote lists' workgroups run beside those that pick the winners: one of either, lists of up to 16,384
+    voted coordinates and longer ones, more workgroups than the chip holds, a row that was selected from memory."""
+    say("random selection, lists beside the pick N=%d d=%d K=%d" % (N, d, K))
+    rng = np.random.default_rng(N + d)
+    g = np.rint(rng.standard_normal((N, d)) * 64).astype(np.float32) / 64 if N == 128 else \
+        rng.standard_normal((N, d)).astype(np.float32)
+    if N > 1:
+        g[1] = 0.0
+    e = np.zeros((N, d), np.float32)
+    with GpuStepper(N, d, K) as gs:
+        for t in range(2):
+            r = rng.standard_exponential(d).astype(np.float32)
+            gs.set_error(e)
+            gs.set_grads(g)
+            gs.step_rs(r)
+            assert_matches_oracle(gs.fetch(), oracle.rs_vote_step(g, e, K, r, threads=8), "step %d" % t)
+
+
 @pytest.mark.parametrize("d,K,N", [(1, 1, 1), (2, 1, 3), (5, 5, 2), (31, 7, 4), (1024, 1024, 2), (1025, 3, 5),
                                    (16385, 100, 3), (70001, 69999, 2), (50000, 500, 255)])
 def test_edge_shapes(oracle, d, K, N):
