@@ -80,7 +80,7 @@ struct Plan {
     bool     keep_samples;      // several sampling workgroups store what they read
     uint32_t crowded;           // samples in tau's bin or above it beyond which tau is placed inside the bin
     uint64_t vector_bytes;      // gradients and errors
-    uint64_t through_most;      // up to so many bytes the streaming pass stores past the caches
+    uint64_t through_most;      // up to so many bytes that a step touches the streaming pass stores past the caches
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
     size_t off_samples, off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_runs, off_runtaken,
@@ -158,17 +158,22 @@ Plan make_plan(const mv_config* c)
     // 217.0 and 219.3).
     p.head_wgs = p.sample_wgs == 1 ? 0 : 2048;
     // Where a step's vectors lie in the last-level cache (256 MB), stores past the dies' L2s spare the kernel's end the
-    // writing back of what they left there.  The line follows the bytes of gradients and errors, in random selection with
-    // the clocks and the votes, which it reads and clears beside them (enqueue_step).  Time written back : time past the
-    // caches, fp32: 34 MB 44.6 43.0; 128 MB (16 x 1 M) 63.0 59.9, (4 x 4 M) 83.5 79.8; 160 MB (2 x 10 M) 95.7 94.4,
-    // (10 x 2 M) 87.3 83.7; beyond it 176 MB 121 127; 204 MB 124 132; 894 MB 332 360.  bf16, whose line lies lower:
-    // 11 MB (7 x 272,475) 31.4 30.1; 114 MB (16 rows) 63.1 60.1; 132 MB (2 rows) 96.7 96.9, (8) 74.1 72.1, (30) 68.0
-    // 66.0; beyond it 150 MB (2) 105.7 106.9, (8) 80.5 81.6, (30) 73.4 74.7; 162 MB 78.6 80.3; 216 MB 112 116.
-    // Random selection, with clocks and votes: 112 MB (1 x 8 M) 81.4 81.2; 154 MB (8 x 2.2 M) 87.5 86.2; 176 MB
-    // (2 x 8 M) 111.1 111.1; 198 MB (2 x 9 M) 106.9 107.8; 224 MB (1 x 16 M) 113.7 119.6; bf16 121 MB (16 rows) 79.4 78.7;
-    // 139 MB (16) 85.2 87.1; 142 MB (4) 92.6 94.1; 162 MB (2 x 9 M) 103.2 104.3; 228 MB (1 x 19 M) 113.4 120.7.
+    // writing back of what they left there.  The line follows the bytes of gradients and errors and of what the step
+    // touches beside them: the votes and their copy, in random selection the votes once more (they are read twice) and
+    // the clocks' lines that it needs (enqueue_step).  Steps on three sets of inputs in turn, with those bytes (MiB) and
+    // the time written back : past the caches; first with scratch and outputs of their own, then shared.
+    //   fp32: 10 x 2.3 M 181: 79.7 78.5, 79.2 77.3; 4 x 5.8 M 182: 102.2 100.6, 83.2 79.7; 2 x 10.9 M 188: 88.5 89.3, 86.7
+    //   83.9; 30 x 0.85 M 197: 102.3 104.6, 80.3 81.5; 1 x 20.6 M 197: 115.4 119.0, 114.5 111.8; 894 MB 332 360.
+    //   bf16: 10 x 2.25 M 133: 93.0 91.8, 73.7 71.4; 4 x 5.6 M 139: 78.7 79.0, 80.5 78.1; 30 x 0.8 M 140: 71.0 71.0, 77.8
+    //   76.8; 4 x 6 M 144: 87.8 88.6, 76.1 74.0; 30 x 0.86 M 149: 94.7 96.7, 82.9 83.7; 216 MB 112 116.
+    //   Random selection: 10 x 2.2 M 181: 110.8 112.3; 10 x 2.2 M 179: 95.5 94.6, 95.2 93.0; 1 x 17.5 M 184: 97.3 101.7,
+    //   102.0 98.3; 1 x 20.6 M 218: 112.3 119.2; bf16 10 x 2.1 M 128: 84.6 83.2, 133: 89.7 87.5; 30 x 0.8 M 144: 86.5 89.4, 86.2
+    //   88.0.
+    // Over 560 steps around the line this rule is 0.1 and 0.4 % from the better of the two; one by the bytes of the
+    // vectors alone 0.7 and 0.6; one with all of the clocks, 160 MiB and, in bf16, 128 0.3 and 1.0 (4 x 5.8 M bf16 75.1 ->
+    // 77.5, with add-drop 121.9 -> 125.6, random selection 1 x 12.5 M 92.3 -> 96.1).
     p.vector_bytes = (uint64_t)p.N * (uint64_t)p.d * (c->grad_dtype == MV_BF16 ? 6 : 8);
-    p.through_most = (c->grad_dtype == MV_BF16 ? 128ull : 160ull) << 20;
+    p.through_most = (c->grad_dtype == MV_BF16 ? 140ull : 184ull) << 20;
     // With few workers the mask is nearly what each of them asked for, every coordinate grows until it is sent, and
     // the magnitudes pile up below the K-th: there several sampling workgroups keep their samples.  That costs every such
     // step a little (2 x 1,000,003 0.3 us of 35.4, 2 x 9 M 0.7 of 88.3, 1 x 16 M 1.1 of 90.1, 3 x 25.6 M 1.6 of 217) and
@@ -581,7 +586,13 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     // also reset the per-step counters), and the streaming pass a = g + e over e, candidates out
     uint32_t* sampledone = ws_ptr<uint32_t>(c, p.off_sampledone);
     uint32_t* readsdone = ws_ptr<uint32_t>(c, p.off_readsdone);
-    const int through = p.vector_bytes + (random_sel ? 6ull * (uint64_t)p.d : 0ull) <= p.through_most ? 1 : 0;
+    uint64_t step_bytes = p.vector_bytes;         // what the step touches: see make_plan
+    if (!add_drop) step_bytes += (a.votes ? 2ull : 1ull) * (uint64_t)p.d;
+    if (random_sel) {
+        const uint64_t lines = 128ull * p.N * p.K, clocks = 4ull * (uint64_t)p.d;
+        step_bytes += (uint64_t)p.d + (lines < clocks ? lines : clocks);
+    }
+    const int through = step_bytes <= p.through_most ? 1 : 0;
     uint32_t* samples = p.keep_samples ? ws_ptr<uint32_t>(c, p.off_samples) : nullptr;
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
