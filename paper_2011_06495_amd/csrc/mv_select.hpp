@@ -217,7 +217,8 @@ __device__ __forceinline__ void clear_fine_histogram(SelectLds& lds)
 }
 // the lane's counter of a bin.  A bin's copies lie in different banks, eight words apart, and neighbouring bins of a
 // copy in neighbouring words: the adds of a crowd do not queue up, nor the reads that sum the copies (with a bin's
-// copies in neighbouring words every thread read 64 bytes in a row: 4 x 2^20, K = 10,486: 49.3 us, so 48.7).
+// copies in neighbouring words every thread read 64 bytes in a row: 4 x 2^20, K = 10,486: 49.3 us, so 48.7).  The bins
+// of a lattice lie far apart and meet in fewer banks so (16 x 11.2 M: 1.0 M conflict cycles for 0.5), in the same time.
 __device__ __forceinline__ uint32_t* fine_counter(SelectLds& lds, uint32_t bin)
 {
     return &lds.rhist[(lane_id() % kRep) * copy_pitch(kFineBins) + bin];
