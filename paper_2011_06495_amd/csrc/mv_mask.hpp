@@ -85,61 +85,70 @@ __device__ __forceinline__ uint32_t bytes_at_least(uint32_t x, uint32_t t)
     const uint32_t low = (x | top) - (t & 127u) * 0x01010101u;
     return ((t & 128u) ? x & low : x | low) >> 7 & 0x01010101u;
 }
-// The thread's coordinates with more than / exactly vstar votes among its 16 Q bytes from j0
-// on: bit b of marks[q] is set if coordinate j0 + 16 q + b has more, bit 16 + b if it has exactly
-// vstar; gt and eq count them.  Four bytes at a time (byte by byte, and once more for the emission, the
-// mask kernel took 18.5 us instead of 14.9 at 10 x 11.2 M, K = 111,740, and 37 instead of 32 at 32 x 25.6 M).  Must be called by all lanes of a wavefront together: a quad that holds no vote
-// in any lane is passed over by the whole wavefront (most quads, where votes are sparse); with
+// A wavefront owns a stretch of 1024 Q coordinates, quad q of lane l being its 16 coordinates from
+// kQuadStep q + 16 l on: 64 lanes read, and copy, a kilobyte in a row (with the Q quads of a thread in a row every
+// instruction touched 64 separate pieces, and the copy of the votes alone took 14 of the mask kernel's 37 us at
+// 32 x 25.6 M).
+constexpr int kQuadStep = 16 * kWave;
+// The thread's coordinates with more than / exactly vstar votes, its first quad lying at coordinate j0: bit b of
+// marks[q] is set if coordinate j0 + kQuadStep q + b has more, bit 16 + b if it has exactly vstar.  Four bytes at a time
+// (byte by byte, and once more for the emission, the mask kernel took 18.5 us instead of 14.9 at 10 x 11.2 M,
+// K = 111,740, and 37 instead of 32 at 32 x 25.6 M).  Must be called by all lanes of a wavefront together: a quad that
+// holds no vote in any lane is passed over by the whole wavefront (most quads, where votes are sparse); with
 // vstar == 0 the coordinates without a vote count too and nothing is passed over.
+// before[q]: those of the stretch that lie before quad q of this lane, above | at << 16; returns the stretch's.
 template <int Q>
-__device__ __forceinline__ void count_above_and_at(const uint32_t (&ww)[4 * Q], int64_t j0, int64_t d,
-                                                   uint32_t vstar, uint32_t (&marks)[Q], uint32_t& gt, uint32_t& eq)
+__device__ __forceinline__ uint32_t count_above_and_at(const u32x4 (&w)[Q], int64_t j0, int64_t d, uint32_t vstar,
+                                                       uint32_t (&marks)[Q], uint32_t (&before)[Q])
 {
-    gt = 0;
-    eq = 0;
+    static_assert(kQuadStep * 8 < 1 << 16, "a stretch's counts fit 16 bits");
+    uint32_t sum = 0;                             // uniform: over the quads so far
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         marks[q] = 0;
-        const uint32_t any = ww[4 * q] | ww[4 * q + 1] | ww[4 * q + 2] | ww[4 * q + 3];
+        before[q] = sum;
+        const uint32_t any = w[q].x | w[q].y | w[q].z | w[q].w;
         if (vstar != 0u && __ballot(any != 0u) == 0ull) continue;     // wave-uniform
         uint32_t above[2] = {0, 0}, from[2] = {0, 0};                 // eight coordinates each
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const uint32_t w = ww[4 * q + k], weights = k & 1 ? 0x80402010u : 0x08040201u;
-            if (vstar < 255u) above[k / 2] = __builtin_amdgcn_udot4(bytes_at_least(w, vstar + 1u), weights, above[k / 2], false);
-            if (vstar != 0u) from[k / 2] = __builtin_amdgcn_udot4(bytes_at_least(w, vstar), weights, from[k / 2], false);
+            const uint32_t x = w[q][k], weights = k & 1 ? 0x80402010u : 0x08040201u;
+            if (vstar < 255u) above[k / 2] = __builtin_amdgcn_udot4(bytes_at_least(x, vstar + 1u), weights, above[k / 2], false);
+            if (vstar != 0u) from[k / 2] = __builtin_amdgcn_udot4(bytes_at_least(x, vstar), weights, from[k / 2], false);
         }
         const uint32_t up = above[0] | above[1] << 8;
         uint32_t all = from[0] | from[1] << 8;
         if (vstar == 0u) {                        // uniform: every coordinate there is
-            const int64_t there = d - (j0 + 16 * q);
+            const int64_t there = d - (j0 + kQuadStep * q);
             all = there >= 16 ? 0xFFFFu : there > 0 ? (1u << there) - 1u : 0u;
         }
         marks[q] = up | (all & ~up) << 16;
-        gt += (uint32_t)__popc(up);
-        eq += (uint32_t)__popc(all & ~up);
+        if (__ballot(marks[q] != 0u) == 0ull) continue;               // wave-uniform
+        const uint32_t mine = (uint32_t)__popc(up) | (uint32_t)__popc(all & ~up) << 16;
+        const uint32_t incl = wave_incl_scan(mine);
+        before[q] = sum + incl - mine;
+        sum += from_lane(incl, kWave - 1);
     }
+    return sum;
 }
 
 // f(position, coordinate) for every mask coordinate among the thread's, g0 being the coordinates above the
-// threshold before it and e0 those at it.
+// threshold before the wavefront's stretch and e0 those at it.
 template <int Q, typename F>
-__device__ __forceinline__ void each_mask_position(const uint32_t (&marks)[Q], int64_t j0, uint32_t g0, uint32_t e0,
-                                                   uint32_t take_eq, F f)
+__device__ __forceinline__ void each_mask_position(const uint32_t (&marks)[Q], const uint32_t (&before)[Q], int64_t j0,
+                                                   uint32_t g0, uint32_t e0, uint32_t take_eq, F f)
 {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
+        uint32_t g = g0 + (before[q] & 0xFFFFu), e = e0 + (before[q] >> 16);
         const uint32_t up = marks[q] & 0xFFFFu, at = marks[q] >> 16;
-        if (up == 0u && e0 >= take_eq) {
-            e0 += (uint32_t)__popc(at);
-            continue;
-        }
+        if (up == 0u && e >= take_eq) continue;
         for (uint32_t m = up | at; m != 0u; m &= m - 1u) {
             const uint32_t low = m & (0u - m);
             const bool is_up = (up & low) != 0u;
-            if (is_up || e0 < take_eq) f(g0 + min(e0, take_eq), (uint32_t)(j0 + 16 * q) + (uint32_t)__ffs((int)low) - 1u);
-            if (is_up) ++g0;
-            else ++e0;
+            if (is_up || e < take_eq) f(g + min(e, take_eq), (uint32_t)(j0 + kQuadStep * q) + (uint32_t)__ffs((int)low) - 1u);
+            if (is_up) ++g;
+            else ++e;
         }
     }
 }
@@ -356,29 +365,29 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
             return;
         }
     }
-    // the block's vote words first: their latency overlaps the level counters' loads.
-    // Thread t owns the block's bytes [16 Q t, 16 Q t + 16 Q).
-    const int64_t j0 = ((int64_t)blockIdx.x * kMaskThreads + threadIdx.x) * (16 * Q);
+    // the block's vote words first: their latency overlaps the level counters' loads
+    const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t j0 = ((int64_t)blockIdx.x * (kMaskThreads / kWave) + wave) * (kQuadStep * Q) + lane * 16;
     u32x4 w[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        const int64_t j = j0 + q * 16;
+        const int64_t j = j0 + q * kQuadStep;
         const u32x4 z = {0u, 0u, 0u, 0u};
         w[q] = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;   // padded to 16 bytes with zeros
     }
     uint32_t vstar = 0, take_eq = 0;
     if constexpr (!RANDOM) vote_threshold(lvl_sets, N, K, lvl, thr, scan_lds, vstar, take_eq, exact_levels);
-    uint32_t ww[4 * Q];
+    if (votes_out) {
+        // (past the caches: nothing of this step reads the copy.  Mask and gather 27.9 + 38.8 us -> 27.7 + 36.1 at 32 x 25.6 M,
+        // 20.3 + 36.3 -> 19.7 + 34.5 at 10 x 11.2 M, K = 111,740; random selection's mask kernel 8.3 -> 7.4 at 16 x 11.2 M)
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        ww[4 * q + 0] = w[q].x; ww[4 * q + 1] = w[q].y; ww[4 * q + 2] = w[q].z; ww[4 * q + 3] = w[q].w;
-        if (votes_out) {
-            const int64_t j = j0 + q * 16;
+        for (int q = 0; q < Q; ++q) {
+            const int64_t j = j0 + q * kQuadStep;
             if (j + 16 <= d && ((reinterpret_cast<uintptr_t>(votes_out) & 15) == 0)) {
-                *reinterpret_cast<u32x4*>(votes_out + j) = w[q];
+                __builtin_nontemporal_store(w[q], reinterpret_cast<u32x4*>(votes_out + j));
             } else {
                 for (int b = 0; b < 16; ++b)
-                    if (j + b < d) votes_out[j + b] = (uint8_t)((ww[4 * q + (b >> 2)] >> (8 * (b & 3))) & 255u);
+                    if (j + b < d) votes_out[j + b] = (uint8_t)((w[q][b >> 2] >> (8 * (b & 3))) & 255u);
             }
         }
     }
@@ -386,25 +395,25 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         write_winners<Q>(winners, winners_per_block, d, K, scan_lds, mask_idx);
         return;
     }
-    uint32_t gt, eq, marks[Q];
-    count_above_and_at<Q>(ww, j0, d, vstar, marks, gt, eq);
-    const uint32_t lane = lane_id(), wave = threadIdx.x / kWave;   // (vote_threshold ended with a barrier)
-    const uint64_t both = pack2(gt, eq);
-    uint64_t block_total;
-    const uint64_t ex = block_excl_scan64<kMaskThreads>(both, scan_lds, block_total);   // before this thread, in the block
+    uint32_t marks[Q], in_stretch[Q];
+    const uint32_t stretch = count_above_and_at<Q>(w, j0, d, vstar, marks, in_stretch);
+    // (vote_threshold ended with a barrier, behind which nobody reads its scratch)
+    if (lane == 0) {
+        // the counts per stretch, and per block below: what mv_gather_update scans when the mask could not be written here
+        u32x2 r;
+        r.x = stretch & 0xFFFFu;
+        r.y = stretch >> 16;
+        sub_cnt[(size_t)blockIdx.x * (kMaskThreads / kWave) + wave] = r;
+        scan_lds[wave] = pack2(r.x, r.y);
+    }
+    __syncthreads();
+    uint64_t block_total, ex;                     // ex: before this wavefront's stretch, in the block
     {
-        // the counts per wavefront stretch and per block: what mv_gather_update scans when the
-        // mask could not be written here
-        const uint64_t incl = ex + both;
-        const uint64_t stretch =
-            pack2(from_lane((uint32_t)(incl >> 32), kWave - 1) - from_lane((uint32_t)(ex >> 32), 0),
-                  from_lane((uint32_t)incl, kWave - 1) - from_lane((uint32_t)ex, 0));
-        if (lane == 0) {
-            u32x2 r;
-            r.x = (uint32_t)(stretch >> 32);
-            r.y = (uint32_t)stretch;
-            sub_cnt[(size_t)blockIdx.x * (kMaskThreads / kWave) + wave] = r;
-        }
+        constexpr uint32_t kStretches = kMaskThreads / kWave;
+        const uint64_t mine = lane < kStretches ? scan_lds[lane] : 0u;
+        const uint32_t hi = row_incl_scan((uint32_t)(mine >> 32)), lo = row_incl_scan((uint32_t)mine);
+        block_total = pack2(from_lane(hi, kStretches - 1), from_lane(lo, kStretches - 1));
+        ex = wave ? pack2(from_lane(hi, wave - 1), from_lane(lo, wave - 1)) : 0u;
         if (threadIdx.x == 0) {
             u32x2 r;
             r.x = (uint32_t)(block_total >> 32);
@@ -480,7 +489,7 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     if (mask_found == 0u) return;                   // whole workgroup
     const uint64_t before = before_sh;
     if ((uint32_t)(before >> 32) + min((uint32_t)before, take_eq) >= K) return;   // the mask is full before this block
-    each_mask_position<Q>(marks, j0, (uint32_t)((before + ex) >> 32), (uint32_t)(before + ex), take_eq,
+    each_mask_position<Q>(marks, in_stretch, j0, (uint32_t)((before + ex) >> 32), (uint32_t)(before + ex), take_eq,
                           [&](uint32_t pos, uint32_t j) {
                               if (pos < K) mask_idx[pos] = j;
                           });
@@ -653,25 +662,22 @@ __global__ __launch_bounds__(kMaskThreads) void mv_gather_update(float* __restri
                 }
             }
             __syncthreads();
-            // one wavefront per needed stretch: its 1024 Q vote bytes, lane l owning bytes [16 Q l, 16 Q l + 16 Q)
+            // one wavefront per needed stretch
             const uint32_t n_need = lds.n_need;
             for (uint32_t i = wave; i < n_need; i += kSubs) {
                 const uint32_t sidx = lds.need[3 * i];
-                const int64_t j0 = ((int64_t)sidx * kWave + lane) * (16 * Q);
-                uint32_t ww[4 * Q];
+                const int64_t j0 = (int64_t)sidx * (kQuadStep * Q) + lane * 16;
+                u32x4 w[Q];
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    const int64_t j = j0 + q * 16;
+                    const int64_t j = j0 + q * kQuadStep;
                     const u32x4 z = {0u, 0u, 0u, 0u};
-                    const u32x4 w = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;
-                    ww[4 * q + 0] = w.x; ww[4 * q + 1] = w.y; ww[4 * q + 2] = w.z; ww[4 * q + 3] = w.w;
+                    w[q] = (j < d) ? *reinterpret_cast<const u32x4*>(votes32 + (j >> 2)) : z;
                 }
-                uint32_t gt, eq, marks[Q];
-                count_above_and_at<Q>(ww, j0, d, vstar, marks, gt, eq);
-                const uint64_t both = pack2(gt, eq);
-                const uint64_t ex = wave_incl_scan64(both) - both;
-                each_mask_position<Q>(marks, j0, lds.need[3 * i + 1] + (uint32_t)(ex >> 32),
-                                      lds.need[3 * i + 2] + (uint32_t)ex, take_eq, [&](uint32_t pos, uint32_t j) {
+                uint32_t marks[Q], in_stretch[Q];
+                (void)count_above_and_at<Q>(w, j0, d, vstar, marks, in_stretch);
+                each_mask_position<Q>(marks, in_stretch, j0, lds.need[3 * i + 1], lds.need[3 * i + 2], take_eq,
+                                      [&](uint32_t pos, uint32_t j) {
                                           if (pos >= q0 && pos < q1) {
                                               lds.slice[pos - k0] = j;
                                               mask_idx[pos] = j;
