@@ -20,6 +20,7 @@ enum KernelId {
     KID_SEL_HIST,
     KID_SEL_SPLIT,
     KID_SEL_FINISH,
+    KID_VOTE_COUNT,
     KID_MASK_COUNT,
     KID_GATHER,
     // add-drop voting only
@@ -37,7 +38,7 @@ enum KernelId {
     KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
-    "mv_stream_collect", "mv_row_select", "mv_sel_hist", "mv_sel_split", "mv_sel_finish", "mv_mask_count", "mv_gather_update",
+    "mv_stream_collect", "mv_row_select", "mv_sel_hist", "mv_sel_split", "mv_sel_finish", "mv_vote_count", "mv_mask_count", "mv_gather_update",
     "mv_ad_collect",     "mv_ad_hist",    "mv_ad_pick",  "mv_ad_emit",   "mv_rs_keys",    "mv_rs_hist",
     "mv_rs_pick",        "mv_small_rows", "mv_small_mask"};
 
@@ -72,6 +73,7 @@ struct Plan {
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
     uint32_t block_shift;         // its blocks of coordinates: 2^block_shift, at most kCoordBlocks of them
+    uint32_t chunk_shift, n_chunks, chunks_per_wg;   // of mv_vote_count
     // random selection
     uint32_t rs_cap;              // most coordinates that can hold a vote: min(N K, d)
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
@@ -244,6 +246,18 @@ Plan make_plan(const mv_config* c)
         p.multi_select = slots > (uint64_t)mvk::kKeepMost;
         p.block_shift = 10;                       // a segment at least
         while (((p.d - 1 + mvk::kMostShift) >> p.block_shift) >= mvk::kCoordBlocks) ++p.block_shift;
+        // mv_vote_count: chunks of 4096 coordinates (a chunk shares a segment with the next one: of 2048, 10 x 11.2 M, K =
+        // 111,740 takes 17.0 us for 14.7 and 32 x 25.6 M 24.5 for 20.2), shorter ones where those are fewer than the chip's
+        // units; as many to a workgroup as leave four workgroups to a unit (three there 14.7 us, two 16.0, one 20.2; at
+        // 32 x 25.6 M six 20.2, four 21.8, two 24.5), and as LDS and the runs have room for
+        static_assert(204 * 5 <= mvk::kVotesRunsMost && 255 * 3 <= mvk::kVotesRunsMost, "the runs of a chunk of 4096, of 2048");
+        p.chunk_shift = p.d >= (1 << 20) && p.N <= 204 ? 12 : p.d >= (1 << 19) ? 11 : 10;
+        p.n_chunks = (uint32_t)((p.d - 1) >> p.chunk_shift) + 1;
+        const uint32_t of_chunk = (1u << p.chunk_shift) / mvk::kSeg + 1;    // segments
+        uint32_t most = (uint32_t)mvk::kVotesBytesMost >> p.chunk_shift;
+        if (most > mvk::kVotesRunsMost / (p.N * of_chunk)) most = mvk::kVotesRunsMost / (p.N * of_chunk);
+        p.chunks_per_wg = (p.n_chunks + 1023) / 1024;
+        if (p.chunks_per_wg > most) p.chunks_per_wg = most;
         // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
         uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
         if (sb > 256) sb = 256;
@@ -597,6 +611,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
     {
+        uint32_t* zero_votes = add_drop || p.multi_select ? nullptr : votes32;    // (mv_vote_count writes all of them)
         const dim3 grid(p.N * p.sample_wgs + p.N * (p.n_runs / mvk::kSegPerBlock));
         before(KID_STREAM);
         if (bf16)
@@ -605,14 +620,14 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                                p.stride, p.n_sampled_chunks, p.m_target, p.crowded, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
                                rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, through,
-                               add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
+                               zero_votes, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         else
             hipLaunchKernelGGL(mvk::mv_stream_collect<float>, grid, dim3(mvk::kStreamThreads), 0, st,
                                static_cast<const float*>(a.grads), a.ld_g, a.err, a.ld_e, p.d, p.N, p.sample_wgs,
                                p.stride, p.n_sampled_chunks, p.m_target, p.crowded, hist, sampledone, readsdone, taupub, stepno,
                                c->spin_limit, poison, lvlsets, p.n_zero_words, adcount, samples, cand, p.cap,
                                rowcnt_sets, rowcnt_set_words, runs, run_taken, p.n_runs, segs, p.head_wgs, through,
-                               add_drop ? (uint32_t*)nullptr : votes32, (int64_t)(((size_t)p.d + 15) / 16 * 16));
+                               zero_votes, (int64_t)(((size_t)p.d + 15) / 16 * 16));
         after(KID_STREAM);
     }
     // 2. exact per-row select; in plain voting and random selection the votes are cast in the same launch (short
@@ -621,25 +636,30 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     uint32_t* tallies = sorted ? run_taken : nullptr;
     const int thresholds_only = add_drop ? 1 : 0;
     if (p.multi_select) {
-        const dim3 grid(p.split_blocks, p.N);
         before(KID_SEL_HIST);
-        hipLaunchKernelGGL(mvk::mv_sel_hist, grid, dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K, rowcnt_sets,
+        hipLaunchKernelGGL(mvk::mv_sel_hist, dim3(p.split_blocks, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K, rowcnt_sets,
                            rowcnt_set_words, stepno, taupub, poison, hist, rowcnt, tau, slow);
         after(KID_SEL_HIST);
         before(KID_SEL_SPLIT);
-        hipLaunchKernelGGL(mvk::mv_sel_split, grid, dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
+        const uint32_t order_blocks = (p.n_runs + mvk::kOrderRuns - 1) / mvk::kOrderRuns;
+        hipLaunchKernelGGL(mvk::mv_sel_split, dim3(p.split_blocks + order_blocks, p.N), dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
-                           kth, tiecut, a.worker_idx, votes32, tallies, p.n_runs, segs,
-                           lvlsets, thresholds_only, taupub, p.block_shift);
+                           kth, tiecut, a.worker_idx, runs, p.n_runs, segs, taupub, p.block_shift, p.split_blocks);
         after(KID_SEL_SPLIT);
-        uint32_t parts = add_drop ? 1 : 256 / p.N;
-        parts = parts > 16 ? 16 : parts < 1 ? 1 : parts;
         before(KID_SEL_FINISH);
-        hipLaunchKernelGGL(mvk::mv_sel_finish, dim3(parts, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
+        hipLaunchKernelGGL(mvk::mv_sel_finish, dim3(p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist, kth, tiecut,
-                           votes32, tallies, p.n_runs, segs, lvlsets, thresholds_only, taupub, (const mvk::u32x2*)runs,
-                           p.block_shift);
+                           p.n_runs, segs, taupub, (const mvk::u32x2*)runs, p.block_shift);
         after(KID_SEL_FINISH);
+        if (!add_drop) {
+            before(KID_VOTE_COUNT);
+            hipLaunchKernelGGL(mvk::mv_vote_count, dim3((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg),
+                               dim3(mvk::kVotesThreads), 0, st, (const float*)a.err, a.ld_e, p.d, p.N,
+                               (const mvk::u32x2*)cand, p.cap, (const mvk::u32x2*)runs, p.n_runs, segs,
+                               (const uint32_t*)kth, (const uint32_t*)tiecut, (const uint32_t*)slow, p.chunk_shift,
+                               p.n_chunks, p.chunks_per_wg, votes32, reinterpret_cast<uint16_t*>(tallies), lvlsets);
+            after(KID_VOTE_COUNT);
+        }
     } else {
         const uint32_t parts = add_drop ? 1 : p.select_parts;
         before(KID_ROW_SELECT);
@@ -690,7 +710,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         mask_votes32 = msum32;
     }
     // the sorted vote lists, written by extra workgroups of one of the kernels from here on
-    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, run_taken, p.n_runs, segs, kth, tiecut,
+    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, p.multi_select ? 1 : 0, run_taken, p.n_runs, segs, kth, tiecut,
                                      slow, a.worker_idx};
     const uint32_t n_list = sorted && !add_drop ? p.N * p.emit_blocks : 0;
     uint32_t* rsbits = ws_ptr<uint32_t>(c, p.off_rsbits);
@@ -753,7 +773,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \
                            block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
                            subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, row_lists,                     \
-                           add_drop ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
+                           add_drop || p.multi_select ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
                            reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
         after(KID_MASK_COUNT);                                                                                   \
         before(KID_GATHER);                                                                                      \

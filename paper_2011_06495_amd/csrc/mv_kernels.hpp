@@ -28,7 +28,8 @@
 //                         the largest coordinate taken among its ties; then every
 //                         workgroup casts the votes of its share of the list.
 //                         Long lists (large K) go through mv_sel_hist,
-//                         mv_sel_split and mv_sel_finish, many workgroups per row
+//                         mv_sel_split and mv_sel_finish, many workgroups per row,
+//                         and mv_vote_count counts the votes in LDS
 //   3. mv_mask_count      counting-sort selection of the K most voted
 //                         coordinates, ties to the lowest coordinate: the vote
 //                         threshold from the level counters, the counts of every
@@ -64,6 +65,7 @@
 #include "mv_common.hpp"
 #include "mv_stream.hpp"
 #include "mv_select.hpp"
+#include "mv_votes.hpp"
 #include "mv_mask.hpp"
 #include "mv_add_drop.hpp"
 #include "mv_random_select.hpp"

@@ -170,10 +170,11 @@ struct EmitLds {
 // candidates in the segments before its own, from the tallies) + (before it in its own run; runs are ascending).
 // A few workgroups per row (`part` of `parts`); each adds up the row's tallies for itself, eight segments to a
 // prefix (1365 for 11.2 M coordinates), which arrive beside the entries, and an entry looks at its own eight segments'
-// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).
+// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).  n_dealt: the segments whose
+// runs lie as the streaming pass noted them (run_place), none once they are in order.
 __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, uint32_t C,
                                                const u32x2* __restrict__ runs, const u32x4* __restrict__ units,
-                                               uint32_t n_segs, uint32_t shift, uint32_t K, uint32_t kth, uint32_t tie_cut,
+                                               uint32_t n_segs, uint32_t n_dealt, uint32_t shift, uint32_t K, uint32_t kth, uint32_t tie_cut,
                                                uint32_t part, uint32_t parts, uint32_t* __restrict__ out, EmitLds& lds,
                                                uint64_t* scan_lds)
 {
@@ -198,11 +199,11 @@ __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, u
             below[u] = 0;
             if (c[u].y != 0xFFFFFFFFu) {
                 const uint32_t s = segment_of(c[u].y, shift);
-                run0[u] = runs[run_place(s, n_segs)].x;
+                run0[u] = runs[run_place(s, n_dealt)].x;
                 below[u] = unit_sum_below(units[s / kTallyUnit], s % kTallyUnit);
             }
         }
-        first_run = runs[run_place(first_run, n_segs)].x;
+        first_run = runs[run_place(first_run, n_dealt)].x;
     };
     load((uint64_t)part * kEmitBatch);
     // `per` units to a prefix: one, in rows of up to 33.5 M coordinates
@@ -288,6 +289,7 @@ struct RowLists {
     uint32_t        cap;
     const uint32_t* row_count;
     const u32x2*    runs;
+    int             in_order;                     // the runs are (see order_runs)
     const uint32_t* run_taken;
     uint32_t        n_runs;
     RowSegments     segs;
@@ -300,7 +302,7 @@ __device__ __forceinline__ void write_row_lists(const RowLists& l, uint32_t bloc
     if (l.slow_flag[row] == 1u) return;                        // its list is written already
     write_row_list(l.cand + (size_t)row * l.cap, l.row_count[row], l.runs + (size_t)row * l.n_runs,
                    reinterpret_cast<const u32x4*>(l.run_taken) + (size_t)row * (l.n_runs / kTallyUnit), l.segs.count(row),
-                   l.segs.shift(row), K, l.kth[row], l.tie_cut[row], part, l.per_row,
+                   l.in_order ? 0u : l.segs.count(row), l.segs.shift(row), K, l.kth[row], l.tie_cut[row], part, l.per_row,
                    l.worker_idx + (size_t)row * K, lds, scan_lds);
 }
 
