@@ -73,6 +73,7 @@ struct Plan {
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
     uint32_t block_shift;         // its blocks of coordinates: 2^block_shift, at most kCoordBlocks of them
+    bool     vote_chunks;         // their votes are counted by mv_vote_count
     uint32_t chunk_shift, n_chunks, chunks_per_wg;   // of mv_vote_count
     // random selection
     uint32_t rs_cap;              // most coordinates that can hold a vote: min(N K, d)
@@ -258,6 +259,19 @@ Plan make_plan(const mv_config* c)
         if (most > mvk::kVotesRunsMost / (p.N * of_chunk)) most = mvk::kVotesRunsMost / (p.N * of_chunk);
         p.chunks_per_wg = (p.n_chunks + 1023) / 1024;
         if (p.chunks_per_wg > most) p.chunks_per_wg = most;
+        {
+            // Counted so, the votes cost a launch more and no atomics: worth it from half a million votes on, where the
+            // list entries of a workgroup's chunks, those it shares among them, are not too many.  Steps with the votes
+            // cast from the lists : counted in chunks, with the entries where they are many: 16 x 6 M, K = 40,000 258.2 : 250.8 us;
+            // 24 x 3 M, K = 30,000 210.4 : 205.9; 4 x 10 M on a lattice, K = 300,000 177.9 : 170.3; random selection 10 x 11.2 M,
+            // K = 111,740 345.6 : 335.5; fewer votes: random selection 12 x 2 M, K = 33,333 114.7 : 117.0, 2 x 10 M, K = 150,000
+            // 117.3 : 119.8; more entries: 40 x 1 M, K = 25,000 (4 K) 140.4 : 142.0, 16 x 300,001, K = 30,000 56.9 : 62.0,
+            // 128 x 400,003, K = 33,333 (28 K) 277.8 : 300, 100 x 60,003, K = 30,000 128 : 263; but 2 x 2 M, K = 10^6 (5 K)
+            // 110 : 103.
+            const double wgs = (double)((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg);
+            const double entries = (double)p.N * (double)p.m_target / frac * (double)of_chunk / (double)(of_chunk - 1) / wgs;
+            p.vote_chunks = p.multi_select && (uint64_t)p.N * p.K >= 500000 && entries <= 3000.0;
+        }
         // one batch of list entries per thread in the many-workgroup select, two when writing the sorted lists
         uint64_t sb = (slots + mvk::kListUnroll - 1) / mvk::kListUnroll, eb2 = (slots + 3) / 4;
         if (sb > 256) sb = 256;
@@ -611,7 +625,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     unsigned long long* taupub = ws_ptr<unsigned long long>(c, p.off_taupub);
     uint32_t* poison = ws_ptr<uint32_t>(c, p.off_poison);
     {
-        uint32_t* zero_votes = add_drop || p.multi_select ? nullptr : votes32;    // (mv_vote_count writes all of them)
+        uint32_t* zero_votes = add_drop || p.vote_chunks ? nullptr : votes32;     // (mv_vote_count writes all of them)
         const dim3 grid(p.N * p.sample_wgs + p.N * (p.n_runs / mvk::kSegPerBlock));
         before(KID_STREAM);
         if (bf16)
@@ -635,23 +649,30 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     const bool sorted = a.worker_idx != nullptr;
     uint32_t* tallies = sorted ? run_taken : nullptr;
     const int thresholds_only = add_drop ? 1 : 0;
+    // (the runs are put in order for the kernels that go through them by chunks of coordinates)
+    const bool in_order = !add_drop && p.vote_chunks;
     if (p.multi_select) {
         before(KID_SEL_HIST);
         hipLaunchKernelGGL(mvk::mv_sel_hist, dim3(p.split_blocks, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K, rowcnt_sets,
                            rowcnt_set_words, stepno, taupub, poison, hist, rowcnt, tau, slow);
         after(KID_SEL_HIST);
         before(KID_SEL_SPLIT);
-        const uint32_t order_blocks = (p.n_runs + mvk::kOrderRuns - 1) / mvk::kOrderRuns;
-        hipLaunchKernelGGL(mvk::mv_sel_split, dim3(p.split_blocks + order_blocks, p.N), dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
+        const bool cast_here = !add_drop && !p.vote_chunks;
+        const uint32_t order_blocks = in_order ? (p.n_runs + mvk::kOrderRuns - 1) / mvk::kOrderRuns : 0;
+        hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_split<true> : &mvk::mv_sel_split<false>), dim3(p.split_blocks + order_blocks, p.N), dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
-                           kth, tiecut, a.worker_idx, runs, p.n_runs, segs, taupub, p.block_shift, p.split_blocks);
+                           kth, tiecut, a.worker_idx, votes32, tallies, runs, p.n_runs, segs, lvlsets, taupub,
+                           p.block_shift, p.split_blocks);
         after(KID_SEL_SPLIT);
+        uint32_t parts = cast_here ? 256 / p.N : 1;
+        parts = parts > 16 ? 16 : parts < 1 ? 1 : parts;
         before(KID_SEL_FINISH);
-        hipLaunchKernelGGL(mvk::mv_sel_finish, dim3(p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
+        hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_finish<true> : &mvk::mv_sel_finish<false>), dim3(parts, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist, kth, tiecut,
-                           p.n_runs, segs, taupub, (const mvk::u32x2*)runs, p.block_shift);
+                           votes32, tallies, p.n_runs, segs, lvlsets, taupub, (const mvk::u32x2*)runs, in_order ? 1 : 0,
+                           p.block_shift);
         after(KID_SEL_FINISH);
-        if (!add_drop) {
+        if (!add_drop && p.vote_chunks) {
             before(KID_VOTE_COUNT);
             hipLaunchKernelGGL(mvk::mv_vote_count, dim3((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg),
                                dim3(mvk::kVotesThreads), 0, st, (const float*)a.err, a.ld_e, p.d, p.N,
@@ -710,7 +731,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         mask_votes32 = msum32;
     }
     // the sorted vote lists, written by extra workgroups of one of the kernels from here on
-    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, p.multi_select ? 1 : 0, run_taken, p.n_runs, segs, kth, tiecut,
+    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, in_order ? 1 : 0, run_taken, p.n_runs, segs, kth, tiecut,
                                      slow, a.worker_idx};
     const uint32_t n_list = sorted && !add_drop ? p.N * p.emit_blocks : 0;
     uint32_t* rsbits = ws_ptr<uint32_t>(c, p.off_rsbits);
@@ -773,7 +794,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \
                            block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
                            subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, row_lists,                     \
-                           add_drop || p.multi_select ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
+                           add_drop || p.vote_chunks ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
                            reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
         after(KID_MASK_COUNT);                                                                                   \
         before(KID_GATHER);                                                                                      \

@@ -450,15 +450,51 @@ __device__ __forceinline__ void select_among_candidates(const Keys& keys, const 
 // tallied in its segment (the tallies were zeroed by the streaming pass).  Lanes of a wavefront
 // mostly hold consecutive list entries, which share a segment: the first lane of each
 // group of equal segments adds the group's count.  All threads of the workgroup must call it.
-template <int U>
+template <int U, bool MERGE>
 __device__ __forceinline__ void cast_votes(const u32x2 (&c)[U], uint32_t taken_mask, uint32_t* __restrict__ votes32,
                                            uint32_t* lvl, SegmentTallies tallies)
 {
+    const uint32_t lane = lane_id();
+    // MERGE (long lists, where the atomics' rate at the memory side is what the step waits for): lanes
+    // hold consecutive list entries, ascending inside a run, and a row votes at most once per
+    // coordinate, so neighbouring taken lanes whose coordinates share a vote word (four bytes) cast
+    // their votes with ONE atomic, the sum of their byte increments, issued by the first of them;
+    // the returned word holds every byte's count before this row's vote.  Where the mask is dense
+    // that is up to four votes per atomic (measured at K = d/100: 27 -> 19 us).  Short lists
+    // wait for latency, not rate: there every taken lane issues its own.
     uint32_t old[U];
+    uint32_t ahead[U];                            // lanes between this lane and the first of its group
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+        const bool taken = (taken_mask >> u) & 1u;
+        const uint32_t inc = taken ? 1u << ((c[u].y & 3u) * 8u) : 0u;
+        uint32_t before = 0;                      // lanes of the same group just below this one
+        uint32_t sum = inc;
+        if (MERGE) {
+            const uint32_t key = taken ? (c[u].y >> 2) : (0xFFFFFF00u | lane);   // never equal to a neighbour's
+            bool run = true;
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {
+                const uint32_t below = __shfl_up(key, k, kWave);
+                run = run && lane >= (uint32_t)k && below == key;
+                before += run ? 1u : 0u;
+            }
+            run = true;
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {
+                const uint32_t above_key = __shfl_down(key, k, kWave);
+                const uint32_t above_inc = __shfl_down(inc, k, kWave);
+                run = run && lane + (uint32_t)k < (uint32_t)kWave && above_key == key;
+                sum += run ? above_inc : 0u;
+            }
+        }
+        ahead[u] = before;
         old[u] = 0;
-        if ((taken_mask >> u) & 1u) old[u] = atomicAdd(&votes32[c[u].y >> 2], 1u << ((c[u].y & 3u) * 8u));
+        if (taken && before == 0u) old[u] = atomicAdd(&votes32[c[u].y >> 2], sum);
+    }
+    if (MERGE) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) old[u] = __shfl(old[u], lane - ahead[u], kWave);   // the group's returned word
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -490,7 +526,7 @@ __device__ __forceinline__ void cast_votes_of_share(const u32x2* __restrict__ cr
 #pragma unroll
         for (int u = 0; u < kU; ++u)
             taken |= (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
-        cast_votes<kU>(c, taken, votes32, lvl, tallies);
+        cast_votes<kU, false>(c, taken, votes32, lvl, tallies);
     }
 }
 
@@ -898,7 +934,7 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
 #pragma unroll
                 for (int i = 0; i < kOwn; ++i)
                     taken |= ((part + i * parts) * kRowThreads + t < C && is_taken(own[i], kth, tie_cut) ? 1u : 0u) << i;
-                cast_votes<kOwn>(own, taken, votes32, lds.lvl, tallies);
+                cast_votes<kOwn, false>(own, taken, votes32, lds.lvl, tallies);
                 first = part + kOwn * parts;
             }
             if (!cast) cast_votes_of_share(crow, C, kth, tie_cut, first, parts, votes32, lds.lvl, tallies);
@@ -918,12 +954,15 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
 // of the keys over the list (see list_bin), (2) every workgroup locates the bin of the
 // want-th largest, acts on its entries of higher bins, and moves that bin's members
 // to a second list, (3) these are ranked exactly and those that are taken are acted on.
-// The add and drop candidates of add-drop voting and the random selection come this way, and the rows' top K when
-// K is large, of which only the K-th magnitude and the tie cut are wanted (mv_vote_count acts on them).
+// The rows' top K when K is large (to act = cast the vote, or leave it to mv_vote_count), the add and drop candidates of
+// add-drop voting, and the random selection all come this way.
 //
-// (3) for the rows' top K is a launch of its own, which reads what the others have stored without going past the caches.
-// The other lists' last workgroup ranks and acts, or the only one, with the histogram in LDS, where one workgroup
-// reads the list in a moment.
+// (3) for the rows' top K is a launch of its own: several workgroups rank the same members, each
+// acts on its share.  It costs an ordinary row nothing (10 x 11.2 M, K = 111,740: 332 us with it and
+// without), and a tie group of a hundred thousand members, which values on a lattice have, is no
+// longer one workgroup's to act on (4 x 10 M, K = 300,000 on a lattice: 297 us, so 193; 2 x 10^6 equal values,
+// K = 500,001: 4040 and 159).  The other lists are shorter: their last workgroup ranks and acts, or
+// the only one, with the histogram in LDS, where one workgroup reads the list in a moment.
 //
 // What the last workgroup reads of the others -- the second list and its length -- goes
 // through atomics, which are performed in memory; the workgroups count themselves done
@@ -1309,7 +1348,8 @@ struct BigGroup {
 // run (runs are ascending).
 template <typename Lds>
 __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const uint32_t (&count)[2], uint32_t key,
-                                                      uint32_t want, const u32x2* __restrict__ runs, uint32_t n_segs, Lds& lds)
+                                                      uint32_t want, const u32x2* __restrict__ runs, uint32_t n_segs, uint32_t n_dealt,
+                                                      Lds& lds)
 {
     static_assert(kCoordBlocks == 2 * kRowThreads, "two blocks to a thread");
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
@@ -1332,7 +1372,7 @@ __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const u
     __syncthreads();
     if (n_here > 1) {                             // uniform: a wavefront per run counts
         for (uint32_t i = wave; i < n_here; i += kRowThreads / kWave) {
-            const u32x2 run = runs[r0 + i];
+            const u32x2 run = runs[run_place(r0 + i, n_dealt)];
             uint32_t k[kSeg / kWave];
             uint32_t n = 0;
 #pragma unroll
@@ -1361,7 +1401,7 @@ __device__ __forceinline__ uint32_t tie_cut_by_blocks(const ListView& v, const u
         lds.bcast[0] = 0;
     }
     __syncthreads();
-    const u32x2 run = runs[r0 + lds.bcast[0]];
+    const u32x2 run = runs[run_place(r0 + lds.bcast[0], n_dealt)];
     __syncthreads();
     static_assert(kSeg == kRowThreads, "a thread per entry of a run");
     const bool tie = t < run.y && v.list[run.x + t].x == key;
@@ -1585,6 +1625,17 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_hist(
     list_hist(row_list(cand, cap, row, C, K, tau, sample_hist, 0, 0), blockIdx.x, gridDim.x, hist);
 }
 
+// Votes for the marked entries of a batch; unless CAST (add-drop voting, or mv_vote_count behind) none are cast.
+template <bool CAST>
+struct CastVotes {
+    uint32_t *votes32, *lvl;
+    SegmentTallies tallies;
+    __device__ __forceinline__ void operator()(const u32x2 (&c)[kListUnroll], uint32_t taken) const
+    {
+        if constexpr (CAST) cast_votes<kListUnroll, true>(c, taken, votes32, lvl, tallies);
+    }
+};
+
 // What mv_sel_split leaves of a row to mv_sel_finish: behind the row's published threshold, on the line it has
 // to itself.
 __device__ __forceinline__ uint32_t* row_rest(unsigned long long* tau_pub, uint32_t row)
@@ -1593,7 +1644,7 @@ __device__ __forceinline__ uint32_t* row_rest(unsigned long long* tau_pub, uint3
 }
 
 // The streaming pass leaves a row's runs as its workgroups noted them; the kernels behind mv_sel_split read them in the order
-// of the segments, a few neighbouring ones at a time.  Workgroup `part` of a row's puts some groups of 64 in order: a wavefront
+// of the segments, a few neighbouring ones at a time, where they go by chunks of coordinates.  Workgroup `part` of a row's puts some groups of 64 in order: a wavefront
 // has a whole one in its registers, so it stays in place.
 constexpr int kOrderGroups = 4;                   // groups per wavefront
 constexpr uint32_t kOrderRuns = kRowThreads * kOrderGroups;
@@ -1617,12 +1668,14 @@ __device__ __forceinline__ void order_runs(u32x2* __restrict__ row_runs, uint32_
 static_assert(kGroupSegs == kWave, "a lane per segment of a group");
 
 // The members of the K-th's bin are left to mv_sel_finish.  Workgroups (split_blocks + part, row) put the row's runs in order.
+template <bool CAST>
 __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     const float* __restrict__ e, int64_t ld_e, int64_t d, u32x2* cand, uint32_t cap, uint32_t K,
     const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist,
     uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
-    u32x2* __restrict__ runs, uint32_t n_runs, RowSegments segs, unsigned long long* __restrict__ tau_pub,
+    uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, u32x2* __restrict__ runs, uint32_t n_runs,
+    RowSegments segs, uint32_t* __restrict__ lvl_sets, unsigned long long* __restrict__ tau_pub,
     uint32_t block_shift, uint32_t split_blocks)
 {
     __shared__ SplitLds<kMembers> lds;
@@ -1634,61 +1687,121 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     if (slow_flag[row] == 1u) {
         if (blockIdx.x == 0)
             select_row_from_memory(lds, e + (int64_t)row * ld_e, d, K, worker_idx ? worker_idx + (size_t)row * K : nullptr,
-                                   nullptr, nullptr, kth_out + row, tie_cut_out + row);
+                                   CAST ? votes32 : nullptr, lvl_sets, kth_out + row, tie_cut_out + row);
         return;
     }
     const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift,
                                 segs.shift(row));
+    for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the barriers before the first act
+    const CastVotes<CAST> act = {votes32, lds.lvl, {run_tallies ? run_tallies + (size_t)row * (n_runs / 2) : nullptr, v.shift}};
     uint32_t kth, tie_cut;
     ListRest rest;
-    (void)list_split<SplitEnd::Later>(v, blockIdx.x, split_blocks, lds, [](const u32x2 (&)[kListUnroll], uint32_t) {}, kth,
-                                      tie_cut, rest);
+    (void)list_split<SplitEnd::Later>(v, blockIdx.x, split_blocks, lds, act, kth, tie_cut, rest);
     if (blockIdx.x == 0 && t == 0) {
         uint32_t* r = row_rest(tau_pub, row);
         r[0] = rest.bin;
         r[1] = rest.want;
         r[2] = rest.n;
     }
+    if constexpr (CAST) {
+        __syncthreads();
+        merge_levels(lds.lvl, lvl_sets, blockIdx.y * split_blocks + blockIdx.x);
+    }
 }
 
-// The end of the rows' select, a workgroup per row: the members are ranked.
+// The end of the rows' select: grid (parts, rows).  Every workgroup of a row ranks the members -- the work
+// is repeated rather than shared so that no workgroup waits for another -- and casts the votes of its share.
+template <bool CAST>
 __global__ __launch_bounds__(kRowThreads) void mv_sel_finish(
     u32x2* cand, uint32_t cap, uint32_t K, const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ tau_bits,
     const uint32_t* __restrict__ slow_flag, uint32_t* __restrict__ sample_hist, uint32_t* __restrict__ kth_out,
-    uint32_t* __restrict__ tie_cut_out, uint32_t n_runs, RowSegments segs, unsigned long long* __restrict__ tau_pub,
-    const u32x2* __restrict__ runs, uint32_t block_shift)
+    uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, uint32_t n_runs,
+    RowSegments segs, uint32_t* __restrict__ lvl_sets, unsigned long long* __restrict__ tau_pub,
+    const u32x2* __restrict__ runs, int in_order, uint32_t block_shift)
 {
     __shared__ SplitLds<kMembers> lds;
-    const uint32_t row = blockIdx.x, t = threadIdx.x;
+    const uint32_t row = blockIdx.y, t = threadIdx.x;
     if (slow_flag[row] == 1u) return;
     const ListView v = row_list(cand, cap, row, cand_count[row], K, tau_bits[row], sample_hist, block_shift,
                                 segs.shift(row));
     const uint32_t* left = row_rest(tau_pub, row);
     const ListRest rest = {left[0], left[1], left[2]};
-    // what the next step must find at zero
-    v.hist[t] = 0;
-    if (t == 0) *v.count2 = 0;
+    const uint32_t share = members_stored(v, rest) ? rest.n : v.n;
+    if (blockIdx.x != 0 && blockIdx.x * (uint32_t)kListBatch >= share) return;      // nothing to act on
+    if (blockIdx.x == 0) {                        // what the next step must find at zero
+        v.hist[t] = 0;
+        if (t == 0) *v.count2 = 0;
+    }
+    for (int i = t; i < 257; i += kRowThreads) lds.lvl[i] = 0;       // ordered by the next barrier
+    const CastVotes<CAST> act = {votes32, lds.lvl, {run_tallies ? run_tallies + (size_t)row * (n_runs / 2) : nullptr, v.shift}};
     uint32_t kth, tie_cut;
+    if (rest.n <= (uint32_t)kMembers && members_stored(v, rest)) {   // uniform; usual: this is the row's only workgroup
+        static_assert(kMembers <= kListBatch, "a batch holds them");
+        u32x2 c[kListUnroll];
+        const u32x2 none = {0u, 0xFFFFFFFFu};
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u) {
+            const uint32_t i = (uint32_t)u * kRowThreads + t;
+            c[u] = i < rest.n ? member_at<false>(v, i) : none;
+        }
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u)
+            if (c[u].y != 0xFFFFFFFFu) {
+                lds.key[0][u * kRowThreads + t] = c[u].x;
+                lds.at[0][u * kRowThreads + t] = c[u].y;
+            }
+        __syncthreads();
+        uint32_t lo, bits;
+        list_bin_range(v, rest.bin, lo, bits);
+        rank_members(lds, rest.n, rest.want, lo, bits, kth, tie_cut);
+        if (t == 0) {
+            kth_out[row] = kth;
+            tie_cut_out[row] = tie_cut;
+        }
+        if constexpr (!CAST) return;
+        uint32_t taken = 0;
+#pragma unroll
+        for (int u = 0; u < kListUnroll; ++u)
+            taken |= (c[u].y != 0xFFFFFFFFu && is_taken(c[u], kth, tie_cut) ? 1u : 0u) << u;
+        if (__ballot(taken != 0u) != 0ull) act(c, taken);            // wave-uniform
+        __syncthreads();
+        merge_levels(lds.lvl, lvl_sets, row);
+        return;
+    }
+    __syncthreads();                              // (a bin that is wanted whole is acted on without another)
     bool ranked = false;
     if (rest.n > (uint32_t)kMembers) {            // uniform: a big group
         const uint32_t count[2] = {v.blocks[2 * t], v.blocks[2 * t + 1]};
         const uint32_t largest = v.count2[1], smallest = ~v.count2[2];
+        // these values are there before the workgroup is counted
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        v.blocks[2 * t] = 0;
-        v.blocks[2 * t + 1] = 0;
-        if (t < 2) v.count2[1 + t] = 0;
+        if (t == 0) lds.last = atomicAdd(v.done, 1u) + 1u == min(gridDim.x, (share + kListBatch - 1) / kListBatch);
+        __syncthreads();
+        if (lds.last) {                           // every workgroup of the row has read them
+            v.blocks[2 * t] = 0;
+            v.blocks[2 * t + 1] = 0;
+            if (t < 2) v.count2[1 + t] = 0;
+            if (t == 0) *v.done = 0;
+        }
         if (largest == smallest && rest.want < rest.n) {
             kth = largest;
-            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, runs + (size_t)row * n_runs, segs.count(row), lds);
+            tie_cut = tie_cut_by_blocks(v, count, kth, rest.want, runs + (size_t)row * n_runs, segs.count(row),
+                                        in_order ? 0u : segs.count(row), lds);
             ranked = true;
         }
     }
     if (!ranked) rank_rest<false>(v, rest, lds, kth, tie_cut);
     kth = max(kth, v.base);                       // (where a bin is wanted whole: what is not in the list stays outside)
-    if (t == 0) {
+    if (blockIdx.x == 0 && t == 0) {
         kth_out[row] = kth;
         tie_cut_out[row] = tie_cut;
     }
+    if constexpr (!CAST) return;
+    act_on_rest<false>(v, rest, kth, tie_cut, blockIdx.x, gridDim.x, act);
+    __syncthreads();
+    merge_levels(lds.lvl, lvl_sets, blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 }  // namespace mvk

@@ -1,5 +1,5 @@
 """The votes of long lists, counted in LDS by chunks of coordinates: vectors at the edges of a chunk, of a workgroup's chunks
-and of each chunk length, the most rows for each, rows shifted against each other, crowded chunks, and rows selected from memory."""
+and of each chunk length, rows shifted against each other, crowded chunks, and rows selected from memory."""
 import numpy as np
 import pytest
 
@@ -22,18 +22,14 @@ def gradients(rng, N, d, kind):
 
 
 @pytest.mark.parametrize("N,d,K,offset,kind", [
-    (2, 40_000, 30_000, 0, "normal"),             # a list without a threshold, 40 chunks of 1024
-    (3, (1 << 19) - 1, 30_000, 4, "normal"),      # the longest with chunks of 1024, ...
-    (3, 1 << 19, 30_000, 1020, "crowded"),        # ... the shortest with 2048, ...
-    (2, (1 << 20) - 1, 40_000, 512, "slow"),
-    (2, 1 << 20, 40_000, 0, "normal"),            # ... and with 4096, rows in step with 4 KB
-    (3, (1 << 20) + 1, 25_000, 4, "slow"),
-    (3, (1 << 20) + 4095, 25_000, 8, "crowded"),
-    (2, 4096 * 1024, 50_000, 12, "normal"),       # a chunk to a workgroup, and one more
-    (2, 4096 * 1024 + 1, 50_000, 1020, "normal"),
-    (204, 1 << 20, 25_000, 4, "levels"),          # the most rows that chunks of 4096 and a workgroup's runs allow, ...
-    (205, 1 << 20, 25_000, 4, "levels"),          # ... and one more
-    (255, 66_049, 28_000, 4, "crowded"),
+    (20, (1 << 19) - 1, 27_000, 4, "normal"),     # chunks of 1024
+    (20, (1 << 20) - 1, 27_000, 512, "normal"),   # the longest with chunks of 2048, ...
+    (5, 1 << 20, 100_000, 0, "normal"),           # ... the shortest with 4096, rows in step with 4 KB
+    (5, (1 << 20) + 1, 100_000, 4, "slow"),
+    (5, (1 << 20) + 4095, 100_000, 8, "crowded"),
+    (13, 4096 * 1024, 40_000, 12, "levels"),      # a chunk to a workgroup, ...
+    (13, 4096 * 1024 + 1, 40_000, 1020, "levels"),    # ... and two
+    (33, 2_200_003, 20_000, 4, "levels"),
 ])
 @pytest.mark.parametrize("lists", [True, False], ids=["lists", "no_lists"])
 def test_votes_by_chunks(oracle, N, d, K, offset, kind, lists):
