@@ -70,6 +70,7 @@ struct Plan {
     uint32_t cap_d;               // capacity of a row's list of removal candidates
     uint32_t bit_blocks;          // workgroups of kBitBlockWords bitmap words per row
     uint32_t collect_threads, collect_blocks;   // of mv_ad_collect: threads per workgroup, workgroups per row for the bitmap
+    bool     collect_chunks;      // mv_ad_collect_chunks in its place
     // rows' select with many workgroups: when about 2K candidates are far more than one workgroup keeps in registers
     bool     multi_select;
     uint32_t block_shift;         // its blocks of coordinates: 2^block_shift, at most kCoordBlocks of them
@@ -278,9 +279,14 @@ Plan make_plan(const mv_config* c)
         if (eb2 * p.N > 512) eb2 = 512 / p.N;      // (10 x 11.2 M, K = 111,740: 346.7 us, with 256 349.6)
         if (eb2 < 1) eb2 = 1;
         p.split_blocks = (uint32_t)sb;
-        // likewise in mv_ad_collect
-        // (a row's bitmap in one workgroup of more threads, where it fits)
-        const bool one = (uint64_t)p.d <= 32ull * mvk::collect_words(mvk::kCollectThreadsShort);
+        // likewise in mv_ad_collect (a row's bitmap in one workgroup of more threads, where it fits), which goes by chunks of
+        // coordinates where lists are long and dense and a workgroup's chunks hold not too many entries of them (steps with
+        // candidates looked up one by one : by chunks; 128 x 400,003, K = 33,333 386 : 357 us; 2 x 4 M, K = 400,000 162 : 140;
+        // 8 x 8 M, K = 80,000 234 : 227; 16 x 8 M, K = 40,000 366 : 359; sparser: 16 x 11.2 M, K = 30,000 452 : 456, 32 x 25.6 M
+        // bf16, K = 25,557 1459 : 1487; fuller: 100 x 60,003, K = 30,000 259 : 293, 4 x 60,003, K = 40,000 131 : 178)
+        const uint64_t per_wg = 32ull * mvk::collect_words(mvk::kCollectThreads);
+        p.collect_chunks = p.multi_select && 256ull * p.K >= (uint64_t)p.d && expect <= 10000 * (((uint64_t)p.d + per_wg - 1) / per_wg);
+        const bool one = !p.collect_chunks && (uint64_t)p.d <= 32ull * mvk::collect_words(mvk::kCollectThreadsShort);
         p.collect_threads = one ? mvk::kCollectThreadsShort : mvk::kCollectThreads;
         const uint64_t batch = mvk::add_batch((int)p.collect_threads);
         uint64_t lb = (expect + batch - 1) / batch;
@@ -650,7 +656,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     uint32_t* tallies = sorted ? run_taken : nullptr;
     const int thresholds_only = add_drop ? 1 : 0;
     // (the runs are put in order for the kernels that go through them by chunks of coordinates)
-    const bool in_order = !add_drop && p.vote_chunks;
+    const bool in_order = add_drop ? p.collect_chunks : p.vote_chunks;
     if (p.multi_select) {
         before(KID_SEL_HIST);
         hipLaunchKernelGGL(mvk::mv_sel_hist, dim3(p.split_blocks, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K, rowcnt_sets,
@@ -700,7 +706,12 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         const uint32_t k_ad = (uint32_t)a.k_ad;
         uint32_t* msum32 = reinterpret_cast<uint32_t*>(a.msum);
         before(KID_AD_COLLECT);
-        hipLaunchKernelGGL((p.collect_threads == (uint32_t)mvk::kCollectThreads
+        if (p.collect_chunks)
+            hipLaunchKernelGGL(mvk::mv_ad_collect_chunks, dim3(p.collect_blocks, p.N), dim3(p.collect_threads), 0, st, a.err,
+                               a.ld_e, p.d, cand, p.cap, (const mvk::u32x2*)runs, p.n_runs, segs, kth, tiecut, slow,
+                               a.vote_bits, a.ld_bits, p.nwords_pad, alist, dlist, p.cap_d, adcount);
+        else
+            hipLaunchKernelGGL((p.collect_threads == (uint32_t)mvk::kCollectThreads
                                 ? &mvk::mv_ad_collect<mvk::kCollectThreads>
                                 : &mvk::mv_ad_collect<mvk::kCollectThreadsShort>),
                            dim3(p.list_blocks + p.collect_blocks, p.N), dim3(p.collect_threads), 0,
