@@ -128,8 +128,11 @@ Plan make_plan(const mv_config* c)
     };
     // list entries to be ready for when so many are expected
     auto with_room = [](double expected) { return expected * 1.25 + 1.0; };
-    // Sample about d/128 coordinates of each row, at least 32K, by up to 16 workgroups (kSampleQuads quads per
-    // thread and round) -- or, where the list does not grow too long for it, 8K by ONE workgroup in one round, whose
+    // Sample about d/128 coordinates of each row, at least 32K and at most the 128K that 16 workgroups take in one round
+    // (kSampleQuads quads per thread: the first row's stream waits for every further round, and scattered lines cost the
+    // memory more than a longer list does; d/128 everywhere : so, 1 x 200 M, K = 200,000 626 : 602 us, 1 x 50 M 178.3 : 172.5,
+    // 3 x 25.6 M 206.1 : 203.3, 32 x 25.6 M bf16 1368.5 : 1366.0, 16 of them with add-drop 760.9 : 757.4; 96K at most
+    // 1363.8 and 755.2 there, but 24 x 20 M bf16, K = 6000 803.0 : 807.0) -- or, where the list does not grow too long for it, 8K by ONE workgroup in one round, whose
     // histogram need not be merged in memory: the step of a short row waits for the estimate.  The line follows the
     // lists, one workgroup's against several's (steps of 2, 4 and 16 rows, time with several : time with one):
     //   up to 8192 entries, whatever the others':   2.7K for 0.9K 1.04 1.04 1.02; 6.3K for 1.6K 1.04 1.04 0.99;
@@ -139,7 +142,9 @@ Plan make_plan(const mv_config* c)
     //                        with 40 rows and add-drop voting 0.90
     const uint64_t nchunks = (uint64_t)(p.d + mvk::kChunk - 1) / mvk::kChunk;
     const uint64_t per_round = (uint64_t)mvk::kSampleQuads * mvk::kStreamThreads;      // quads
-    const uint64_t want = (uint64_t)p.d / 128 > 32768 ? (uint64_t)p.d / 128 : 32768;
+    const uint64_t one_round = 4 * per_round * mvk::kSampleWgs;
+    uint64_t want = (uint64_t)p.d / 128 > 32768 ? (uint64_t)p.d / 128 : 32768;
+    if (want > one_round) want = one_round;
     const double one = 4.0 * (double)per_round / (double)p.d, many = (double)want / (double)p.d;   // fractions
     const double list_one = sampled_above(one) / one, list_many = sampled_above(many) / many;
     uint64_t stride;
@@ -148,11 +153,14 @@ Plan make_plan(const mv_config* c)
         stride = (nchunks + chunks - 1) / chunks;
         p.sample_wgs = 1;
     } else {
-        stride = nchunks / ((want + mvk::kChunk - 1) / mvk::kChunk);
+        const uint64_t chunks = (want + mvk::kChunk - 1) / mvk::kChunk;
+        stride = nchunks / chunks;
         if (stride < 1) stride = 1;
         if (stride > 128) stride = 128;
+        const uint64_t most = one_round / mvk::kChunk;
+        if ((nchunks + stride - 1) / stride > most) stride = (nchunks + most - 1) / most;
         const uint64_t bx = ((nchunks + stride - 1) / stride * (mvk::kChunk / 4) + per_round - 1) / per_round;
-        p.sample_wgs = (uint32_t)(bx > 16 ? 16 : bx);
+        p.sample_wgs = (uint32_t)(bx > mvk::kSampleWgs ? mvk::kSampleWgs : bx);
     }
     // Loads of the grid's head beside the sampling bring a short grid's data earlier and the estimate later.  One
     // sampling workgroup per row has little to fetch: no loads are held back (7 x 272,475 bf16: 33.7 -> 33.0 us;
@@ -203,13 +211,9 @@ Plan make_plan(const mv_config* c)
     {
         // A crowded bin makes the list longer than it has to be, and the search inside it holds the row's stream up:
         // it is made where the list would be twice as long (one sampling workgroup, whose samples are at hand) or three
-        // times (several, whose samples one has to fetch: up to 32,768 quads of them), and in longer rows only where the
-        // list nears its storage.  K = d / 1000, lists of 6K to 8K entries kept : searched: 1 x 8 M 86.3 us 73.0;
-        // 1 x 14 M 100.8 99.9; 1 x 25 M 134.2 138.7, 1 x 50 M 209.3 222.8, 1 x 200 M 638 745; of 13K: 1 x 25 M 153.3 139.7,
-        // 1 x 50 M 229.1 223.5, 1 x 200 M 665 772.
-        const bool long_row = (uint64_t)p.n_sampled_chunks * (mvk::kChunk / 4) > 32768;
-        double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
-        if (long_row && 0.875 * (double)p.cap * frac > most) most = 0.875 * (double)p.cap * frac;
+        // times (several, whose samples one has to fetch: up to 32,768 quads of them; K = d / 1000, lists of 6K to 8K entries
+        // kept : searched: 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9).
+        const double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
         p.crowded = (p.sample_wgs > 1 && !p.keep_samples) || most >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)most;
     }
 

@@ -71,7 +71,8 @@ constexpr int      kSubBins = kStreamThreads;
 constexpr int      kSubShift = kHistShift - 9;
 static_assert(kSubBins == 512, "9 bits behind the bin's");
 constexpr int      kSampleQuads = 4;              // quads of samples a sampling thread has in flight
-constexpr int      kAgainQuads = 8;               // and one that goes through them once more (1 x 200 M: four 761 us, eight 738)
+constexpr uint32_t kSampleWgs = 16;               // at most so many workgroups sample a row
+constexpr int      kAgainQuads = 8;               // and one that goes through them once more (1.6 M samples: four 761 us a step, eight 738)
 constexpr uint32_t kRowPoison = 0x80000000u;      // set in a marked row's candidate counter by mv_row_select
 
 struct StreamLds {
@@ -154,14 +155,14 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     __syncthreads();
     const GT*    grow = g + (int64_t)row * ld_g;
     const float* erow = e + (int64_t)row * ld_e;
-    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most one coordinate in 64, or 65,536
+    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most 32,768
     uint32_t* samples = all_samples ? all_samples + (size_t)row * nquads * 4 : nullptr;
     const uint32_t step = spr * kStreamThreads;
     auto start_of = [stride](uint32_t q) {
         return (int64_t)(q / (kChunk / 4)) * stride * kChunk + (int64_t)(q % (kChunk / 4)) * 4;
     };
     // The samples lie far apart in memory and every load pays the full latency: kSampleQuads
-    // quads' loads are in flight per thread and the grid is sized for one or two rounds.  A round loads in every
+    // quads' loads are in flight per thread and the grid is sized for one round.  A round loads in every
     // lane (past the samples: the row's first quad) and assigns all of `kept`, which is therefore not alive in the
     // next round's loads.  The streaming workgroups have to do with the registers that this takes: 60, eight
     // waves to a SIMD.  Where a thread only assigned what it had loaded, 78 and six (7 x 1,000,003 bf16, K = 2000:
