@@ -142,9 +142,19 @@ Plan make_plan(const mv_config* c)
     //                        with 40 rows and add-drop voting 0.90
     const uint64_t nchunks = (uint64_t)(p.d + mvk::kChunk - 1) / mvk::kChunk;
     const uint64_t per_round = (uint64_t)mvk::kSampleQuads * mvk::kStreamThreads;      // quads
-    const uint64_t one_round = 4 * per_round * mvk::kSampleWgs;
+    // More than a round where the list would take more than a quarter of its storage otherwise (fewer than a few thousand
+    // of tens of millions: 128 sampled ones stand for 128 d / 131,072 entries).
+    uint64_t cap = 16ull * p.K;
+    if (cap < 65536) cap = 65536;
+    if (cap > (uint64_t)p.d) cap = (uint64_t)p.d;
     uint64_t want = (uint64_t)p.d / 128 > 32768 ? (uint64_t)p.d / 128 : 32768;
-    if (want > one_round) want = one_round;
+    uint64_t most_sampled = 4 * per_round * mvk::kSampleWgs;
+    while (most_sampled < want) {
+        const double frac = (double)most_sampled / (double)p.d;
+        if (sampled_above(frac) / frac <= 0.25 * (double)cap) break;
+        most_sampled *= 2;
+    }
+    if (want > most_sampled) want = most_sampled;
     const double one = 4.0 * (double)per_round / (double)p.d, many = (double)want / (double)p.d;   // fractions
     const double list_one = sampled_above(one) / one, list_many = sampled_above(many) / many;
     uint64_t stride;
@@ -157,7 +167,7 @@ Plan make_plan(const mv_config* c)
         stride = nchunks / chunks;
         if (stride < 1) stride = 1;
         if (stride > 128) stride = 128;
-        const uint64_t most = one_round / mvk::kChunk;
+        const uint64_t most = most_sampled / mvk::kChunk;
         if ((nchunks + stride - 1) / stride > most) stride = (nchunks + most - 1) / most;
         const uint64_t bx = ((nchunks + stride - 1) / stride * (mvk::kChunk / 4) + per_round - 1) / per_round;
         p.sample_wgs = (uint32_t)(bx > mvk::kSampleWgs ? mvk::kSampleWgs : bx);
@@ -204,16 +214,16 @@ Plan make_plan(const mv_config* c)
     const double m = sampled_above(frac) + 1.0;
     p.m_target = (m >= 4294967295.0) ? 0xFFFFFFFFu : (uint32_t)m;
 
-    uint64_t cap = 16ull * p.K;
-    if (cap < 65536) cap = 65536;
-    if (cap > (uint64_t)p.d) cap = (uint64_t)p.d;
     p.cap = (uint32_t)cap;
     {
         // A crowded bin makes the list longer than it has to be, and the search inside it holds the row's stream up:
         // it is made where the list would be twice as long (one sampling workgroup, whose samples are at hand) or three
         // times (several, whose samples one has to fetch: up to 32,768 quads of them; K = d / 1000, lists of 6K to 8K entries
-        // kept : searched: 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9).
-        const double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
+        // kept : searched: 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9), and with more samples only where the list nears its
+        // storage (390,000 quads: 638 : 745).
+        const bool many_samples = (uint64_t)p.n_sampled_chunks * (mvk::kChunk / 4) > 32768;
+        double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
+        if (many_samples && 0.875 * (double)p.cap * frac > most) most = 0.875 * (double)p.cap * frac;
         p.crowded = (p.sample_wgs > 1 && !p.keep_samples) || most >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)most;
     }
 

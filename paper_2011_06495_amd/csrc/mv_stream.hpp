@@ -155,14 +155,14 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     __syncthreads();
     const GT*    grow = g + (int64_t)row * ld_g;
     const float* erow = e + (int64_t)row * ld_e;
-    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most 32,768
+    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most 32,768, or one coordinate in 512
     uint32_t* samples = all_samples ? all_samples + (size_t)row * nquads * 4 : nullptr;
     const uint32_t step = spr * kStreamThreads;
     auto start_of = [stride](uint32_t q) {
         return (int64_t)(q / (kChunk / 4)) * stride * kChunk + (int64_t)(q % (kChunk / 4)) * 4;
     };
     // The samples lie far apart in memory and every load pays the full latency: kSampleQuads
-    // quads' loads are in flight per thread and the grid is sized for one round.  A round loads in every
+    // quads' loads are in flight per thread and the grid is sized for one round, or a few.  A round loads in every
     // lane (past the samples: the row's first quad) and assigns all of `kept`, which is therefore not alive in the
     // next round's loads.  The streaming workgroups have to do with the registers that this takes: 60, eight
     // waves to a SIMD.  Where a thread only assigned what it had loaded, 78 and six (7 x 1,000,003 bf16, K = 2000:

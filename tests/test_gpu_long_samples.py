@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 MOST = 131_072 * 128
 
 
-@pytest.mark.parametrize("N,d,K", [(1, MOST - 33, 8000), (1, MOST + 128, 8000), (2, 24_000_001, 30_000), (5, MOST + 1, 3000)])
+@pytest.mark.parametrize("N,d,K", [(1, MOST - 33, 8000), (1, MOST + 128, 8000), (2, 24_000_001, 30_000), (5, MOST + 1, 3000),
+                                   (2, 40_000_003, 500), (1, 40_000_003, 5000)])       # few: more than a round is sampled
 def test_long_rows_are_selected_from_their_lists(oracle, N, d, K):
     print("[case] long samples N=%d d=%d K=%d" % (N, d, K), flush=True)
     rng = np.random.default_rng(d)
