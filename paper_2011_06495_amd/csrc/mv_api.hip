@@ -25,6 +25,7 @@ enum KernelId {
     KID_GATHER,
     // add-drop voting only
     KID_AD_COLLECT,
+    KID_AD_CHUNKS,                                // long, dense lists, in place of the one above
     KID_AD_HIST,
     KID_AD_PICK,
     KID_AD_EMIT,
@@ -38,9 +39,9 @@ enum KernelId {
     KID_COUNT
 };
 const char* const kKernelNames[KID_COUNT] = {
-    "mv_stream_collect", "mv_row_select", "mv_sel_hist", "mv_sel_split", "mv_sel_finish", "mv_vote_count", "mv_mask_count", "mv_gather_update",
-    "mv_ad_collect",     "mv_ad_hist",    "mv_ad_pick",  "mv_ad_emit",   "mv_rs_keys",    "mv_rs_hist",
-    "mv_rs_pick",        "mv_small_rows", "mv_small_mask"};
+    "mv_stream_collect", "mv_row_select",        "mv_sel_hist", "mv_sel_split",  "mv_sel_finish", "mv_vote_count",
+    "mv_mask_count",     "mv_gather_update",     "mv_ad_collect", "mv_ad_collect_chunks", "mv_ad_hist", "mv_ad_pick",
+    "mv_ad_emit",        "mv_rs_keys",           "mv_rs_hist",  "mv_rs_pick",    "mv_small_rows", "mv_small_mask"};
 
 constexpr size_t kAlign = 256;
 constexpr int kEventRing = 64;   // steps whose kernel durations stay readable
@@ -719,11 +720,12 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         // then the sorted add / drop lists, the standing votes and the levels of msum
         const uint32_t k_ad = (uint32_t)a.k_ad;
         uint32_t* msum32 = reinterpret_cast<uint32_t*>(a.msum);
-        before(KID_AD_COLLECT);
+        const int kid_collect = p.collect_chunks ? KID_AD_CHUNKS : KID_AD_COLLECT;
+        before(kid_collect);
         if (p.collect_chunks)
-            hipLaunchKernelGGL(mvk::mv_ad_collect_chunks, dim3(p.collect_blocks, p.N), dim3(p.collect_threads), 0, st, a.err,
-                               a.ld_e, p.d, cand, p.cap, (const mvk::u32x2*)runs, p.n_runs, segs, kth, tiecut, slow,
-                               a.vote_bits, a.ld_bits, p.nwords_pad, alist, dlist, p.cap_d, adcount);
+            hipLaunchKernelGGL(mvk::mv_ad_collect_chunks, dim3(p.collect_blocks, p.N), dim3(p.collect_threads), 0, st,
+                               a.err, a.ld_e, p.d, cand, p.cap, (const mvk::u32x2*)runs, p.n_runs, segs, kth, tiecut,
+                               slow, a.vote_bits, a.ld_bits, p.nwords_pad, alist, dlist, p.cap_d, adcount);
         else
             hipLaunchKernelGGL((p.collect_threads == (uint32_t)mvk::kCollectThreads
                                 ? &mvk::mv_ad_collect<mvk::kCollectThreads>
@@ -731,7 +733,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
                            dim3(p.list_blocks + p.collect_blocks, p.N), dim3(p.collect_threads), 0,
                            st, a.err, a.ld_e, p.d, cand, p.cap, rowcnt, kth, tiecut, slow, a.vote_bits, a.ld_bits,
                            p.nwords_pad, alist, dlist, p.cap_d, adcount, p.list_blocks);
-        after(KID_AD_COLLECT);
+        after(kid_collect);
         // (a list has at most K entries; the candidate lists have been used and lend their storage)
         const bool alone = p.K <= mvk::kAloneList;
         uint32_t parts = (p.K + mvk::kListBatch - 1) / mvk::kListBatch;
