@@ -16,16 +16,22 @@ namespace mvk {
 // next chunk: its entries are read by both, its tally is the next one's.
 //
 // Entries are dealt to threads by their number among all of the workgroup's, so that no thread has more than one more than
-// another, however long a run is.  Which run an entry belongs to: the runs that are not empty are numbered, and a bit
+// another.  Which run an entry belongs to: the runs that are not empty are numbered, and a bit
 // marks each entry that begins one, so the number is a count of bits, most of it a scalar's (found by bisection in the
 // runs' summed lengths, with its place taken apart by divisions: 20.5 us instead of 15.2 at 10 x 11.2 M, K = 111,740).
+// A batch of 4096 entries takes 3 us so, 2.3 of them finding the runs, and where the largest tensors' errors are zero the
+// fullest workgroup has five.  So the runs of at least kLongRun entries go to a wavefront each, which has nothing to find:
+// that workgroup is through with its entries in 7 us for 17.  10 x 11.2 M, K = 111,740, from a zero buffer 20.7 us for 25.7
+// (all of these between events around the kernel; runs from 64 entries on 20.6, but 15.8 for 13.4 at 16 x 6 M,
+// K = 40,000; from 32 on 24.4), with carried errors 15.9 for 17.2.  The crowded chunks' pieces dealt over the grid, with the
+// chunks' entries counted beside order_runs: 23.5 and 19.5.
 //
-// What it takes there, 14.7 us, is 4.6 for the launch, 1.8 for the runs, 7 for the entries -- the fullest workgroup, with
-// a small tensor's hot chunk, has three batches -- and 1.5 for the bytes and their levels; at 32 x 25.6 M, 20.2 us, the
-// runs are 7.  With workgroups of 1024 threads 15.2 and 26: four short ones to a unit fill each other's waits.
+// Of the kernel's time with carried errors 4.6 are the launch, 1.8 the runs, 6 the entries and 1.5 the bytes and their
+// levels; at 32 x 25.6 M, 20.2 us by the trace, the runs are 7.  With workgroups of 1024 threads 26 there: four short ones to
+// a unit fill each other's waits.
 // With the votes as returning atomics in memory, cast by mv_sel_split and mv_sel_finish, these two took 37.5 and 45 us;
-// with this kernel behind them the three take 29 and 39, and the vote bytes need not be cleared beforehand: steps
-// 346.3 -> 335.5 us and 1413.7 -> 1406.4.
+// with this kernel behind them the three take 28 and 39, and the vote bytes need not be cleared beforehand: steps
+// 337.7 -> 321.2 us and 1413.7 -> 1406.4.  From a zero buffer, whose votes lie close together and share atomics, 306.8 -> 308.7.
 constexpr int kVotesThreads = 512;
 constexpr int kVotesWaves = kVotesThreads / kWave;
 constexpr int kVotesRunsMost = 1024;              // runs of a workgroup: two to a thread
@@ -33,6 +39,8 @@ constexpr int kVotesBytesMost = 6 * 4096;         // coordinates of a workgroup
 constexpr int kVotesUnroll = 8;                   // entries per thread in flight together
 constexpr uint32_t kVotesBatch = kVotesThreads * kVotesUnroll;
 static_assert(kVotesWaves * kVotesUnroll == kWave, "a lane per wavefront's part of a batch");
+constexpr uint32_t kLongRun = 128;                // a run of so many entries is one wavefront's
+constexpr int kLongUnroll = 4;                    // loads of it in flight together, twice
 constexpr int kLvlCopies = 2;                     // copies of the level counters, one per lane % kLvlCopies
 
 struct VotesLds {
@@ -40,7 +48,8 @@ struct VotesLds {
     __attribute__((aligned(8))) uint32_t begins[kVotesBatch / 32];   // bit i: entry i of the batch begins a run
     uint32_t from[kVotesRunsMost];                // entry number i of the workgroup's, in run r: entry from[r] + i of the row's list
     uint16_t place[kVotesRunsMost];               // the run's row | the workgroup's chunk << 8
-    uint32_t taken[kVotesRunsMost];
+    uint32_t taken[kVotesRunsMost];               // (of a long run that is still to be walked: its length)
+    uint32_t n_long;                              // long runs: they have the arrays' ends
     uint32_t lvl[kLvlCopies * 257];
     uint32_t kth[256], tie_cut[256];              // of the rows
     uint64_t scan[kVotesWaves];
@@ -57,7 +66,7 @@ struct SmallDivisor {
     __device__ __forceinline__ uint32_t quotient(uint32_t x) const { return x * m >> 20; }
 };
 
-__global__ __launch_bounds__(kVotesThreads) void mv_vote_count(
+__global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
     const float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N, const u32x2* __restrict__ cand, uint32_t cap,
     const u32x2* __restrict__ runs, uint32_t n_runs, RowSegments segs, const uint32_t* __restrict__ kth_in,
     const uint32_t* __restrict__ tie_cut_in, const uint32_t* __restrict__ slow_flag, uint32_t chunk_shift, uint32_t n_chunks,
@@ -97,7 +106,7 @@ __global__ __launch_bounds__(kVotesThreads) void mv_vote_count(
         slow = slow_flag[t] == 1u;
     }
     // cleared while those loads are under way
-    if (t == 0) lds.any_slow = 0;
+    if (t == 0) lds.any_slow = lds.n_long = 0;
     {
         const u32x4 z = {0u, 0u, 0u, 0u};
         u32x4* v = reinterpret_cast<u32x4*>(lds.votes);
@@ -111,21 +120,33 @@ __global__ __launch_bounds__(kVotesThreads) void mv_vote_count(
         lds.tie_cut[t] = tie_cut;
         if (slow) lds.any_slow = 1u;
     }
-    // their entries' numbers, and their own among the runs that are not empty
-    uint32_t first[2], number[2], total;
+    uint32_t number[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (run[q].y >= kLongRun) {
+            number[q] = (uint32_t)kVotesRunsMost - 1u - atomicAdd(&lds.n_long, 1u);
+            lds.from[number[q]] = run[q].x;
+            lds.place[number[q]] = (uint16_t)place[q];
+            lds.taken[number[q]] = run[q].y;
+            run[q].y = kLongRun;
+        }
+    // the other runs' entries' numbers, and their own among those that are not empty
+    uint32_t first[2], total;
+    auto is_short = [&](int q) { return run[q].y - 1u < kLongRun - 1u; };
     {
-        const uint32_t there[2] = {run[0].y != 0u ? 1u : 0u, run[1].y != 0u ? 1u : 0u};
+        const uint32_t there[2] = {is_short(0) ? 1u : 0u, is_short(1) ? 1u : 0u}, there0 = is_short(0) ? run[0].y : 0u;
         uint64_t sums;
-        const uint64_t ex = block_excl_scan64<kVotesThreads>(pack2(run[0].y + run[1].y, there[0] + there[1]), lds.scan, sums);
+        const uint64_t ex = block_excl_scan64<kVotesThreads>(
+            pack2(there0 + (is_short(1) ? run[1].y : 0u), there[0] + there[1]), lds.scan, sums);
         total = (uint32_t)(sums >> 32);
         first[0] = (uint32_t)(ex >> 32);
-        first[1] = first[0] + run[0].y;
-        number[0] = (uint32_t)ex;
-        number[1] = number[0] + there[0];
+        first[1] = first[0] + there0;
+        if (there[0]) number[0] = (uint32_t)ex;
+        if (there[1]) number[1] = (uint32_t)ex + there[0];
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-        if (run[q].y != 0u) {
+        if (is_short(q)) {
             lds.from[number[q]] = run[q].x - first[q];
             lds.place[number[q]] = (uint16_t)place[q];
             lds.taken[number[q]] = 0;
@@ -138,7 +159,7 @@ __global__ __launch_bounds__(kVotesThreads) void mv_vote_count(
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-            if (run[q].y != 0u && first[q] - i0 < kVotesBatch)
+            if (is_short(q) && first[q] - i0 < kVotesBatch)
                 atomicOr(&lds.begins[(first[q] - i0) / 32], 1u << ((first[q] - i0) & 31u));
         __syncthreads();
         const u32x2 bits = reinterpret_cast<const u32x2*>(lds.begins)[lane];       // lane l: of the batch's entries 64 l ..
@@ -175,6 +196,64 @@ __global__ __launch_bounds__(kVotesThreads) void mv_vote_count(
                 if (end >> lane & 1ull) atomicAdd(&lds.taken[r[u]], below + (taken ? 1u : 0u));
                 if ((begin >> lane & 1ull) && below != 0u) atomicAdd(&lds.taken[r[u]], 0u - below);
             }
+        }
+    }
+    // The long runs, a wavefront each; the next loads are under way while these are counted.
+    const uint32_t n_long = lds.n_long;           // (behind the scan's barrier)
+    if (wave < n_long) {                          // uniform
+        struct Run {
+            const u32x2* entries;
+            uint32_t n, place;
+            u32x2 cut;                            // the row's K-th magnitude and tie cut
+        };
+        auto run_at = [&](uint32_t k) {
+            const uint32_t at = (uint32_t)kVotesRunsMost - 1u - k;
+            Run l;
+            l.place = from_lane((uint32_t)lds.place[at], 0);
+            l.n = from_lane(lds.taken[at], 0);
+            l.entries = cand + ((size_t)(l.place & 255u) * cap + from_lane(lds.from[at], 0));
+            l.cut = u32x2{lds.kth[l.place & 255u], lds.tie_cut[l.place & 255u]};
+            return l;
+        };
+        auto load = [&](const Run& l, uint32_t i0, u32x2 (&c)[kLongUnroll]) {
+#pragma unroll
+            for (int u = 0; u < kLongUnroll; ++u) {
+                const uint32_t i = i0 + (uint32_t)u * kWave + lane;
+                c[u] = l.entries[min(i, l.n - 1u)];
+            }
+        };
+        uint32_t k = wave, i0 = 0, n_taken = 0;
+        Run l = run_at(k);
+        u32x2 c[kLongUnroll];
+        load(l, 0, c);
+        while (true) {
+            const bool ends = i0 + kLongUnroll * kWave >= l.n;       // uniform, as all that follows
+            const uint32_t next_k = ends ? k + kVotesWaves : k, next_i0 = ends ? 0u : i0 + kLongUnroll * kWave;
+            Run next = l;
+            u32x2 ahead[kLongUnroll];
+            if (next_k < n_long) {
+                if (ends) next = run_at(next_k);
+                load(next, next_i0, ahead);
+            }
+            const uint32_t m = l.place >> 8, base = chunk_of(m) << chunk_shift;
+#pragma unroll
+            for (int u = 0; u < kLongUnroll; ++u) {
+                if (i0 + (uint32_t)u * kWave >= l.n) break;
+                const bool taken = i0 + (uint32_t)u * kWave + lane < l.n && is_taken(c[u], l.cut.x, l.cut.y);
+                n_taken += (uint32_t)__popcll(__ballot(taken));
+                const uint32_t j = c[u].y - base;
+                if (taken && j < chunk) atomicAdd(&lds.votes[((m << chunk_shift) + j) >> 2], 1u << (j & 3u) * 8u);
+            }
+            if (ends) {
+                if (lane == 0) lds.taken[(uint32_t)kVotesRunsMost - 1u - k] = n_taken;
+                n_taken = 0;
+            }
+            if (next_k >= n_long) break;
+            k = next_k;
+            i0 = next_i0;
+            l = next;
+#pragma unroll
+            for (int u = 0; u < kLongUnroll; ++u) c[u] = ahead[u];
         }
     }
     if (lds.any_slow)                             // uniform: the rows that were selected from memory are read again
