@@ -296,11 +296,14 @@ Plan make_plan(const mv_config* c)
         p.split_blocks = (uint32_t)sb;
         // likewise in mv_ad_collect (a row's bitmap in one workgroup of more threads, where it fits), which goes by chunks of
         // coordinates where lists are long and dense and a workgroup's chunks hold not too many entries of them (steps with
-        // candidates looked up one by one : by chunks; 128 x 400,003, K = 33,333 386 : 357 us; 2 x 4 M, K = 400,000 162 : 140;
-        // 8 x 8 M, K = 80,000 234 : 227; 16 x 8 M, K = 40,000 366 : 359; sparser: 16 x 11.2 M, K = 30,000 452 : 456, 32 x 25.6 M
-        // bf16, K = 25,557 1459 : 1487; fuller: 100 x 60,003, K = 30,000 259 : 293, 4 x 60,003, K = 40,000 131 : 178)
+        // candidates looked up one by one : by chunks; 2 x 4 M, K = 400,000 (9 K entries to a workgroup) 162 : 140;
+        // 8 x 1.5 M, K = 200,000 (12 K) 195 : 174; 4 x 3 M, K = 450,000 (14 K) 220 : 192; 16 x 600,000, K = 100,000 (14 K)
+        // 172 : 162; 2 x 1.5 M, K = 300,000 (18 K) 177 : 149; 32 x 131,000, K = 50,000 (33 K) 193 : 185; sparser:
+        // 16 x 11.2 M, K = 30,000 452 : 456, 32 x 25.6 M bf16, K = 25,557 1459 : 1487; fuller, either: 40 x 65,536,
+        // K = 25,000 (33 K) 135 : 154, 2 x 2 M, K = 800,000 (34 K) 242 : 221, 100 x 60,003, K = 30,000 (39 K) 249 : 289)
         const uint64_t per_wg = 32ull * mvk::collect_words(mvk::kCollectThreads);
-        p.collect_chunks = p.multi_select && 256ull * p.K >= (uint64_t)p.d && expect <= 10000 * (((uint64_t)p.d + per_wg - 1) / per_wg);
+        p.collect_chunks = p.multi_select && 256ull * p.K >= (uint64_t)p.d &&
+                           expect <= 25000 * (((uint64_t)p.d + per_wg - 1) / per_wg);
         const bool one = !p.collect_chunks && (uint64_t)p.d <= 32ull * mvk::collect_words(mvk::kCollectThreadsShort);
         p.collect_threads = one ? mvk::kCollectThreadsShort : mvk::kCollectThreads;
         const uint64_t batch = mvk::add_batch((int)p.collect_threads);

@@ -18,6 +18,9 @@ pytestmark = pytest.mark.gpu
     (3, 1_000_003, 40_000, 8, "slow", True),      # equal magnitudes overflow the list: selected from memory
     (2, 300_001, 25_000, 512, "crowded", True),   # more removals in a workgroup's chunks than are staged at once
     (3, 400_003, 40_000, 4, "turned", True),      # nearly all of the standing votes leave
+    (2, 262_145, 70_000, 1020, "normal", True),   # full lists
+    (3, 400_003, 80_000, 4, "crowded", True),
+    (2, 786_432, 200_000, 0, "turned", True),
     (2, 131_073, 20_000, 4, "normal", False),     # lists that one workgroup selects
     (2, 98_304, 40_000, 512, "normal", False),    # too full for chunks
 ])
