@@ -237,13 +237,13 @@ struct ChunksLds {
     uint32_t bcast[1];
 };
 
-// Both lists of a row whose list is long, in one pass over its candidates and its standing vote's bitmap.  A workgroup owns chunks of 4096
-// coordinates, gridDim.x apart (votes crowd where gradients are large; see mv_vote_count), finds their candidates through
-// the segments' runs, marks the row's top K in a bitmap in LDS and has the standing vote's beside it: an
-// addition is a marked candidate without a standing vote, a removal a standing vote without a mark, and only the removals'
-// magnitudes have to be fetched from e (looked up candidate by candidate in memory, and all of the standing vote fetched,
-// this took 31.5 us instead of 22.8 at 10 x 11.2 M, K = 111,740).  Removals go to the list with the complemented magnitude,
-// so that "largest first" selects the smallest magnitudes.
+// Both lists of a row whose list is long, in one pass over its candidates and its standing vote's bitmap.  A workgroup
+// owns chunks of 4096 coordinates, gridDim.x apart (votes crowd where gradients are large; see mv_vote_count), finds
+// their candidates through the segments' runs, marks the row's top K in a bitmap in LDS and has the standing vote's
+// beside it: an addition is a marked candidate without a standing vote, a removal a standing vote without a mark, and
+// only the removals' magnitudes have to be fetched from e (looked up candidate by candidate in memory, and all of the
+// standing vote fetched, this took 31.5 us instead of 22.8 at 10 x 11.2 M, K = 111,740).  Removals go to the list with
+// the complemented magnitude, so that "largest first" selects the smallest magnitudes.
 // Rows selected from memory (slow_flag == 1) have no list: their chunks are read instead.
 __global__ __launch_bounds__(kCollectThreads) void mv_ad_collect_chunks(
     const float* __restrict__ e, int64_t ld_e, int64_t d, const u32x2* __restrict__ cand, uint32_t cap,
@@ -265,13 +265,16 @@ __global__ __launch_bounds__(kCollectThreads) void mv_ad_collect_chunks(
     const uint32_t own = t * 4, m_own = own / kChunkWords;
     const uint64_t w0 = (uint64_t)chunk_of(m_own) * kChunkWords + own % kChunkWords;
     u32x4 w = {0u, 0u, 0u, 0u};
-    if (w0 < nwords) w = *reinterpret_cast<const u32x4*>(vote_bits + (int64_t)row * ld_bits + w0);   // padded to a multiple of 4 words
+    if (w0 < nwords)                              // (padded to a multiple of 4 words)
+        w = *reinterpret_cast<const u32x4*>(vote_bits + (int64_t)row * ld_bits + w0);
     u32x2 run = {0u, 0u};
     if (t < (uint32_t)Lds::kRuns) {
-        const uint32_t m = t / (kChunkSegs + 1), slot = t % (kChunkSegs + 1), shift = segs.shift(row), n_segs = segs.count(row);
+        const uint32_t m = t / (kChunkSegs + 1), slot = t % (kChunkSegs + 1);
+        const uint32_t shift = segs.shift(row), n_segs = segs.count(row);
         const uint64_t s = (uint64_t)chunk_of(m) * kChunkSegs + slot;
         // (a chunk's last segment is shared with the next one where the row is shifted)
-        if (s < n_segs && (uint64_t)chunk_of(m) * kCollectChunk < (uint64_t)d && (slot < (uint32_t)kChunkSegs || shift != 0u) && !slow)
+        if (s < n_segs && (uint64_t)chunk_of(m) * kCollectChunk < (uint64_t)d &&
+            (slot < (uint32_t)kChunkSegs || shift != 0u) && !slow)
             run = runs[(size_t)row * n_runs + s];           // (in order: see order_runs)
     }
     if (w0 < nwords && w0 * 32 + 128 > (uint64_t)d) {                // bits at or beyond d do not exist
@@ -334,8 +337,8 @@ __global__ __launch_bounds__(kCollectThreads) void mv_ad_collect_chunks(
             }
     }
     __syncthreads();
-    // the removals: their coordinates are parked in LDS (kRemovalStage at a time; one round unless the chunks are crowded
-    // with them) and their values then fetched by all lanes together, instead of one dependent load per set
+    // the removals: their coordinates are parked in LDS (kRemovalStage at a time; one round unless the chunks are
+    // crowded with them) and their values then fetched by all lanes together, instead of one dependent load per set
     // bit inside each thread's own loop
     uint32_t n_bits = 0;
     {
@@ -357,7 +360,8 @@ __global__ __launch_bounds__(kCollectThreads) void mv_ad_collect_chunks(
         for (int q = 0; q < 4; ++q)
             for (uint32_t m = w[q]; m != 0u; m &= m - 1) {
                 const uint32_t b = __ffs((int)m) - 1;
-                if (sp - c0 < (uint32_t)kRemovalStage) lds.stage[sp - c0] = (uint32_t)(w0 + q) * 32 + b;       // sp < c0 wraps: not staged
+                if (sp - c0 < (uint32_t)kRemovalStage)           // (sp < c0 wraps: not staged)
+                    lds.stage[sp - c0] = (uint32_t)(w0 + q) * 32 + b;
                 ++sp;
             }
         __syncthreads();

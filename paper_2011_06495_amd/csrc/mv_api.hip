@@ -129,13 +129,14 @@ Plan make_plan(const mv_config* c)
     };
     // list entries to be ready for when so many are expected
     auto with_room = [](double expected) { return expected * 1.25 + 1.0; };
-    // Sample about d/128 coordinates of each row, at least 32K and at most the 128K that 16 workgroups take in one round
-    // (kSampleQuads quads per thread: the first row's stream waits for every further round, and scattered lines cost the
-    // memory more than a longer list does; d/128 everywhere : so, 1 x 200 M, K = 200,000 626 : 602 us, 1 x 50 M 178.3 : 172.5,
-    // 3 x 25.6 M 206.1 : 203.3, 32 x 25.6 M bf16 1368.5 : 1366.0, 16 of them with add-drop 760.9 : 757.4; 96K at most
-    // 1363.8 and 755.2 there, but 24 x 20 M bf16, K = 6000 803.0 : 807.0) -- or, where the list does not grow too long for it, 8K by ONE workgroup in one round, whose
-    // histogram need not be merged in memory: the step of a short row waits for the estimate.  The line follows the
-    // lists, one workgroup's against several's (steps of 2, 4 and 16 rows, time with several : time with one):
+    // Sample about d/128 coordinates of each row, at least 32K and at most the 128K that 16 workgroups take in one
+    // round (kSampleQuads quads per thread: the first row's stream waits for every further round, and scattered lines
+    // cost the memory more than a longer list does; d/128 everywhere : so, 1 x 200 M, K = 200,000 626 : 602 us, 1 x 50
+    // M 178.3 : 172.5, 3 x 25.6 M 206.1 : 203.3, 32 x 25.6 M bf16 1368.5 : 1366.0, 16 of them with add-drop 760.9 :
+    // 757.4; 96K at most 1363.8 and 755.2 there, but 24 x 20 M bf16, K = 6000 803.0 : 807.0) -- or, where the list does
+    // not grow too long for it, 8K by ONE workgroup in one round, whose histogram need not be merged in memory: the
+    // step of a short row waits for the estimate.  The line follows the lists, one workgroup's against several's (steps
+    // of 2, 4 and 16 rows, time with several : time with one):
     //   up to 8192 entries, whatever the others':   2.7K for 0.9K 1.04 1.04 1.02; 6.3K for 1.6K 1.04 1.04 0.99;
     //                        beyond it, at four times theirs:   14K for 3.5K 0.92 0.90 0.93
     //   up to half as long again, as far as mv_row_select serves them: 20K for 13K 1.05 1.03 1.02; 25K for 17K 1.07 1.03
@@ -143,8 +144,8 @@ Plan make_plan(const mv_config* c)
     //                        with 40 rows and add-drop voting 0.90
     const uint64_t nchunks = (uint64_t)(p.d + mvk::kChunk - 1) / mvk::kChunk;
     const uint64_t per_round = (uint64_t)mvk::kSampleQuads * mvk::kStreamThreads;      // quads
-    // More than a round where the list would take more than a quarter of its storage otherwise (fewer than a few thousand
-    // of tens of millions: 128 sampled ones stand for 128 d / 131,072 entries).
+    // More than a round where the list would take more than a quarter of its storage otherwise (fewer than a few
+    // thousand of tens of millions: 128 sampled ones stand for 128 d / 131,072 entries).
     uint64_t cap = 16ull * p.K;
     if (cap < 65536) cap = 65536;
     if (cap > (uint64_t)p.d) cap = (uint64_t)p.d;
@@ -219,10 +220,10 @@ Plan make_plan(const mv_config* c)
     {
         // A crowded bin makes the list longer than it has to be, and the search inside it holds the row's stream up:
         // it is made where the list would be twice as long (one sampling workgroup, whose samples are at hand) or three
-        // times (several, whose samples one has to fetch: 32,768 quads of them, up to 78,000 where few of tens of millions
-        // are selected).  Lists kept : searched, after thousands of steps on the same gradients, K = d / 1000:
-        // 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9; 1 x 25 M 140.4 132.9, Student-t 148.7 132.5; 2 x 20 M bf16 171.3 152.0;
-        // 1 x 50 M 208.1 198.8; 1 x 200 M 586.0 558.7; 1 x 100 M, K = 2000 327.5 328.9.
+        // times (several, whose samples one has to fetch: 32,768 quads of them, up to 78,000 where few of tens of
+        // millions are selected).  Lists kept : searched, after thousands of steps on the same gradients, K = d / 1000:
+        // 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9; 1 x 25 M 140.4 132.9, Student-t 148.7 132.5; 2 x 20 M bf16 171.3
+        // 152.0; 1 x 50 M 208.1 198.8; 1 x 200 M 586.0 558.7; 1 x 100 M, K = 2000 327.5 328.9.
         const double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
         p.crowded = (p.sample_wgs > 1 && !p.keep_samples) || most >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)most;
     }
@@ -262,10 +263,10 @@ Plan make_plan(const mv_config* c)
         p.multi_select = slots > (uint64_t)mvk::kKeepMost;
         p.block_shift = 10;                       // a segment at least
         while (((p.d - 1 + mvk::kMostShift) >> p.block_shift) >= mvk::kCoordBlocks) ++p.block_shift;
-        // mv_vote_count: chunks of 4096 coordinates (a chunk shares a segment with the next one: of 2048, 10 x 11.2 M, K =
-        // 111,740 takes 17.0 us for 14.7 and 32 x 25.6 M 24.5 for 20.2), shorter ones where those are fewer than the chip's
-        // units; as many to a workgroup as leave four workgroups to a unit (three there 14.7 us, two 16.0, one 20.2; at
-        // 32 x 25.6 M six 20.2, four 21.8, two 24.5), and as LDS and the runs have room for
+        // mv_vote_count: chunks of 4096 coordinates (a chunk shares a segment with the next one: of 2048, 10 x 11.2 M,
+        // K = 111,740 takes 17.0 us for 14.7 and 32 x 25.6 M 24.5 for 20.2), shorter ones where those are fewer than
+        // the chip's units; as many to a workgroup as leave four workgroups to a unit (three there 14.7 us, two 16.0,
+        // one 20.2; at 32 x 25.6 M six 20.2, four 21.8, two 24.5), and as LDS and the runs have room for
         static_assert(204 * 5 <= mvk::kVotesRunsMost && 255 * 3 <= mvk::kVotesRunsMost, "the runs of a chunk of 4096, of 2048");
         p.chunk_shift = p.d >= (1 << 20) && p.N <= 204 ? 12 : p.d >= (1 << 19) ? 11 : 10;
         p.n_chunks = (uint32_t)((p.d - 1) >> p.chunk_shift) + 1;
@@ -277,12 +278,14 @@ Plan make_plan(const mv_config* c)
         {
             // Counted so, the votes cost a launch more and no atomics: worth it from half a million votes on, where the
             // list entries of a workgroup's chunks, those it shares among them, are not too many.  Steps with the votes
-            // cast from the lists : counted in chunks, with the entries where they are many: 16 x 6 M, K = 40,000 258.2 : 250.8 us;
-            // 24 x 3 M, K = 30,000 210.4 : 205.9; 4 x 10 M on a lattice, K = 300,000 177.9 : 170.3; random selection 10 x 11.2 M,
-            // K = 111,740 345.6 : 335.5; fewer votes: random selection 12 x 2 M, K = 33,333 114.7 : 117.0, 2 x 10 M, K = 150,000
-            // 117.3 : 119.8; more entries: 40 x 1 M, K = 25,000 (4 K) 140.4 : 142.0, 16 x 300,001, K = 30,000 56.9 : 62.0,
-            // 128 x 400,003, K = 33,333 (28 K) 277.8 : 300, 100 x 60,003, K = 30,000 128 : 263; but 2 x 2 M, K = 10^6 (5 K)
-            // 110 : 103.
+            // cast from the lists : counted in chunks: 16 x 6 M, K = 40,000 258.2 : 250.8 us; 24 x 3 M, K = 30,000
+            // 210.4 : 205.9; 4 x 10 M on a lattice, K = 300,000 177.9 : 170.3; random selection 10 x 11.2 M, K =
+            // 111,740 345.6 : 335.5; 20 x 2 M, K = 40,000 from a zero buffer (2.7 K entries) 153 : 150; fewer votes:
+            // random selection 12 x 2 M, K = 33,333 114.7 : 117.0, 2 x 10 M, K = 150,000 117.3 : 119.8.  With more
+            // entries either may be faster, with carried errors and from a zero buffer: 40 x 1 M, K = 25,000 (3.9 K)
+            // 157 : 152 and 147 : 155; 64 x 2 M, K = 22,000 (5.2 K) 376 : 362 and 354 : 370; 2 x 2 M, K = 10^6 (5.4 K)
+            // 110 : 101 and 121 : 111; 20 x 300,001, K = 30,000 (4.6 K) 61.1 : 64.9; 50 x 400,003, K = 40,000 (12 K)
+            // 136 : 138; 8 x 600,000, K = 300,000 (13 K) 117 : 108; 100 x 200,000, K = 30,000 (34 K) 163 : 183.
             const double wgs = (double)((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg);
             const double entries = (double)p.N * (double)p.m_target / frac * (double)of_chunk / (double)(of_chunk - 1) / wgs;
             p.vote_chunks = p.multi_select && (uint64_t)p.N * p.K >= 500000 && entries <= 3000.0;
@@ -293,13 +296,14 @@ Plan make_plan(const mv_config* c)
         if (eb2 * p.N > 512) eb2 = 512 / p.N;      // (10 x 11.2 M, K = 111,740: 346.7 us, with 256 349.6)
         if (eb2 < 1) eb2 = 1;
         p.split_blocks = (uint32_t)sb;
-        // likewise in mv_ad_collect (a row's bitmap in one workgroup of more threads, where it fits), which goes by chunks of
-        // coordinates where lists are long and dense and a workgroup's chunks hold not too many entries of them (steps with
-        // candidates looked up one by one : by chunks; 2 x 4 M, K = 400,000 (9 K entries to a workgroup) 162 : 140;
-        // 8 x 1.5 M, K = 200,000 (12 K) 195 : 174; 4 x 3 M, K = 450,000 (14 K) 220 : 192; 16 x 600,000, K = 100,000 (14 K)
-        // 172 : 162; 2 x 1.5 M, K = 300,000 (18 K) 177 : 149; 32 x 131,000, K = 50,000 (33 K) 193 : 185; sparser:
-        // 16 x 11.2 M, K = 30,000 452 : 456, 32 x 25.6 M bf16, K = 25,557 1459 : 1487; fuller, either: 40 x 65,536,
-        // K = 25,000 (33 K) 135 : 154, 2 x 2 M, K = 800,000 (34 K) 242 : 221, 100 x 60,003, K = 30,000 (39 K) 249 : 289)
+        // likewise in mv_ad_collect (a row's bitmap in one workgroup of more threads, where it fits), which goes by
+        // chunks of coordinates where lists are long and dense and a workgroup's chunks hold not too many entries of
+        // them (steps with candidates looked up one by one : by chunks; 2 x 4 M, K = 400,000 (9 K entries to a
+        // workgroup) 162 : 140; 8 x 1.5 M, K = 200,000 (12 K) 195 : 174; 4 x 3 M, K = 450,000 (14 K) 220 : 192; 16 x
+        // 600,000, K = 100,000 (14 K) 172 : 162; 2 x 1.5 M, K = 300,000 (18 K) 177 : 149; 32 x 131,000, K = 50,000 (33
+        // K) 193 : 185; sparser: 16 x 11.2 M, K = 30,000 452 : 456, 32 x 25.6 M bf16, K = 25,557 1459 : 1487; fuller,
+        // either: 40 x 65,536, K = 25,000 (33 K) 135 : 154, 2 x 2 M, K = 800,000 (34 K) 242 : 221, 100 x 60,003, K =
+        // 30,000 (39 K) 249 : 289)
         const uint64_t per_wg = 32ull * mvk::collect_words(mvk::kCollectThreads);
         p.collect_chunks = p.multi_select && 256ull * p.K >= (uint64_t)p.d &&
                            expect <= 25000 * (((uint64_t)p.d + per_wg - 1) / per_wg);
@@ -676,21 +680,23 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
     const bool in_order = add_drop ? p.collect_chunks : p.vote_chunks;
     if (p.multi_select) {
         before(KID_SEL_HIST);
-        hipLaunchKernelGGL(mvk::mv_sel_hist, dim3(p.split_blocks, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K, rowcnt_sets,
-                           rowcnt_set_words, stepno, taupub, poison, hist, rowcnt, tau, slow);
+        hipLaunchKernelGGL(mvk::mv_sel_hist, dim3(p.split_blocks, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
+                           rowcnt_sets, rowcnt_set_words, stepno, taupub, poison, hist, rowcnt, tau, slow);
         after(KID_SEL_HIST);
         before(KID_SEL_SPLIT);
         const bool cast_here = !add_drop && !p.vote_chunks;
         const uint32_t order_blocks = in_order ? (p.n_runs + mvk::kOrderRuns - 1) / mvk::kOrderRuns : 0;
-        hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_split<true> : &mvk::mv_sel_split<false>), dim3(p.split_blocks + order_blocks, p.N), dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d, cand, p.cap, p.K,
-                           (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
+        hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_split<true> : &mvk::mv_sel_split<false>),
+                           dim3(p.split_blocks + order_blocks, p.N), dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d,
+                           cand, p.cap, p.K, (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
                            kth, tiecut, a.worker_idx, votes32, tallies, runs, p.n_runs, segs, lvlsets, taupub,
                            p.block_shift, p.split_blocks);
         after(KID_SEL_SPLIT);
         uint32_t parts = cast_here ? 256 / p.N : 1;
         parts = parts > 16 ? 16 : parts < 1 ? 1 : parts;
         before(KID_SEL_FINISH);
-        hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_finish<true> : &mvk::mv_sel_finish<false>), dim3(parts, p.N), dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
+        hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_finish<true> : &mvk::mv_sel_finish<false>), dim3(parts, p.N),
+                           dim3(mvk::kRowThreads), 0, st, cand, p.cap, p.K,
                            (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist, kth, tiecut,
                            votes32, tallies, p.n_runs, segs, lvlsets, taupub, (const mvk::u32x2*)runs, in_order ? 1 : 0,
                            p.block_shift);
@@ -760,8 +766,8 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         mask_votes32 = msum32;
     }
     // the sorted vote lists, written by extra workgroups of one of the kernels from here on
-    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, in_order ? 1 : 0, run_taken, p.n_runs, segs, kth, tiecut,
-                                     slow, a.worker_idx};
+    const mvk::RowLists row_lists = {p.emit_blocks, cand, p.cap, rowcnt, runs, in_order ? 1 : 0, run_taken, p.n_runs, segs,
+                                     kth, tiecut, slow, a.worker_idx};
     const uint32_t n_list = sorted && !add_drop ? p.N * p.emit_blocks : 0;
     uint32_t* rsbits = ws_ptr<uint32_t>(c, p.off_rsbits);
     if (random_sel) {
@@ -823,7 +829,7 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         hipLaunchKernelGGL((random_sel ? &mvk::mv_mask_count<Q, true> : &mvk::mv_mask_count<Q, false>), grid_c,   \
                            block, 0, st, mask_votes32, p.d, p.N, p.K, lvlsets,                                   \
                            subcnt, blockcnt, votethr, votes_out, p.n_vote_blocks, row_lists,                     \
-                           add_drop || p.vote_chunks ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,                      \
+                           add_drop || p.vote_chunks ? 1 : 0, lookback, emitfail, c->spin_limit, a.mask_idx,     \
                            reinterpret_cast<uint16_t*>(rsbits), (const uint32_t*)rsblk);             \
         after(KID_MASK_COUNT);                                                                                   \
         before(KID_GATHER);                                                                                      \

@@ -18,11 +18,11 @@ constexpr int kLookBack = 256;       // earlier blocks whose totals a block of m
 // 5. global mask = the K most voted coordinates, ties to the lowest coordinate
 // ----------------------------------------------------------------------------
 // Counting sort over the vote levels 0..N in two kernels.  The level counters (summed
-// over their sets) say how many coordinates hold at least v votes (plain voting: filled
-// while the votes were cast) or exactly v votes (add-drop voting: a histogram of the
-// vote sum).  The threshold v* is the level at which K coordinates are covered walking
-// down from N: all coordinates above v* are taken, and the first K - (#above)
-// coordinates, in coordinate order, with exactly v* votes.  A block is the 16384 Q
+// over their sets) say how many coordinates hold at least v votes (where the votes were
+// cast from the lists) or exactly v votes (where mv_vote_count counted them, and in
+// add-drop voting: a histogram of the vote sum).  The threshold v* is the level at which
+// K coordinates are covered walking down from N: all coordinates above v* are taken, and
+// the first K - (#above) coordinates, in coordinate order, with exactly v* votes.  A block is the 16384 Q
 // coordinates of one workgroup (Q = 1 to 8 quads of 16 vote bytes per thread, chosen
 // so that the grid stays at a few hundred workgroups).  mv_mask_count counts, per
 // wavefront's stretch of the vote bytes, the coordinates above and at v*;
@@ -91,12 +91,12 @@ __device__ __forceinline__ uint32_t bytes_at_least(uint32_t x, uint32_t t)
 // 32 x 25.6 M).
 constexpr int kQuadStep = 16 * kWave;
 // The thread's coordinates with more than / exactly vstar votes, its first quad lying at coordinate j0: bit b of
-// marks[q] is set if coordinate j0 + kQuadStep q + b has more, bit 16 + b if it has exactly vstar.  Four bytes at a time
-// (byte by byte, and once more for the emission, the mask kernel took 18.5 us instead of 14.9 at 10 x 11.2 M,
+// marks[q] is set if coordinate j0 + kQuadStep q + b has more, bit 16 + b if it has exactly vstar.  Four bytes at a
+// time (byte by byte, and once more for the emission, the mask kernel took 18.5 us instead of 14.9 at 10 x 11.2 M,
 // K = 111,740, and 37 instead of 32 at 32 x 25.6 M).  Must be called by all lanes of a wavefront together: a quad that
 // holds no vote in any lane is passed over by the whole wavefront (most quads, where votes are sparse); with
-// vstar == 0 the coordinates without a vote count too and nothing is passed over.  A thread's only quad is not worth the
-// question (7 x 272,475 bf16, steps 30.76 us : 30.65).
+// vstar == 0 the coordinates without a vote count too and nothing is passed over.  A thread's only quad is not worth
+// the question (7 x 272,475 bf16, steps 30.76 us : 30.65).
 // before[q]: those of the stretch that lie before quad q of this lane, above | at << 16; returns the stretch's.
 template <int Q>
 __device__ __forceinline__ uint32_t count_above_and_at(const u32x4 (&w)[Q], int64_t j0, int64_t d, uint32_t vstar,
@@ -171,8 +171,8 @@ struct EmitLds {
 // candidates in the segments before its own, from the tallies) + (before it in its own run; runs are ascending).
 // A few workgroups per row (`part` of `parts`); each adds up the row's tallies for itself, eight segments to a
 // prefix (1365 for 11.2 M coordinates), which arrive beside the entries, and an entry looks at its own eight segments'
-// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).  n_dealt: the segments whose
-// runs lie as the streaming pass noted them (run_place), none once they are in order.
+// tallies again (32 x 25.6 M: mask kernel 36.6 us, 73 with a prefix for every two segments).  n_dealt: the segments
+// whose runs lie as the streaming pass noted them (run_place), none once they are in order.
 __device__ __forceinline__ void write_row_list(const u32x2* __restrict__ crow, uint32_t C,
                                                const u32x2* __restrict__ runs, const u32x4* __restrict__ units,
                                                uint32_t n_segs, uint32_t n_dealt, uint32_t shift, uint32_t K, uint32_t kth, uint32_t tie_cut,
@@ -381,8 +381,9 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
     uint32_t vstar = 0, take_eq = 0;
     if constexpr (!RANDOM) vote_threshold(lvl_sets, N, K, lvl, thr, scan_lds, vstar, take_eq, exact_levels);
     if (votes_out) {
-        // (past the caches: nothing of this step reads the copy.  Mask and gather 27.9 + 38.8 us -> 27.7 + 36.1 at 32 x 25.6 M,
-        // 20.3 + 36.3 -> 19.7 + 34.5 at 10 x 11.2 M, K = 111,740; random selection's mask kernel 8.3 -> 7.4 at 16 x 11.2 M)
+        // (past the caches: nothing of this step reads the copy.  Mask and gather 27.9 + 38.8 us -> 27.7 + 36.1 at 32 x
+        // 25.6 M, 20.3 + 36.3 -> 19.7 + 34.5 at 10 x 11.2 M, K = 111,740; random selection's mask kernel 8.3 -> 7.4 at
+        // 16 x 11.2 M)
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int64_t j = j0 + q * kQuadStep;
@@ -476,8 +477,8 @@ __global__ __launch_bounds__(kMaskThreads) void mv_mask_count(const uint32_t* __
         }
     }
     __syncthreads();
-    // the counts per stretch and per block: what mv_gather_update scans when the mask could not be written here (behind the
-    // exchange: the other blocks wait for what this one publishes, and nobody in this kernel for these)
+    // the counts per stretch and per block: what mv_gather_update scans when the mask could not be written here (behind
+    // the exchange: the other blocks wait for what this one publishes, and nobody in this kernel for these)
     if (lane == 0) sub_cnt[(size_t)blockIdx.x * (kMaskThreads / kWave) + wave] = u32x2{stretch & 0xFFFFu, stretch >> 16};
     if (threadIdx.x == 0) block_cnt[blockIdx.x] = u32x2{(uint32_t)(block_total >> 32), (uint32_t)block_total};
     if (mask_found == 0u) return;                   // whole workgroup

@@ -954,8 +954,8 @@ __global__ __launch_bounds__(kRowThreads) void mv_row_select(
 // of the keys over the list (see list_bin), (2) every workgroup locates the bin of the
 // want-th largest, acts on its entries of higher bins, and moves that bin's members
 // to a second list, (3) these are ranked exactly and those that are taken are acted on.
-// The rows' top K when K is large (to act = cast the vote, or leave it to mv_vote_count), the add and drop candidates of
-// add-drop voting, and the random selection all come this way.
+// The rows' top K when K is large (to act = cast the vote, or leave it to mv_vote_count), the add and drop candidates
+// of add-drop voting, and the random selection all come this way.
 //
 // (3) for the rows' top K is a launch of its own: several workgroups rank the same members, each
 // acts on its share.  It costs an ordinary row nothing (10 x 11.2 M, K = 111,740: 332 us with it and
@@ -1643,9 +1643,9 @@ __device__ __forceinline__ uint32_t* row_rest(unsigned long long* tau_pub, uint3
     return reinterpret_cast<uint32_t*>(tau_pub + row * (kCounterStride / 2) + 1);
 }
 
-// The streaming pass leaves a row's runs as its workgroups noted them; the kernels behind mv_sel_split read them in the order
-// of the segments, a few neighbouring ones at a time, where they go by chunks of coordinates.  Workgroup `part` of a row's puts some groups of 64 in order: a wavefront
-// has a whole one in its registers, so it stays in place.
+// The streaming pass leaves a row's runs as its workgroups noted them; the kernels behind mv_sel_split read them in the
+// order of the segments, a few neighbouring ones at a time, where they go by chunks of coordinates.  Workgroup `part`
+// of a row's puts some groups of 64 in order: a wavefront has a whole one in its registers, so it stays in place.
 constexpr int kOrderGroups = 4;                   // groups per wavefront
 constexpr uint32_t kOrderRuns = kRowThreads * kOrderGroups;
 __device__ __forceinline__ void order_runs(u32x2* __restrict__ row_runs, uint32_t n, uint32_t part)
@@ -1667,7 +1667,8 @@ __device__ __forceinline__ void order_runs(u32x2* __restrict__ row_runs, uint32_
 }
 static_assert(kGroupSegs == kWave, "a lane per segment of a group");
 
-// The members of the K-th's bin are left to mv_sel_finish.  Workgroups (split_blocks + part, row) put the row's runs in order.
+// The members of the K-th's bin are left to mv_sel_finish.  Workgroups (split_blocks + part, row) put the row's runs in
+// order.
 template <bool CAST>
 __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     const float* __restrict__ e, int64_t ld_e, int64_t d, u32x2* cand, uint32_t cap, uint32_t K,

@@ -72,7 +72,7 @@ constexpr int      kSubShift = kHistShift - 9;
 static_assert(kSubBins == 512, "9 bits behind the bin's");
 constexpr int      kSampleQuads = 4;              // quads of samples a sampling thread has in flight
 constexpr uint32_t kSampleWgs = 16;               // at most so many workgroups sample a row
-constexpr int      kAgainQuads = 8;               // and one that goes through them once more (1.6 M samples: four 761 us a step, eight 738)
+constexpr int      kAgainQuads = 8;               // ... that goes through them once more (1.6 M: four 761 us, eight 738)
 constexpr uint32_t kRowPoison = 0x80000000u;      // set in a marked row's candidate counter by mv_row_select
 
 struct StreamLds {
@@ -155,7 +155,7 @@ __device__ __forceinline__ void sample_and_pick(StreamLds& lds, const GT* __rest
     __syncthreads();
     const GT*    grow = g + (int64_t)row * ld_g;
     const float* erow = e + (int64_t)row * ld_e;
-    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most 32,768, or one coordinate in 512
+    const uint32_t nquads = n_sampled_chunks * (kChunk / 4);       // at most 32,768, or about one coordinate in 512
     uint32_t* samples = all_samples ? all_samples + (size_t)row * nquads * 4 : nullptr;
     const uint32_t step = spr * kStreamThreads;
     auto start_of = [stride](uint32_t q) {

@@ -1,5 +1,5 @@
-// The votes of long lists (the rows' select went through mv_sel_hist, mv_sel_split and mv_sel_finish): counted in LDS by
-// the workgroup that owns a coordinate, without an atomic in memory.
+// The votes of long lists (the rows' select went through mv_sel_hist, mv_sel_split and mv_sel_finish): counted in LDS
+// by the workgroup that owns a coordinate, without an atomic in memory.
 #pragma once
 
 #include "mv_common.hpp"
@@ -9,29 +9,30 @@ namespace mvk {
 
 // A workgroup owns `per_wg` chunks of 2^chunk_shift coordinates, chunks gridDim.x apart: masks crowd in the few tensors
 // with the largest gradients, and chunks dealt round give every workgroup its part of them.  (Handed stretches of
-// coordinates in a row, one unit walked tens of thousands of entries while the others idled: 100 us and more.)  It finds its
-// chunks' candidates of every row through the segments' runs, adds the votes of the taken ones up in LDS, and
+// coordinates in a row, one unit walked tens of thousands of entries while the others idled: 100 us and more.)  It
+// finds its chunks' candidates of every row through the segments' runs, adds the votes of the taken ones up in LDS, and
 // writes the vote bytes, the number of coordinates with exactly v votes for every v, and the segments' tallies for the
-// sorted lists.  Rows are shifted against each other (RowSegments), so a chunk's last segment is usually shared with the
-// next chunk: its entries are read by both, its tally is the next one's.
+// sorted lists.  Rows are shifted against each other (RowSegments), so a chunk's last segment is usually shared with
+// the next chunk: its entries are read by both, its tally is the next one's.
 //
-// Entries are dealt to threads by their number among all of the workgroup's, so that no thread has more than one more than
-// another.  Which run an entry belongs to: the runs that are not empty are numbered, and a bit
+// Entries are dealt to threads by their number among all of the workgroup's, so that no thread has more than one more
+// than another.  Which run an entry belongs to: the runs that are not empty are numbered, and a bit
 // marks each entry that begins one, so the number is a count of bits, most of it a scalar's (found by bisection in the
 // runs' summed lengths, with its place taken apart by divisions: 20.5 us instead of 15.2 at 10 x 11.2 M, K = 111,740).
-// A batch of 4096 entries takes 3 us so, 2.3 of them finding the runs, and where the largest tensors' errors are zero the
-// fullest workgroup has five.  So the runs of at least kLongRun entries go to a wavefront each, which has nothing to find:
-// that workgroup is through with its entries in 7 us for 17.  10 x 11.2 M, K = 111,740, from a zero buffer 20.7 us for 25.7
-// (all of these between events around the kernel; runs from 64 entries on 20.6, but 15.8 for 13.4 at 16 x 6 M,
-// K = 40,000; from 32 on 24.4), with carried errors 15.9 for 17.2.  The crowded chunks' pieces dealt over the grid, with the
-// chunks' entries counted beside order_runs: 23.5 and 19.5.
+// A batch of 4096 entries takes 3 us so, 2.3 of them finding the runs, and where the largest tensors' errors are zero
+// the fullest workgroup has five.  So the runs of at least kLongRun entries go to a wavefront each, which has nothing
+// to find: that workgroup is through with its entries in 7 us for 17.  10 x 11.2 M, K = 111,740, from a zero buffer
+// 20.7 us for 25.7 (all of these between events around the kernel; runs from 64 entries on 20.6, but 15.8 for 13.4 at
+// 16 x 6 M, K = 40,000; from 32 on 24.4), with carried errors 15.9 for 17.2.  The crowded chunks' pieces dealt over the
+// grid, with the chunks' entries counted beside order_runs: 23.5 and 19.5.
 //
 // Of the kernel's time with carried errors 4.6 are the launch, 1.8 the runs, 6 the entries and 1.5 the bytes and their
-// levels; at 32 x 25.6 M, 20.2 us by the trace, the runs are 7.  With workgroups of 1024 threads 26 there: four short ones to
-// a unit fill each other's waits.
+// levels; at 32 x 25.6 M, 20.2 us by the trace, the runs are 7.  With workgroups of 1024 threads 26 there: four short
+// ones to a unit fill each other's waits.
 // With the votes as returning atomics in memory, cast by mv_sel_split and mv_sel_finish, these two took 37.5 and 45 us;
 // with this kernel behind them the three take 28 and 39, and the vote bytes need not be cleared beforehand: steps
-// 337.7 -> 321.2 us and 1413.7 -> 1406.4.  From a zero buffer, whose votes lie close together and share atomics, 306.8 -> 308.7.
+// 337.7 -> 321.2 us and 1413.7 -> 1406.4.  From a zero buffer, whose votes lie close together and share atomics, 306.8
+// -> 308.7.
 constexpr int kVotesThreads = 512;
 constexpr int kVotesWaves = kVotesThreads / kWave;
 constexpr int kVotesRunsMost = 1024;              // runs of a workgroup: two to a thread
@@ -189,7 +190,8 @@ __global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
             const uint32_t j = c[u].y - (chunk_of(m) << chunk_shift);
             if (taken && j < chunk) atomicAdd(&lds.votes[((m << chunk_shift) + j) >> 2], 1u << (j & 3u) * 8u);
             if (run_taken) {
-                // a run's taken ones among the wavefront's entries: those up to its last lane less those below its first
+                // a run's taken ones among the wavefront's entries: those up to its last lane less those below its
+                // first
                 const uint64_t all = __ballot(taken);
                 const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, 0u));
                 const uint64_t begin = begins[u] | 1ull, end = begins[u] >> 1 | 1ull << 63;
