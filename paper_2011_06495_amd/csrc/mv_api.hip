@@ -220,11 +220,15 @@ Plan make_plan(const mv_config* c)
     {
         // A crowded bin makes the list longer than it has to be, and the search inside it holds the row's stream up:
         // it is made where the list would be twice as long (one sampling workgroup, whose samples are at hand) or three
-        // times (several, whose samples one has to fetch: 32,768 quads of them, up to 78,000 where few of tens of
-        // millions are selected).  Lists kept : searched, after thousands of steps on the same gradients, K = d / 1000:
-        // 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9; 1 x 25 M 140.4 132.9, Student-t 148.7 132.5; 2 x 20 M bf16 171.3
-        // 152.0; 1 x 50 M 208.1 198.8; 1 x 200 M 586.0 558.7; 1 x 100 M, K = 2000 327.5 328.9.
-        const double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
+        // times (several, whose samples one has to fetch: up to 32,768 quads of them; K = d / 1000, lists of 6K to 8K
+        // entries kept : searched: 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9), and in longer rows only where the list nears
+        // its storage: one workgroup searches while the row's stream waits, whose list is the shorter part of the step the
+        // longer the row is.  (Samples that grew with the row made the search the slower way there; with those of one round
+        // it gains after thousands of steps on the same gradients: 1 x 25 M 140.4 : 132.9, 2 x 20 M bf16 171.3 : 152.0,
+        // 1 x 200 M 586.0 : 558.7.)
+        const bool long_row = (uint64_t)p.d > 128ull * 4 * per_round * mvk::kSampleWgs;
+        double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
+        if (long_row && 0.875 * (double)p.cap * frac > most) most = 0.875 * (double)p.cap * frac;
         p.crowded = (p.sample_wgs > 1 && !p.keep_samples) || most >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)most;
     }
 
