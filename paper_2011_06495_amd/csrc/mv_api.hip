@@ -77,6 +77,7 @@ struct Plan {
     uint32_t block_shift;         // its blocks of coordinates: 2^block_shift, at most kCoordBlocks of them
     bool     vote_chunks;         // their votes are counted by mv_vote_count
     uint32_t chunk_shift, n_chunks, chunks_per_wg;   // of mv_vote_count
+    uint32_t crowd_least;                            // see CrowdedChunks
     // random selection
     uint32_t rs_cap;              // most coordinates that can hold a vote: min(N K, d)
     size_t   off_rscount, off_rsbits, off_rsblk, off_rslist, off_rslist2;
@@ -88,6 +89,7 @@ struct Plan {
     uint64_t through_most;      // up to so many bytes that a step touches the streaming pass stores past the caches
     uint32_t head_wgs;          // streaming workgroups behind them that wait for the sampling before they load
     size_t off_samples, off_sampledone, off_readsdone, off_taupub, off_poison, off_stepno, off_candcount;
+    size_t off_crowd, off_crowdlist;
     size_t off_hist, off_tau, off_rowcnt, off_slow, off_kth, off_tiecut, off_lvlsets, off_runs, off_runtaken,
         off_alist, off_dlist, off_adcount, off_adbits, off_adblk, off_cand, off_votes, off_blockcnt, off_subcnt, off_votethr, off_emitfail,
         off_lookback;
@@ -222,9 +224,8 @@ Plan make_plan(const mv_config* c)
         // it is made where the list would be twice as long (one sampling workgroup, whose samples are at hand) or three
         // times (several, whose samples one has to fetch: up to 32,768 quads of them; K = d / 1000, lists of 6K to 8K
         // entries kept : searched: 1 x 8 M 86.3 us 73.0; 1 x 14 M 100.8 99.9), and in longer rows only where the list nears
-        // its storage: one workgroup searches while the row's stream waits, whose list is the shorter part of the step the
-        // longer the row is.  (Samples that grew with the row made the search the slower way there; with those of one round
-        // it gains after thousands of steps on the same gradients: 1 x 25 M 140.4 : 132.9, 2 x 20 M bf16 171.3 : 152.0,
+        // its storage.  (Samples that grew with the row made the search the slower way there.  With those of one round it
+        // gains, after thousands of steps on the same gradients: 1 x 25 M 140.4 : 132.9, 2 x 20 M bf16 171.3 : 152.0,
         // 1 x 200 M 586.0 : 558.7.)
         const bool long_row = (uint64_t)p.d > 128ull * 4 * per_round * mvk::kSampleWgs;
         double most = p.sample_wgs == 1 ? 2.0 * m : 3.0 * m;
@@ -279,6 +280,7 @@ Plan make_plan(const mv_config* c)
         if (most > mvk::kVotesRunsMost / (p.N * of_chunk)) most = mvk::kVotesRunsMost / (p.N * of_chunk);
         p.chunks_per_wg = (p.n_chunks + 1023) / 1024;
         if (p.chunks_per_wg > most) p.chunks_per_wg = most;
+        p.crowd_least = mvk::kCrowdedEntries / (2 * p.N);
         {
             // Counted so, the votes cost a launch more and no atomics: worth it from half a million votes on, where the
             // list entries of a workgroup's chunks, those it shares among them, are not too many.  Steps with the votes
@@ -337,6 +339,8 @@ Plan make_plan(const mv_config* c)
     // and two 64-bit words per block): one stretch of words that every step's first kernel leaves at zero
     p.off_lvlsets = off;  off += (size_t)mvk::kLvlSets * 256 * 4;
     p.off_emitfail = off; off += 8;
+    // (and how many chunks are crowded, in two words, and their list entries)
+    p.off_crowd = off;    off += 8 + (p.vote_chunks ? ((size_t)p.n_chunks + 1) / 2 * 8 : 0);
     p.off_lookback = off; off += (size_t)p.n_vote_blocks * 16;
     // (and the counts per block of the winners of the random selection and of the additions and removals)
     p.add_drop = (c->flags & MV_FLAG_ADD_DROP) != 0;
@@ -353,6 +357,9 @@ Plan make_plan(const mv_config* c)
     p.n_zero_words = (uint32_t)((off - p.off_lvlsets) / 4);
     off = align_up(off);
     p.off_runs = off;     off += align_up((size_t)p.N * p.n_runs * 8);
+    if (p.vote_chunks) {
+        p.off_crowdlist = off; off += align_up((size_t)p.n_chunks * 4);
+    }
     p.off_runtaken = off; off += align_up((size_t)p.N * p.n_runs * 2);
     if (p.keep_samples) {                         // their magnitudes
         p.off_samples = off; off += align_up((size_t)p.N * p.n_sampled_chunks * mvk::kChunk * 4);
@@ -689,12 +696,15 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
         after(KID_SEL_HIST);
         before(KID_SEL_SPLIT);
         const bool cast_here = !add_drop && !p.vote_chunks;
+        uint32_t* n_crowded = ws_ptr<uint32_t>(c, p.off_crowd);
+        const mvk::CrowdedChunks crowd = {n_crowded, !add_drop && p.vote_chunks ? n_crowded + 2 : nullptr,
+                                          ws_ptr<uint32_t>(c, p.off_crowdlist), p.n_chunks, p.chunk_shift, p.crowd_least};
         const uint32_t order_blocks = in_order ? (p.n_runs + mvk::kOrderRuns - 1) / mvk::kOrderRuns : 0;
         hipLaunchKernelGGL((cast_here ? &mvk::mv_sel_split<true> : &mvk::mv_sel_split<false>),
                            dim3(p.split_blocks + order_blocks, p.N), dim3(mvk::kRowThreads), 0, st, a.err, a.ld_e, p.d,
                            cand, p.cap, p.K, (const uint32_t*)rowcnt, (const uint32_t*)tau, (const uint32_t*)slow, hist,
                            kth, tiecut, a.worker_idx, votes32, tallies, runs, p.n_runs, segs, lvlsets, taupub,
-                           p.block_shift, p.split_blocks);
+                           p.block_shift, p.split_blocks, crowd);
         after(KID_SEL_SPLIT);
         uint32_t parts = cast_here ? 256 / p.N : 1;
         parts = parts > 16 ? 16 : parts < 1 ? 1 : parts;
@@ -710,8 +720,8 @@ mv_status enqueue_step(mv_ctx* c, const StepArgs& a, void* stream_v)
             hipLaunchKernelGGL(mvk::mv_vote_count, dim3((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg),
                                dim3(mvk::kVotesThreads), 0, st, (const float*)a.err, a.ld_e, p.d, p.N,
                                (const mvk::u32x2*)cand, p.cap, (const mvk::u32x2*)runs, p.n_runs, segs,
-                               (const uint32_t*)kth, (const uint32_t*)tiecut, (const uint32_t*)slow, p.chunk_shift,
-                               p.n_chunks, p.chunks_per_wg, votes32, reinterpret_cast<uint16_t*>(tallies), lvlsets);
+                               (const uint32_t*)kth, (const uint32_t*)tiecut, (const uint32_t*)slow, crowd,
+                               p.chunks_per_wg, votes32, reinterpret_cast<uint16_t*>(tallies), lvlsets);
             after(KID_VOTE_COUNT);
         }
     } else {

@@ -1643,20 +1643,34 @@ __device__ __forceinline__ uint32_t* row_rest(unsigned long long* tau_pub, uint3
     return reinterpret_cast<uint32_t*>(tau_pub + row * (kCounterStride / 2) + 1);
 }
 
+// Chunks of coordinates with so many list entries that mv_vote_count deals them out in pieces.
+struct CrowdedChunks {
+    uint32_t* n;                                  // how many there are
+    uint32_t* entries;                            // of each chunk (null: they are not looked for)
+    uint32_t* list;                               // of them, in any order
+    uint32_t  n_chunks, chunk_shift;
+    uint32_t  least;                              // what a row has less of in a chunk is passed over
+};
+constexpr uint32_t kCrowdedEntries = 8192;        // a chunk is crowded from so many entries on
+
 // The streaming pass leaves a row's runs as its workgroups noted them; the kernels behind mv_sel_split read them in the
 // order of the segments, a few neighbouring ones at a time, where they go by chunks of coordinates.  Workgroup `part`
-// of a row's puts some groups of 64 in order: a wavefront has a whole one in its registers, so it stays in place.
+// of a row's puts some groups of 64 in order: a wavefront has a whole one in its registers, so it stays in place.  The
+// addition that takes a chunk's entries to kCrowdedEntries puts it on the list.
 constexpr int kOrderGroups = 4;                   // groups per wavefront
 constexpr uint32_t kOrderRuns = kRowThreads * kOrderGroups;
-__device__ __forceinline__ void order_runs(u32x2* __restrict__ row_runs, uint32_t n, uint32_t part)
+__device__ __forceinline__ void order_runs(u32x2* __restrict__ row_runs, uint32_t n, uint32_t part,
+                                           const CrowdedChunks& crowd)
 {
     const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t g0 = (part * (kRowThreads / kWave) + wave) * kOrderGroups;
     const uint32_t from = run_place(lane, kWave);                    // of the group's segment number `lane`
     u32x2 r[kOrderGroups];
 #pragma unroll
-    for (int q = 0; q < kOrderGroups; ++q)
-        if ((g0 + q + 1) * kWave <= n) r[q] = row_runs[(g0 + q) * kWave + lane];
+    for (int q = 0; q < kOrderGroups; ++q) {
+        r[q] = u32x2{0u, 0u};
+        if ((g0 + q) * kWave + lane < n) r[q] = row_runs[(g0 + q) * kWave + lane];
+    }
 #pragma unroll
     for (int q = 0; q < kOrderGroups; ++q)
         if ((g0 + q + 1) * kWave <= n) {           // uniform; less than a group at the row's end is in order
@@ -1664,6 +1678,18 @@ __device__ __forceinline__ void order_runs(u32x2* __restrict__ row_runs, uint32_
             r[q].y = __shfl(r[q].y, from, kWave);
             row_runs[(g0 + q) * kWave + lane] = r[q];
         }
+    if (!crowd.entries) return;                    // uniform
+    const uint32_t own = (1u << crowd.chunk_shift) / kSeg;           // segments to a chunk: 1, 2 or 4
+#pragma unroll
+    for (int q = 0; q < kOrderGroups; ++q) {
+        uint32_t sum = r[q].y;
+        if (own > 1) sum += __shfl_xor(sum, 1, kWave);
+        if (own > 2) sum += __shfl_xor(sum, 2, kWave);
+        const uint32_t c = ((g0 + q) * kWave + lane) / own;          // (a shifted row may have a segment behind the last)
+        if ((lane & (own - 1)) != 0u || sum < crowd.least || c >= crowd.n_chunks) continue;
+        const uint32_t before = atomicAdd(crowd.entries + c, sum);
+        if (before < kCrowdedEntries && before + sum >= kCrowdedEntries) crowd.list[atomicAdd(crowd.n, 1u)] = c;
+    }
 }
 static_assert(kGroupSegs == kWave, "a lane per segment of a group");
 
@@ -1677,12 +1703,13 @@ __global__ __launch_bounds__(kRowThreads) void mv_sel_split(
     uint32_t* __restrict__ kth_out, uint32_t* __restrict__ tie_cut_out, uint32_t* __restrict__ worker_idx,
     uint32_t* __restrict__ votes32, uint32_t* __restrict__ run_tallies, u32x2* __restrict__ runs, uint32_t n_runs,
     RowSegments segs, uint32_t* __restrict__ lvl_sets, unsigned long long* __restrict__ tau_pub,
-    uint32_t block_shift, uint32_t split_blocks)
+    uint32_t block_shift, uint32_t split_blocks, CrowdedChunks crowd)
 {
     __shared__ SplitLds<kMembers> lds;
     const uint32_t row = blockIdx.y, t = threadIdx.x;
     if (blockIdx.x >= split_blocks) {
-        order_runs(runs + (size_t)row * n_runs, segs.count(row), blockIdx.x - split_blocks);
+        if (slow_flag[row] == 1u) crowd.entries = nullptr;           // (its runs are not read)
+        order_runs(runs + (size_t)row * n_runs, segs.count(row), blockIdx.x - split_blocks, crowd);
         return;
     }
     if (slow_flag[row] == 1u) {

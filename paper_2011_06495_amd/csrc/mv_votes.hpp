@@ -23,16 +23,21 @@ namespace mvk {
 // the fullest workgroup has five.  So the runs of at least kLongRun entries go to a wavefront each, which has nothing
 // to find: that workgroup is through with its entries in 7 us for 17.  10 x 11.2 M, K = 111,740, from a zero buffer
 // 20.7 us for 25.7 (all of these between events around the kernel; runs from 64 entries on 20.6, but 15.8 for 13.4 at
-// 16 x 6 M, K = 40,000; from 32 on 24.4), with carried errors 15.9 for 17.2.  The crowded chunks' pieces dealt over the
-// grid, with the chunks' entries counted beside order_runs: 23.5 and 19.5.
+// 16 x 6 M, K = 40,000; from 32 on 24.4), with carried errors 16.3 for 17.2.
+// A chunk with kCrowdedEntries of them and more would hold the step up all the same.  order_runs lists such chunks, their
+// owner leaves them out, and behind its own chunks every workgroup takes pieces of them, a segment's length each: all votes
+// of 32 x 3 M, K = 30,000 in the same 30,000 coordinates 38 us for 77 (135 without long runs), steps 283 us for 319 (379;
+// votes cast by atomics 259); all of 10 x 11.2 M, K = 111,740 in 111,740 305 for 311 (329; 306).  From 24,576 entries on 285
+// and 309.  It costs the other steps 0.1 %, that from a zero buffer above 1.5 us.  Pieces as further units of the pass over
+// the own chunks, or to workgroups of their own: 2 us more for everyone, who have to know the list before their first load.
 //
 // Of the kernel's time with carried errors 4.6 are the launch, 1.8 the runs, 6 the entries and 1.5 the bytes and their
 // levels; at 32 x 25.6 M, 20.2 us by the trace, the runs are 7.  With workgroups of 1024 threads 26 there: four short
 // ones to a unit fill each other's waits.
 // With the votes as returning atomics in memory, cast by mv_sel_split and mv_sel_finish, these two took 37.5 and 45 us;
 // with this kernel behind them the three take 28 and 39, and the vote bytes need not be cleared beforehand: steps
-// 337.7 -> 321.2 us and 1413.7 -> 1406.4.  From a zero buffer, whose votes lie close together and share atomics, 306.8
-// -> 308.7.
+// 337.7 -> 322.5 us and 1413.7 -> 1406.4.  From a zero buffer, whose votes lie close together and share atomics,
+// 307.3 -> 311.2.
 constexpr int kVotesThreads = 512;
 constexpr int kVotesWaves = kVotesThreads / kWave;
 constexpr int kVotesRunsMost = 1024;              // runs of a workgroup: two to a thread
@@ -55,8 +60,10 @@ struct VotesLds {
     uint32_t kth[256], tie_cut[256];              // of the rows
     uint64_t scan[kVotesWaves];
     uint32_t any_slow;
+    uint8_t  left_out[kVotesBytesMost >> 10];     // the workgroup's chunks that are crowded
 };
 static_assert(4 * sizeof(VotesLds) <= 160 * 1024, "four workgroups share a compute unit");
+static_assert(2 * 255 <= kVotesThreads, "a thread for each of a piece's runs");
 static_assert((kVotesBytesMost >> 10) <= 256, "a chunk's number fits a byte");
 
 // x / divisor for x < 2048 and divisor <= 512 by m = ceil(2^20 / divisor): x m / 2^20 exceeds the quotient by less than
@@ -70,11 +77,12 @@ struct SmallDivisor {
 __global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
     const float* __restrict__ e, int64_t ld_e, int64_t d, uint32_t N, const u32x2* __restrict__ cand, uint32_t cap,
     const u32x2* __restrict__ runs, uint32_t n_runs, RowSegments segs, const uint32_t* __restrict__ kth_in,
-    const uint32_t* __restrict__ tie_cut_in, const uint32_t* __restrict__ slow_flag, uint32_t chunk_shift, uint32_t n_chunks,
+    const uint32_t* __restrict__ tie_cut_in, const uint32_t* __restrict__ slow_flag, CrowdedChunks crowd,
     uint32_t per_wg, uint32_t* __restrict__ votes32, uint16_t* __restrict__ run_taken, uint32_t* __restrict__ lvl_sets)
 {
     __shared__ VotesLds lds;
     const uint32_t t = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+    const uint32_t chunk_shift = crowd.chunk_shift, n_chunks = crowd.n_chunks, n_crowded = *crowd.n;
     const uint32_t chunk = 1u << chunk_shift, own = chunk / kSeg, slots = own + 1;      // segments of a chunk
     const uint32_t n = N * per_wg * slots;        // runs, row after row
     const SmallDivisor by_slots(slots), by_row(slots * per_wg);
@@ -97,8 +105,13 @@ __global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
             tally[q] = slot < own || chunk_of(m) == n_chunks - 1;
             run[q] = runs[(size_t)row * n_runs + s];                 // (in order: see order_runs)
             if (slow_flag[row] == 1u) run[q].y = 0;
+            if (crowd.entries[chunk_of(m)] >= kCrowdedEntries) {     // not here, but in pieces
+                run[q].y = 0;
+                tally[q] = false;
+            }
         }
     }
+    if (t < per_wg) lds.left_out[t] = chunk_of(t) < n_chunks && crowd.entries[chunk_of(t)] >= kCrowdedEntries ? 1 : 0;
     uint32_t kth = 0, tie_cut = 0;
     bool slow = false;
     if (t < N) {
@@ -201,8 +214,9 @@ __global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
         }
     }
     // The long runs, a wavefront each; the next loads are under way while these are counted.
-    const uint32_t n_long = lds.n_long;           // (behind the scan's barrier)
-    if (wave < n_long) {                          // uniform
+    auto walk_long_runs = [&](auto base_of, uint32_t length) {
+        const uint32_t n_long = lds.n_long;
+        if (wave >= n_long) return;               // uniform
         struct Run {
             const u32x2* entries;
             uint32_t n, place;
@@ -237,14 +251,14 @@ __global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
                 if (ends) next = run_at(next_k);
                 load(next, next_i0, ahead);
             }
-            const uint32_t m = l.place >> 8, base = chunk_of(m) << chunk_shift;
+            const uint32_t m = l.place >> 8, base = base_of(m);
 #pragma unroll
             for (int u = 0; u < kLongUnroll; ++u) {
-                if (i0 + (uint32_t)u * kWave >= l.n) break;
+                if (i0 + (uint32_t)u * kWave >= l.n) continue;
                 const bool taken = i0 + (uint32_t)u * kWave + lane < l.n && is_taken(c[u], l.cut.x, l.cut.y);
                 n_taken += (uint32_t)__popcll(__ballot(taken));
                 const uint32_t j = c[u].y - base;
-                if (taken && j < chunk) atomicAdd(&lds.votes[((m << chunk_shift) + j) >> 2], 1u << (j & 3u) * 8u);
+                if (taken && j < length) atomicAdd(&lds.votes[((m << chunk_shift) + j) >> 2], 1u << (j & 3u) * 8u);
             }
             if (ends) {
                 if (lane == 0) lds.taken[(uint32_t)kVotesRunsMost - 1u - k] = n_taken;
@@ -254,42 +268,79 @@ __global__ __launch_bounds__(kVotesThreads, 8) void mv_vote_count(
             k = next_k;
             i0 = next_i0;
             l = next;
-#pragma unroll
             for (int u = 0; u < kLongUnroll; ++u) c[u] = ahead[u];
         }
-    }
-    if (lds.any_slow)                             // uniform: the rows that were selected from memory are read again
+    };
+    walk_long_runs([&](uint32_t m) { return chunk_of(m) << chunk_shift; }, chunk);    // (behind the scan's barrier)
+    // the rows that were selected from memory are read again: `bytes` vote bytes, byte i's coordinate being at(i)
+    auto read_slow_rows = [&](uint32_t bytes, auto at) {
         for (uint32_t row = 0; row < N; ++row) {
             if (slow_flag[row] != 1u) continue;
-            for (uint32_t i = t; i < per_wg << chunk_shift; i += kVotesThreads) {
-                const uint64_t j = ((uint64_t)chunk_of(i >> chunk_shift) << chunk_shift) + (i & (chunk - 1));
+            for (uint32_t i = t; i < bytes; i += kVotesThreads) {
+                const uint64_t j = at(i);
                 if (j >= (uint64_t)d) continue;
                 const u32x2 c = {__float_as_uint(e[(int64_t)row * ld_e + (int64_t)j]) & kAbsMask, (uint32_t)j};
                 if (is_taken(c, lds.kth[row], lds.tie_cut[row])) atomicAdd(&lds.votes[i >> 2], 1u << (i & 3u) * 8u);
             }
         }
-    __syncthreads();
-
+    };
     // the vote bytes, 16 at a time, and their levels
-    uint32_t* lvl = lds.lvl + (lane % kLvlCopies) * 257;
-    const u32x4* v = reinterpret_cast<const u32x4*>(lds.votes);
-    for (uint32_t i = t; i < (per_wg << chunk_shift) / 16; i += kVotesThreads) {
-        const uint64_t j = ((uint64_t)chunk_of(i * 16 >> chunk_shift) << chunk_shift) + (i * 16 & (chunk - 1));
-        if (j >= (uint64_t)d) continue;
-        const u32x4 w = v[i];
-        *reinterpret_cast<u32x4*>(votes32 + (j >> 2)) = w;           // zero from d on, up to a multiple of 16
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            for (uint32_t x = w[k]; x != 0u;) {
-                const uint32_t sh = (uint32_t)(__ffs((int)x) - 1) & 24u, b = x >> sh & 255u;
-                atomicAdd(&lvl[b], 1u);
-                x &= ~(255u << sh);
-            }
-    }
+    auto write_votes = [&](uint32_t bytes, auto at, auto skip) {
+        uint32_t* lvl = lds.lvl + (lane % kLvlCopies) * 257;
+        const u32x4* v = reinterpret_cast<const u32x4*>(lds.votes);
+        for (uint32_t i = t; i < bytes / 16; i += kVotesThreads) {
+            const uint64_t j = at(i * 16);
+            if (j >= (uint64_t)d || skip(i * 16)) continue;
+            const u32x4 w = v[i];
+            *reinterpret_cast<u32x4*>(votes32 + (j >> 2)) = w;       // zero from d on, up to a multiple of 16
+            for (uint32_t x : {w.x, w.y, w.z, w.w})
+                while (x != 0u) {
+                    const uint32_t sh = (uint32_t)(__ffs((int)x) - 1) & 24u, b = x >> sh & 255u;
+                    atomicAdd(&lvl[b], 1u);
+                    x &= ~(255u << sh);
+                }
+        }
+    };
+    auto of_chunks = [&](uint32_t i) { return ((uint64_t)chunk_of(i >> chunk_shift) << chunk_shift) + (i & (chunk - 1)); };
+    if (lds.any_slow) read_slow_rows(per_wg << chunk_shift, of_chunks);      // uniform
+    __syncthreads();
+    write_votes(per_wg << chunk_shift, of_chunks, [&](uint32_t i) { return lds.left_out[i >> chunk_shift] != 0; });
     if (run_taken)
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             if (tally[q]) run_taken[(size_t)row_of[q] * n_runs + seg[q]] = (uint16_t)(run[q].y != 0u ? lds.taken[number[q]] : 0u);
+    // The crowded chunks' pieces, a segment's length each, are dealt round the grid; a thread has one of a piece's two
+    // segments of a row, and all that are not empty are walked as long runs are.
+    for (uint32_t p = blockIdx.x; p < n_crowded * own; p += gridDim.x) {     // uniform
+        const uint32_t base = (crowd.list[p / own] << chunk_shift) + p % own * kSeg, row = t / 2, s = base / kSeg + t % 2;
+        if (base >= (uint64_t)d) continue;
+        u32x2 r = {0u, 0u};
+        bool written_here = false;
+        if (row < N && s < segs.count(row) && (t % 2 == 0 || segs.shift(row) != 0u)) {
+            written_here = t % 2 == 0 || (uint64_t)base + kSeg >= (uint64_t)d;
+            r = runs[(size_t)row * n_runs + s];
+            if (slow_flag[row] == 1u) r.y = 0;
+        }
+        __syncthreads();                          // LDS is free again
+        if (t == 0) lds.n_long = 0;
+        if (t < kSeg / 16) reinterpret_cast<u32x4*>(lds.votes)[t] = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+        uint32_t at = 0;
+        if (r.y != 0u) {
+            at = (uint32_t)kVotesRunsMost - 1u - atomicAdd(&lds.n_long, 1u);
+            lds.from[at] = r.x;
+            lds.place[at] = (uint16_t)row;
+            lds.taken[at] = r.y;
+        }
+        __syncthreads();
+        walk_long_runs([&](uint32_t) { return base; }, (uint32_t)kSeg);
+        auto of_piece = [&](uint32_t i) { return (uint64_t)base + i; };
+        if (lds.any_slow) read_slow_rows(kSeg, of_piece);
+        __syncthreads();
+        write_votes(kSeg, of_piece, [](uint32_t) { return false; });
+        if (run_taken && written_here)
+            run_taken[(size_t)row * n_runs + s] = (uint16_t)(r.y != 0u ? lds.taken[at] : 0u);
+    }
     __syncthreads();
     for (uint32_t b = t + 1; b < 256u; b += kVotesThreads) {
         uint32_t k = 0;

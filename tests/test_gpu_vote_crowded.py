@@ -1,5 +1,5 @@
 """The votes of crowded chunks: long runs of list entries are walked by a wavefront each, short ones dealt to the threads entry by
-entry.  Runs around the length from which they are long and around a wavefront's loads, whole segments, chunks of each length,
+entry, and the pieces of very crowded chunks dealt round the grid.  Runs around the length from which they are long and around a wavefront's loads, whole segments, chunks of each length,
 rows that begin anywhere, crowded coordinates at the vector's end and elsewhere in the next step, and rows from memory beside."""
 import numpy as np
 import pytest
@@ -23,6 +23,11 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("lists", [True, False], ids=["lists", "no_lists"])
 def test_crowded_chunks(oracle, N, d, K, offset, hot, gain, slow, lists):
     crowded_steps(oracle, N, d, K, offset, hot, gain, slow, lists, 2)
+
+
+def test_more_pieces_than_workgroups(oracle):
+    """257 very crowded chunks of 4096 for 1023 workgroups."""
+    crowded_steps(oracle, 64, 4_190_001, 21_000, 4, 1_050_000, 100, False, True, 1)
 
 
 def test_more_rows_than_are_counted_in_chunks_of_4096(oracle):
