@@ -292,6 +292,13 @@ Plan make_plan(const mv_config* c)
             // 157 : 152 and 147 : 155; 64 x 2 M, K = 22,000 (5.2 K) 376 : 362 and 354 : 370; 2 x 2 M, K = 10^6 (5.4 K)
             // 110 : 101 and 121 : 111; 20 x 300,001, K = 30,000 (4.6 K) 61.1 : 64.9; 50 x 400,003, K = 40,000 (12 K)
             // 136 : 138; 8 x 600,000, K = 300,000 (13 K) 117 : 108; 100 x 200,000, K = 30,000 (34 K) 163 : 183.
+            // The gain is that of steps with carried errors.  From a zero buffer, where votes share atomics, and of fewer
+            // than about three workgroups to a unit the counted votes can be the slower ones; with carried errors and from
+            // a zero buffer: 10 x 2.5 M, K = 100,000 133 : 128.5 and 123 : 129.5; 33 x 2.2 M, K = 20,000 218 : 212 and
+            // 213 : 220; 20 x 4 M, K = 27,000 221 : 217 and 220 : 226; 8 x 2 M, K = 80,000 95.6 : 94.0 and 88 : 98;
+            // 4 x 2 M, K = 200,000 78.7 : 80.5 and 84 : 91; 5 x 2^20, K = 100,000 61.6 : 63.3 and 67 : 72; from 3 M
+            // coordinates and 600,000 votes on 6 x 6 M, K = 150,000 160 : 153 and 150 : 152; 20 x 5 M, K = 50,000
+            // 292 : 280 and 280 : 279; 40 x 4 M, K = 20,000 396 : 386 and 402 : 402.
             const double wgs = (double)((p.n_chunks + p.chunks_per_wg - 1) / p.chunks_per_wg);
             const double entries = (double)p.N * (double)p.m_target / frac * (double)of_chunk / (double)(of_chunk - 1) / wgs;
             p.vote_chunks = p.multi_select && (uint64_t)p.N * p.K >= 500000 && entries <= 3000.0;
